@@ -1,0 +1,846 @@
+"""The workloads that the library's speed is measured on.
+
+Each case is one call, or one cycle of calls, that a program built on the
+package makes again and again: a few coarse steps of an adaptive hierarchy
+(Context.amr_coarse_steps), a run of steps on a one-level grid
+(Context.level_advance), a regrid cycle with the learned tagger, a training
+step of the tagger.  Sizes, patch widths and Courant numbers are those of the
+repository's own configurations and tests.
+
+State tensors are returned as views of the entries that a step defines: the
+interior averages and the nodes of each patch's closed square.  The ghost
+layers around them are scratch between calls (a step leaves them unfilled).
+
+exact() advances the same inputs with a plain FP64 torch version of the
+method on dense periodic grids, one per level, written here from the method's
+definition.
+"""
+import math
+
+import numpy as np
+import torch
+
+import paper_2205_07572_amd as af
+
+DEV = "cuda"
+F64 = torch.float64
+EQ = {"advection": af.ADVECTION, "acoustics": af.ACOUSTICS, "rotation": af.ROTATION, "swirl": af.SWIRL,
+      "burgers": af.BURGERS}
+COURANT = {"advection": 0.4, "acoustics": 0.4, "rotation": 0.6, "swirl": 0.6, "burgers": 0.5}
+QMAX = 1.1  # Burgers: largest |q| of the data
+# operations of one cell-update in the method's cheapest known form: constant
+# advection one 25-term and three 9-term sums, acoustics mirror-orbit sums;
+# variable fields two traced feet and biquadratic evaluations per node
+FLOPS = {"advection": 104, "acoustics": 706, "rotation": 420, "swirl": 900, "burgers": 640}
+
+
+# ---------------------------------------------------------------------------
+# the cases
+# ---------------------------------------------------------------------------
+
+def listed():
+    return [
+        # the benchmark's hierarchy: wave packet, 4 levels of 16^2 patches,
+        # about 2000 leaves; the four coarse steps between two regrids
+        amr("packet_4lev_fp32", "acoustics", "fp32", 16, 8, 8, 3, 0.325, 4),
+        amr("packet_4lev_fp64", "acoustics", "fp64", 16, 8, 8, 3, 0.325, 4),
+        # a small adaptive run, where a step is mostly launches: one coarse
+        # step of 3 levels on a 4 x 4 base
+        amr("pulse_small_fp32", "acoustics", "fp32", 16, 4, 4, 2, 0.12, 1),
+        # adaptive advection of the smoothed disc, a non-square base
+        amr("disc_3lev_fp64", "advection", "fp64", 16, 10, 7, 2, 0.22, 2),
+        # uniform advection, 512^2 cells in 32^2 patches: a tenth of a period
+        level("advect_512_fp32", "advection", "fp32", 32, 16, 16, 1.0, 0.5, 128),
+        # the same path with a velocity against the axes, an odd grid of
+        # 16^2 patches, a step count that is no multiple of anything
+        level("advect_back_fp64", "advection", "fp64", 16, 45, 37, -0.8, 0.6, 37),
+        # uniform acoustics, 2048^2 cells: the largest state
+        level("acoustics_2048_fp32", "acoustics", "fp32", 16, 128, 128, 0.0, 0.0, 4),
+        # solid-body rotation and Burgers on uniform grids (2048^2, 1024^2)
+        amr("rotation_2048_fp32", "rotation", "fp32", 32, 64, 64, 0, 0.0, 4),
+        amr("burgers_1024_fp64", "burgers", "fp64", 32, 32, 32, 0, 0.0, 4),
+        # swirl with two refined Gaussians, levels 3-5 of the paper's table:
+        # one coarse step, after which such a run regrids
+        amr("swirl_3lev_fp64", "swirl", "fp64", 16, 8, 8, 2, 0.16, 1),
+        # a regrid: ghost fill, plain and learned tags, new leaf set,
+        # transfer, fill
+        regrid("regrid_4lev_fp32", "fp32", 8, 3, 0.325),
+        # a training step of the tagger (batch of the training run)
+        train("tagger_train_256", 256),
+    ]
+
+
+def amr(name, eq, prec, m, n0x, n0y, lmax, radius, steps):
+    return {"name": name, "kind": "amr", "eq": eq, "prec": prec, "m": m, "n0x": n0x, "n0y": n0y, "lmax": lmax,
+            "radius": radius, "steps": steps}
+
+
+def level(name, eq, prec, m, n0x, n0y, a, b, steps):
+    return {"name": name, "kind": "level", "eq": eq, "prec": prec, "m": m, "n0x": n0x, "n0y": n0y, "lmax": 0, "a": a,
+            "b": b, "steps": steps}
+
+
+def regrid(name, prec, n0, lmax, radius):
+    return {"name": name, "kind": "regrid", "eq": "acoustics", "prec": prec, "m": 16, "n0x": n0, "n0y": n0,
+            "lmax": lmax, "radius": radius}
+
+
+def train(name, batch):
+    return {"name": name, "kind": "train", "batch": batch}
+
+
+def log_int(rng, lo, hi):
+    return min(hi, max(lo, int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))))
+
+
+def draw(rng):
+    kind = rng.choice(["amr", "amr", "uniform", "level", "level", "regrid", "train"])
+    prec = rng.choice(["fp32", "fp64"])
+    if kind == "amr":
+        eq = rng.choice(["acoustics", "acoustics", "advection", "swirl", "burgers"])
+        m = rng.choice([8, 16, 16, 32])
+        lmax = rng.choice([1, 2, 3]) if m == 16 else rng.choice([1, 2])
+        n0 = log_int(rng, 3, 8)
+        n0y = n0 if eq == "swirl" else log_int(rng, 3, 8)
+        c = amr("", eq, prec, m, n0, n0y, lmax, round(rng.uniform(0.08, 0.3), 3), rng.choice([1, 2, 3, 4]))
+    elif kind == "uniform":
+        eq = rng.choice(["rotation", "swirl", "burgers", "acoustics"])
+        m = rng.choice([16, 32, 32, 64])
+        n0 = log_int(rng, 2, (1536 if prec == "fp32" else 1024) // m)
+        c = amr("", eq, prec, m, n0, n0 if eq in ("swirl", "rotation") else log_int(rng, 2, 1024 // m), 0, 0.0,
+                rng.choice([1, 2, 4]))
+    elif kind == "level":
+        eq = rng.choice(["advection", "advection", "acoustics"])
+        m = rng.choice([16, 32]) if eq == "advection" or prec == "fp32" else 16
+        hi = 2048 if eq == "advection" else 1024
+        n0x, n0y = log_int(rng, 3, hi // m), log_int(rng, 3, hi // m)
+        a, b = (round(rng.choice([-1, 1, 1]) * rng.uniform(0.2, 1.0), 2) for _ in range(2))
+        c = level("", eq, prec, m, n0x, n0y, a if eq == "advection" else 0.0, b if eq == "advection" else 0.0,
+                  log_int(rng, 1, 40) if eq == "advection" else log_int(rng, 1, 8))
+    elif kind == "regrid":
+        c = regrid("", prec, log_int(rng, 4, 8), rng.choice([1, 2, 3]), round(rng.uniform(0.08, 0.3), 3))
+    else:
+        c = train("", log_int(rng, 16, 256))
+    del c["name"]
+    return c
+
+
+# ---------------------------------------------------------------------------
+# inputs
+# ---------------------------------------------------------------------------
+
+def problem(c):
+    eq = c["eq"]
+    kw = {"eq": EQ[eq], "prec": af.FP32 if c["prec"] == "fp32" else af.FP64, "m": c["m"], "n0x": c["n0x"],
+          "n0y": c["n0y"], "lmax": c["lmax"]}
+    if eq == "advection":
+        kw.update(a=c.get("a", 1.0), b=c.get("b", 0.5))
+    elif eq == "acoustics":
+        kw.update(c=1.0)
+    elif eq == "rotation":
+        kw.update(x0=-1.0, y0=-1.0, lx=2.0, ly=2.0, omega=math.pi)
+    elif eq == "burgers":
+        kw.update(qmax=QMAX)
+    return af.Problem(**kw)
+
+
+def coarse_dt(c, P):
+    speed = {"advection": max(abs(P.a), abs(P.b)), "acoustics": 1.0, "rotation": math.pi, "swirl": 1.0,
+             "burgers": QMAX}[c["eq"]]
+    return COURANT[c["eq"]] * min(P.dx(0), P.dy(0)) / speed
+
+
+def field(c, seed):
+    """The initial data as a function (x, y) -> [ncomp, ...] of FP64 tensors,
+    periodic on the domain (rotation: vanishing at its boundary)."""
+    r = np.random.RandomState(seed % (1 << 31))
+    jx, jy = r.uniform(-0.01, 0.01, 2)
+    amp = r.uniform(0.8, 1.0)
+    eq = c["eq"]
+
+    def gauss(x, y, cx, cy, alpha):
+        dx, dy = x - cx, y - cy
+        dx, dy = dx - torch.round(dx), dy - torch.round(dy)
+        return torch.exp(-alpha * (dx * dx + dy * dy))
+
+    if eq == "acoustics":
+        # a wave packet (|k| = 80 pi when the grid resolves it) and the flow it drives
+        n = max(1, min(40, c["n0x"] * c["m"] * 2 ** c["lmax"] // 24, c["n0y"] * c["m"] * 2 ** c["lmax"] // 24))
+        th = r.uniform(0, 2 * math.pi)
+        k, l = round(n * math.cos(th)), round(n * math.sin(th))
+        d = max(1.0, math.hypot(k, l))
+
+        def f(x, y):
+            g = amp * gauss(x, y, 0.5 + jx, 0.5 + jy, 50.0)
+            p = g * torch.cos(2 * math.pi * (k * x + l * y))
+            q = g * torch.sin(2 * math.pi * (k * x + l * y) + 0.3)
+            return torch.stack([p, 0.5 * (k / d) * q + 0.1 * g, 0.5 * (l / d) * q])
+    elif eq == "advection":
+        modes = [(r.uniform(-1, 1), r.randint(-6, 7), r.randint(-6, 7), r.uniform(0, 2 * math.pi)) for _ in range(6)]
+
+        def f(x, y):
+            rr = torch.sqrt((x - 0.5 - jx) ** 2 + (y - 0.5 - jy) ** 2)
+            s = 0.5 * (torch.tanh((rr + 0.15) / 0.02) - torch.tanh((rr - 0.15) / 0.02))
+            for A, k, l, p in modes:
+                s = s + 0.1 * A * torch.sin(2 * math.pi * (k * x + l * y) + p)
+            return s[None]
+    elif eq == "rotation":
+        def f(x, y):
+            rr = torch.sqrt((x - 0.4 - jx) ** 2 + (y - 0.4 - jy) ** 2)
+            return amp * 0.5 * (torch.tanh((rr + 0.15) / 0.02) - torch.tanh((rr - 0.15) / 0.02))[None]
+    elif eq == "swirl":
+        def f(x, y):
+            return (amp * gauss(x, y, 0.5 + jx, 0.25, 100.0) + gauss(x, y, 0.5, 0.75 + jy, 100.0))[None]
+    else:
+        def f(x, y):
+            return (amp * torch.sin(2 * math.pi * (x + jx)) * torch.sin(2 * math.pi * (y + jy)) + 0.1)[None]
+    return f
+
+
+def near(c, P, leaves):
+    """Which leaves touch the region the data asks to refine: discs of the
+    case's radius about the features."""
+    L = np.asarray(leaves)
+    s = 2.0 ** L[:, 0]
+    w, h = 1.0 / (P.n0x * s), 1.0 / (P.n0y * s)
+    x, y = L[:, 1] * w, L[:, 2] * h  # in units of the domain
+    hit = np.zeros(len(L), bool)
+    for cx, cy in ([(0.5, 0.25), (0.5, 0.75)] if c["eq"] == "swirl" else [(0.5, 0.5)]):
+        dx = np.maximum(0, np.maximum(x - cx, cx - x - w))
+        dy = np.maximum(0, np.maximum(y - cy, cy - y - h))
+        hit |= np.hypot(dx, dy) < c["radius"]
+    return hit
+
+
+def hierarchy(c, ctx):
+    P = ctx.prob
+    h = af.Hierarchy(ctx, [(0, i, j) for j in range(P.n0y) for i in range(P.n0x)])
+    for _ in range(P.lmax):
+        lv = h.leaves()
+        h = h.regrid(near(c, P, lv).astype(np.int8))
+    return h
+
+
+def positions(P, lv, n, half_x, half_y):
+    """Coordinates of entries 0 .. n-1 of each leaf's rows and columns, from
+    global indices, so that a node shared by two patches has one position:
+    x[leaf, 1, n], y[leaf, n, 1]; half_x, half_y: offset of half a cell."""
+    L = torch.as_tensor(np.asarray(lv), device=DEV).to(F64)
+    s = 2.0 ** L[:, 0]
+    k = torch.arange(n, device=DEV, dtype=F64)
+    nx, ny = P.n0x * P.m * s, P.n0y * P.m * s
+    gx = torch.remainder(L[:, 1:2] * P.m + k, nx[:, None])
+    gy = torch.remainder(L[:, 2:3] * P.m + k, ny[:, None])
+    x = P.x0 + P.lx * ((gx + 0.5 * half_x) / nx[:, None])
+    y = P.y0 + P.ly * ((gy + 0.5 * half_y) / ny[:, None])
+    return x[:, None, :], y[:, :, None], P.lx / nx[:, None, None], P.ly / ny[:, None, None]
+
+
+def dofs(c, P, lv, seed):
+    """The four DOF arrays of every leaf, [ncomp][leaf][rows][cols] of the
+    entries a step defines, in the problem's precision."""
+    f, m = field(c, seed), P.m
+    out = []
+    x, y, dx, dy = positions(P, lv, m, 1, 1)
+    g, w = np.polynomial.legendre.leggauss(3)
+    avg = 0.0
+    for a in range(3):
+        for b in range(3):
+            avg = avg + 0.25 * w[a] * w[b] * f(x + 0.5 * dx * g[a] + 0 * y, y + 0.5 * dy * g[b] + 0 * x)
+    out.append(avg)
+    for hx, hy in ((0, 0), (0, 1), (1, 0)):
+        x, y, _, _ = positions(P, lv, m + 1, hx, hy)
+        v = f(x + 0 * y, y + 0 * x)
+        out.append(v[:, :, :m if hy else m + 1, :m if hx else m + 1])
+    t = torch.float32 if P.prec == af.FP32 else F64
+    return [v.to(t) for v in out]
+
+
+def views(state, m, first, count):
+    """Views of the entries of leaves [first, first + count) that a step defines."""
+    return [state[k][:, first:first + count, 2:2 + (m if k in (0, 2) else m + 1), 2:2 + (m if k in (0, 3) else m + 1)]
+            for k in range(4)]
+
+
+def ranges(h, P):
+    return [(l,) + h.level_range(l) for l in range(P.lmax + 1) if h.level_range(l)[1]]
+
+
+class Run:
+    pass
+
+
+def prepare(case, seed):
+    c, s = case, Run()
+    s.case = c
+    if c["kind"] == "train":
+        return prepare_train(c, seed, s)
+    P = problem(c)
+    s.ctx = af.Context(P)
+    s.h = hierarchy(c, s.ctx)
+    n = len(s.h)
+    lv = s.h.leaves()
+    s.bufs = [s.ctx.new_state(n), s.ctx.new_state(n)]
+    for v, d in zip(views(s.bufs[0], P.m, 0, n), dofs(c, P, lv, seed)):
+        v.copy_(d)
+    s.mask, s.t, s.dt = 0, 0.0, coarse_dt(c, P)
+    s.reg = torch.zeros((n, 4, P.m, P.ncomp), dtype=F64, device=DEV)
+    # the result's views, per level and buffer
+    s.views = [(l, [views(b, P.m, f, k) for b in s.bufs]) for l, f, k in ranges(s.h, P)]
+    if c["kind"] == "regrid":
+        s.tagger = af.Tagger()
+        s.tagger.set_params(tagger_params(0))
+        s.cap = capacity(P, n)
+        s.tags = torch.zeros(n, dtype=torch.int8, device=DEV)
+        s.values = torch.zeros(n, dtype=F64, device=DEV)
+    return s
+
+
+def capacity(P, n):
+    """Patches a state holds across regrids: the leaf count changes with the
+    data, a run keeps room for that."""
+    return min(P.n0x * P.n0y * 4 ** P.lmax, 4 * n)
+
+
+def result(s):
+    return [v[(s.mask >> l) & 1] for l, v in s.views]
+
+
+def run(s):
+    c = s.case
+    if c["kind"] == "amr":
+        s.mask = s.ctx.amr_coarse_steps(s.h, s.bufs, s.mask, s.dt, c["steps"], s.reg, t0=s.t)
+        s.t += c["steps"] * s.dt
+        return result(s)
+    if c["kind"] == "level":
+        s.mask = s.ctx.level_advance(s.h, s.bufs, s.mask, 0, s.dt, c["steps"])
+        return result(s)
+    if c["kind"] == "regrid":
+        ctx = s.ctx
+        ctx.ghost_fill(s.h, s.bufs, s.mask)
+        ctx.regrid_tag(s.h, s.bufs, s.mask, af.TAG_GRADIENT, 0, THETA[0], THETA[1], s.tags, s.values)
+        tags, learned = s.tagger.tag(ctx, s.h, s.bufs, s.mask, s.tags)
+        host = tags.cpu().numpy()  # the new leaf set is made on the host
+        new = s.h.regrid(host)
+        dst = ctx.new_state(s.cap)
+        ctx.regrid_apply(s.h, s.bufs, s.mask, new, dst)
+        ctx.ghost_fill(new, [dst], 0)
+        leaves = np.full((s.cap, 3), -1)
+        leaves[:len(new)] = new.leaves()
+        return {"plain": s.tags, "values": s.values, "learned": learned, "tags": tags, "leaves": leaves, "state": dst}
+    s.t += 1
+    loss = s.tagger.loss_grad(s.x, s.labels, grad=s.grad)
+    s.tagger.adam_step(2e-3, grad=s.grad)
+    return {"loss": loss, "grad": s.grad}
+
+
+THETA = (8.0, 2.0)  # refine at, coarsen below (gradient of p)
+
+
+# ---------------------------------------------------------------------------
+# the tagger
+# ---------------------------------------------------------------------------
+
+NIN, WIDTH, IMG = 13, 32, 16
+
+
+def split(p):
+    """Packed parameters -> [(W, b)] of the three convolutions and the head."""
+    out, o = [], 0
+    for cin in (NIN, WIDTH, WIDTH):
+        k = WIDTH * cin * 9
+        out.append((p[o:o + k].reshape(WIDTH, cin, 3, 3), p[o + k:o + k + WIDTH]))
+        o += k + WIDTH
+    out.append((p[o:o + 3 * WIDTH].reshape(3, WIDTH), p[o + 3 * WIDTH:o + 3 * WIDTH + 3]))
+    return out
+
+
+def count_params():
+    return sum(WIDTH * cin * 9 + WIDTH for cin in (NIN, WIDTH, WIDTH)) + 3 * WIDTH + 3
+
+
+def tagger_params(seed, trained=True):
+    """He-style random parameters; `trained`: four channels of every layer
+    carry the positive parts of the p-average differences and the head reads
+    their mean, so that the classes follow the gradient as a trained
+    network's do."""
+    r = np.random.RandomState(977 + seed)
+    p = np.zeros(count_params(), np.float32)
+    for W, b in split(p):
+        fan = W[0].size
+        W[...] = r.standard_normal(W.shape) * math.sqrt(2.0 / fan)
+        b[...] = 0.05 * r.standard_normal(b.shape)
+    if trained:
+        (w1, b1), (w2, b2), (w3, b3), (wh, bh) = split(p)
+        w1[:4], b1[:4] = 0, 0
+        for k, (y, x) in enumerate(((1, 2), (1, 0), (2, 1), (0, 1))):
+            w1[k, 0, y, x], w1[k, 0, 1, 1] = 1, -1
+        for w, b in ((w2, b2), (w3, b3)):
+            w[:4], b[:4] = 0, 0
+            w[range(4), range(4), 1, 1] = 1
+        wh[...] *= 0.02
+        wh[2, :4] = 40
+        wh[0, :4] = -40
+        bh[...] = (0.4, 0.0, -1.6)
+    return p
+
+
+def prepare_train(c, seed, s):
+    g = torch.Generator(device=DEV).manual_seed(seed % (1 << 31))
+    B = c["batch"]
+    # standardised features are smooth over a patch, with a constant level channel
+    k = torch.arange(IMG, device=DEV, dtype=torch.float32) / IMG
+    co = torch.randn((4, B, NIN, 1, 1), generator=g, device=DEV)
+    y, x = k[:, None], k[None, :]
+    s.x = (co[0] + co[1] * torch.sin(2 * math.pi * x + co[3]) + co[2] * torch.cos(2 * math.pi * y - co[3]) +
+           0.1 * torch.randn((B, NIN, IMG, IMG), generator=g, device=DEV))
+    s.x[:, 12] = co[0][:, 12]
+    s.x = s.x.contiguous()
+    s.labels = torch.randint(0, 3, (B,), generator=g, device=DEV, dtype=torch.int32)
+    s.tagger = af.Tagger()
+    s.tagger.set_params(tagger_params(seed % 1000, trained=False))
+    s.grad = torch.zeros(count_params(), dtype=torch.float32, device=DEV)
+    s.t = 0
+    return s
+
+
+def bf(t):
+    """Rounded to BF16, as the operands of the tagger's products are."""
+    return t.to(torch.float32).to(torch.bfloat16).to(F64)
+
+
+def exact_train(c, seed):
+    s = prepare_train(c, seed, Run())
+    (w1, b1), (w2, b2), (w3, b3), (wh, bh) = split(torch.from_numpy(tagger_params(seed % 1000, trained=False)).to(DEV).to(F64))
+    B = c["batch"]
+    conv = torch.nn.functional.conv2d
+    ws, bs = [bf(w1), bf(w2), bf(w3)], [b1, b2, b3]
+    ins, zs, a = [], [], s.x.to(F64)
+    for w, b in zip(ws, bs):
+        ins.append(bf(a))
+        z = sum(conv(ins[-1][:, k:k + 1], w[:, k:k + 1], padding=1) for k in range(w.shape[1])) + b[None, :, None, None]
+        zs.append(z)
+        a = z.clamp_min(0)
+    pooled = a.mean(dim=(2, 3))
+    logits = pooled @ wh.T + bh
+    lab = torch.nn.functional.one_hot(s.labels.long(), 3).to(F64)
+    loss = -(torch.log_softmax(logits, 1) * lab).sum() / B
+    dl = (torch.softmax(logits, 1) - lab) / B
+    grads = [None] * 4
+    grads[3] = torch.cat([(dl.T @ pooled).reshape(-1), dl.sum(0)])
+    da = ((dl @ wh) / (IMG * IMG))[:, :, None, None].expand(B, WIDTH, IMG, IMG)
+    for l in (2, 1, 0):
+        gz = torch.where(zs[l] > 0, da, torch.zeros_like(da))
+        gb = bf(gz)
+        pad = torch.nn.functional.pad(ins[l], (1, 1, 1, 1))
+        gf = gb.permute(1, 0, 2, 3).reshape(WIDTH, -1)
+        gw = torch.stack([gf @ pad[:, :, y:y + IMG, x:x + IMG].permute(0, 2, 3, 1).reshape(gf.shape[1], -1)
+                          for y in range(3) for x in range(3)], -1)  # [co][ci][tap]
+        grads[l] = torch.cat([gw.reshape(-1), gz.sum(dim=(0, 2, 3))])
+        if l:
+            gp = torch.nn.functional.pad(gb, (1, 1, 1, 1)).permute(0, 2, 3, 1)
+            da = sum((gp[:, 2 - y:2 - y + IMG, 2 - x:2 - x + IMG].reshape(-1, WIDTH) @ ws[l][:, :, y, x])
+                     for y in range(3) for x in range(3)).reshape(B, IMG, IMG, WIDTH).permute(0, 3, 1, 2)
+    return {"loss": loss.reshape(1), "grad": torch.cat(grads)}
+
+
+# ---------------------------------------------------------------------------
+# the method in FP64 on dense periodic grids (cells own their left-edge,
+# bottom-edge and lower-left corner values): D = [avg, corner, xedge, yedge],
+# each [ncomp][ny][nx]
+# ---------------------------------------------------------------------------
+
+def at(t, di, dj):
+    """t at cell (i + di, j + dj)."""
+    return torch.roll(t, (-dj, -di), (-2, -1)) if di or dj else t
+
+
+# raw DOFs of a cell: (array, di, dj), reference position (None: the average)
+RAW = [(0, 0, 0), (1, 0, 0), (1, 1, 0), (1, 0, 1), (1, 1, 1), (2, 0, 0), (2, 1, 0), (3, 0, 0), (3, 0, 1)]
+POS = [None, (-1, -1), (1, -1), (-1, 1), (1, 1), (-1, 0), (1, 0), (0, -1), (0, 1)]
+NODE = [(-0.5, -0.5), (-0.5, 0.0), (0.0, -0.5)]  # corner, x-edge, y-edge in cell units
+
+
+def lag(a, s):
+    return (0.5 * s * (s - 1), 1 - s * s, 0.5 * s * (s + 1))[a + 1]
+
+
+def dlag(a, s):
+    return (s - 0.5, -2 * s, s + 0.5)[a + 1]
+
+
+def basis(xi, eta, fx=lag, fy=lag):
+    """Weights of the 9 raw DOFs for the biquadratic (fx, fy = lag) or one of
+    its reference derivatives (dlag) at (xi, eta); the centre value is
+    (36 average - corners - 4 edge midpoints) / 16."""
+    c = fx(0, xi) * fy(0, eta)
+    out = [36.0 / 16.0 * c]
+    for k in range(1, 9):
+        out.append(fx(POS[k][0], xi) * fy(POS[k][1], eta) - (1.0 if k <= 4 else 4.0) / 16.0 * c)
+    return out
+
+
+def combine(D, w, di=0, dj=0):
+    return sum(w[k] * at(D[RAW[k][0]], di + RAW[k][1], dj + RAW[k][2]) for k in range(9) if w[k] != 0)
+
+
+def sphere_weights(rx, ry):
+    """Acoustics: for each node kind, {cell offset: [K, Dx, Dy] weights of its
+    raw DOFs} of the spherical means over the disc sectors in each cell, by
+    Gauss-Legendre quadrature over the sphere's two angles; rx = 2 c tau / dx."""
+    g, w = np.polynomial.legendre.leggauss(20)
+    th, tw = (g + 1) * math.pi / 4, w * math.pi / 4
+    quad = [[(0, 0), (-1, 0), (-1, -1), (0, -1)], [(0, 0), (-1, 0), (-1, 0), (0, 0)], [(0, 0), (0, 0), (0, -1), (0, -1)]]
+    out = []
+    for nk in range(3):
+        cells = {}
+        for q in range(4):
+            di, dj = quad[nk][q]
+            x0, y0 = 2 * (NODE[nk][0] - di), 2 * (NODE[nk][1] - dj)
+            ph = th + q * math.pi / 2
+            zx = rx * np.sin(th)[:, None] * np.cos(ph)[None, :]
+            zy = ry * np.sin(th)[:, None] * np.sin(ph)[None, :]
+            wt = tw[:, None] * tw[None, :] * np.sin(th)[:, None] / (2 * math.pi)
+            v = basis(x0 + zx, y0 + zy)
+            vx = basis(x0 + zx, y0 + zy, dlag, lag)
+            vy = basis(x0 + zx, y0 + zy, lag, dlag)
+            acc = cells.setdefault((di, dj), [[0.0] * 9 for _ in range(3)])
+            for k in range(9):
+                acc[0][k] += float((wt * (v[k] + zx * vx[k] + zy * vy[k])).sum())
+                acc[1][k] += float((wt * rx * vx[k]).sum())
+                acc[2][k] += float((wt * ry * vy[k]).sum())
+        out.append(cells)
+    return out
+
+
+def gather_eval(D, ci, cj, xi, eta):
+    """Reconstruction of cells (ci, cj) (index tensors) at (xi, eta)."""
+    ny, nx = D[0].shape[-2:]
+    w = basis(xi, eta)
+    return sum(w[k] * D[RAW[k][0]][0][(cj + RAW[k][2]) % ny, (ci + RAW[k][1]) % nx] for k in range(9))
+
+
+def foot_cell(s, disp):
+    return torch.where(disp < 0, torch.ceil(s + 0.5) - 1, torch.floor(s + 0.5)).long()
+
+
+def swirl_velocity(x, y, t, dx, dy):
+    def psi(u, v):
+        return torch.sin(math.pi * u) ** 2 * torch.sin(math.pi * v) ** 2 * math.cos(math.pi * t) / math.pi
+    return -(psi(x, y + dy / 2) - psi(x, y - dy / 2)) / dy, (psi(x + dx / 2, y) - psi(x - dx / 2, y)) / dx
+
+
+class Dense:
+    """One step of an equation on the periodic grid of one level."""
+
+    def __init__(self, c, P, lvl, dt):
+        self.eq, self.P, self.dt = c["eq"], P, dt
+        self.dx, self.dy = P.dx(lvl), P.dy(lvl)
+        self.taus = (0.5 * dt, dt)
+        if self.eq == "acoustics":
+            self.w = [sphere_weights(2 * P.c * t / self.dx, 2 * P.c * t / self.dy) for t in self.taus]
+
+    def nodes(self, D, nk, t):
+        """Values of node kind nk at t0 + tau (tau = dt/2, dt)."""
+        eq, P = self.eq, self.P
+        out = []
+        for h, tau in enumerate(self.taus):
+            if eq == "advection":
+                off, ref = [], []
+                for d, (v, dl) in enumerate(((P.a, self.dx), (P.b, self.dy))):
+                    s = NODE[nk][d] - v * tau / dl
+                    k = math.floor(s + 0.5)
+                    k -= 1 if v < 0 and s + 0.5 == k else 0
+                    off.append(int(k))
+                    ref.append(2 * (s - k))
+                out.append(combine(D, basis(*ref), *off))
+                continue
+            if eq == "acoustics":
+                acc = [0.0, 0.0, 0.0]
+                for (di, dj), (K, X, Y) in self.w[h][nk].items():
+                    k, x, y = (combine(D, w, di, dj) for w in (K, X, Y))
+                    acc[0] = acc[0] + k[0] - x[1] - y[2]
+                    acc[1] = acc[1] + k[1] - x[0]
+                    acc[2] = acc[2] + k[2] - y[0]
+                out.append(torch.stack(acc))
+                continue
+            ny, nx = D[0].shape[-2:]
+            I = torch.arange(nx, device=DEV, dtype=F64)[None, :].expand(ny, nx)
+            J = torch.arange(ny, device=DEV, dtype=F64)[:, None].expand(ny, nx)
+            X, Y = I + NODE[nk][0], J + NODE[nk][1]
+            if eq == "burgers":
+                A = D[0][0]
+                if nk == 0:
+                    q = 0.25 * (A + at(A, -1, 0) + at(A, 0, -1) + at(A, -1, -1))
+                else:
+                    q = 0.5 * (A + (at(A, -1, 0) if nk == 1 else at(A, 0, -1)))
+                for _ in range(2):
+                    sx, sy = X - q * tau / self.dx, Y - q * tau / self.dy
+                    ci, cj = foot_cell(sx, q), foot_cell(sy, q)
+                    q = gather_eval(D, ci, cj, 2 * (sx - ci), 2 * (sy - cj))
+                out.append(q[None])
+                continue
+            x, y = P.x0 + (X + 0.5) * self.dx, P.y0 + (Y + 0.5) * self.dy
+            if eq == "rotation":
+                cs, sn = math.cos(P.omega * tau), math.sin(P.omega * tau)
+                rx, ry = x - P.xc, y - P.yc
+                fx, fy = P.xc + rx * cs + ry * sn, P.yc - rx * sn + ry * cs
+            else:
+                s = t + tau
+                a1, b1 = swirl_velocity(x, y, s, self.dx, self.dy)
+                a2, b2 = swirl_velocity(x - 0.5 * tau * a1, y - 0.5 * tau * b1, s - 0.5 * tau, self.dx, self.dy)
+                a3, b3 = swirl_velocity(x - 0.5 * tau * a2, y - 0.5 * tau * b2, s - 0.5 * tau, self.dx, self.dy)
+                a4, b4 = swirl_velocity(x - tau * a3, y - tau * b3, t, self.dx, self.dy)
+                fx = x - tau / 6 * (a1 + 2 * a2 + 2 * a3 + a4)
+                fy = y - tau / 6 * (b1 + 2 * b2 + 2 * b3 + b4)
+            sx, sy = (fx - P.x0) / self.dx - 0.5, (fy - P.y0) / self.dy - 0.5
+            ci, cj = foot_cell(sx, x - fx), foot_cell(sy, y - fy)
+            out.append(gather_eval(D, ci, cj, 2 * (sx - ci), 2 * (sy - cj))[None])
+        return out
+
+    def step(self, D, t):
+        """(D at t + dt, x-face fluxes at the cells' left faces, y-face fluxes
+        at their bottom faces), Simpson's rule in space and time."""
+        eq, P = self.eq, self.P
+        times = [[D[nk + 1]] + self.nodes(D, nk, t) for nk in range(3)]  # [kind][time]
+        ny, nx = D[0].shape[-2:]
+        I = torch.arange(nx, device=DEV, dtype=F64)[None, :]
+        J = torch.arange(ny, device=DEV, dtype=F64)[:, None]
+        x, y = P.x0 + I * self.dx, P.y0 + J * self.dy  # lower-left corners
+        FX = FY = 0.0
+        for k, wt in enumerate((1, 4, 1)):
+            co, xe, ye = times[0][k], times[1][k], times[2][k]
+            fx = ((1, co), (4, xe), (1, at(co, 0, 1)))
+            fy = ((1, co), (4, ye), (1, at(co, 1, 0)))
+            if eq == "swirl":
+                tk = t + 0.5 * k * self.dt
+                a = swirl_velocity(x + 0 * y, y + 0.5 * self.dy, tk, self.dx, self.dy)[0]
+                b = swirl_velocity(x + 0.5 * self.dx, y + 0 * x, tk, self.dx, self.dy)[1]
+                sx, sy = a * sum(w * q for w, q in fx), b * sum(w * q for w, q in fy)
+            elif eq == "rotation":
+                sx = sum(w * -P.omega * (y + 0.5 * n * self.dy - P.yc) * q for n, (w, q) in enumerate(fx))
+                sy = sum(w * P.omega * (x + 0.5 * n * self.dx - P.xc) * q for n, (w, q) in enumerate(fy))
+            elif eq == "burgers":
+                sx, sy = (sum(w * 0.5 * q * q for w, q in f) for f in (fx, fy))
+            else:
+                sx, sy = (sum(w * q for w, q in f) for f in (fx, fy))
+                if eq == "advection":
+                    sx, sy = P.a * sx, P.b * sy
+                else:
+                    z = torch.zeros_like(sx[0])
+                    sx, sy = P.c * torch.stack([sx[1], sx[0], z]), P.c * torch.stack([sy[2], z, sy[0]])
+            FX, FY = FX + wt * sx / 36, FY + wt * sy / 36
+        avg = (D[0] - self.dt / self.dx * (at(FX, 1, 0) - FX) - self.dt / self.dy * (at(FY, 0, 1) - FY))
+        return [avg, times[0][2], times[1][2], times[2][2]], FX, FY
+
+
+def up2(t):
+    return t.repeat_interleave(2, -2).repeat_interleave(2, -1)
+
+
+def closed(mask):
+    """Node masks (corner, x-edge, y-edge) of the closed cells of a cell mask."""
+    xe, ye = mask | at(mask, -1, 0), mask | at(mask, 0, -1)
+    return [ye | at(ye, -1, 0), xe, ye]
+
+
+class Composite:
+    """A hierarchy's state as one dense grid per level."""
+
+    def __init__(self, c, P, lv):
+        self.c, self.P, self.lv, self.steps = c, P, lv, {}
+        self.F = max(l for l, _, _ in lv)
+        self.cell, self.D = [], []
+        for l in range(self.F + 1):
+            ny, nx = P.n0y * P.m << l, P.n0x * P.m << l
+            self.cell.append(torch.zeros((ny, nx), dtype=torch.bool, device=DEV))
+            self.D.append([torch.zeros((P.ncomp, ny, nx), dtype=F64, device=DEV) for _ in range(4)])
+        for l, _, idx in self.index():
+            self.cell[l][idx[0]] = True
+        self.node = [closed(m) for m in self.cell]
+
+    def load(self, data):
+        """The leaves' DOFs (nodes that two leaves share hold one value)."""
+        for l, ids, idx in self.index():
+            for k in range(4):
+                self.D[l][k][:, idx[k][0], idx[k][1]] = data[k][:, ids].to(F64)
+
+    def index(self, lo=0, extra=0):
+        """Per level: (level, leaf ids, per kind the (row, column) indices of
+        the leaves' entries lo .. m or m + 1 (+ extra))."""
+        P, L = self.P, np.asarray(self.lv)
+        for l in range(self.F + 1):
+            ids = np.nonzero(L[:, 0] == l)[0]
+            if not len(ids):
+                continue
+            ny, nx = P.n0y * P.m << l, P.n0x * P.m << l
+            ix, iy = (torch.as_tensor(L[ids, d], device=DEV) for d in (1, 2))
+            idx = []
+            for k in range(4):
+                r = torch.arange(lo, P.m + extra + (k in (1, 3)), device=DEV)
+                q = torch.arange(lo, P.m + extra + (k in (1, 2)), device=DEV)
+                idx.append(((iy[:, None, None] * P.m + r[None, :, None]) % ny, (ix[:, None, None] * P.m + q[None, None, :]) % nx))
+            yield l, torch.as_tensor(ids, device=DEV), idx
+
+    def prolong(self, l):
+        """Level l's DOFs from the reconstructions of level l - 1: averages
+        over quarter cells, values at the fine nodes."""
+        C = self.D[l - 1]
+        shape = self.D[l][0].shape
+        out = [torch.zeros(shape, dtype=F64, device=DEV) for _ in range(4)]
+        g = (-math.sqrt(1 / 3), math.sqrt(1 / 3))  # two Gauss points per direction: exact for biquadratics' averages
+        for qy in range(2):
+            for qx in range(2):
+                out[0][:, qy::2, qx::2] = sum(0.25 * combine(C, basis(qx - 0.5 + 0.5 * a, qy - 0.5 + 0.5 * b)) for a in g for b in g)
+                out[1][:, qy::2, qx::2] = combine(C, basis(qx - 1.0, qy - 1.0))
+                out[2][:, qy::2, qx::2] = combine(C, basis(qx - 1.0, qy - 0.5))
+                out[3][:, qy::2, qx::2] = combine(C, basis(qx - 0.5, qy - 1.0))
+        return out
+
+    def restrict(self, l):
+        """Level l's DOFs from level l + 1: means of four averages, coincident
+        vertices."""
+        f = self.D[l + 1]
+        a = f[0]
+        mean = 0.25 * (a[:, ::2, ::2] + a[:, ::2, 1::2] + a[:, 1::2, ::2] + a[:, 1::2, 1::2])
+        return [mean, f[1][:, ::2, ::2], f[1][:, 1::2, ::2], f[1][:, ::2, 1::2]]
+
+    def fill(self, tmin, smin):
+        for l in range(tmin, self.F):  # finer sources
+            if l + 1 < smin:
+                continue
+            R = self.restrict(l)
+            fm = self.cell[l + 1][::2, ::2]
+            nm = self.node[l + 1][0]
+            take = [fm, nm[::2, ::2], nm[1::2, ::2], nm[::2, 1::2]]
+            self.D[l] = [torch.where(take[k], R[k], self.D[l][k]) for k in range(4)]
+        for l in range(max(tmin, smin + 1, 1), self.F + 1):  # coarser sources
+            cm = up2(self.cell[l - 1])
+            finer = [torch.zeros_like(cm)] * 4
+            if l < self.F:
+                nm = self.node[l + 1][0]
+                finer = [self.cell[l + 1][::2, ::2], nm[::2, ::2], nm[1::2, ::2], nm[::2, 1::2]]
+            own = [self.cell[l]] + self.node[l]
+            src = [cm] + closed(cm)
+            Q = self.prolong(l)
+            self.D[l] = [torch.where(src[k] & ~own[k] & ~finer[k], Q[k], self.D[l][k]) for k in range(4)]
+
+    def advance(self, l, t, dt):
+        """One step of level l with the finer levels' substeps and the
+        conservative fix; returns the face fluxes times length and time."""
+        S = self.steps.get((l, dt))
+        if S is None:
+            S = self.steps[l, dt] = Dense(self.c, self.P, l, dt)
+        self.D[l], FX, FY = S.step(self.D[l], t)
+        RX, RY = FX * (S.dy * dt), FY * (S.dx * dt)
+        if l < self.F:
+            a = self.advance(l + 1, t, 0.5 * dt)
+            self.fill(l + 1, l + 1)
+            b = self.advance(l + 1, t + 0.5 * dt, 0.5 * dt)
+            fx, fy = a[0] + b[0], a[1] + b[1]
+            ex = RX - fx[:, ::2, ::2] - fx[:, 1::2, ::2]  # at left faces
+            ey = RY - fy[:, ::2, ::2] - fy[:, ::2, 1::2]  # at bottom faces
+            fine = self.cell[l + 1][::2, ::2]
+            fix = at(ex, 1, 0) * at(fine, 1, 0) - ex * at(fine, -1, 0) + at(ey, 0, 1) * at(fine, 0, 1) - ey * at(fine, 0, -1)
+            self.D[l][0] = self.D[l][0] + fix * self.cell[l] / (S.dx * S.dy)
+        return RX, RY
+
+    def read(self):
+        return [[self.D[l][k][:, idx[k][0], idx[k][1]] for k in range(4)] for l, _, idx in self.index()]
+
+
+def exact_steps(c, seed):
+    P = problem(c)
+    S = Composite(c, P, hierarchy(c, af.Context(P)).leaves())
+    S.load(dofs(c, P, S.lv, seed))
+    dt = coarse_dt(c, P)
+    for k in range(c["steps"]):
+        if c["kind"] == "amr":
+            S.fill(0, 0)
+        S.advance(0, k * dt, dt)
+    return S.read()
+
+
+def exact_regrid(c, seed):
+    P = problem(c)
+    h = hierarchy(c, af.Context(P))
+    m, lv = P.m, h.leaves()
+    S = Composite(c, P, lv)
+    S.load(dofs(c, P, lv, seed))
+    S.fill(0, 0)
+    values = torch.zeros(len(lv), dtype=F64, device=DEV)
+    feats = torch.zeros((len(lv), NIN, m, m), dtype=F64, device=DEV)
+    for l, ids, idx in S.index():
+        q = S.D[l][0][0]
+        g = torch.maximum((at(q, 1, 0) - at(q, -1, 0)).abs() / (2 * P.dx(l)), (at(q, 0, 1) - at(q, 0, -1)).abs() / (2 * P.dy(l)))
+        values[ids] = g[idx[0]].amax(dim=(1, 2))
+        for ch in range(12):
+            feats[ids, ch] = S.D[l][ch % 4][ch // 4][idx[0]]
+        feats[ids, 12] = float(l)
+    # the tags, and the leaf set they lead to
+    lev = torch.as_tensor(np.asarray(lv)[:, 0], device=DEV)
+    plain = torch.where((values >= THETA[0]) & (lev < P.lmax), 1, torch.where((values < THETA[1]) & (lev > 0), -1, 0))
+    a = feats
+    *convs, (wh, bh) = split(torch.from_numpy(tagger_params(0)).to(DEV).to(F64))
+    for w, b in convs:
+        a = (torch.nn.functional.conv2d(bf(a), bf(w), padding=1) + b[None, :, None, None]).clamp_min(0)
+    L = a.mean(dim=(2, 3)) @ wh.T + bh
+    net = torch.where((L[:, 2] > L[:, 1]) & (L[:, 2] > L[:, 0]), 1, torch.where(L[:, 0] > L[:, 1], -1, 0))
+    tags = torch.where((net == 1) | (plain == 1), 1, torch.where((net == -1) & (plain == -1), -1, 0))
+    tags = torch.where((tags == 1) & (lev >= P.lmax) | (tags == -1) & (lev == 0), 0, tags)
+    new = h.regrid(tags.to(torch.int8).cpu().numpy()).leaves()
+    N = Composite(c, P, new)
+    for l in range(N.F + 1):
+        # the three transfers, and per DOF that of the new leaf owning it
+        modes = []
+        if l <= S.F:
+            modes.append((S.cell[l], S.D[l]))
+        if 0 < l <= S.F + 1:
+            modes.append((up2(S.cell[l - 1]), S.prolong(l)))
+        if l < S.F:
+            modes.append((S.cell[l + 1][::2, ::2], S.restrict(l)))
+        cand = [[(0, 0)], [(0, 0), (-1, 0), (0, -1), (-1, -1)], [(0, 0), (-1, 0)], [(0, 0), (0, -1)]]
+        for k in range(4):
+            left = torch.ones_like(N.cell[l])
+            for di, dj in cand[k]:
+                here = left & at(N.cell[l], di, dj)
+                left = left & ~here
+                for mask, src in modes:
+                    N.D[l][k] = torch.where(here & at(mask, di, dj), src[k], N.D[l][k])
+    N.fill(0, 0)
+    state = torch.zeros((4, P.ncomp, capacity(P, len(lv)), m + 5, m + 5), dtype=F64, device=DEV)
+    for l, ids, idx in N.index(-2, 2):
+        for k in range(4):
+            v = N.D[l][k][:, idx[k][0], idx[k][1]]
+            state[k][:, ids, :v.shape[-2], :v.shape[-1]] = v
+    return {"plain": None, "values": values, "learned": None, "tags": None, "leaves": None, "state": state}
+
+
+def exact(case, seed):
+    if case["kind"] == "train":
+        return exact_train(case, seed)
+    return exact_regrid(case, seed) if case["kind"] == "regrid" else exact_steps(case, seed)
+
+
+# ---------------------------------------------------------------------------
+
+def work(case):
+    """Bytes: the state read once and written once over the whole call.
+    Operations: those of every cell-update (subcycled: level l counts 2^l)."""
+    c = case
+    if c["kind"] == "train":
+        n = c["batch"] * IMG * IMG
+        macs = n * 9 * WIDTH * (NIN + 2 * WIDTH)  # one product over all layers; the first layer has no input gradient
+        return {"bytes": 4 * (c["batch"] * NIN * IMG * IMG + 8 * count_params()),
+                "flops": 2 * (3 * macs - n * 9 * WIDTH * NIN)}
+    word, comp = (4 if c["prec"] == "fp32" else 8), (3 if c["eq"] == "acoustics" else 1)
+    per = [c["n0x"] * c["n0y"]] + [0] * c["lmax"]
+    if c["lmax"]:
+        lv = hierarchy(c, af.Context(problem(c))).leaves()
+        per = [sum(1 for t in lv if t[0] == l) for l in range(c["lmax"] + 1)]
+    cells = sum(per) * c["m"] ** 2
+    state = cells * 4 * comp * word
+    if c["kind"] == "regrid":
+        return {"bytes": 2 * state, "flops": 2.0 * cells * 9 * WIDTH * (NIN + 2 * WIDTH)}
+    updates = sum(n << l for l, n in enumerate(per)) * c["m"] ** 2
+    return {"bytes": 2 * state, "flops": float(FLOPS[c["eq"]] * updates * c["steps"])}
