@@ -6,11 +6,12 @@
 // 32 -> 3 (coarsen / keep / refine), softmax cross-entropy.  Parameters are
 // FP32 masters packed as W1[co][ci][3][3], b1, W2, b2, W3, b3, Wh[3][32], bh.
 //
-// The convolutions run as implicit GEMMs on the matrix cores: im2col gathers
-// (BF16), one strided GEMM kernel built on v_mfma_f32_16x16x32_bf16 (BF16
-// operands, FP32 accumulation) for forward, input-gradient and
-// weight-gradient products, col2im sums.  Bias, ReLU, pooling, head, loss
-// and the Adam update are FP32 elementwise kernels.
+// One block holds one 16x16 sample at a time in LDS and takes it through the
+// whole network, and in training back again: the convolutions are implicit
+// GEMMs on v_mfma_f32_16x16x32_bf16 (BF16 operands, FP32 accumulation) that
+// read their operands from LDS; bias, ReLU, pooling, head and loss are FP32.
+// Nothing but the input, the logits and one row of gradient sums per block
+// crosses HBM.  A second kernel adds the blocks' rows, a third is Adam.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -26,7 +27,9 @@
 namespace af {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef unsigned short u16x4 __attribute__((ext_vector_type(4)));
 typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kImg = 16, kPix = 256, kWidth = 32, kClasses = 3;
@@ -41,296 +44,490 @@ __device__ __forceinline__ uint16_t f2bf(float f) {
 __device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float(uint32_t(h) << 16); }
 
 // ---------------------------------------------------------------------------
-// C(i,j) (+)= sum_k A(i,k) B(j,k), A and B BF16 with arbitrary strides, C FP32.
-// One wavefront computes a 16x16 tile: lane l loads A row i0 + l%16 and
-// B row j0 + l%16 at k = k0 + 8 (l/16) + e, e < 8 (the same k order for both
-// operands, so the hardware's internal k order does not matter), and the
-// accumulator holds C rows i0 + 4 (l/16) + r, r < 4, column j0 + l%16.
-// blockIdx.z splits K into chunks (multiples of 32); chunk z writes its
-// partial product to part[z][i][j] and k_sum_chunks adds the chunks in
-// order, so the result does not depend on scheduling.
-// A lane's 8 values of one operand are one 16-byte load where they are
-// contiguous and aligned (unit k stride, row stride a multiple of 8, K a
-// multiple of 8, so that a group of 8 lies wholly inside or outside
-// [0, K)); else 8 element loads.  With X set, A is the im2col matrix of the
-// BF16 NHWC images X (cp channels, cp a multiple of 8), read in place: the
-// 8 values of a lane are 8 channels of one pixel of one tap, zero outside
-// the image.
+// The network on one sample at a time (k_cnn).
+//
+// LDS holds images channel-innermost with a zero ring, [18][18][channels]
+// BF16 (the first layer's channels padded to CP, a multiple of 8), and the
+// weights as [co][tap * channels + ci] with a row pitch of an odd number of
+// 16-byte units.  A wave takes two image rows: a 16x16 tile's A rows are the
+// 16 pixels of an image row, its B rows 16 output channels, and a lane's 8
+// k values are 8 channels of one pixel of one tap, one 16-byte LDS load.
+// The k steps run in ascending order of (tap, channel).
+//
+// Training goes on in the same block.  For layer l it needs the upstream
+// gradient G = dA relu'(z) (the signs of z stay in registers), twice: G
+// channel-innermost for the input gradient, where the products of a tap are
+// one k step of 32 output channels, and G^T [co][pixel] for the weight
+// gradient, whose k runs over pixels.  The weight gradient's other operand is
+// the layer's input as [ci][18 rows][pitch 24], so that 8 pixels of a row are
+// one 16-byte load; a tap's shift by one column is an alignment of that load
+// with the dword beside it.  G overwrites the layer's input image once its
+// transpose is made.  Weight gradients stay in registers over all samples of
+// a block (5 accumulator tiles a layer and wave) and leave as one row of
+// sums per block.
+//
+// What bounds it: the chain of k loops, epilogues and barriers of one sample
+// per CU (a product of the largest layer is 9 MFMA steps); 11 MFLOP of a
+// sample's forward pass are about 1 us of a CU's BF16 rate.  Measured: a
+// training step of 256 samples (with Adam) 53.6 us, the tagging of 1792
+// leaves 83 us in this kernel.  Before, with im2col matrices, GEMMs and
+// elementwise kernels in HBM: 6424 us (5556 of them in a one-block sum of
+// 8192 bias rows, 545 in the GEMMs) and 290 us.
 // ---------------------------------------------------------------------------
-struct GemmArgs {
-  const uint16_t* A;
-  long sai, sak;
-  const uint16_t* B;
-  long sbj, sbk;
-  float* C;
-  long sci, scj;
-  int M, N, K, kchunk;
-  float* part;  // [nz][M][N] when K is split, else null
-  const uint16_t* X = nullptr;  // implicit im2col source (then A is unused)
-  int cp = 0;
-  int avec = 0, bvec = 0;       // set by gemm(): 16-byte loads for A, B
+constexpr int kCnnThreads = 512, kCnnWaves = kCnnThreads / 64;
+static_assert(kCnnWaves * 2 == kImg, "a wave takes two image rows");
+constexpr int kRing = kImg + 2, kRingPix = kRing * kRing;
+constexpr int kTapsW = 9 * kWidth;            // k extent of layers 2 and 3
+constexpr int kPitchW = kTapsW + 8;           // their weight rows (592 bytes)
+constexpr int kPitchWt = kWidth + 8;          // rows of W^T [tap * 32 + ci][co] (80 bytes)
+constexpr int kPitchG = kPix + 8;             // rows of G^T (528 bytes)
+constexpr int kXtRow = 24, kPitchXt = kRing * kXtRow + 8;  // transposed input: pixel x at column x + 8 (880 bytes)
+constexpr int kPitchA3 = kWidth + 1;
+constexpr int kCnnRows = 256;                 // blocks of a launch: one per CU
+// a block's row of gradient sums: [layer][tap][co][ci], biases [layer][co],
+// then loss, Wh [3][32], bh [3]
+constexpr int kPartW = 9 * kWidth * kWidth, kPartB = 3 * kPartW, kPartH = kPartB + 3 * kWidth;
+constexpr int kPartN = kPartH + 1 + kClasses * kWidth + kClasses;
+constexpr int kPart = (kPartN + 63) / 64 * 64;
+
+struct CnnOffsets {
+  int w[3], b[3], wh, bh;
 };
 
-__global__ __launch_bounds__(256) void k_gemm_bf16(const GemmArgs g) {
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int tiles_n = (g.N + 15) >> 4;
-  const int tile = blockIdx.x * 4 + wave;
-  const int ti = tile / tiles_n, tj = tile - ti * tiles_n;
-  if (ti * 16 >= g.M) return;  // uniform per wavefront
-  const int i = ti * 16 + (lane & 15), j = tj * 16 + (lane & 15);
-  const int kb = blockIdx.z * g.kchunk;
-  const int ke = min(g.K, kb + g.kchunk);
-  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+struct CnnArgs {
+  const float* params;   // packed FP32 parameters
+  CnnOffsets off;
+  const float* x;        // [B][nin][16][16]
+  int nin, B;
+  float* logits;         // [B][3] or null
+  const int32_t* labels; // training
+  float* acts;           // null or [3][B*256][32]: pre-activations
+  float* dacts;          // null or [3][B*256][32]: gradients of the post-ReLU outputs
+  float* part;           // training: [gridDim.x][kPart]
+};
+
+template <int CP, bool TRAIN>
+struct CnnLds {
+  static constexpr int STEPS1 = (9 * CP + 31) / 32;
+  static constexpr int PITCH1 = STEPS1 * 32 + 8;  // 16 bytes times an odd number, as kPitchW
+  static constexpr int WFWD = kWidth * PITCH1 + 2 * kWidth * kPitchW;
+  static_assert(!TRAIN || (WFWD >= kTapsW * kPitchWt + kWidth * kPitchG && WFWD >= 2 * kPix * kPitchA3),
+                "the backward operands and the last layer fit the forward weights' place");
+  alignas(16) uint16_t w[WFWD];
+  alignas(16) uint16_t x0[kRingPix * CP];
+  alignas(16) uint16_t a1[kRingPix * kWidth];
+  alignas(16) uint16_t a2[kRingPix * kWidth];
+  alignas(16) uint16_t xt[TRAIN ? kWidth * kPitchXt : 8];
+  float a3[TRAIN ? 4 : kPix * kPitchA3];  // training: in the weights' place
+  float bias[3][kWidth], wh[kClasses * kWidth], bh[4], pooled[kWidth], lg[4], red[kCnnWaves][kWidth];
+};
+
+// acc += the convolution of image rows 2 wave, 2 wave + 1 (C channels).
+template <int C>
+__device__ __forceinline__ void cnn_conv(const uint16_t* img, const uint16_t* w, int wave, int lane,
+                                         f32x4 (&acc)[2][2]) {
+  constexpr int K = 9 * C, STEPS = (K + 31) / 32, PITCH = STEPS * 32 + 8;
+  const int g = lane >> 4, c = lane & 15;
   const u16x8 zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
-  for (int k0 = kb; k0 < ke; k0 += 32) {
-    u16x8 a, b;
-    const int ks = k0 + 8 * (lane >> 4);  // this lane's first k
-    if (g.X) {
-      a = zero8;
-      if (ks < ke && i < g.M) {
-        const int tap = ks / g.cp, ci = ks - tap * g.cp;
-        const int bi = i / kPix, p = i - bi * kPix;
-        const int y = p / kImg + tap / 3 - 1, x = p % kImg + tap % 3 - 1;
-        if (y >= 0 && y < kImg && x >= 0 && x < kImg)
-          a = *reinterpret_cast<const u16x8*>(g.X + (long(bi) * kPix + y * kImg + x) * g.cp + ci);
-      }
-    } else if (g.avec) {
-      a = (ks < ke && i < g.M) ? *reinterpret_cast<const u16x8*>(g.A + i * g.sai + ks) : zero8;
-    } else {
+#pragma unroll 3
+  for (int s = 0; s < STEPS; ++s) {
+    const int ks = s * 32 + 8 * g;
+    const bool valid = STEPS * 32 == K || ks < K;  // past K the weights are zero, the image must not be NaN
+    const int tap = valid ? ks / C : 0, ci = valid ? ks - tap * C : 0;
+    const int ty = tap / 3, tx = tap - 3 * ty;
+    bf16x8 a[2], b[2];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const int k = ks + e;
-        a[e] = (k < ke && i < g.M) ? g.A[i * g.sai + k * g.sak] : uint16_t(0);
+    for (int t = 0; t < 2; ++t) {
+      const u16x8 v = *reinterpret_cast<const u16x8*>(img + ((2 * wave + t + ty) * kRing + c + tx) * C + ci);
+      a[t] = __builtin_bit_cast(bf16x8, valid ? v : zero8);
+      b[t] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u16x8*>(w + (t * 16 + c) * PITCH + ks));
+    }
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int n = 0; n < 2; ++n) acc[t][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[t], b[n], acc[t][n], 0, 0, 0);
+  }
+}
+
+// Weight gradient tiles of one layer: acc[k] (+)= G^T X of tap T0 + k for
+// output channels 16 coh .. and input channels 16 cih .., over the sample's
+// pixels (8 k steps of two image rows).
+template <int T0, int NTAP>
+__device__ __forceinline__ void cnn_wgrad(const uint16_t* gt, const uint16_t* xt, int coh, int cih, int lane,
+                                          f32x4 (&acc)[5]) {
+  const int g = lane >> 4, c = lane & 15;
+  const uint16_t* const ga = gt + (coh * 16 + c) * kPitchG + 8 * g;
+  const uint16_t* const xa = xt + (cih * 16 + c) * kPitchXt + (g >> 1) * kXtRow + 8 + 8 * (g & 1);
+#pragma unroll 1
+  for (int s = 0; s < kImg / 2; ++s) {
+    const bf16x8 a = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u16x8*>(ga + 32 * s));
+#pragma unroll
+    for (int ty = T0 / 3; ty <= (T0 + NTAP - 1) / 3; ++ty) {
+      const uint16_t* const p = xa + (2 * s + ty) * kXtRow;
+      const u32x4 d = *reinterpret_cast<const u32x4*>(p);
+      const unsigned lo = *reinterpret_cast<const unsigned*>(p - 2), hi = *reinterpret_cast<const unsigned*>(p + 8);
+#pragma unroll
+      for (int tx = 0; tx < 3; ++tx) {
+        const int k = 3 * ty + tx - T0;
+        if (k < 0 || k >= NTAP) continue;
+        u32x4 v = d;
+        if (tx == 0) {
+          v[0] = __builtin_amdgcn_alignbit(d[0], lo, 16);
+          v[1] = __builtin_amdgcn_alignbit(d[1], d[0], 16);
+          v[2] = __builtin_amdgcn_alignbit(d[2], d[1], 16);
+          v[3] = __builtin_amdgcn_alignbit(d[3], d[2], 16);
+        } else if (tx == 2) {
+          v[0] = __builtin_amdgcn_alignbit(d[1], d[0], 16);
+          v[1] = __builtin_amdgcn_alignbit(d[2], d[1], 16);
+          v[2] = __builtin_amdgcn_alignbit(d[3], d[2], 16);
+          v[3] = __builtin_amdgcn_alignbit(hi, d[3], 16);
+        }
+        acc[k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(bf16x8, v), acc[k], 0, 0, 0);
       }
     }
-    if (g.bvec) {
-      b = (ks < ke && j < g.N) ? *reinterpret_cast<const u16x8*>(g.B + j * g.sbj + ks) : zero8;
-    } else {
+  }
+}
+
+// out = the input gradient of image rows 2 wave, 2 wave + 1: each tap's
+// product over the 32 output channels, added in ascending order of the taps.
+__device__ __forceinline__ void cnn_dgrad(const uint16_t* gi, const uint16_t* wt, int wave, int lane,
+                                          f32x4 (&out)[2][2]) {
+  const int g = lane >> 4, c = lane & 15;
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const int k = ks + e;
-        b[e] = (k < ke && j < g.N) ? g.B[j * g.sbj + k * g.sbk] : uint16_t(0);
-      }
-    }
-    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b),
-                                                  acc, 0, 0, 0);
-  }
+  for (int t = 0; t < 2; ++t)
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int row = ti * 16 + 4 * (lane >> 4) + r, col = tj * 16 + (lane & 15);
-    if (row < g.M && col < g.N) {
-      if (g.part) g.part[(size_t(blockIdx.z) * g.M + row) * g.N + col] = acc[r];
-      else g.C[row * g.sci + col * g.scj] = acc[r];
+    for (int n = 0; n < 2; ++n) out[t][n] = zero;
+#pragma unroll 3
+  for (int tap = 0; tap < 9; ++tap) {
+    const int ty = tap / 3, tx = tap - 3 * ty;
+    bf16x8 a[2], b[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      a[t] = __builtin_bit_cast(
+          bf16x8, *reinterpret_cast<const u16x8*>(gi + ((2 * wave + t + 2 - ty) * kRing + c + 2 - tx) * kWidth + 8 * g));
+      b[t] = __builtin_bit_cast(bf16x8,
+                                *reinterpret_cast<const u16x8*>(wt + (tap * kWidth + t * 16 + c) * kPitchWt + 8 * g));
     }
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int n = 0; n < 2; ++n)
+        out[t][n] += __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[t], b[n], zero, 0, 0, 0);
   }
 }
 
-// C(i, j) = sum over z = 0, 1, ... of part[z][i][j], in that order.
-__global__ void k_sum_chunks(const float* part, int nz, int M, int N, float* C, long sci, long scj) {
-  const long n = long(M) * N;
-  for (long e = blockIdx.x * long(blockDim.x) + threadIdx.x; e < n; e += long(gridDim.x) * blockDim.x) {
-    float s = part[e];
-    for (int z = 1; z < nz; ++z) s += part[size_t(z) * n + e];
-    const long i = e / N, j = e - i * N;
-    C[i * sci + j * scj] = s;
-  }
-}
-
-// Chunks a split GEMM of this K uses: about K / 4096, at most kMaxChunks.
-constexpr int kMaxChunks = 64;
-int gemm_chunks(long K, int ksplit) {
-  const long kc = ((K + ksplit - 1) / ksplit + 31) / 32 * 32;
-  return int((K + kc - 1) / kc);
-}
-
-// ws: workspace of at least nz * M * N floats when ksplit > 1.
-static hipError_t gemm(const GemmArgs& g0, int ksplit, float* ws, hipStream_t st) {
-  GemmArgs g = g0;
-  auto al16 = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
-  g.avec = !g.X && g.sak == 1 && g.sai % 8 == 0 && g.K % 8 == 0 && al16(g.A);
-  g.bvec = g.sbk == 1 && g.sbj % 8 == 0 && g.K % 8 == 0 && al16(g.B);
-  if (g.X && (g.cp % 8 != 0 || g.K != 9 * g.cp || !al16(g.X))) return hipErrorInvalidValue;
-  const int tiles = ((g.M + 15) / 16) * ((g.N + 15) / 16);
-  const int kc = ((g.K + ksplit - 1) / ksplit + 31) / 32 * 32;
-  g.kchunk = kc;
-  const int nz = (g.K + kc - 1) / kc;
-  g.part = nz > 1 ? ws : nullptr;
-  hipLaunchKernelGGL(k_gemm_bf16, dim3(unsigned((tiles + 3) / 4), 1, unsigned(nz)), dim3(256), 0, st, g);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || nz == 1) return e;
-  const long n = long(g.M) * g.N;
-  hipLaunchKernelGGL(k_sum_chunks, dim3(unsigned(std::min<long>((n + 255) / 256, 4096))), dim3(256), 0, st, ws, nz,
-                     g.M, g.N, g.C, g.sci, g.scj);
-  return hipGetLastError();
-}
-
-// ---------------------------------------------------------------------------
-// im2col: Xcol[m = b*256 + y*16 + x][k = tap*cp + ci] = X(b, y+ky-1, x+kx-1, ci)
-// (zero outside the image and for ci >= c).  Source either FP32 NCHW (the
-// API input, rounded to BF16 here) or BF16 NHWC with cp channels.
-// ---------------------------------------------------------------------------
-__global__ void k_im2col(const float* xf, const uint16_t* xb, int B, int c, int cp, uint16_t* col) {
-  const long K = 9L * cp;
-  const long total = long(B) * kPix * K;
-  for (long e = blockIdx.x * long(blockDim.x) + threadIdx.x; e < total; e += long(gridDim.x) * blockDim.x) {
-    const long m = e / K;
-    const int k = int(e - m * K);
-    const int tap = k / cp, ci = k - tap * cp;
-    const int b = int(m / kPix), p = int(m - long(b) * kPix);
-    const int y = p / kImg + tap / 3 - 1, x = p % kImg + tap % 3 - 1;
-    uint16_t v = 0;
-    if (ci < c && y >= 0 && y < kImg && x >= 0 && x < kImg) {
-      if (xf) v = f2bf(xf[(long(b) * c + ci) * kPix + y * kImg + x]);
-      else v = xb[(long(b) * kPix + y * kImg + x) * cp + ci];
-    }
-    col[e] = v;
-  }
-}
-
-// X(b, c, y, x) FP32 NCHW -> BF16 NHWC with cp >= c channels (zero-padded)
-__global__ void k_to_nhwc(const float* xf, int B, int c, int cp, uint16_t* xb) {
-  const long total = long(B) * kPix * cp;
-  for (long e = blockIdx.x * long(blockDim.x) + threadIdx.x; e < total; e += long(gridDim.x) * blockDim.x) {
-    const int ci = int(e % cp);
-    const long bp = e / cp;
-    const int b = int(bp / kPix), p = int(bp - long(b) * kPix);
-    xb[e] = ci < c ? f2bf(xf[(long(b) * c + ci) * kPix + p]) : uint16_t(0);
-  }
-}
-
-// dX(b, y, x, ci) = sum over taps of dXcol[b, (y-ky+1, x-kx+1)][tap*cp + ci]
-__global__ void k_col2im(const float* dcol, int B, int cp, float* dx) {
-  const long total = long(B) * kPix * cp;
-  const long K = 9L * cp;
-  for (long e = blockIdx.x * long(blockDim.x) + threadIdx.x; e < total; e += long(gridDim.x) * blockDim.x) {
-    const int ci = int(e % cp);
-    const long bp = e / cp;
-    const int b = int(bp / kPix), p = int(bp - long(b) * kPix);
+// Transposed copy of an image of C channels, [ci][row][x + 8]; its ring
+// columns and rows stay zero.
+template <int C>
+__device__ __forceinline__ void cnn_transpose(const uint16_t* img, uint16_t* xt, int tid) {
+#pragma unroll 1
+  for (int e = tid; e < kPix * (C / 8); e += kCnnThreads) {
+    const int p = e & (kPix - 1), c0 = (e / kPix) * 8;
     const int y = p / kImg, x = p % kImg;
-    float s = 0.f;
-    for (int tap = 0; tap < 9; ++tap) {
-      const int yy = y - tap / 3 + 1, xx = x - tap % 3 + 1;
-      if (yy < 0 || yy >= kImg || xx < 0 || xx >= kImg) continue;
-      s += dcol[(long(b) * kPix + yy * kImg + xx) * K + tap * cp + ci];
+    const u16x8 v = *reinterpret_cast<const u16x8*>(img + ((y + 1) * kRing + x + 1) * C + c0);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) xt[(c0 + k) * kPitchXt + (y + 1) * kXtRow + x + 8] = v[k];
+  }
+}
+
+// BF16 weights of a layer with cin input channels, [co][tap * C + ci] with
+// the given row pitch.
+template <int C>
+__device__ __forceinline__ void cnn_weights(const float* W, int cin, int pitch, uint16_t* w, int tid) {
+#pragma unroll 6
+  for (int e = tid; e < kWidth * cin * 9; e += kCnnThreads) {
+    const int co = e / (cin * 9), r = e - co * cin * 9, ci = r / 9, tap = r - ci * 9;
+    w[co * pitch + tap * C + ci] = f2bf(W[e]);
+  }
+}
+
+// W^T [tap * 32 + ci][co] of a layer with 32 input channels.
+__device__ __forceinline__ void cnn_weights_t(const float* W, uint16_t* wt, int tid) {
+#pragma unroll 6
+  for (int e = tid; e < kWidth * kTapsW; e += kCnnThreads) {
+    const int co = e / kTapsW, r = e - co * kTapsW, ci = r / 9, tap = r - ci * 9;
+    wt[(tap * kWidth + ci) * kPitchWt + co] = f2bf(W[e]);
+  }
+}
+
+template <int CP, bool TRAIN>
+__global__ __launch_bounds__(kCnnThreads) void k_cnn(const CnnArgs A) {
+  using L_t = CnnLds<CP, TRAIN>;
+  __shared__ L_t S;
+  const int tid0 = threadIdx.x;
+  uint16_t* const w1 = S.w;
+  uint16_t* const w2 = w1 + kWidth * L_t::PITCH1;
+  uint16_t* const w3 = w2 + kWidth * kPitchW;
+  float* const a3 = TRAIN ? reinterpret_cast<float*>(S.w) : S.a3;
+  uint16_t* const wt = S.w;                       // training, backward
+  uint16_t* const gt = S.w + kTapsW * kPitchWt;
+
+  auto zero = [&](uint16_t* p, int n) {  // n even
+#pragma unroll 1
+    for (int e = tid0; e < n / 2; e += kCnnThreads) reinterpret_cast<unsigned*>(p)[e] = 0;
+  };
+  auto weights = [&](int tid) {  // w1's padding (channels past nin, k past 9 CP) must be zero
+    cnn_weights<CP>(A.params + A.off.w[0], A.nin, L_t::PITCH1, w1, tid);
+    cnn_weights<kWidth>(A.params + A.off.w[1], kWidth, kPitchW, w2, tid);
+    cnn_weights<kWidth>(A.params + A.off.w[2], kWidth, kPitchW, w3, tid);
+  };
+  zero(S.x0, kRingPix * CP);
+  zero(S.a1, kRingPix * kWidth);
+  zero(S.a2, kRingPix * kWidth);
+  if (TRAIN) zero(S.xt, kWidth * kPitchXt);
+  if (tid0 < 3 * kWidth) S.bias[tid0 / kWidth][tid0 % kWidth] = A.params[A.off.b[tid0 / kWidth] + tid0 % kWidth];
+  if (tid0 < kClasses * kWidth) S.wh[tid0] = A.params[A.off.wh + tid0];
+  if (tid0 < kClasses) S.bh[tid0] = A.params[A.off.bh + tid0];
+  if (!TRAIN) {
+    zero(w1, kWidth * L_t::PITCH1);
+    __syncthreads();
+    weights(tid0);
+  }
+
+  f32x4 gw[3][5];  // weight gradients, TRAIN
+  float gb[3][2] = {{0.f, 0.f}, {0.f, 0.f}, {0.f, 0.f}};
+  float gh[kClasses] = {0.f, 0.f, 0.f}, gbh = 0.f, gloss = 0.f;
+  if (TRAIN)
+#pragma unroll
+    for (int l = 0; l < 3; ++l)
+#pragma unroll
+      for (int k = 0; k < 5; ++k) gw[l][k] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  for (int b = blockIdx.x; b < A.B; b += gridDim.x) {
+    // opaque to the compiler, so that the addresses made from it are not all
+    // kept in registers across the sample loop (they spilled)
+    int tid = tid0;
+    asm volatile("" : "+v"(tid));
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int g = lane >> 4, c = lane & 15;
+    const int coh = wave & 1, cih = (wave >> 1) & 1;
+    if (TRAIN) {  // the last sample's backward pass used the weights' place
+      __syncthreads();
+      zero(w1, kWidth * L_t::PITCH1);
     }
-    dx[e] = s;
+    __syncthreads();
+    if (TRAIN) weights(tid);
+    for (int e = tid; e < kPix * (CP / 8); e += kCnnThreads) {
+      const int p = e & (kPix - 1), c0 = (e / kPix) * 8;
+      u16x8 v;
+#pragma unroll
+      for (int k = 0; k < 8; ++k)
+        v[k] = c0 + k < A.nin ? f2bf(A.x[(size_t(b) * A.nin + c0 + k) * kPix + p]) : uint16_t(0);
+      *reinterpret_cast<u16x8*>(S.x0 + ((p / kImg + 1) * kRing + p % kImg + 1) * CP + c0) = v;
+    }
+    __syncthreads();
+
+    // ---- forward.  zpos[l]: bit t * 8 + n * 4 + r set where the lane's z > 0
+    unsigned zpos[3];
+    auto layer = [&](int l, f32x4 (&acc)[2][2], uint16_t* out) {
+      unsigned m = 0;
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int n = 0; n < 2; ++n)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int y = 2 * wave + t, x = 4 * g + r, ch = n * 16 + c;
+            const float z = acc[t][n][r] + S.bias[l][ch];
+            const bool pos = z > 0.f;
+            acc[t][n][r] = pos ? z : 0.f;
+            if (pos) m |= 1u << (t * 8 + n * 4 + r);
+            if (out) out[((y + 1) * kRing + x + 1) * kWidth + ch] = f2bf(acc[t][n][r]);
+            if (A.acts) A.acts[((size_t(l) * A.B + b) * kPix + y * kImg + x) * kWidth + ch] = z;
+          }
+      zpos[l] = m;
+    };
+    f32x4 acc[2][2];
+    auto clear = [&]() {
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int n = 0; n < 2; ++n) acc[t][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+    };
+    clear();
+    cnn_conv<CP>(S.x0, w1, wave, lane, acc);
+    layer(0, acc, S.a1);
+    __syncthreads();
+    clear();
+    cnn_conv<kWidth>(S.a1, w2, wave, lane, acc);
+    layer(1, acc, S.a2);
+    __syncthreads();
+    clear();
+    cnn_conv<kWidth>(S.a2, w3, wave, lane, acc);
+    layer(2, acc, nullptr);
+    if (TRAIN) __syncthreads();  // a3 takes the weights' place
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int n = 0; n < 2; ++n)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          a3[((2 * wave + t) * kImg + 4 * g + r) * kPitchA3 + n * 16 + c] = acc[t][n][r];
+    __syncthreads();
+
+    // ---- head: the pooled mean adds the pixels in order
+    if (tid < kWidth) {
+      float s = 0.f;
+#pragma unroll 16
+      for (int p = 0; p < kPix; ++p) s += a3[p * kPitchA3 + tid];
+      S.pooled[tid] = s * (1.0f / kPix);
+    }
+    __syncthreads();
+    if (tid < kClasses) {
+      float s = S.bh[tid];
+      for (int k = 0; k < kWidth; ++k) s += S.wh[tid * kWidth + k] * S.pooled[k];
+      S.lg[tid] = s;
+      if (A.logits) A.logits[size_t(b) * kClasses + tid] = s;
+    }
+    if (!TRAIN) continue;  // pooled is written again several barriers later
+    __syncthreads();
+    // softmax cross-entropy: every thread forms dl, then dA of the pooling
+    // for its two channels
+    const int lab = min(max(int(A.labels[b]), 0), kClasses - 1);
+    const float mx = fmaxf(S.lg[0], fmaxf(S.lg[1], S.lg[2]));
+    float den = 0.f;
+    for (int k = 0; k < kClasses; ++k) den += expf(S.lg[k] - mx);
+    float dl[kClasses];
+    for (int k = 0; k < kClasses; ++k) dl[k] = (expf(S.lg[k] - mx) / den - (k == lab ? 1.f : 0.f)) / A.B;
+    if (tid == 0) gloss += -(S.lg[lab] - mx - logf(den)) / A.B;
+    if (tid < kWidth)
+      for (int k = 0; k < kClasses; ++k) gh[k] += dl[k] * S.pooled[tid];
+    if (tid < kClasses) gbh += dl[tid];
+    f32x4 dA[2][2];
+#pragma unroll
+    for (int n = 0; n < 2; ++n) {
+      float dp = 0.f;
+      for (int k = 0; k < kClasses; ++k) dp += dl[k] * S.wh[k * kWidth + n * 16 + c];
+      dp *= 1.0f / kPix;
+#pragma unroll
+      for (int t = 0; t < 2; ++t) dA[t][n] = f32x4{dp, dp, dp, dp};
+    }
+
+    // ---- backward.  put: G = dA relu'(z) of layer l into G^T and, where
+    // gi is given, channel-innermost
+    auto put = [&](int l, uint16_t* gi) {
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int n = 0; n < 2; ++n) {
+          const int y = 2 * wave + t, ch = n * 16 + c;
+          u16x4 h;
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const float v = (zpos[l] >> (t * 8 + n * 4 + r)) & 1u ? dA[t][n][r] : 0.f;
+            h[r] = f2bf(v);
+            gb[l][n] += v;
+            if (gi) gi[((y + 1) * kRing + 4 * g + r + 1) * kWidth + ch] = h[r];
+            if (A.dacts)
+              A.dacts[((size_t(l) * A.B + b) * kPix + y * kImg + 4 * g + r) * kWidth + ch] = dA[t][n][r];
+          }
+          *reinterpret_cast<u16x4*>(gt + ch * kPitchG + y * kImg + 4 * g) = h;
+        }
+    };
+    auto wgrad = [&](f32x4 (&acc)[5]) {
+      if (wave < kCnnWaves / 2)
+        cnn_wgrad<0, 5>(gt, S.xt, coh, cih, lane, acc);
+      else
+        cnn_wgrad<5, 4>(gt, S.xt, coh, cih, lane, acc);
+    };
+    __syncthreads();  // a3 has been read
+#pragma unroll
+    for (int l = 2; l >= 1; --l) {
+      uint16_t* const in = l == 2 ? S.a2 : S.a1;
+      cnn_weights_t(A.params + A.off.w[l], wt, tid);
+      cnn_transpose<kWidth>(in, S.xt, tid);
+      __syncthreads();
+      put(l, in);
+      __syncthreads();
+      wgrad(gw[l]);
+      cnn_dgrad(in, wt, wave, lane, dA);
+      __syncthreads();
+    }
+    cnn_transpose<CP>(S.x0, S.xt, tid);
+    put(0, nullptr);
+    __syncthreads();
+    if (16 * cih < CP) wgrad(gw[0]);
   }
+
+  if (!TRAIN) return;
+  // ---- the block's row of sums
+  const int tid = tid0, wave = tid >> 6, lane = tid & 63;
+  const int g = lane >> 4, c = lane & 15;
+  const int coh = wave & 1, cih = (wave >> 1) & 1;
+  float* const P = A.part + size_t(blockIdx.x) * kPart;
+  const int tap0 = wave < kCnnWaves / 2 ? 0 : 5, ntap = wave < kCnnWaves / 2 ? 5 : 4;
+#pragma unroll
+  for (int l = 0; l < 3; ++l) {
+#pragma unroll
+    for (int k = 0; k < 5; ++k)
+      if (k < ntap)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          P[l * kPartW + ((tap0 + k) * kWidth + coh * 16 + 4 * g + r) * kWidth + cih * 16 + c] = gw[l][k][r];
+    // bias: over the wave's pixels, then the waves in order
+#pragma unroll
+    for (int n = 0; n < 2; ++n) {
+      float v = gb[l][n];
+      v += __shfl_xor(v, 16);
+      v += __shfl_xor(v, 32);
+      if (g == 0) S.red[wave][n * 16 + c] = v;
+    }
+    __syncthreads();
+    if (tid < kWidth) {
+      float s = 0.f;
+      for (int k = 0; k < kCnnWaves; ++k) s += S.red[k][tid];
+      P[kPartB + l * kWidth + tid] = s;
+    }
+    __syncthreads();
+  }
+  if (tid == 0) P[kPartH] = gloss;
+  if (tid < kWidth)
+    for (int k = 0; k < kClasses; ++k) P[kPartH + 1 + k * kWidth + tid] = gh[k];
+  if (tid < kClasses) P[kPartH + 1 + kClasses * kWidth + tid] = gbh;
 }
 
-// Z = Y + bias (FP32 [M][32]); A = relu(Z) stored BF16 (next layer input)
-// and FP32 (pooling of the last layer).
-__global__ void k_bias_relu(float* z, const float* bias, long M, uint16_t* ab, float* af32) {
-  for (long e = blockIdx.x * long(blockDim.x) + threadIdx.x; e < M * kWidth; e += long(gridDim.x) * blockDim.x) {
-    const float v = z[e] + bias[e % kWidth];
-    z[e] = v;
-    const float a = v > 0.f ? v : 0.f;
-    ab[e] = f2bf(a);
-    if (af32) af32[e] = a;
-  }
-}
-
-// Weight matrices from the FP32 masters: Wm[co][tap*cp + ci] (forward) and
-// Wt[tap*cp + ci][co] (input gradient), BF16; zero for padded ci.
-__global__ void k_pack_weights(const float* W, int c, int cp, uint16_t* Wm, uint16_t* Wt) {
-  const int K = 9 * cp;
-  for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < kWidth * K; e += gridDim.x * blockDim.x) {
-    const int co = e / K, k = e - co * K, tap = k / cp, ci = k - tap * cp;
-    const uint16_t v = ci < c ? f2bf(W[((co * c + ci) * 3 + tap / 3) * 3 + tap % 3]) : uint16_t(0);
-    Wm[e] = v;
-    Wt[k * kWidth + co] = v;
-  }
-}
-
-// Head: pooled mean, logits, and (if labels) softmax cross-entropy, its
-// gradient w.r.t. the head parameters and the broadcast pooling gradient.
-// One block of 32 x 8 threads per 8 samples.  Sample b writes its terms of
-// the batch sums to hp[b][kHeadTerms] (loss, Wh [3][32], bh [3]);
-// k_head_sum adds them in sample order.
-constexpr int kHeadTerms = 1 + kClasses * kWidth + kClasses;
-__global__ void k_head(const float* a3, int B, const float* Wh, const float* bh, float* logits, const int32_t* labels,
-                       float* hp, float* dA3) {
-  const int c = threadIdx.x & 31, sb = threadIdx.x >> 5;
-  const int b = blockIdx.x * 8 + sb;
-  __shared__ float pooled[8][kWidth], lg[8][4];
-  if (b < B) {
-    float s = 0.f;
-    for (int p = 0; p < kPix; ++p) s += a3[(long(b) * kPix + p) * kWidth + c];
-    pooled[sb][c] = s * (1.0f / kPix);
-  }
-  __syncthreads();
-  if (b < B && c < kClasses) {
-    float s = bh[c];
-    for (int k = 0; k < kWidth; ++k) s += Wh[c * kWidth + k] * pooled[sb][k];
-    lg[sb][c] = s;
-    logits[b * kClasses + c] = s;
-  }
-  __syncthreads();
-  if (!labels || b >= B) return;
-  const int lab = min(max(int(labels[b]), 0), kClasses - 1);
-  const float mx = fmaxf(lg[sb][0], fmaxf(lg[sb][1], lg[sb][2]));
-  float den = 0.f;
-  for (int k = 0; k < kClasses; ++k) den += expf(lg[sb][k] - mx);
-  float dl[kClasses];
-  for (int k = 0; k < kClasses; ++k) dl[k] = (expf(lg[sb][k] - mx) / den - (k == lab ? 1.f : 0.f)) / B;
-  float* const t = hp + size_t(b) * kHeadTerms;
-  if (c == 0) t[0] = -(lg[sb][lab] - mx - logf(den)) / B;
-  float dp = 0.f;
-  for (int k = 0; k < kClasses; ++k) {
-    t[1 + k * kWidth + c] = dl[k] * pooled[sb][c];
-    dp += dl[k] * Wh[k * kWidth + c];
-  }
-  if (c < kClasses) t[1 + kClasses * kWidth + c] = dl[c];
-  for (int p = 0; p < kPix; ++p) dA3[(long(b) * kPix + p) * kWidth + c] = dp * (1.0f / kPix);
-}
-
-// loss, gWh, gbh: the per-sample terms summed over b = 0, 1, ... in order.
-__global__ void k_head_sum(const float* hp, int B, float* loss, float* gWh, float* gbh) {
-  const int e = threadIdx.x;
-  if (e >= kHeadTerms) return;
+// grad (packed order) and loss: the blocks' rows added in a fixed order, four
+// runs of rows side by side and then their sums.
+__global__ __launch_bounds__(256) void k_cnn_grad(const float* part, int rows, CnnOffsets off, int nin, float* grad,
+                                                  float* loss) {
+  __shared__ float red[4][64];
+  const int e = blockIdx.x * 64 + (threadIdx.x & 63), q = threadIdx.x >> 6;
+  const int per = (rows + 3) / 4, r1 = min(rows, (q + 1) * per);
   float s = 0.f;
-  for (int b = 0; b < B; ++b) s += hp[size_t(b) * kHeadTerms + e];
-  if (e == 0) *loss = s;
-  else if (e <= kClasses * kWidth) gWh[e - 1] = s;
-  else gbh[e - 1 - kClasses * kWidth] = s;
-}
-
-// G = dA * relu'(Z): FP32 for the bias gradient, BF16 for the products.
-// Block k writes its bias partial sums to bpart[k][32] (a thread's elements
-// all belong to channel threadIdx.x % 32, since the stride is a multiple of
-// 32); k_bias_sum adds the blocks in order.
-__global__ void k_relu_back(const float* dA, const float* z, long M, uint16_t* gb, float* bpart) {
-  __shared__ float part[256];
-  const int c = threadIdx.x & 31;
-  float s = 0.f;
-  for (long e = blockIdx.x * long(blockDim.x) + threadIdx.x; e < M * kWidth; e += long(gridDim.x) * blockDim.x) {
-    const float g = z[e] > 0.f ? dA[e] : 0.f;
-    gb[e] = f2bf(g);
-    s += g;
-  }
-  part[threadIdx.x] = s;
+#pragma unroll 8
+  for (int r = q * per; r < r1; ++r) s += part[size_t(r) * kPart + e];
+  red[q][threadIdx.x & 63] = s;
   __syncthreads();
-  if (threadIdx.x < 32) {
-    float t = 0.f;
-    for (int w = 0; w < 8; ++w) t += part[w * 32 + c];
-    bpart[size_t(blockIdx.x) * kWidth + c] = t;
+  if (q != 0 || e >= kPartN) return;
+  s = (red[0][threadIdx.x] + red[1][threadIdx.x]) + (red[2][threadIdx.x] + red[3][threadIdx.x]);
+  if (e < kPartB) {
+    const int l = e / kPartW, f = e - l * kPartW;
+    const int tap = f / (kWidth * kWidth), co = f / kWidth % kWidth, ci = f % kWidth;
+    const int cin = l == 0 ? nin : kWidth;
+    if (ci < cin) grad[off.w[l] + (co * cin + ci) * 9 + tap] = s;
+  } else if (e < kPartH) {
+    grad[off.b[(e - kPartB) / kWidth] + (e - kPartB) % kWidth] = s;
+  } else if (e == kPartH) {
+    *loss = s;
+  } else if (e <= kPartH + kClasses * kWidth) {
+    grad[off.wh + e - kPartH - 1] = s;
+  } else {
+    grad[off.bh + e - kPartH - 1 - kClasses * kWidth] = s;
   }
 }
 
-__global__ void k_bias_sum(const float* bpart, int nblocks, float* gbias) {
-  const int c = threadIdx.x;
-  if (c >= kWidth) return;
-  float s = 0.f;
-  for (int k = 0; k < nblocks; ++k) s += bpart[size_t(k) * kWidth + c];
-  gbias[c] = s;
-}
-
-// dW packed order from the GEMM layout dWm[co][tap*cp + ci].
-__global__ void k_unpack_wgrad(const float* dWm, int c, int cp, float* gW) {
-  const int n = kWidth * c * 9;
-  for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < n; e += gridDim.x * blockDim.x) {
-    const int co = e / (c * 9), r = e - co * c * 9, ci = r / 9, tap = r - ci * 9;
-    gW[e] = dWm[co * 9 * cp + tap * cp + ci];
+template <bool TRAIN>
+static hipError_t launch_cnn(int cp, const CnnArgs& A, int blocks, hipStream_t st) {
+  const dim3 grid(static_cast<unsigned>(blocks)), thr(kCnnThreads);
+  switch (cp) {
+    case 8: hipLaunchKernelGGL((k_cnn<8, TRAIN>), grid, thr, 0, st, A); break;
+    case 16: hipLaunchKernelGGL((k_cnn<16, TRAIN>), grid, thr, 0, st, A); break;
+    case 24: hipLaunchKernelGGL((k_cnn<24, TRAIN>), grid, thr, 0, st, A); break;
+    case 32: hipLaunchKernelGGL((k_cnn<32, TRAIN>), grid, thr, 0, st, A); break;
+    default: return hipErrorInvalidValue;
   }
+  return hipGetLastError();
 }
 
 __global__ void k_adam(float* p, float* m1, float* m2, const float* g, int n, float lr, float b1, float b2, float eps,
@@ -414,29 +611,19 @@ using namespace af;
 
 struct af_cnn {
   int nin, cp1, nparams;
-  size_t off_w[3], off_b[3], off_wh, off_bh;
+  CnnOffsets off;
   float* d_params = nullptr;  // FP32 masters
   float* d_m1 = nullptr;
   float* d_m2 = nullptr;
   float* d_grad = nullptr;
-  // packed BF16 weights
-  uint16_t* d_wm[3] = {nullptr, nullptr, nullptr};
-  uint16_t* d_wt[3] = {nullptr, nullptr, nullptr};
-  // activation workspace for a batch of up to cap samples
+  // inputs and logits of af_cnn_tag for up to cap leaves
   int cap = 0;
-  uint16_t* d_col[3] = {nullptr, nullptr, nullptr};
-  float* d_z[3] = {nullptr, nullptr, nullptr};
-  uint16_t* d_ab[3] = {nullptr, nullptr, nullptr};
-  float* d_a3 = nullptr;
-  float* d_dA = nullptr;
-  float* d_dcol = nullptr;
-  uint16_t* d_g = nullptr;
-  float* d_dwm = nullptr;
   float* d_logits = nullptr;
   float* d_feat = nullptr;
-  float* d_part = nullptr;  // split-K, bias and head partial sums (fixed-order reductions)
+  // training: the blocks' rows of gradient sums
+  int part_rows = 0;
+  float* d_part = nullptr;
   float* d_norm = nullptr;  // mean[nin], inv_std[nin]
-  std::string err;
 };
 
 namespace {
@@ -452,89 +639,27 @@ af_status cfail(af_status s, const std::string& m) {
   } while (0)
 
 int grid_for(long n) { return int(std::min<long>((n + 255) / 256, 8192)); }
-// K split of the weight-gradient GEMMs (K = B * 256 pixels): chunks of about
-// 4096 pixels, at most kMaxChunks
-int wgrad_split(long M) { return int(std::min<long>(std::max<long>(1, M / 4096), kMaxChunks)); }
 
-af_status ensure_batch(af_cnn* c, int B) {
-  if (B <= c->cap) return AF_OK;
-  for (int l = 0; l < 3; ++l) {
-    (void)hipFree(c->d_col[l]);
-    (void)hipFree(c->d_z[l]);
-    (void)hipFree(c->d_ab[l]);
-  }
-  (void)hipFree(c->d_a3);
-  (void)hipFree(c->d_dA);
-  (void)hipFree(c->d_dcol);
-  (void)hipFree(c->d_g);
+af_status ensure_tag(af_cnn* c, int n) {
+  if (n <= c->cap) return AF_OK;
   (void)hipFree(c->d_logits);
   (void)hipFree(c->d_feat);
-  (void)hipFree(c->d_part);
-  const long M = long(B) * kPix;
-  for (int l = 0; l < 3; ++l) {
-    const int cp = l == 0 ? c->cp1 : kWidth;
-    CNN_HIP(hipMalloc(&c->d_col[l], size_t(M) * 9 * cp * 2));
-    CNN_HIP(hipMalloc(&c->d_z[l], size_t(M) * kWidth * 4));
-    CNN_HIP(hipMalloc(&c->d_ab[l], size_t(M) * kWidth * 2));
-  }
-  CNN_HIP(hipMalloc(&c->d_a3, size_t(M) * kWidth * 4));
-  CNN_HIP(hipMalloc(&c->d_dA, size_t(M) * kWidth * 4));
-  CNN_HIP(hipMalloc(&c->d_dcol, size_t(M) * 9 * kWidth * 4));
-  CNN_HIP(hipMalloc(&c->d_g, size_t(M) * kWidth * 2));
-  CNN_HIP(hipMalloc(&c->d_logits, size_t(B) * kClasses * 4));
-  CNN_HIP(hipMalloc(&c->d_feat, size_t(B) * c->nin * kPix * 4));
-  // partial sums: split-K chunks of the weight-gradient GEMMs, per-block
-  // bias sums, per-sample head terms
-  const size_t part = std::max({size_t(gemm_chunks(M, wgrad_split(M))) * kWidth * 9 * kWidth,
-                                size_t(grid_for(M * kWidth)) * kWidth, size_t(B) * kHeadTerms});
-  CNN_HIP(hipMalloc(&c->d_part, part * 4));
-  c->cap = B;
+  c->d_logits = c->d_feat = nullptr;
+  c->cap = 0;
+  CNN_HIP(hipMalloc(&c->d_logits, size_t(n) * kClasses * 4));
+  CNN_HIP(hipMalloc(&c->d_feat, size_t(n) * c->nin * kPix * 4));
+  c->cap = n;
   return AF_OK;
 }
 
-af_status pack_weights(af_cnn* c, hipStream_t st) {
-  for (int l = 0; l < 3; ++l) {
-    const int cin = l == 0 ? c->nin : kWidth, cp = l == 0 ? c->cp1 : kWidth;
-    hipLaunchKernelGGL(k_pack_weights, dim3(grid_for(kWidth * 9 * cp)), dim3(256), 0, st, c->d_params + c->off_w[l],
-                       cin, cp, c->d_wm[l], c->d_wt[l]);
-    CNN_HIP(hipGetLastError());
-  }
-  return AF_OK;
-}
-
-// With cols (training), each layer's im2col matrix is written to d_col[l]
-// (the weight gradient reads it); without (inference), the input is
-// converted once to BF16 NHWC and every layer's GEMM reads its im2col
-// matrix in place from the NHWC images.  Both give the same products in the
-// same k order, bit for bit.
-af_status forward(af_cnn* c, const float* x, int B, hipStream_t st, bool cols = true) {
-  af_status s = ensure_batch(c, B);
-  if (s != AF_OK) return s;
-  if ((s = pack_weights(c, st)) != AF_OK) return s;
-  const long M = long(B) * kPix;
-  if (!cols) {
-    // layer-0 input as BF16 NHWC with cp1 channels (d_col[0] holds 9x that)
-    hipLaunchKernelGGL(k_to_nhwc, dim3(grid_for(M * c->cp1)), dim3(256), 0, st, x, B, c->nin, c->cp1, c->d_col[0]);
-    CNN_HIP(hipGetLastError());
-  }
-  for (int l = 0; l < 3; ++l) {
-    const int cp = l == 0 ? c->cp1 : kWidth;
-    const int K = 9 * cp;
-    GemmArgs g{c->d_col[l], K, 1, c->d_wm[l], K, 1, c->d_z[l], kWidth, 1, int(M), kWidth, K, 0, nullptr};
-    if (cols) {
-      hipLaunchKernelGGL(k_im2col, dim3(grid_for(M * K)), dim3(256), 0, st, l == 0 ? x : nullptr,
-                         l == 0 ? nullptr : c->d_ab[l - 1], B, l == 0 ? c->nin : kWidth, cp, c->d_col[l]);
-      CNN_HIP(hipGetLastError());
-    } else {
-      g.X = l == 0 ? c->d_col[0] : c->d_ab[l - 1];
-      g.cp = cp;
-    }
-    CNN_HIP(gemm(g, 1, nullptr, st));
-    hipLaunchKernelGGL(k_bias_relu, dim3(grid_for(M * kWidth)), dim3(256), 0, st, c->d_z[l],
-                       c->d_params + c->off_b[l], M, c->d_ab[l], l == 2 ? c->d_a3 : nullptr);
-    CNN_HIP(hipGetLastError());
-  }
-  return AF_OK;
+CnnArgs cnn_args(const af_cnn* c, const float* x, int B) {
+  CnnArgs A{};
+  A.params = c->d_params;
+  A.off = c->off;
+  A.x = x;
+  A.nin = c->nin;
+  A.B = B;
+  return A;
 }
 
 }  // namespace
@@ -548,32 +673,26 @@ af_status af_cnn_create(int32_t nin, af_cnn** out) {
   auto c = std::make_unique<af_cnn>();
   c->nin = nin;
   c->cp1 = (nin + 7) / 8 * 8;
-  size_t o = 0;
+  int o = 0;
   for (int l = 0; l < 3; ++l) {
     const int cin = l == 0 ? nin : kWidth;
-    c->off_w[l] = o;
-    o += size_t(kWidth) * cin * 9;
-    c->off_b[l] = o;
+    c->off.w[l] = o;
+    o += kWidth * cin * 9;
+    c->off.b[l] = o;
     o += kWidth;
   }
-  c->off_wh = o;
+  c->off.wh = o;
   o += kClasses * kWidth;
-  c->off_bh = o;
+  c->off.bh = o;
   o += kClasses;
-  c->nparams = int(o);
-  CNN_HIP(hipMalloc(&c->d_params, o * 4));
-  CNN_HIP(hipMalloc(&c->d_m1, o * 4));
-  CNN_HIP(hipMalloc(&c->d_m2, o * 4));
-  CNN_HIP(hipMalloc(&c->d_grad, o * 4));
-  CNN_HIP(hipMemset(c->d_params, 0, o * 4));
-  CNN_HIP(hipMemset(c->d_m1, 0, o * 4));
-  CNN_HIP(hipMemset(c->d_m2, 0, o * 4));
-  for (int l = 0; l < 3; ++l) {
-    const int cp = l == 0 ? c->cp1 : kWidth;
-    CNN_HIP(hipMalloc(&c->d_wm[l], size_t(kWidth) * 9 * cp * 2));
-    CNN_HIP(hipMalloc(&c->d_wt[l], size_t(kWidth) * 9 * cp * 2));
-  }
-  CNN_HIP(hipMalloc(&c->d_dwm, size_t(kWidth) * 9 * kWidth * 4));
+  c->nparams = o;
+  CNN_HIP(hipMalloc(&c->d_params, size_t(o) * 4));
+  CNN_HIP(hipMalloc(&c->d_m1, size_t(o) * 4));
+  CNN_HIP(hipMalloc(&c->d_m2, size_t(o) * 4));
+  CNN_HIP(hipMalloc(&c->d_grad, size_t(o) * 4));
+  CNN_HIP(hipMemset(c->d_params, 0, size_t(o) * 4));
+  CNN_HIP(hipMemset(c->d_m1, 0, size_t(o) * 4));
+  CNN_HIP(hipMemset(c->d_m2, 0, size_t(o) * 4));
   CNN_HIP(hipMalloc(&c->d_norm, size_t(2) * nin * 4));
   std::vector<float> norm(2 * nin, 0.f);
   for (int i = 0; i < nin; ++i) norm[nin + i] = 1.f;
@@ -588,18 +707,6 @@ af_status af_cnn_destroy(af_cnn* c) {
   (void)hipFree(c->d_m1);
   (void)hipFree(c->d_m2);
   (void)hipFree(c->d_grad);
-  for (int l = 0; l < 3; ++l) {
-    (void)hipFree(c->d_wm[l]);
-    (void)hipFree(c->d_wt[l]);
-    (void)hipFree(c->d_col[l]);
-    (void)hipFree(c->d_z[l]);
-    (void)hipFree(c->d_ab[l]);
-  }
-  (void)hipFree(c->d_a3);
-  (void)hipFree(c->d_dA);
-  (void)hipFree(c->d_dcol);
-  (void)hipFree(c->d_g);
-  (void)hipFree(c->d_dwm);
   (void)hipFree(c->d_logits);
   (void)hipFree(c->d_feat);
   (void)hipFree(c->d_part);
@@ -634,58 +741,33 @@ af_status af_cnn_set_normalization(af_cnn* c, const float* mean, const float* in
 
 af_status af_cnn_forward(af_cnn* c, const float* x, int32_t B, float* logits, float* acts, hipStream_t st) {
   if (!c || !x || !logits || B <= 0) return cfail(AF_ERR_ARG, "bad argument");
-  af_status s = forward(c, x, B, st, false);
-  if (s != AF_OK) return s;
-  hipLaunchKernelGGL(k_head, dim3((B + 7) / 8), dim3(256), 0, st, c->d_a3, B, c->d_params + c->off_wh,
-                     c->d_params + c->off_bh, logits, nullptr, nullptr, nullptr);
-  CNN_HIP(hipGetLastError());
-  if (acts) {
-    // pre-activations of the three layers, FP32 [3][B*256][32] (NHWC)
-    const size_t M = size_t(B) * kPix;
-    for (int l = 0; l < 3; ++l)
-      CNN_HIP(hipMemcpyAsync(acts + l * M * kWidth, c->d_z[l], M * kWidth * 4, hipMemcpyDeviceToDevice, st));
-  }
+  CnnArgs A = cnn_args(c, x, B);
+  A.logits = logits;
+  A.acts = acts;
+  CNN_HIP(launch_cnn<false>(c->cp1, A, std::min(B, kCnnRows), st));
   return AF_OK;
 }
 
 af_status af_cnn_loss_grad(af_cnn* c, const float* x, const int32_t* labels, int32_t B, float* loss, float* grad,
                            float* dacts, hipStream_t st) {
   if (!c || !x || !labels || !loss || B <= 0) return cfail(AF_ERR_ARG, "bad argument");
-  float* G = grad ? grad : c->d_grad;
-  af_status s = forward(c, x, B, st);
-  if (s != AF_OK) return s;
-  const long M = long(B) * kPix;
-  // every entry of G and loss is written below (no accumulation across calls)
-  hipLaunchKernelGGL(k_head, dim3((B + 7) / 8), dim3(256), 0, st, c->d_a3, B, c->d_params + c->off_wh,
-                     c->d_params + c->off_bh, c->d_logits, labels, c->d_part, c->d_dA);
-  CNN_HIP(hipGetLastError());
-  hipLaunchKernelGGL(k_head_sum, dim3(1), dim3(128), 0, st, c->d_part, B, loss, G + c->off_wh, G + c->off_bh);
-  CNN_HIP(hipGetLastError());
-  for (int l = 2; l >= 0; --l) {
-    const int cin = l == 0 ? c->nin : kWidth, cp = l == 0 ? c->cp1 : kWidth;
-    const int K = 9 * cp;
-    if (dacts)  // the upstream gradient this layer's backward consumes
-      CNN_HIP(hipMemcpyAsync(dacts + size_t(l) * M * kWidth, c->d_dA, size_t(M) * kWidth * 4, hipMemcpyDeviceToDevice,
-                             st));
-    const int nb = grid_for(M * kWidth);
-    hipLaunchKernelGGL(k_relu_back, dim3(nb), dim3(256), 0, st, c->d_dA, c->d_z[l], M, c->d_g, c->d_part);
-    CNN_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_bias_sum, dim3(1), dim3(64), 0, st, c->d_part, nb, G + c->off_b[l]);
-    CNN_HIP(hipGetLastError());
-    // dWm[co][k] = sum_m G[m][co] Xcol[m][k]
-    GemmArgs gw{c->d_g, 1, kWidth, c->d_col[l], 1, K, c->d_dwm, K, 1, kWidth, K, int(M), 0, nullptr};
-    CNN_HIP(gemm(gw, wgrad_split(M), c->d_part, st));
-    hipLaunchKernelGGL(k_unpack_wgrad, dim3(grid_for(kWidth * cin * 9)), dim3(256), 0, st, c->d_dwm, cin, cp,
-                       G + c->off_w[l]);
-    CNN_HIP(hipGetLastError());
-    if (l > 0) {
-      // dXcol[m][k] = sum_co G[m][co] Wm[co][k]
-      GemmArgs gx{c->d_g, kWidth, 1, c->d_wt[l], kWidth, 1, c->d_dcol, K, 1, int(M), K, kWidth, 0, nullptr};
-      CNN_HIP(gemm(gx, 1, nullptr, st));
-      hipLaunchKernelGGL(k_col2im, dim3(grid_for(M * cp)), dim3(256), 0, st, c->d_dcol, B, cp, c->d_dA);
-      CNN_HIP(hipGetLastError());
-    }
+  const int rows = std::min(B, kCnnRows);
+  if (rows > c->part_rows) {
+    (void)hipFree(c->d_part);
+    c->d_part = nullptr;
+    c->part_rows = 0;
+    CNN_HIP(hipMalloc(&c->d_part, size_t(rows) * kPart * 4));
+    c->part_rows = rows;
   }
+  CnnArgs A = cnn_args(c, x, B);
+  A.labels = labels;
+  A.dacts = dacts;
+  A.part = c->d_part;
+  CNN_HIP(launch_cnn<true>(c->cp1, A, rows, st));
+  // every entry of the gradient and the loss is written (no accumulation across calls)
+  hipLaunchKernelGGL(k_cnn_grad, dim3(kPart / 64), dim3(256), 0, st, c->d_part, rows, c->off, c->nin,
+                     grad ? grad : c->d_grad, loss);
+  CNN_HIP(hipGetLastError());
   return AF_OK;
 }
 
@@ -749,7 +831,7 @@ af_status af_cnn_tag(af_ctx* ctx, af_cnn* c, const af_hier* h, const af_state* b
   AfTagView v;
   af_status s = af_internal_tag_view(ctx, h, bufs, &v);
   if (s != AF_OK) return cfail(s, "af_cnn_tag: bad context, hierarchy or buffers");
-  if ((s = ensure_batch(c, v.nleaves)) != AF_OK) return s;
+  if ((s = ensure_tag(c, v.nleaves)) != AF_OK) return s;
   if ((s = af_cnn_features(ctx, c, h, bufs, mask, c->d_feat, st)) != AF_OK) return s;
   if ((s = af_cnn_forward(c, c->d_feat, v.nleaves, c->d_logits, nullptr, st)) != AF_OK) return s;
   hipLaunchKernelGGL(k_combine_tags, dim3((v.nleaves + 255) / 256), dim3(256), 0, st, c->d_logits, plain, v.plevel,
