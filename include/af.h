@@ -282,8 +282,8 @@ af_status af_reduce_sum_noalloc(af_ctx* ctx, const af_hier* h, const af_state* b
  * copy), advances K steps in LDS and writes the interior averages and the
  * closed-square nodes to the other buffer.  Equal to nsteps x (af_ghost_fill
  * + af_patch_step) up to rounding order: for advection with the upwind source
- * pattern (a, b > 0, both directional Courant numbers below 1/2) each step is
- * one pass in which a cell's new average is a fixed combination of the 25 old
+ * pattern (a, b > 0, both directional Courant numbers below 1/2) or a mirror
+ * image of it (a < 0, b < 0) each step is one pass in which a cell's new average is a fixed combination of the 25 old
  * DOFs of its source cells, composed on the host from eq. 2dfv and eq.
  * Simpson-2d.  AF_ADVECTION and AF_ACOUSTICS only (AF_ERR_ARG for the other
  * equations, which step with af_patch_step).  The level's data moves between

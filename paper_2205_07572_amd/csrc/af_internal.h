@@ -164,6 +164,16 @@ struct AdvWeights {
 };
 constexpr int kUpA = 0, kUpC = 4, kUpX = 13, kUpY = 19;
 
+// The weights of one step (first, so that a pointer to it serves the patch
+// steps), and those of the step with velocity (|a|, |b|): on a grid mirrored
+// in x (a < 0) and in y (b < 0) they are the same step, which the level
+// advance takes when their sources have the upwind pattern.
+template <typename T>
+struct AdvAllWeights {
+  AdvWeights<T> w, mirrored;
+  int32_t mirror_x, mirror_y;
+};
+
 // Acoustics: p = K.p - Dx.u - Dy.v ; u = K.u - Dx.p ; v = K.v - Dy.p
 // (eq. ERFormula: K is M_R + R d/dR M_R, Dx and Dy are R M_R of the x- and
 // y-derivative), each a vector over the node's neighbourhood.

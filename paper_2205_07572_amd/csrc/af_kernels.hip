@@ -882,6 +882,8 @@ struct AdvanceArgs {
   int32_t npatch, pitch, first;
   int32_t nx, ny;  // patches per side of the level; leaf first + iy * nx + ix is patch (ix, iy)
   T dtdx, dtdy, a, b, c;
+  // k_level_advance_up: the grid is read and written mirrored in x, in y
+  int32_t mirror_x, mirror_y;
 };
 
 // Patch index of the periodic neighbour (ox, oy) in {-1, 0, 1}^2 of patch
@@ -1040,7 +1042,8 @@ __global__ __launch_bounds__(NT) void k_level_advance(const AdvanceArgs<T> A, co
 //    dot products.
 //  * The upwind pattern (a, b > 0 with both directional Courant numbers
 //    below 1/2: sources corner (i-1, j-1), x-edge (i-1, j), y-edge (i, j-1))
-//    runs in k_level_advance_up instead, one pass per step.
+//    and its mirror images (a < 0, b < 0) run in k_level_advance_up instead,
+//    one pass per step.
 //  * A wave whose 64 cells of a slot all lie outside the region skips it.
 // ---------------------------------------------------------------------------
 
@@ -1248,6 +1251,11 @@ __global__ __launch_bounds__(NT) void k_level_advance_adv(const AdvanceArgs<T> A
 // averages and edge values at index M that come from them are not among
 // the ones above, and nothing needed reads them.
 //
+// Mirror images.  A negative velocity component is the same step on the grid
+// mirrored in that direction, with the weights of (|a|, |b|): a cell's average
+// moves to cell M - 1 - i, a node to M - i.  MIR gathers and stores through
+// that map and computes as above.
+//
 // LDS layouts.  Step s reads layout s and writes layout s + 1; the layouts
 // alternate between the two buffers.  Layout s puts local cell (s - K, s - K)
 // at position 0 and has row pitch pitch(s): the gather fills layout 0, the
@@ -1383,7 +1391,22 @@ struct UpLds {
   T q[UpGeom<T, M, K, NT>::WORDS];  // buffer 0 then 1, each: average, corner, x-edge, y-edge
 };
 
-template <typename T, int M, int K, int NT>
+// Stores the values of position (i, j), 0 <= i, j <= M, of the closed square
+// (mirrored as the gather was): interior averages and closed-square nodes.
+template <typename T, int M, bool MIR>
+__device__ __forceinline__ void up_store(const AdvanceArgs<T>& A, size_t plane, int patch, int i, int j, T avg, T co,
+                                         T xe, T ye) {
+  const int cx = MIR && A.mirror_x ? M - 1 - i : i, cy = MIR && A.mirror_y ? M - 1 - j : j;  // cell
+  const int nx = MIR && A.mirror_x ? M - i : i, ny = MIR && A.mirror_y ? M - j : j;          // node
+  const size_t p = size_t(patch) * plane;
+  const size_t rc = p + size_t(cy + kGhost) * A.pitch + kGhost, rn = p + size_t(ny + kGhost) * A.pitch + kGhost;
+  A.out[1][rn + nx] = co;
+  if (j < M) A.out[2][rc + nx] = xe;
+  if (i < M) A.out[3][rn + cx] = ye;
+  if (i < M && j < M) A.out[0][rc + cx] = avg;
+}
+
+template <typename T, int M, int K, int NT, bool MIR>
 __global__ __launch_bounds__(NT, (UpGeom<T, M, K, NT>::OCC)) void k_level_advance_up(const AdvanceArgs<T> A,
                                                                                    const AdvWeights<T> W) {
   constexpr int R = UpStripRows<M, K, NT>::value;
@@ -1402,11 +1425,11 @@ __global__ __launch_bounds__(NT, (UpGeom<T, M, K, NT>::OCC)) void k_level_advanc
   // for the whole launch (FP32; 52 of the 128 registers a lane has at this
   // occupancy).  Held as kernel arguments they overflow the scalar registers,
   // and every reload is a scalar load whose wait also drains all outstanding
-  // LDS loads.  FP64 blocks of 512 or more threads have room for the 18
-  // weights of the corner and x-edge stencils (36 registers); the other 34
-  // then fit in scalar registers.  Without them the compiler parked FP64
-  // weights in vector lanes, 48 lane moves per step beside 96 FMAs.  (The
-  // 256-thread FP64 shapes got slower with them.)  The empty asm statements
+  // LDS loads.  FP64 has room for the 18 weights of the corner and x-edge
+  // stencils (36 registers); the other 34 then fit in scalar registers.
+  // Without them the compiler parked FP64 weights in vector lanes, 48 lane
+  // moves per step beside 96 FMAs (m = 16, K = 4, 256 threads, 1665 patches:
+  // 24 us per launch without, 18 with).  The empty asm statements
   // only pin the register class.
   T wf[3][9], wq[25];
 #pragma unroll
@@ -1414,7 +1437,7 @@ __global__ __launch_bounds__(NT, (UpGeom<T, M, K, NT>::OCC)) void k_level_advanc
 #pragma unroll
     for (int e = 0; e < 9; ++e) {
       wf[k][e] = W.w[k][1][e];
-      if (sizeof(T) == 4 || (k < 2 && NT >= 512)) asm volatile("" : "+v"(wf[k][e]));
+      if (sizeof(T) == 4 || k < 2) asm volatile("" : "+v"(wf[k][e]));
     }
 #pragma unroll
   for (int e = 0; e < 25; ++e) {
@@ -1423,7 +1446,8 @@ __global__ __launch_bounds__(NT, (UpGeom<T, M, K, NT>::OCC)) void k_level_advanc
   }
 
   // ---- gather into layout 0: position (r, c) of the E0 x E0 block holds
-  // local index (c - K, r - K); one source offset serves the four kinds
+  // local index (c - K, r - K); one source offset serves the four kinds (MIR:
+  // a cell's and a node's mirror image differ by one)
   {
     constexpr int EE = E0 * E0;
     constexpr int P0 = kTab.pitch[0];
@@ -1435,13 +1459,32 @@ __global__ __launch_bounds__(NT, (UpGeom<T, M, K, NT>::OCC)) void k_level_advanc
       const int e = int(threadIdx.x) + u * NT;
       if (u + 1 < NP || EE % NT == 0 || e < EE) {
         const int rr = e / E0, x = e - rr * E0;
-        const int j = rr - K, i = x - K;
-        const int oy = j < 0 ? -1 : (j >= M ? 1 : 0);
-        const int ox = i < 0 ? -1 : (i >= M ? 1 : 0);
-        const int src = level_nbr(A, pix, piy, ox, oy);
-        const size_t off = size_t(src) * plane + size_t(j - oy * M + kGhost) * A.pitch + (i - ox * M + kGhost);
+        const int i = x - K, j = rr - K;
+        if constexpr (!MIR) {
+          const int oy = j < 0 ? -1 : (j >= M ? 1 : 0);
+          const int ox = i < 0 ? -1 : (i >= M ? 1 : 0);
+          const int src = level_nbr(A, pix, piy, ox, oy);
+          const size_t off = size_t(src) * plane + size_t(j - oy * M + kGhost) * A.pitch + (i - ox * M + kGhost);
 #pragma unroll
-        for (int kind = 0; kind < 4; ++kind) v[u][kind] = A.in[kind][off];
+          for (int kind = 0; kind < 4; ++kind) v[u][kind] = A.in[kind][off];
+          continue;
+        }
+        // the cell and node positions of the patch that (i, j) stands for
+        size_t ox[2], oy[2];  // [0] cell, [1] node
+#pragma unroll
+        for (int n = 0; n < 2; ++n) {
+          const int ii = A.mirror_x ? M - 1 + n - i : i, jj = A.mirror_y ? M - 1 + n - j : j;
+          const int dx = ii < 0 ? -1 : (ii >= M ? 1 : 0), dy = jj < 0 ? -1 : (jj >= M ? 1 : 0);
+          int px = pix + dx, py = piy + dy;
+          px = px < 0 ? px + A.nx : (px >= A.nx ? px - A.nx : px);
+          py = py < 0 ? py + A.ny : (py >= A.ny ? py - A.ny : py);
+          ox[n] = size_t(px) * plane + (ii - dx * M + kGhost);
+          oy[n] = size_t(A.first + py * A.nx) * plane + size_t(jj - dy * M + kGhost) * A.pitch;
+        }
+        v[u][0] = A.in[0][oy[0] + ox[0]];
+        v[u][1] = A.in[1][oy[1] + ox[1]];
+        v[u][2] = A.in[2][oy[0] + ox[1]];
+        v[u][3] = A.in[3][oy[1] + ox[0]];
       }
     }
 #pragma unroll
@@ -1515,12 +1558,12 @@ __global__ __launch_bounds__(NT, (UpGeom<T, M, K, NT>::OCC)) void k_level_advanc
           for (int e = 1; e < 9; ++e) v += wf[k][e] * d[e];
           f[k] = v;
         }
-        // new average: the 25 old DOFs of the source cells (-1..0)^2
+        // new average: the 25 old DOFs of the source cells (-1..0)^2.  The
+        // cell's own average, by far the largest term, comes last: the
+        // partial sums before it round at the size of the update (FP32, 11
+        // to 128 steps: half the error against 64 bits of the order that
+        // began with it)
         T avg = T(0);
-#pragma unroll
-        for (int dj = -1; dj <= 0; ++dj)
-#pragma unroll
-          for (int di = -1; di <= 0; ++di) avg += wq[kUpA + (dj + 1) * 2 + (di + 1)] * wa[u + 1 + dj][1 + di];
 #pragma unroll
         for (int dj = -1; dj <= 1; ++dj)
 #pragma unroll
@@ -1533,6 +1576,10 @@ __global__ __launch_bounds__(NT, (UpGeom<T, M, K, NT>::OCC)) void k_level_advanc
         for (int dj = -1; dj <= 1; ++dj)
 #pragma unroll
           for (int di = -1; di <= 0; ++di) avg += wq[kUpY + (dj + 1) * 2 + (di + 1)] * w2[u + 1 + dj][1 + di];
+        avg += wq[kUpA] * wa[u][0];
+        avg += wq[kUpA + 1] * wa[u][1];
+        avg += wq[kUpA + 2] * wa[u + 1][0];
+        avg += wq[kUpA + 3] * wa[u + 1][1];
         if (s + 1 < K || !UpGeom<T, M, K, NT>::DIRECT) {
           if (tok) {  // strips past the region store into rows no later read touches
             const int idx = bw + u * PO;
@@ -1546,13 +1593,7 @@ __global__ __launch_bounds__(NT, (UpGeom<T, M, K, NT>::OCC)) void k_level_advanc
           // 0..M: store the interior averages and the closed-square nodes
           // straight to the output
           const int i = ci, j = q * R + u;
-          if (tok && j <= M) {
-            const size_t g = size_t(patch) * plane + size_t(j + kGhost) * A.pitch + (i + kGhost);
-            A.out[1][g] = f[0];
-            if (j < M) A.out[2][g] = f[1];
-            if (i < M) A.out[3][g] = f[2];
-            if (i < M && j < M) A.out[0][g] = avg;
-          }
+          if (tok && j <= M) up_store<T, M, MIR>(A, plane, patch, i, j, avg, f[0], f[1], f[2]);
         }
       }
     }
@@ -1568,11 +1609,7 @@ __global__ __launch_bounds__(NT, (UpGeom<T, M, K, NT>::OCC)) void k_level_advanc
     for (Walk2 w(threadIdx.x, NT, M + 1); w.y < M + 1; w.next()) {
       const int i = w.x, j = w.y;
       const int idx = j * PK + i;
-      const size_t g = size_t(patch) * plane + size_t(j + kGhost) * A.pitch + (i + kGhost);
-      A.out[1][g] = qf[AF + idx];
-      if (j < M) A.out[2][g] = qf[2 * AF + idx];
-      if (i < M) A.out[3][g] = qf[3 * AF + idx];
-      if (i < M && j < M) A.out[0][g] = qf[idx];
+      up_store<T, M, MIR>(A, plane, patch, i, j, qf[idx], qf[AF + idx], qf[2 * AF + idx], qf[3 * AF + idx]);
     }
   }
 }
@@ -2465,7 +2502,8 @@ hipError_t scratch_sums(double** ptr) {
 // ---------------------------------------------------------------------------
 
 // The weights a patch step of equation EQ takes from the host's table
-// (acoustics: the orbit form of AcAllWeights).
+// (acoustics: the orbit form of AcAllWeights; advection: the first member of
+// AdvAllWeights).
 template <typename T, int EQ>
 static const typename WSel<T, EQ>::type& step_weights(const void* p) {
   if constexpr (EQ == 1)
@@ -2649,6 +2687,7 @@ static AdvanceArgs<T> advance_args(const AdvanceLaunch& s) {
   }
   A.npatch = s.npatch; A.pitch = s.pitch; A.first = s.first; A.nx = s.nx; A.ny = s.ny;
   A.dtdx = T(s.dtdx); A.dtdy = T(s.dtdy); A.a = T(s.a); A.b = T(s.b); A.c = T(s.c);
+  A.mirror_x = A.mirror_y = 0;
   return A;
 }
 
@@ -2663,21 +2702,32 @@ static bool adv_up_pattern(const AdvWeights<T>& W) {
 
 bool level_advance_up_pattern(bool fp32, int eq, const void* weights) {
   if (eq != 0) return false;
-  return fp32 ? adv_up_pattern(*static_cast<const AdvWeights<float>*>(weights))
-              : adv_up_pattern(*static_cast<const AdvWeights<double>*>(weights));
+  return fp32 ? adv_up_pattern(static_cast<const AdvAllWeights<float>*>(weights)->w)
+              : adv_up_pattern(static_cast<const AdvAllWeights<double>*>(weights)->w);
 }
 
 template <typename T, int EQ, int M, int K, int NT>
 static hipError_t launch_adv_t(const AdvanceLaunch& s, hipStream_t st) {
-  const AdvanceArgs<T> A = advance_args<T>(s);
+  AdvanceArgs<T> A = advance_args<T>(s);
   const dim3 grid(unsigned(s.count));
   if constexpr (EQ == 0) {
-    const AdvWeights<T>& W = *static_cast<const AdvWeights<T>*>(s.weights);
+    const AdvAllWeights<T>& all = *static_cast<const AdvAllWeights<T>*>(s.weights);
+    const AdvWeights<T>& W = all.w;
     bool ss = true;
     for (int k = 0; k < 3; ++k)
       for (int t = 0; t < 2; ++t) ss = ss && W.off[k][t][0] == W.off[k][0][0] && W.off[k][t][1] == W.off[k][0][1];
+    // One pass per step for every sign of the velocity, mirrored where a
+    // component is negative (45 x 37 patches of 16^2, FP64, (-0.8, 0.6),
+    // K = 4: 44.0 us per launch in the two-pass kernel, 17.7 here); two
+    // passes where the sources lack the pattern: a zero component, or a
+    // directional Courant number of 1/2 or more.
+    // The mirrored variant is compiled apart: its gather cost the others 3%.
+    A.mirror_x = all.mirror_x;
+    A.mirror_y = all.mirror_y;
     if (adv_up_pattern(W))
-      hipLaunchKernelGGL((k_level_advance_up<T, M, K, NT>), grid, dim3(NT), 0, st, A, W);
+      hipLaunchKernelGGL((k_level_advance_up<T, M, K, NT, false>), grid, dim3(NT), 0, st, A, W);
+    else if (adv_up_pattern(all.mirrored))
+      hipLaunchKernelGGL((k_level_advance_up<T, M, K, NT, true>), grid, dim3(NT), 0, st, A, all.mirrored);
     else if (ss)
       hipLaunchKernelGGL((k_level_advance_adv<T, M, K, NT, true>), grid, dim3(NT), 0, st, A, W);
     else
@@ -2716,9 +2766,9 @@ static hipError_t launch_adv_t(const AdvanceLaunch& s, hipStream_t st) {
 
 template <typename T, int M, int K, int NT>
 static hipError_t launch_up_t(const AdvanceLaunch& s, hipStream_t st) {
-  const AdvWeights<T>& W = *static_cast<const AdvWeights<T>*>(s.weights);
+  const AdvWeights<T>& W = static_cast<const AdvAllWeights<T>*>(s.weights)->w;
   if (!adv_up_pattern(W)) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((k_level_advance_up<T, M, K, NT>), dim3(unsigned(s.count)), dim3(NT), 0, st, advance_args<T>(s),
+  hipLaunchKernelGGL((k_level_advance_up<T, M, K, NT, false>), dim3(unsigned(s.count)), dim3(NT), 0, st, advance_args<T>(s),
                      W);
   return hipGetLastError();
 }

@@ -149,16 +149,15 @@ void adv_locate(double node, double disp, int* off, double* ref) {
 // factor, so the mean drifts linearly with the step count (about 5e-5 after
 // 1280 steps).  The residual is folded into the smallest weights, whose
 // finer spacing then bounds it (an absolute change of the size of the
-// rounding of the larger weights).  For T = double the weights are rounded
-// plainly.
+// rounding of the larger weights).  FP64 weights drift the same way, by a few
+// 1e-17 per step; their sum is taken in long double.
 template <typename T>
 void round_sum(const double* w, T* out, int n, double target) {
   for (int e = 0; e < n; ++e) out[e] = T(w[e]);
-  if (sizeof(T) == sizeof(double)) return;
   for (int pass = 0; pass < 3; ++pass) {
-    double sum = 0.0;  // exact: FP32 values spanning far fewer than 53 bits
-    for (int e = 0; e < n; ++e) sum += double(out[e]);
-    const double r = target - sum;
+    long double sum = 0.0L;  // exact for FP32 values spanning far fewer than 64 bits
+    for (int e = 0; e < n; ++e) sum += static_cast<long double>(out[e]);
+    const double r = double(static_cast<long double>(target) - sum);
     if (r == 0.0) return;
     // smallest weight that the change leaves well away from zero
     int best = -1;
