@@ -233,15 +233,12 @@ const void* weights_for(af_ctx* c, double dtdx, double dtdy) {
   } else {
     bool sym;
     if (c->fp32()) {
-      buf.resize(sizeof(AcAllWeights<float>));
-      auto* W = reinterpret_cast<AcAllWeights<float>*>(buf.data());
-      make_ac_weights<float>(c->P.c * dtdx, c->P.c * dtdy, &W->dense);
-      sym = make_ac_orbit_weights<float>(c->P.c * dtdx, c->P.c * dtdy, &W->orbit);
+      buf.resize(sizeof(AcOrbitWeights<float>));
+      sym = make_ac_orbit_weights<float>(c->P.c * dtdx, c->P.c * dtdy, reinterpret_cast<AcOrbitWeights<float>*>(buf.data()));
     } else {
-      buf.resize(sizeof(AcAllWeights<double>));
-      auto* W = reinterpret_cast<AcAllWeights<double>*>(buf.data());
-      make_ac_weights<double>(c->P.c * dtdx, c->P.c * dtdy, &W->dense);
-      sym = make_ac_orbit_weights<double>(c->P.c * dtdx, c->P.c * dtdy, &W->orbit);
+      buf.resize(sizeof(AcOrbitWeights<double>));
+      sym = make_ac_orbit_weights<double>(c->P.c * dtdx, c->P.c * dtdy,
+                                          reinterpret_cast<AcOrbitWeights<double>*>(buf.data()));
     }
     if (!sym) return nullptr;  // cannot happen: the sector means are mirror symmetric
   }
@@ -257,12 +254,10 @@ const void* weights_dev_for(af_ctx* c, double dtdx, double dtdy) {
   if (it != c->wdev.end()) return it->second;
   const void* host = weights_for(c, dtdx, dtdy);
   if (!host || c->P.eq != AF_ACOUSTICS) return nullptr;
-  const void* src = c->fp32() ? static_cast<const void*>(&static_cast<const AcAllWeights<float>*>(host)->orbit)
-                              : static_cast<const void*>(&static_cast<const AcAllWeights<double>*>(host)->orbit);
   const size_t bytes = c->fp32() ? sizeof(AcOrbitWeights<float>) : sizeof(AcOrbitWeights<double>);
   void* d = nullptr;
   if (hipMalloc(&d, bytes) != hipSuccess) return nullptr;
-  if (hipMemcpy(d, src, bytes, hipMemcpyHostToDevice) != hipSuccess) {
+  if (hipMemcpy(d, host, bytes, hipMemcpyHostToDevice) != hipSuccess) {
     (void)hipFree(d);
     return nullptr;
   }

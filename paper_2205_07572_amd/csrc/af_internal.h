@@ -184,14 +184,6 @@ struct AcWeights {
   T yedge[2][3][kNbEdge];
 };
 
-// Both forms of one step's acoustic stencils: the dense tables (level
-// advance) and the orbit form (patch steps).
-template <typename T>
-struct AcAllWeights {
-  AcWeights<T> dense;
-  AcOrbitWeights<T> orbit;
-};
-
 // Device tables of a hierarchy.
 struct HierDev {
   const int32_t* lut;        // per-level dense patch lookup: leaf id or -1

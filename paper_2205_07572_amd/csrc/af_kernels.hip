@@ -65,12 +65,12 @@ struct Walk2 {
   }
 };
 
-// Block gather of NPL planes of an NR x NC image into LDS [plane][row][col]:
-// position (r, x) of plane p is read from plane(p) + pos(r, x).  A thread's
-// positions are the same in every plane, so their source offsets are
-// computed once; all loads are issued before the first store.
-template <typename T, int NT, int NPL, int NR, int NC, typename Plane, typename Pos>
-__device__ __forceinline__ void gather_planes(T* lds, Plane plane, Pos pos) {
+// Block gather of NPL planes of an NR x NC image into LDS: position (r, x) of
+// plane p is read from plane(p) + pos(r, x) and goes to lpos(p, r, x).  A
+// thread's positions are the same in every plane, so their source offsets
+// are computed once; all loads are issued before the first store.
+template <typename T, int NT, int NPL, int NR, int NC, typename Plane, typename Pos, typename LPos>
+__device__ __forceinline__ void gather_planes(T* lds, Plane plane, Pos pos, LPos lpos) {
   constexpr int PE = NR * NC;
   constexpr int PER = (PE + NT - 1) / NT;
   size_t off[PER];
@@ -89,12 +89,14 @@ __device__ __forceinline__ void gather_planes(T* lds, Plane plane, Pos pos) {
       if (u + 1 < PER || PE % NT == 0 || int(threadIdx.x) + u * NT < PE) v[p][u] = b[off[u]];
   }
 #pragma unroll
-  for (int p = 0; p < NPL; ++p)
+  for (int u = 0; u < PER; ++u) {
+    const int e = int(threadIdx.x) + u * NT;
+    const int r = e / NC, x = e - r * NC;
+    if (u + 1 < PER || PE % NT == 0 || e < PE) {
 #pragma unroll
-    for (int u = 0; u < PER; ++u) {
-      const int e = int(threadIdx.x) + u * NT;
-      if (u + 1 < PER || PE % NT == 0 || e < PE) lds[p * PE + e] = v[p][u];
+      for (int p = 0; p < NPL; ++p) lds[lpos(p, r, x)] = v[p][u];
     }
+  }
 }
 
 // Workgroups are handed to the 8 XCDs round-robin (workgroup b to XCD b % 8),
@@ -110,36 +112,47 @@ __device__ __forceinline__ int xcd_patch(int b, int n) {
   return x * q + min(x, r) + b / kXcd;
 }
 
-// LDS of a patch step: the staged DOFs, then the nodes' time sums.
+// LDS of a patch step: the staged DOFs [kind][component][row][column], then
+// the nodes' time sums.
 // kLdsAlias: the update reads only the averages and the sums, so the sums
 // overwrite the staged node values once every node is evaluated; the block
 // then holds 4 NCOMP NR NC values, not 7 NCOMP NR NC, and more blocks fit on
 // a CU.  The first of a fused pair of substeps uses it too: its new node
 // values wait in registers until the update is done and then replace the
-// sums.  kLdsSwirl: separate sums, and the swirl's values at t+dt (tsum2);
-// its update also reads the nodes at t.
+// sums.  kLdsSwirl: separate sums, and the swirl's values at t+dt (ts2); its
+// update also reads the nodes at t.
 enum StepLdsKind { kLdsAlias, kLdsSwirl };
+
+template <typename T, int NCOMP, int NR, int NC>
+struct StepDofs {
+  static constexpr int RS = NC, CS = NR * NC, KS = NCOMP * CS;  // strides of row, component, kind
+  T v[4 * KS];
+  __device__ __forceinline__ static int pos(int kind, int q, int r, int c) { return kind * KS + r * RS + q * CS + c; }
+  __device__ __forceinline__ T& operator()(int kind, int q, int r, int c) { return v[pos(kind, q, r, c)]; }
+  __device__ __forceinline__ const T& operator()(int kind, int q, int r, int c) const { return v[pos(kind, q, r, c)]; }
+};
 
 template <typename T, int NCOMP, int NR, int NC, int KIND>
 struct StepLds;
 
 template <typename T, int NCOMP, int NR, int NC>
 struct StepLds<T, NCOMP, NR, NC, kLdsAlias> {
-  using TS = T[3][NCOMP][NR - 2][NC];
+  using D = StepDofs<T, NCOMP, NR, NC>;
   static constexpr bool kSeparate = false;
-  T in[4][NCOMP][NR][NC];
-  __device__ __forceinline__ TS& tsum() { return *reinterpret_cast<TS*>(&in[1][0][0][0]); }
-  __device__ __forceinline__ TS& tsum2() { return tsum(); }  // unused without the swirl
+  D in;
+  // the sum of node kind k at extended cell (ii, jj)
+  __device__ __forceinline__ T& ts(int k, int q, int jj, int ii) { return in(k + 1, q, jj, ii); }
+  __device__ __forceinline__ T& ts2(int k, int q, int jj, int ii) { return in(k + 1, q, jj, ii); }  // swirl only
 };
 
 template <typename T, int NCOMP, int NR, int NC>
 struct StepLds<T, NCOMP, NR, NC, kLdsSwirl> {
-  using TS = T[3][NCOMP][NR - 2][NC];
+  using D = StepDofs<T, NCOMP, NR, NC>;
   static constexpr bool kSeparate = true;
-  T in[4][NCOMP][NR][NC];
-  TS ts, ts2;
-  __device__ __forceinline__ TS& tsum() { return ts; }
-  __device__ __forceinline__ TS& tsum2() { return ts2; }
+  D in;
+  T s[2][3][NCOMP][NR - 2][NC];
+  __device__ __forceinline__ T& ts(int k, int q, int jj, int ii) { return s[0][k][q][jj][ii]; }
+  __device__ __forceinline__ T& ts2(int k, int q, int jj, int ii) { return s[1][k][q][jj][ii]; }
 };
 
 // Simpson space-time sum of one face from the time sums of its three nodes
@@ -149,28 +162,28 @@ __device__ __forceinline__ T face_sum(T lo, T mid, T hi) {
   return (lo + T(4) * mid) + hi;
 }
 
-template <typename T, int NR, int NC>
-__device__ __forceinline__ T adv_eval(const T (&s)[4][1][NR][NC], int r, int c, const T* w) {
+template <typename T, typename D>
+__device__ __forceinline__ T adv_eval(const D& s, int r, int c, const T* w) {
   // raw-DOF order of af_internal.h: avg, corners ll, rl, lu, ru, xedges l, r, yedges b, t
-  T v = w[0] * s[0][0][r][c];
-  v += w[1] * s[1][0][r][c];
-  v += w[2] * s[1][0][r][c + 1];
-  v += w[3] * s[1][0][r + 1][c];
-  v += w[4] * s[1][0][r + 1][c + 1];
-  v += w[5] * s[2][0][r][c];
-  v += w[6] * s[2][0][r][c + 1];
-  v += w[7] * s[3][0][r][c];
-  v += w[8] * s[3][0][r + 1][c];
+  T v = w[0] * s(0, 0, r, c);
+  v += w[1] * s(1, 0, r, c);
+  v += w[2] * s(1, 0, r, c + 1);
+  v += w[3] * s(1, 0, r + 1, c);
+  v += w[4] * s(1, 0, r + 1, c + 1);
+  v += w[5] * s(2, 0, r, c);
+  v += w[6] * s(2, 0, r, c + 1);
+  v += w[7] * s(3, 0, r, c);
+  v += w[8] * s(3, 0, r + 1, c);
   return v;
 }
 
 // Both time levels of a node kind evaluated from one source cell (the usual
 // case): one pass over the 9 raw DOFs feeds both dot products.
-template <typename T, int NR, int NC>
-__device__ __forceinline__ void adv_eval2(const T (&s)[4][1][NR][NC], int r, int c, const T* w0, const T* w1,
+template <typename T, typename D>
+__device__ __forceinline__ void adv_eval2(const D& s, int r, int c, const T* w0, const T* w1,
                                           T* h, T* f) {
-  const T d[9] = {s[0][0][r][c],     s[1][0][r][c],     s[1][0][r][c + 1], s[1][0][r + 1][c], s[1][0][r + 1][c + 1],
-                  s[2][0][r][c],     s[2][0][r][c + 1], s[3][0][r][c],     s[3][0][r + 1][c]};
+  const T d[9] = {s(0, 0, r, c),     s(1, 0, r, c),     s(1, 0, r, c + 1), s(1, 0, r + 1, c), s(1, 0, r + 1, c + 1),
+                  s(2, 0, r, c),     s(2, 0, r, c + 1), s(3, 0, r, c),     s(3, 0, r + 1, c)};
   T a = w0[0] * d[0], b = w1[0] * d[0];
 #pragma unroll
   for (int k = 1; k < 9; ++k) {
@@ -181,77 +194,6 @@ __device__ __forceinline__ void adv_eval2(const T (&s)[4][1][NR][NC], int r, int
   *f = b;
 }
 
-// Acoustic node evaluation (eq. ERFormula with the sector weights collapsed
-// on the host): the neighbourhood walked row by row.  Each table is four
-// rectangles of source offsets, one per DOF kind, listed row by row (checked
-// below), so entry e follows from (kind, row, column).  Fully unrolled, the
-// three node kinds keep 330 weights live, more than the scalar registers
-// hold, and the compiler parks them in vector lanes and reads each back
-// before its use.  Here the rows are a loop that is not unrolled: the
-// weights of a row are uniform loads issued in the iteration that uses them.
-struct NbRect {
-  int di0, di1, dj0, dj1;
-};
-constexpr NbRect kNbRects[3][4] = {
-    {{-1, 0, -1, 0}, {-1, 1, -1, 1}, {-1, 1, -1, 0}, {-1, 0, -1, 1}},  // corner
-    {{-1, 0, 0, 0}, {-1, 1, 0, 1}, {-1, 1, 0, 0}, {-1, 0, 0, 1}},      // x-edge
-    {{0, 0, -1, 0}, {0, 1, -1, 1}, {0, 1, -1, 0}, {0, 0, -1, 1}}};     // y-edge
-
-template <int NB>
-constexpr bool rects_match(int nk, const NbEntry (&tab)[NB]) {
-  int e = 0;
-  for (int kind = 0; kind < 4; ++kind) {
-    const NbRect R = kNbRects[nk][kind];
-    for (int dj = R.dj0; dj <= R.dj1; ++dj)
-      for (int di = R.di0; di <= R.di1; ++di, ++e)
-        if (e >= NB || tab[e].kind != kind || tab[e].di != di || tab[e].dj != dj) return false;
-  }
-  return e == NB;
-}
-static_assert(rects_match(0, kNbCornerTab) && rects_match(1, kNbXedgeTab) && rects_match(2, kNbYedgeTab),
-              "neighbourhood tables are four row-major rectangles");
-
-template <typename T, int NR, int NC, int NK, int NB>
-__device__ __forceinline__ void ac_eval_rows(const T (&s)[4][3][NR][NC], int r, int c, const T (&w)[2][3][NB],
-                                             T out[2][3]) {
-  T kp[2] = {T(0), T(0)}, ku[2] = {T(0), T(0)}, kv[2] = {T(0), T(0)};
-  T dxu[2] = {T(0), T(0)}, dyv[2] = {T(0), T(0)}, dxp[2] = {T(0), T(0)}, dyp[2] = {T(0), T(0)};
-  int ebase = 0;
-#pragma unroll
-  for (int kind = 0; kind < 4; ++kind) {
-    const NbRect R = kNbRects[NK][kind];
-    const int ndi = R.di1 - R.di0 + 1;
-#pragma unroll 1
-    for (int dj = R.dj0; dj <= R.dj1; ++dj) {
-      const int e0 = ebase + (dj - R.dj0) * ndi;
-#pragma unroll
-      for (int q = 0; q < 3; ++q) {
-        if (q >= ndi) break;
-        const int di = R.di0 + q;
-        const T p = s[kind][0][r + dj][c + di], u = s[kind][1][r + dj][c + di], v = s[kind][2][r + dj][c + di];
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-          const T wk = w[t][0][e0 + q], wx = w[t][1][e0 + q], wy = w[t][2][e0 + q];
-          kp[t] += wk * p;
-          ku[t] += wk * u;
-          kv[t] += wk * v;
-          dxu[t] += wx * u;
-          dyv[t] += wy * v;
-          dxp[t] += wx * p;
-          dyp[t] += wy * p;
-        }
-      }
-    }
-    ebase += ndi * (R.dj1 - R.dj0 + 1);
-  }
-#pragma unroll
-  for (int t = 0; t < 2; ++t) {
-    out[t][0] = kp[t] - dxu[t] - dyv[t];
-    out[t][1] = ku[t] - dxp[t];
-    out[t][2] = kv[t] - dyp[t];
-  }
-}
-
 // Acoustic node evaluation in mirror-orbit form (af_internal.h): each node
 // kind sums its neighbourhood orbit by orbit, reading an orbit's members
 // from LDS just before use.  For an orbit of four members (+x,+y), (-x,+y),
@@ -259,69 +201,69 @@ __device__ __forceinline__ void ac_eval_rows(const T (&s)[4][3][NR][NC], int r, 
 // from the pair sums and differences; K multiplies the sum of every
 // component, Dx the x-odd sums of u (into p) and p (into u), Dy the y-odd
 // sums of v (into p) and p (into v).
-// v1: the node's value at t + dt; vs: 4 q(t + dt/2) + q(t + dt).
-// Orbit o of node kind NK added to acc: the orbit sum S and odd parts Dx,
-// Dy of the neighbourhood values, times the orbit's weights.
-template <typename T, int NK, int NR, int NC>
-__device__ __forceinline__ void ac_orbit(const T (&s)[4][3][NR][NC], int r, int c,
-                                         const T (&w)[kMaxOrbits][2][3], int o, T (&acc)[2][3]) {
-  const NbOrbit& O = kOrbitTab[NK].o[o];
-  T S[3], Dx[3] = {T(0), T(0), T(0)}, Dy[3] = {T(0), T(0), T(0)};
+// acc[0]: the node's value at t + dt; acc[1]: 4 q(t + dt/2) + q(t + dt).
+// Orbits [O0, O1) of node kind NK added to acc: the orbit sum S and odd
+// parts Dx, Dy of the neighbourhood values, times the orbit's weights.
+// BULK: every value is loaded before the first is used.  One wait instead of
+// many suits launches of few blocks (the batched step with 256 threads: 86.4
+// against 88.6 us for 2 coarse steps of a small m = 8 hierarchy, FP32); the
+// interleaved loads take fewer registers, which suits full ones (1024^2
+// uniform, 4 steps: 171 against 178 us).
+template <typename T, int NK, int O0, int O1, bool BULK, typename D>
+__device__ __forceinline__ void ac_orbits(const D& s, int r, int c, const T (&w)[kMaxOrbits][2][3], T (&acc)[2][3]) {
+  T v[O1 - O0][4][3];
+  if constexpr (BULK) {
 #pragma unroll
-  for (int q = 0; q < 3; ++q) {
-    const T m0 = s[O.m[0].kind][q][r + O.m[0].dj][c + O.m[0].di];
-    if (O.n == 1) {
-      S[q] = m0;
-    } else if (O.n == 2) {
-      const T m1 = s[O.m[1].kind][q][r + O.m[1].dj][c + O.m[1].di];
-      S[q] = m0 + m1;
-      if (O.hasx && q != 2) Dx[q] = m0 - m1;
-      if (O.hasy && q != 1) Dy[q] = m0 - m1;
-    } else {
-      const T m1 = s[O.m[1].kind][q][r + O.m[1].dj][c + O.m[1].di];
-      const T m2 = s[O.m[2].kind][q][r + O.m[2].dj][c + O.m[2].di];
-      const T m3 = s[O.m[3].kind][q][r + O.m[3].dj][c + O.m[3].di];
-      const T hi = m0 + m1, lo = m2 + m3;
-      S[q] = hi + lo;
-      if (q != 1) Dy[q] = hi - lo;
-      if (q != 2) Dx[q] = (m0 - m1) + (m2 - m3);
-    }
+    for (int o = O0; o < O1; ++o)
+#pragma unroll
+      for (int k = 0; k < kOrbitTab[NK].o[o].n; ++k)
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+          const OrbitMember& M = kOrbitTab[NK].o[o].m[k];
+          v[o - O0][k][q] = s(M.kind, q, r + M.dj, c + M.di);
+        }
+    __builtin_amdgcn_sched_barrier(0);
   }
 #pragma unroll
-  for (int cc = 0; cc < 2; ++cc) {
-    const T wk = w[o][cc][0], wx = w[o][cc][1], wy = w[o][cc][2];
-    acc[cc][0] += wk * S[0];
-    acc[cc][1] += wk * S[1];
-    acc[cc][2] += wk * S[2];
-    if (O.hasx) {
-      acc[cc][0] -= wx * Dx[1];
-      acc[cc][1] -= wx * Dx[0];
+  for (int o = O0; o < O1; ++o) {
+    const NbOrbit& O = kOrbitTab[NK].o[o];
+    auto m = [&](int k, int q) {
+      return BULK ? v[o - O0][k][q] : s(O.m[k].kind, q, r + O.m[k].dj, c + O.m[k].di);
+    };
+    T S[3], Dx[3] = {T(0), T(0), T(0)}, Dy[3] = {T(0), T(0), T(0)};
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      const T m0 = m(0, q);
+      if (O.n == 1) {
+        S[q] = m0;
+      } else if (O.n == 2) {
+        const T m1 = m(1, q);
+        S[q] = m0 + m1;
+        if (O.hasx && q != 2) Dx[q] = m0 - m1;
+        if (O.hasy && q != 1) Dy[q] = m0 - m1;
+      } else {
+        const T m1 = m(1, q), m2 = m(2, q), m3 = m(3, q);
+        const T hi = m0 + m1, lo = m2 + m3;
+        S[q] = hi + lo;
+        if (q != 1) Dy[q] = hi - lo;
+        if (q != 2) Dx[q] = (m0 - m1) + (m2 - m3);
+      }
     }
-    if (O.hasy) {
-      acc[cc][0] -= wy * Dy[2];
-      acc[cc][2] -= wy * Dy[0];
+#pragma unroll
+    for (int cc = 0; cc < 2; ++cc) {
+      const T wk = w[o][cc][0], wx = w[o][cc][1], wy = w[o][cc][2];
+      acc[cc][0] += wk * S[0];
+      acc[cc][1] += wk * S[1];
+      acc[cc][2] += wk * S[2];
+      if (O.hasx) {
+        acc[cc][0] -= wx * Dx[1];
+        acc[cc][1] -= wx * Dx[0];
+      }
+      if (O.hasy) {
+        acc[cc][0] -= wy * Dy[2];
+        acc[cc][2] -= wy * Dy[0];
+      }
     }
-  }
-}
-
-// Orbits [O0, O1) of node kind NK added to acc.
-template <typename T, int NK, int NR, int NC, int O0, int O1>
-__device__ __forceinline__ void ac_orbit_range(const T (&s)[4][3][NR][NC], int r, int c,
-                                               const T (&w)[kMaxOrbits][2][3], T (&acc)[2][3]) {
-#pragma unroll
-  for (int o = O0; o < O1; ++o) ac_orbit<T, NK, NR, NC>(s, r, c, w, o, acc);
-}
-
-template <typename T, int NK, int NR, int NC>
-__device__ __forceinline__ void ac_node(const T (&s)[4][3][NR][NC], int r, int c,
-                                        const T (&w)[kMaxOrbits][2][3], T v1[3], T vs[3]) {
-  T acc[2][3] = {{T(0), T(0), T(0)}, {T(0), T(0), T(0)}};
-#pragma unroll
-  for (int o = 0; o < kOrbitTab[NK].n; ++o) ac_orbit<T, NK, NR, NC>(s, r, c, w, o, acc);
-#pragma unroll
-  for (int q = 0; q < 3; ++q) {
-    v1[q] = acc[0][q];
-    vs[q] = acc[1][q];
   }
 }
 
@@ -337,6 +279,24 @@ template <typename T>
 struct WSel<T, 3> { using type = SwirlParams<T>; };
 template <typename T>
 struct WSel<T, 4> { using type = BurgersParams<T>; };
+
+// A kernel's arguments A and stencil weights W as one argument.  Weights taken
+// by value are loaded into scalar registers at kernel entry, more than there
+// are, and the compiler parks the rest in vector lanes; read through their
+// address in the argument segment they are scalar loads where they are used.
+// (k_amr_step reads the acoustic weights from a device copy instead, made once
+// per time-step ratio outside any capture; this needs none.)
+template <typename A, typename W>
+struct WithWeights {
+  A a;
+  W w;
+};
+template <typename A, typename W>
+__device__ __forceinline__ const W& weights_of(const WithWeights<A, W>&) {
+  using S = WithWeights<A, W>;
+  typedef const __attribute__((address_space(4))) char* kernarg_t;
+  return *(const W*)((kernarg_t)__builtin_amdgcn_kernarg_segment_ptr() + __builtin_offsetof(S, w));
+}
 
 constexpr double kPiD = 3.14159265358979323846264338327950288;
 
@@ -371,20 +331,20 @@ __device__ __forceinline__ int foot_cell(T s, T disp) {
 // Reconstruction (Sec. 2, eq. poly) of the staged cell at LDS (r, c),
 // evaluated at reference point (xi, eta): tensor Lagrange interpolant of the
 // 9 nodal values, centre value from "average = Simpson sum".
-template <typename T, int NR, int NC>
-__device__ __forceinline__ T rot_eval(const T (&s)[4][1][NR][NC], int r, int c, T xi, T eta) {
+template <typename T, typename D>
+__device__ __forceinline__ T rot_eval(const D& s, int r, int c, T xi, T eta) {
   const T lx[3] = {T(0.5) * xi * (xi - T(1)), T(1) - xi * xi, T(0.5) * xi * (xi + T(1))};
   const T ly[3] = {T(0.5) * eta * (eta - T(1)), T(1) - eta * eta, T(0.5) * eta * (eta + T(1))};
   T q[3][3];  // [x node][y node]
-  q[0][0] = s[1][0][r][c];
-  q[2][0] = s[1][0][r][c + 1];
-  q[0][2] = s[1][0][r + 1][c];
-  q[2][2] = s[1][0][r + 1][c + 1];
-  q[0][1] = s[2][0][r][c];
-  q[2][1] = s[2][0][r][c + 1];
-  q[1][0] = s[3][0][r][c];
-  q[1][2] = s[3][0][r + 1][c];
-  q[1][1] = (T(36) * s[0][0][r][c] - (q[0][0] + q[2][0] + q[0][2] + q[2][2]) -
+  q[0][0] = s(1, 0, r, c);
+  q[2][0] = s(1, 0, r, c + 1);
+  q[0][2] = s(1, 0, r + 1, c);
+  q[2][2] = s(1, 0, r + 1, c + 1);
+  q[0][1] = s(2, 0, r, c);
+  q[2][1] = s(2, 0, r, c + 1);
+  q[1][0] = s(3, 0, r, c);
+  q[1][2] = s(3, 0, r + 1, c);
+  q[1][1] = (T(36) * s(0, 0, r, c) - (q[0][0] + q[2][0] + q[0][2] + q[2][2]) -
              T(4) * (q[0][1] + q[2][1] + q[1][0] + q[1][2])) / T(16);
   T v = T(0);
 #pragma unroll
@@ -407,6 +367,11 @@ struct StepIO {
   double len_dt_x, len_dt_y;  // dy * dt, dx * dt of the patch's level
   double* reg;             // FP64 registers [npatch][4][M][NCOMP]; null: nothing recorded
   uint32_t smask;          // sides whose faces are recorded
+  // the patch's plane of (kind, component): uniform, so that a store takes it
+  // from scalar registers and a 32-bit byte offset per lane
+  __device__ __forceinline__ char* plane_of(int kind, int q, size_t plane) const {
+    return reinterpret_cast<char*>(out[kind] + (size_t(q) * npatch + patch) * plane);
+  }
 };
 
 // TO_LDS: the first substep of a fused pair (no HBM output): new node values
@@ -415,13 +380,12 @@ struct StepIO {
 // reads the sums from where they will be stored.  rofs: staged row of cell
 // row j is j - jlo + 1 + rofs (the pair's second substep reads the first's
 // rows).
-template <typename T, int EQ, int M, int TY, bool TO_LDS = false, typename L_t>
+template <typename T, int EQ, int M, int TY, bool TO_LDS = false, int NT = kThreads, bool BULK = false, typename L_t>
 __device__ __forceinline__ void step_compute(L_t& L, const StepIO<T>& A, const typename WSel<T, EQ>::type& W,
                                              int jlo, int jhi, T px0, T py0, int rofs = 0) {
   static_assert(!TO_LDS || ((EQ == 0 || EQ == 1) && !L_t::kSeparate),
                 "a fused pair needs a constant-coefficient equation and the aliased LDS layout");
   constexpr int NCOMP = EQ == 1 ? 3 : 1;
-  constexpr int NR = TY + 3;
   constexpr int NC = M + 5;
   const int patch = A.patch;
   const int region = A.region;
@@ -449,19 +413,21 @@ __device__ __forceinline__ void step_compute(L_t& L, const StepIO<T>& A, const t
   // stored on the same pitch.
   constexpr bool kWide = EQ == 1;
   const int WN = kWide ? NC : EC;
-  constexpr int MAXIT = ((kWide ? M + 5 : M + 3) * (TY + 1) + kThreads - 1) / kThreads;
+  constexpr int MAXIT = ((kWide ? M + 5 : M + 3) * (TY + 1) + NT - 1) / NT;
   T tsv[MAXIT][3][NCOMP];
   T nv[TO_LDS ? MAXIT : 1][3][NCOMP];  // TO_LDS: the new node values, stored after the barrier
   // a new node value: to HBM (if `keep`, the rows and columns this tile
   // owns), or held for LDS
-  auto emit = [&](int it, int kind, int q, bool keep, size_t o, T v) {
+  auto emit = [&](int it, int kind, int q, bool keep, uint32_t o, T v) {
     if constexpr (TO_LDS) {
       nv[it][kind][q] = v;
     } else {
-      if (keep) A.out[kind + 1][o] = v;
+      if (keep) *reinterpret_cast<T*>(A.plane_of(kind + 1, q, plane) + o) = v;
     }
   };
-  Walk2 w(threadIdx.x, kThreads, WN);
+  // byte offset of entry (i, j) in a plane
+  auto entry = [&](int i, int j) { return uint32_t((j + kGhost) * A.pitch + (i + kGhost)) * uint32_t(sizeof(T)); };
+  Walk2 w(threadIdx.x, NT, WN);
 #pragma unroll
   for (int it = 0; it < MAXIT; ++it, w.next()) {
     if (w.y >= ER) break;
@@ -472,7 +438,7 @@ __device__ __forceinline__ void step_compute(L_t& L, const StepIO<T>& A, const t
     const bool wrow = (jj < nrow) || last_tile;
     const bool has_x = jj < nrow;      // xedge (i,j) belongs to rows [jlo, jhi)
     const bool has_y = ii < span;      // yedge (i,j) belongs to cols [ilo, ihi)
-    const size_t obase = size_t(j + kGhost) * A.pitch + (i + kGhost);
+    const uint32_t obase = entry(i, j);
     if constexpr (EQ == 0) {
 #pragma unroll
       for (int kind = 0; kind < 3; ++kind) {
@@ -480,14 +446,14 @@ __device__ __forceinline__ void step_compute(L_t& L, const StepIO<T>& A, const t
         if (kind == NK_YEDGE && !has_y) continue;
         T h, f;
         if (shared_src) {
-          adv_eval2<T, NR, NC>(L.in, r + W.off[kind][0][1], c + W.off[kind][0][0], W.w[kind][0], W.w[kind][1], &h, &f);
+          adv_eval2<T>(L.in, r + W.off[kind][0][1], c + W.off[kind][0][0], W.w[kind][0], W.w[kind][1], &h, &f);
         } else {
-          h = adv_eval<T, NR, NC>(L.in, r + W.off[kind][0][1], c + W.off[kind][0][0], W.w[kind][0]);
-          f = adv_eval<T, NR, NC>(L.in, r + W.off[kind][1][1], c + W.off[kind][1][0], W.w[kind][1]);
+          h = adv_eval<T>(L.in, r + W.off[kind][0][1], c + W.off[kind][0][0], W.w[kind][0]);
+          f = adv_eval<T>(L.in, r + W.off[kind][1][1], c + W.off[kind][1][0], W.w[kind][1]);
         }
-        const T cur = L.in[kind + 1][0][r][c];
+        const T cur = L.in(kind + 1, 0, r, c);
         tsv[it][kind][0] = (cur + T(4) * h) + f;
-        emit(it, kind, 0, wrow, size_t(patch) * plane + obase, f);
+        emit(it, kind, 0, wrow, obase, f);
       }
     } else if constexpr (EQ == 2 || EQ == 3) {
       // solid-body rotation (Sec. 4.2): the foot is the node turned back by
@@ -525,33 +491,33 @@ __device__ __forceinline__ void step_compute(L_t& L, const StepIO<T>& A, const t
           int ci = foot_cell(sx, x - fx), cj = foot_cell(sy, y - fy);
           ci = min(max(ci, i - 1), kind == NK_YEDGE ? i + 1 : i);
           cj = min(max(cj, j - 1), kind == NK_XEDGE ? j + 1 : j);
-          val[t] = rot_eval<T, NR, NC>(L.in, r + (cj - j), c + (ci - i), T(2) * (sx - T(ci)), T(2) * (sy - T(cj)));
+          val[t] = rot_eval<T>(L.in, r + (cj - j), c + (ci - i), T(2) * (sx - T(ci)), T(2) * (sy - T(cj)));
         }
         if constexpr (EQ == 2) {
-          const T cur = L.in[kind + 1][0][r][c];
+          const T cur = L.in(kind + 1, 0, r, c);
           tsv[it][kind][0] = (cur + T(4) * val[0]) + val[1];
         } else {
           tsv[it][kind][0] = val[0];
-          L.tsum2()[kind][0][jj][ii] = val[1];
+          L.ts2(kind, 0, jj, ii) = val[1];
         }
-        if (wrow) A.out[kind + 1][size_t(patch) * plane + obase] = val[1];
+        emit(it, kind, 0, wrow, obase, val[1]);
       }
     } else if constexpr (EQ == 4) {
       // Burgers (Sec. 2.2): the point value solves q = q^n(P - q tau (1, 1));
       // two fixed-point iterations from the mean of the averages around the
       // node.  The time sum holds the fluxes q^2/2 (Simpson in time).
-      const auto& av = L.in[0][0];
+      auto av = [&](int rr, int cc) { return L.in(0, 0, rr, cc); };
 #pragma unroll
       for (int kind = 0; kind < 3; ++kind) {
         if (kind == NK_XEDGE && !has_x) continue;
         if (kind == NK_YEDGE && !has_y) continue;
         T Q0;
         if (kind == NK_CORNER) {
-          Q0 = T(0.25) * ((av[r][c - 1] + av[r][c]) + (av[r - 1][c - 1] + av[r - 1][c]));
+          Q0 = T(0.25) * ((av(r, c - 1) + av(r, c)) + (av(r - 1, c - 1) + av(r - 1, c)));
         } else if (kind == NK_XEDGE) {
-          Q0 = T(0.5) * (av[r][c - 1] + av[r][c]);
+          Q0 = T(0.5) * (av(r, c - 1) + av(r, c));
         } else {
-          Q0 = T(0.5) * (av[r][c] + av[r - 1][c]);
+          Q0 = T(0.5) * (av(r, c) + av(r - 1, c));
         }
         const T X = kind == NK_YEDGE ? T(i) : T(i) - T(0.5);  // node in cell units
         const T Y = kind == NK_XEDGE ? T(j) : T(j) - T(0.5);
@@ -566,13 +532,13 @@ __device__ __forceinline__ void step_compute(L_t& L, const StepIO<T>& A, const t
             int ci = foot_cell(sx, Q), cj = foot_cell(sy, Q);
             ci = min(max(ci, i - 1), kind == NK_YEDGE ? i + 1 : i);
             cj = min(max(cj, j - 1), kind == NK_XEDGE ? j + 1 : j);
-            Q = rot_eval<T, NR, NC>(L.in, r + (cj - j), c + (ci - i), T(2) * (sx - T(ci)), T(2) * (sy - T(cj)));
+            Q = rot_eval<T>(L.in, r + (cj - j), c + (ci - i), T(2) * (sx - T(ci)), T(2) * (sy - T(cj)));
           }
           val[t] = Q;
         }
-        const T cur = L.in[kind + 1][0][r][c];
+        const T cur = L.in(kind + 1, 0, r, c);
         tsv[it][kind][0] = (T(0.5) * cur * cur + T(2) * val[0] * val[0]) + T(0.5) * val[1] * val[1];
-        if (wrow) A.out[kind + 1][size_t(patch) * plane + obase] = val[1];
+        emit(it, kind, 0, wrow, obase, val[1]);
       }
     }
   }
@@ -587,7 +553,7 @@ __device__ __forceinline__ void step_compute(L_t& L, const StepIO<T>& A, const t
     // not 2).
     auto kind_pass = [&](auto kc) {
       constexpr int K = decltype(kc)::value;
-      Walk2 v(threadIdx.x, kThreads, WN);
+      Walk2 v(threadIdx.x, NT, WN);
 #pragma unroll
       for (int it = 0; it < MAXIT; ++it, v.next()) {
         if (v.y >= ER) break;
@@ -596,26 +562,20 @@ __device__ __forceinline__ void step_compute(L_t& L, const StepIO<T>& A, const t
         if (K == NK_XEDGE && jj >= nrow) continue;  // x-edges of rows [jlo, jhi)
         if (K == NK_YEDGE && ii >= span) continue;  // y-edges of cols [ilo, ihi)
         const int r = jj + 1 + rofs, c = ii + coff;
-        const size_t obase = size_t(jlo + jj + kGhost) * A.pitch + (ilo + ii + kGhost);
+        const uint32_t obase = entry(ilo + ii, jlo + jj);
         const bool wst = K == NK_XEDGE || jj < nrow || last_tile;
-        T v1[3], vs[3];
+        T acc[2][3] = {{T(0), T(0), T(0)}, {T(0), T(0), T(0)}};
         if constexpr (sizeof(T) == 8) {
           constexpr int H = K == NK_CORNER ? 5 : 3;
-          T acc[2][3] = {{T(0), T(0), T(0)}, {T(0), T(0), T(0)}};
-          ac_orbit_range<T, K, NR, NC, 0, H>(L.in, r, c, W.w[K], acc);
-          ac_orbit_range<T, K, NR, NC, H, kOrbitTab[K].n>(L.in, r, c, W.w[K], acc);
-#pragma unroll
-          for (int q = 0; q < 3; ++q) {
-            v1[q] = acc[0][q];
-            vs[q] = acc[1][q];
-          }
+          ac_orbits<T, K, 0, H, BULK>(L.in, r, c, W.w[K], acc);
+          ac_orbits<T, K, H, kOrbitTab[K].n, BULK>(L.in, r, c, W.w[K], acc);
         } else {
-          ac_node<T, K, NR, NC>(L.in, r, c, W.w[K], v1, vs);
+          ac_orbits<T, K, 0, kOrbitTab[K].n, BULK>(L.in, r, c, W.w[K], acc);
         }
 #pragma unroll
         for (int q = 0; q < 3; ++q) {
-          tsv[it][K][q] = L.in[K + 1][q][r][c] + vs[q];
-          emit(it, K, q, wst, (size_t(q) * A.npatch + patch) * plane + obase, v1[q]);
+          tsv[it][K][q] = L.in(K + 1, q, r, c) + acc[1][q];
+          emit(it, K, q, wst, obase, acc[0][q]);
         }
       }
     };
@@ -624,9 +584,9 @@ __device__ __forceinline__ void step_compute(L_t& L, const StepIO<T>& A, const t
     kind_pass(std::integral_constant<int, NK_YEDGE>());
   }
   __syncthreads();
-  auto& ts = L.tsum();
+  auto ts = [&](int k, int q, int jj, int ii) -> T& { return L.ts(k, q, jj, ii); };
   {
-    Walk2 v(threadIdx.x, kThreads, WN);
+    Walk2 v(threadIdx.x, NT, WN);
 #pragma unroll
     for (int it = 0; it < MAXIT; ++it, v.next()) {
       if (v.y >= ER) break;
@@ -634,9 +594,9 @@ __device__ __forceinline__ void step_compute(L_t& L, const StepIO<T>& A, const t
       const int ii = v.x, jj = v.y;
 #pragma unroll
       for (int q = 0; q < NCOMP; ++q) {
-        ts[NK_CORNER][q][jj][ii] = tsv[it][NK_CORNER][q];
-        if (jj < nrow) ts[NK_XEDGE][q][jj][ii] = tsv[it][NK_XEDGE][q];
-        if (ii < span) ts[NK_YEDGE][q][jj][ii] = tsv[it][NK_YEDGE][q];
+        ts(NK_CORNER, q, jj, ii) = tsv[it][NK_CORNER][q];
+        if (jj < nrow) ts(NK_XEDGE, q, jj, ii) = tsv[it][NK_XEDGE][q];
+        if (ii < span) ts(NK_YEDGE, q, jj, ii) = tsv[it][NK_YEDGE][q];
       }
     }
   }
@@ -645,19 +605,19 @@ __device__ __forceinline__ void step_compute(L_t& L, const StepIO<T>& A, const t
   // ---- fluxes and conservative update (eq. 2dfv) of cells [ilo,ihi) x [jlo,jhi)
   const uint32_t smask = A.reg ? A.smask : 0u;
   const T inv36 = T(1) / T(36);
-  for (Walk2 w(threadIdx.x, kThreads, span); w.y < nrow; w.next()) {
+  for (Walk2 w(threadIdx.x, NT, span); w.y < nrow; w.next()) {
     const int ii = w.x, jj = w.y;
     const int i = ilo + ii, j = jlo + jj;
-    const size_t obase = size_t(j + kGhost) * A.pitch + (i + kGhost);
+    const uint32_t obase = entry(i, j);
     T FL[NCOMP], FR[NCOMP], GB[NCOMP], GT[NCOMP];
 #pragma unroll
     for (int q = 0; q < NCOMP; ++q) {
-      FL[q] = face_sum(ts[NK_CORNER][q][jj][ii], ts[NK_XEDGE][q][jj][ii], ts[NK_CORNER][q][jj + 1][ii]);
-      FR[q] = face_sum(ts[NK_CORNER][q][jj][ii + 1], ts[NK_XEDGE][q][jj][ii + 1],
-                       ts[NK_CORNER][q][jj + 1][ii + 1]);
-      GB[q] = face_sum(ts[NK_CORNER][q][jj][ii], ts[NK_YEDGE][q][jj][ii], ts[NK_CORNER][q][jj][ii + 1]);
-      GT[q] = face_sum(ts[NK_CORNER][q][jj + 1][ii], ts[NK_YEDGE][q][jj + 1][ii],
-                       ts[NK_CORNER][q][jj + 1][ii + 1]);
+      FL[q] = face_sum(ts(NK_CORNER, q, jj, ii), ts(NK_XEDGE, q, jj, ii), ts(NK_CORNER, q, jj + 1, ii));
+      FR[q] = face_sum(ts(NK_CORNER, q, jj, ii + 1), ts(NK_XEDGE, q, jj, ii + 1),
+                       ts(NK_CORNER, q, jj + 1, ii + 1));
+      GB[q] = face_sum(ts(NK_CORNER, q, jj, ii), ts(NK_YEDGE, q, jj, ii), ts(NK_CORNER, q, jj, ii + 1));
+      GT[q] = face_sum(ts(NK_CORNER, q, jj + 1, ii), ts(NK_YEDGE, q, jj + 1, ii),
+                       ts(NK_CORNER, q, jj + 1, ii + 1));
     }
     // physical fluxes of the Simpson sums: advection f = a q, g = b q;
     // acoustics f = c (u, p, 0), g = c (v, 0, p)  (Sec. 2.3)
@@ -669,9 +629,9 @@ __device__ __forceinline__ void step_compute(L_t& L, const StepIO<T>& A, const t
       // swirl (eq. swirlF, swirlG): the face-midpoint velocity at t, t+dt/2,
       // t+dt times the Simpson sum of the three nodes at that time
       const int rr = jj + 1 + rofs, cc = ii + coff;  // staged position of cell (i, j)
-      const auto& Q0 = L.in;
-      const auto& Qh = ts;
-      const auto& Qf = L.tsum2();
+      auto Q0 = [&](int k, int q, int r, int c) { return L.in(k, q, r, c); };
+      auto Qh = [&](int k, int q, int j, int i) { return L.ts(k, q, j, i); };
+      auto Qf = [&](int k, int q, int j, int i) { return L.ts2(k, q, j, i); };
       const T xl = px0 + T(i) * W.dx, xr = px0 + T(i + 1) * W.dx, xm = px0 + (T(i) + T(0.5)) * W.dx;
       const T yb = py0 + T(j) * W.dy, yt = py0 + T(j + 1) * W.dy, ym = py0 + (T(j) + T(0.5)) * W.dy;
       // the spatial factors of the face-midpoint velocities, then one
@@ -694,18 +654,18 @@ __device__ __forceinline__ void step_compute(L_t& L, const StepIO<T>& A, const t
         bB[k] = W.cos_fx[k] * BB;
         bT[k] = W.cos_fx[k] * BT;
       }
-      const T SL[3] = {face_sum(Q0[1][0][rr][cc], Q0[2][0][rr][cc], Q0[1][0][rr + 1][cc]),
-                       face_sum(Qh[NK_CORNER][0][jj][ii], Qh[NK_XEDGE][0][jj][ii], Qh[NK_CORNER][0][jj + 1][ii]),
-                       face_sum(Qf[NK_CORNER][0][jj][ii], Qf[NK_XEDGE][0][jj][ii], Qf[NK_CORNER][0][jj + 1][ii])};
-      const T SR[3] = {face_sum(Q0[1][0][rr][cc + 1], Q0[2][0][rr][cc + 1], Q0[1][0][rr + 1][cc + 1]),
-                       face_sum(Qh[NK_CORNER][0][jj][ii + 1], Qh[NK_XEDGE][0][jj][ii + 1], Qh[NK_CORNER][0][jj + 1][ii + 1]),
-                       face_sum(Qf[NK_CORNER][0][jj][ii + 1], Qf[NK_XEDGE][0][jj][ii + 1], Qf[NK_CORNER][0][jj + 1][ii + 1])};
-      const T SB[3] = {face_sum(Q0[1][0][rr][cc], Q0[3][0][rr][cc], Q0[1][0][rr][cc + 1]),
-                       face_sum(Qh[NK_CORNER][0][jj][ii], Qh[NK_YEDGE][0][jj][ii], Qh[NK_CORNER][0][jj][ii + 1]),
-                       face_sum(Qf[NK_CORNER][0][jj][ii], Qf[NK_YEDGE][0][jj][ii], Qf[NK_CORNER][0][jj][ii + 1])};
-      const T ST[3] = {face_sum(Q0[1][0][rr + 1][cc], Q0[3][0][rr + 1][cc], Q0[1][0][rr + 1][cc + 1]),
-                       face_sum(Qh[NK_CORNER][0][jj + 1][ii], Qh[NK_YEDGE][0][jj + 1][ii], Qh[NK_CORNER][0][jj + 1][ii + 1]),
-                       face_sum(Qf[NK_CORNER][0][jj + 1][ii], Qf[NK_YEDGE][0][jj + 1][ii], Qf[NK_CORNER][0][jj + 1][ii + 1])};
+      const T SL[3] = {face_sum(Q0(1, 0, rr, cc), Q0(2, 0, rr, cc), Q0(1, 0, rr + 1, cc)),
+                       face_sum(Qh(NK_CORNER, 0, jj, ii), Qh(NK_XEDGE, 0, jj, ii), Qh(NK_CORNER, 0, jj + 1, ii)),
+                       face_sum(Qf(NK_CORNER, 0, jj, ii), Qf(NK_XEDGE, 0, jj, ii), Qf(NK_CORNER, 0, jj + 1, ii))};
+      const T SR[3] = {face_sum(Q0(1, 0, rr, cc + 1), Q0(2, 0, rr, cc + 1), Q0(1, 0, rr + 1, cc + 1)),
+                       face_sum(Qh(NK_CORNER, 0, jj, ii + 1), Qh(NK_XEDGE, 0, jj, ii + 1), Qh(NK_CORNER, 0, jj + 1, ii + 1)),
+                       face_sum(Qf(NK_CORNER, 0, jj, ii + 1), Qf(NK_XEDGE, 0, jj, ii + 1), Qf(NK_CORNER, 0, jj + 1, ii + 1))};
+      const T SB[3] = {face_sum(Q0(1, 0, rr, cc), Q0(3, 0, rr, cc), Q0(1, 0, rr, cc + 1)),
+                       face_sum(Qh(NK_CORNER, 0, jj, ii), Qh(NK_YEDGE, 0, jj, ii), Qh(NK_CORNER, 0, jj, ii + 1)),
+                       face_sum(Qf(NK_CORNER, 0, jj, ii), Qf(NK_YEDGE, 0, jj, ii), Qf(NK_CORNER, 0, jj, ii + 1))};
+      const T ST[3] = {face_sum(Q0(1, 0, rr + 1, cc), Q0(3, 0, rr + 1, cc), Q0(1, 0, rr + 1, cc + 1)),
+                       face_sum(Qh(NK_CORNER, 0, jj + 1, ii), Qh(NK_YEDGE, 0, jj + 1, ii), Qh(NK_CORNER, 0, jj + 1, ii + 1)),
+                       face_sum(Qf(NK_CORNER, 0, jj + 1, ii), Qf(NK_YEDGE, 0, jj + 1, ii), Qf(NK_CORNER, 0, jj + 1, ii + 1))};
       fL[0] = (aL[0] * SL[0] + T(4) * aL[1] * SL[1] + aL[2] * SL[2]) * inv36;
       fR[0] = (aR[0] * SR[0] + T(4) * aR[1] * SR[1] + aR[2] * SR[2]) * inv36;
       gB[0] = (bB[0] * SB[0] + T(4) * bB[1] * SB[1] + bB[2] * SB[2]) * inv36;
@@ -723,12 +683,12 @@ __device__ __forceinline__ void step_compute(L_t& L, const StepIO<T>& A, const t
       const T b0 = W.omega * (px0 + T(i) * W.dx - W.xc);
       const T b1 = W.omega * (px0 + (T(i) + T(0.5)) * W.dx - W.xc);
       const T b2 = W.omega * (px0 + T(i + 1) * W.dx - W.xc);
-      fL[0] = (a0 * ts[NK_CORNER][0][jj][ii] + T(4) * a1 * ts[NK_XEDGE][0][jj][ii] + a2 * ts[NK_CORNER][0][jj + 1][ii]) * inv36;
-      fR[0] = (a0 * ts[NK_CORNER][0][jj][ii + 1] + T(4) * a1 * ts[NK_XEDGE][0][jj][ii + 1] +
-               a2 * ts[NK_CORNER][0][jj + 1][ii + 1]) * inv36;
-      gB[0] = (b0 * ts[NK_CORNER][0][jj][ii] + T(4) * b1 * ts[NK_YEDGE][0][jj][ii] + b2 * ts[NK_CORNER][0][jj][ii + 1]) * inv36;
-      gT[0] = (b0 * ts[NK_CORNER][0][jj + 1][ii] + T(4) * b1 * ts[NK_YEDGE][0][jj + 1][ii] +
-               b2 * ts[NK_CORNER][0][jj + 1][ii + 1]) * inv36;
+      fL[0] = (a0 * ts(NK_CORNER, 0, jj, ii) + T(4) * a1 * ts(NK_XEDGE, 0, jj, ii) + a2 * ts(NK_CORNER, 0, jj + 1, ii)) * inv36;
+      fR[0] = (a0 * ts(NK_CORNER, 0, jj, ii + 1) + T(4) * a1 * ts(NK_XEDGE, 0, jj, ii + 1) +
+               a2 * ts(NK_CORNER, 0, jj + 1, ii + 1)) * inv36;
+      gB[0] = (b0 * ts(NK_CORNER, 0, jj, ii) + T(4) * b1 * ts(NK_YEDGE, 0, jj, ii) + b2 * ts(NK_CORNER, 0, jj, ii + 1)) * inv36;
+      gT[0] = (b0 * ts(NK_CORNER, 0, jj + 1, ii) + T(4) * b1 * ts(NK_YEDGE, 0, jj + 1, ii) +
+               b2 * ts(NK_CORNER, 0, jj + 1, ii + 1)) * inv36;
     } else {
       fL[0] = A.c * FL[1] * inv36; fL[1] = A.c * FL[0] * inv36; fL[2] = T(0);
       fR[0] = A.c * FR[1] * inv36; fR[1] = A.c * FR[0] * inv36; fR[2] = T(0);
@@ -737,12 +697,12 @@ __device__ __forceinline__ void step_compute(L_t& L, const StepIO<T>& A, const t
     }
 #pragma unroll
     for (int q = 0; q < NCOMP; ++q) {
-      const T Q = L.in[0][q][jj + 1 + rofs][ii + coff];
+      const T Q = L.in(0, q, jj + 1 + rofs, ii + coff);
       const T Qn = Q - A.dtdx * (fR[q] - fL[q]) - A.dtdy * (gT[q] - gB[q]);
       if constexpr (TO_LDS) {
-        L.in[0][q][jj + 1 + rofs][ii + coff] = Qn;  // read only by this thread
+        L.in(0, q, jj + 1 + rofs, ii + coff) = Qn;  // read only by this thread
       } else {
-        A.out[0][(size_t(q) * A.npatch + patch) * plane + obase] = Qn;
+        *reinterpret_cast<T*>(A.plane_of(0, q, plane) + obase) = Qn;
       }
     }
     if (smask) {
@@ -763,7 +723,7 @@ __device__ __forceinline__ void step_compute(L_t& L, const StepIO<T>& A, const t
   if constexpr (TO_LDS) {
     // the new node values of the extended cells, over the time sums
     __syncthreads();
-    Walk2 v(threadIdx.x, kThreads, WN);
+    Walk2 v(threadIdx.x, NT, WN);
 #pragma unroll
     for (int it = 0; it < MAXIT; ++it, v.next()) {
       if (v.y >= ER) break;
@@ -772,9 +732,9 @@ __device__ __forceinline__ void step_compute(L_t& L, const StepIO<T>& A, const t
       const int r = jj + 1 + rofs, c = ii + coff;
 #pragma unroll
       for (int q = 0; q < NCOMP; ++q) {
-        L.in[1][q][r][c] = nv[it][NK_CORNER][q];
-        if (jj < nrow) L.in[2][q][r][c] = nv[it][NK_XEDGE][q];
-        if (ii < span) L.in[3][q][r][c] = nv[it][NK_YEDGE][q];
+        L.in(1, q, r, c) = nv[it][NK_CORNER][q];
+        if (jj < nrow) L.in(2, q, r, c) = nv[it][NK_XEDGE][q];
+        if (ii < span) L.in(3, q, r, c) = nv[it][NK_YEDGE][q];
       }
     }
   }
@@ -782,14 +742,20 @@ __device__ __forceinline__ void step_compute(L_t& L, const StepIO<T>& A, const t
 
 
 template <typename T, int EQ, int M, int TY, bool GN>
-__global__ __launch_bounds__(kThreads) void k_patch_step(const StepArgs<T> A,
-                                                         const typename WSel<T, EQ>::type W) {
+__global__ __launch_bounds__(kThreads) void k_patch_step(
+    const WithWeights<StepArgs<T>, typename WSel<T, EQ>::type> P) {
+  const StepArgs<T>& A = P.a;
+  const typename WSel<T, EQ>::type& W = EQ <= 1 ? weights_of(P) : P.w;
   constexpr int NCOMP = EQ == 1 ? 3 : 1;
   constexpr int NR = TY + 3;
   constexpr int NC = M + 5;
   __shared__ StepLds<T, NCOMP, NR, NC, EQ == 3 ? kLdsSwirl : kLdsAlias> L;
 
-  const int region = A.region;
+  // A complete level steps its interior region in whole tiles: with the
+  // region and the tile height known to the compiler the acoustic step takes
+  // 60 instead of 94 registers (FP32; FP64 106 instead of 180).
+  static_assert(M % TY == 0, "whole tiles");
+  const int region = GN ? 0 : A.region;
   const int ilo = -region, ihi = M + region;
   const int span = ihi - ilo;
   const int tiles = (span + TY - 1) / TY;
@@ -799,9 +765,8 @@ __global__ __launch_bounds__(kThreads) void k_patch_step(const StepArgs<T> A,
   const int patch = A.first + pl;
   const int tile = w - pl * tiles;
   const int jlo = ilo + tile * rows;
-  const int jhi = min(jlo + rows, ihi);
+  const int jhi = GN ? jlo + TY : min(jlo + rows, ihi);
   if (jlo >= jhi) return;  // block-uniform; cannot happen for the compiled (m, TY) pairs
-  const int nrow = jhi - jlo;
   const size_t plane = size_t(M + 5) * A.pitch;
 
   // ---- stage NR rows from j = jlo-1 (clamped to the array for a short last
@@ -814,7 +779,7 @@ __global__ __launch_bounds__(kThreads) void k_patch_step(const StepArgs<T> A,
     // the source patch and offset of a position are the same for every
     // (kind, component) plane
     gather_planes<T, kThreads, 4 * NCOMP, NR, NC>(
-        &L.in[0][0][0][0], [&](int p) { return A.in[p / NCOMP] + size_t(p % NCOMP) * A.npatch * plane; },
+        L.in.v, [&](int p) { return A.in[p / NCOMP] + size_t(p % NCOMP) * A.npatch * plane; },
         [&](int rr, int x) {
           const int j = min(jlo - 1 + rr, M + 2), i = x - kGhost;
           const int oy = j < 0 ? -1 : (j >= M ? 1 : 0);
@@ -824,14 +789,15 @@ __global__ __launch_bounds__(kThreads) void k_patch_step(const StepArgs<T> A,
           yy = yy < 0 ? yy + A.gny : (yy >= A.gny ? yy - A.gny : yy);
           const int src = A.first + yy * A.gnx + xx;
           return size_t(src) * plane + size_t(j - oy * M + kGhost) * A.pitch + (i - ox * M + kGhost);
-        });
+        },
+        [&](int p, int r, int x) { return L.in.pos(p / NCOMP, p % NCOMP, r, x); });
   } else {
     // the patch's own planes, (kind, component) in the image's order; rows
     // from jlo - 1, clamped to the array for a short last tile
     gather_planes<T, kThreads, 4 * NCOMP, NR, NC>(
-        &L.in[0][0][0][0],
-        [&](int p) { return A.in[p / NCOMP] + (size_t(p % NCOMP) * A.npatch + patch) * plane; },
-        [&](int rr, int x) { return size_t(min(jlo - 1 + rr, M + 2) + kGhost) * A.pitch + x; });
+        L.in.v, [&](int p) { return A.in[p / NCOMP] + (size_t(p % NCOMP) * A.npatch + patch) * plane; },
+        [&](int rr, int x) { return size_t(min(jlo - 1 + rr, M + 2) + kGhost) * A.pitch + x; },
+        [&](int p, int r, int x) { return L.in.pos(p / NCOMP, p % NCOMP, r, x); });
   }
   __syncthreads();
   // rotation, swirl: lower-left corner of the patch's cell (0,0)
@@ -863,7 +829,7 @@ __global__ __launch_bounds__(kThreads) void k_patch_step(const StepArgs<T> A,
 // Level advance: K steps of every patch of a level whose eight neighbours
 // are leaves of the same level, in one launch (temporal blocking).
 //
-// A block owns one patch.  It gathers the patch and a K-cell halo from the
+// A block owns one patch.  It gathers the patch and a halo of K cells from the
 // interiors of the 3x3 neighbourhood (each DOF from the patch owning its
 // cell, Sec. 2 ownership: exactly the values a same-level ghost fill copies),
 // then takes K steps in LDS on shrinking regions (step s updates cells
@@ -872,7 +838,14 @@ __global__ __launch_bounds__(kThreads) void k_patch_step(const StepArgs<T> A,
 // its own block, so K fused steps equal K separate fill+step passes.
 //
 // k_level_advance below is the acoustic kernel (three components, sector
-// means); advection has its own layout in k_level_advance_adv.
+// means): one step, or the fused pair of k_amr_step (the first step on the
+// layer-1 region into LDS, the second from there), both in the orbit form.
+// The dense stencils (770 multiply-adds per cell) took 405 us per launch of
+// two steps at 2048^2 (FP32, m = 16), this takes 247.  LDS reads (174 words
+// per cell and step) and vector instructions both fill about two thirds of
+// it; reading each cell's 75 neighbourhood values once into registers for all
+// three node kinds halves the reads, but at 144 registers gains nothing (264).  Advection has
+// its own layout in k_level_advance_adv.
 // ---------------------------------------------------------------------------
 
 template <typename T>
@@ -897,124 +870,53 @@ __device__ __forceinline__ int level_nbr(const AdvanceArgs<T>& A, int ix, int iy
 }
 
 template <typename T, int M, int K, int NT>
-__global__ __launch_bounds__(NT) void k_level_advance(const AdvanceArgs<T> A, const AcWeights<T> W) {
-  constexpr int NCOMP = 3;
-  constexpr int E = M + 2 * K + 1;     // node extent of the gathered block
-  constexpr int EMAX = M + 2 * K - 1;  // extended cells per side in the first step
-  constexpr int CPT = (EMAX * EMAX + NT - 1) / NT;  // extended cells per thread (first step)
-  __shared__ T st[4][NCOMP][E][E];
-  __shared__ T ts[3][NCOMP][E][E];
+__global__ __launch_bounds__(NT) void k_level_advance(
+    const WithWeights<AdvanceArgs<T>, AcOrbitWeights<T>> P) {
+  const AdvanceArgs<T>& A = P.a;
+  const AcOrbitWeights<T>& W = weights_of(P);
+  static_assert(K == 1 || K == 2, "one step, or a fused pair");
+  constexpr int NCOMP = 3, TY = K == 2 ? M + 2 : M, NR = TY + 3, NC = M + 5;
+  __shared__ StepLds<T, NCOMP, NR, NC, kLdsAlias> L;
 
   const int pl = xcd_patch(int(blockIdx.x), int(gridDim.x));
   const int patch = A.first + pl;
   const int pix = pl % A.nx, piy = pl / A.nx;
   const size_t plane = size_t(M + 5) * A.pitch;
+  const int jlo = K == 2 ? -1 : 0;  // row 0 of the staged block is jlo - 1, column 0 is -2
 
-  // ---- gather: LDS position (r, c) holds local index (c - K, r - K)
-  gather_planes<T, NT, 4 * NCOMP, E, E>(
-      &st[0][0][0][0], [&](int p) { return A.in[p / NCOMP] + size_t(p % NCOMP) * A.npatch * plane; },
+  gather_planes<T, NT, 4 * NCOMP, NR, NC>(
+      L.in.v, [&](int p) { return A.in[p / NCOMP] + size_t(p % NCOMP) * A.npatch * plane; },
       [&](int rr, int x) {
-        const int j = rr - K, i = x - K;
+        const int j = jlo - 1 + rr, i = x - kGhost;
         const int oy = j < 0 ? -1 : (j >= M ? 1 : 0);
         const int ox = i < 0 ? -1 : (i >= M ? 1 : 0);
         const int src = level_nbr(A, pix, piy, ox, oy);
-        const int li = i - ox * M, lj = j - oy * M;
-        return size_t(src) * plane + size_t(lj + kGhost) * A.pitch + (li + kGhost);
-      });
+        return size_t(src) * plane + size_t(j - oy * M + kGhost) * A.pitch + (i - ox * M + kGhost);
+      },
+      [&](int p, int r, int x) { return L.in.pos(p / NCOMP, p % NCOMP, r, x); });
   __syncthreads();
 
-  const T inv36 = T(1) / T(36);
-#pragma unroll 1
-  for (int s = 0; s < K; ++s) {
-    const int lo = -(K - 1 - s), hi = M + (K - 1 - s);
-    const int EC = hi - lo + 1;
-    T fnew[CPT][3][NCOMP];
-    // ---- node values of the extended cells [lo, hi]^2
-    {
-      Walk2 w(threadIdx.x, NT, EC);
+  StepIO<T> io;
 #pragma unroll
-      for (int u = 0; u < CPT; ++u, w.next()) {
-        const int ii = w.x, jj = w.y;
-        if (jj >= EC) break;
-        const int r = lo + jj + K, c = lo + ii + K;  // LDS position of cell (i, j)
-        const bool has_x = jj < EC - 1, has_y = ii < EC - 1;
-        {
-          T res[2][3];
-          ac_eval_rows<T, E, E, 0, kNbCorner>(st, r, c, W.corner, res);
-#pragma unroll
-          for (int q = 0; q < 3; ++q) {
-            ts[NK_CORNER][q][r][c] = (st[1][q][r][c] + T(4) * res[0][q]) + res[1][q];
-            fnew[u][NK_CORNER][q] = res[1][q];
-          }
-          if (has_x) {
-            ac_eval_rows<T, E, E, 1, kNbEdge>(st, r, c, W.xedge, res);
-#pragma unroll
-            for (int q = 0; q < 3; ++q) {
-              ts[NK_XEDGE][q][r][c] = (st[2][q][r][c] + T(4) * res[0][q]) + res[1][q];
-              fnew[u][NK_XEDGE][q] = res[1][q];
-            }
-          }
-          if (has_y) {
-            ac_eval_rows<T, E, E, 2, kNbEdge>(st, r, c, W.yedge, res);
-#pragma unroll
-            for (int q = 0; q < 3; ++q) {
-              ts[NK_YEDGE][q][r][c] = (st[3][q][r][c] + T(4) * res[0][q]) + res[1][q];
-              fnew[u][NK_YEDGE][q] = res[1][q];
-            }
-          }
-        }
-      }
-    }
-    __syncthreads();
-    // ---- commit the new point values, then update the averages of [lo, hi)^2
-    {
-      Walk2 w(threadIdx.x, NT, EC);
-#pragma unroll
-      for (int u = 0; u < CPT; ++u, w.next()) {
-        const int ii = w.x, jj = w.y;
-        if (jj >= EC) break;
-        const int r = lo + jj + K, c = lo + ii + K;
-        const bool has_x = jj < EC - 1, has_y = ii < EC - 1;
-#pragma unroll
-        for (int q = 0; q < NCOMP; ++q) {
-          st[1][q][r][c] = fnew[u][NK_CORNER][q];
-          if (has_x) st[2][q][r][c] = fnew[u][NK_XEDGE][q];
-          if (has_y) st[3][q][r][c] = fnew[u][NK_YEDGE][q];
-        }
-        if (!has_x || !has_y) continue;  // cells with i or j == hi are not updated
-        T FL[NCOMP], FR[NCOMP], GB[NCOMP], GT[NCOMP];
-#pragma unroll
-        for (int q = 0; q < NCOMP; ++q) {
-          FL[q] = face_sum(ts[NK_CORNER][q][r][c], ts[NK_XEDGE][q][r][c], ts[NK_CORNER][q][r + 1][c]);
-          FR[q] = face_sum(ts[NK_CORNER][q][r][c + 1], ts[NK_XEDGE][q][r][c + 1], ts[NK_CORNER][q][r + 1][c + 1]);
-          GB[q] = face_sum(ts[NK_CORNER][q][r][c], ts[NK_YEDGE][q][r][c], ts[NK_CORNER][q][r][c + 1]);
-          GT[q] = face_sum(ts[NK_CORNER][q][r + 1][c], ts[NK_YEDGE][q][r + 1][c], ts[NK_CORNER][q][r + 1][c + 1]);
-        }
-        T fL[NCOMP], fR[NCOMP], gB[NCOMP], gT[NCOMP];
-        fL[0] = A.c * FL[1] * inv36; fL[1] = A.c * FL[0] * inv36; fL[2] = T(0);
-        fR[0] = A.c * FR[1] * inv36; fR[1] = A.c * FR[0] * inv36; fR[2] = T(0);
-        gB[0] = A.c * GB[2] * inv36; gB[1] = T(0); gB[2] = A.c * GB[0] * inv36;
-        gT[0] = A.c * GT[2] * inv36; gT[1] = T(0); gT[2] = A.c * GT[0] * inv36;
-#pragma unroll
-        for (int q = 0; q < NCOMP; ++q)
-          st[0][q][r][c] = st[0][q][r][c] - A.dtdx * (fR[q] - fL[q]) - A.dtdy * (gT[q] - gB[q]);
-      }
-    }
+  for (int k = 0; k < 4; ++k) io.out[k] = A.out[k];
+  io.npatch = A.npatch;
+  io.pitch = A.pitch;
+  io.patch = patch;
+  io.dtdx = A.dtdx;
+  io.dtdy = A.dtdy;
+  io.a = A.a;
+  io.b = A.b;
+  io.c = A.c;
+  io.len_dt_x = io.len_dt_y = 0.0;
+  io.reg = nullptr;
+  io.smask = 0u;
+  if constexpr (K == 2) {
+    io.region = 1;
+    step_compute<T, 1, M, TY, true, NT>(L, io, W, -1, M + 1, T(0), T(0));
     __syncthreads();
   }
-
-  // ---- write the interior averages and the closed-square nodes
-  constexpr int NN = (M + 1) * (M + 1);
-  for (int e = threadIdx.x; e < NCOMP * NN; e += NT) {
-    const int q = e / NN, f = e - q * NN;
-    const int i = f % (M + 1), j = f / (M + 1);
-    const int r = j + K, c = i + K;
-    const size_t g = (size_t(q) * A.npatch + patch) * plane + size_t(j + kGhost) * A.pitch + (i + kGhost);
-    A.out[1][g] = st[1][q][r][c];
-    if (j < M) A.out[2][g] = st[2][q][r][c];
-    if (i < M) A.out[3][g] = st[3][q][r][c];
-    if (i < M && j < M) A.out[0][g] = st[0][q][r][c];
-  }
+  io.region = 0;
+  step_compute<T, 1, M, TY, false, NT>(L, io, W, 0, M, T(0), T(0), -jlo);
 }
 
 // ---------------------------------------------------------------------------
@@ -2010,28 +1912,49 @@ __device__ __forceinline__ T planned_value(T* const (&p)[2][4], uint32_t mask, i
   return T(v);
 }
 
-// The stencil weights a batched step reads: acoustics through wdev, the
-// advection weights (the kernel argument) as they are.  As a kernel argument
-// the acoustic table is loaded into scalar registers at entry, more than
-// there are, and the compiler parked the rest in vector lanes (a quarter of
-// the node phase's vector instructions were lane reads).  Through a
-// read-only pointer argument each node kind's weights are scalar loads where
-// the kind is evaluated.
+// Threads of a batched step's block, and the waves per SIMD its registers are
+// held to.  A fused pair at m = 16 walks 399 positions a substep: with 512
+// threads a thread has one node of each kind and its sums and new values take
+// half the registers of two.  Together with regions that the compiler knows
+// (below) the FP32 kernel fits 64 registers and the FP64 one 88, not 96 and
+// 168, and 8 and 4 waves of a SIMD hide latency, not 5 and 3.  On 1792 leaves
+// of four levels a coarse step went from 204 to 180 us (FP32) and from 329 to
+// 288 us (FP64), on 40 leaves of three levels from 57.9 to 47.4 us.  256
+// threads with known regions: 182 and 325 us; 448 (the 7 waves that 399
+// positions need): 191 us (FP32).
+template <int M, bool PAIR>
+constexpr int amr_threads() {
+  return PAIR && M == 16 ? 512 : kThreads;
+}
+template <typename T, int EQ, int M, bool PAIR>
+constexpr int amr_waves() {
+  return EQ == 1 && amr_threads<M, PAIR>() == 512 ? (sizeof(T) == 4 ? 8 : 5) : 1;
+}
+
+// The stencil weights a batched step reads: advection those of its argument,
+// acoustics a device copy through wdev (a read-only pointer argument; the
+// argument segment cost the launches of small hierarchies 0.7 us each).
+struct NoWeights {};
 template <typename T, int EQ>
-__device__ __forceinline__ const typename WSel<T, EQ>::type& amr_weights(const AcOrbitWeights<T>* wdev,
-                                                                        const typename WSel<T, EQ>::type& W) {
+struct AmrW { using type = AdvWeights<T>; };
+template <typename T>
+struct AmrW<T, 1> { using type = NoWeights; };
+template <typename T, int EQ, typename P_t>
+__device__ __forceinline__ const typename WSel<T, EQ>::type& amr_weights(const AcOrbitWeights<T>* wdev, const P_t& P) {
   if constexpr (EQ == 1)
     return *wdev;
   else
-    return W;
+    return weights_of(P);
 }
 
 template <typename T, int EQ, int M, int TY, bool PAIR>
-__global__ __launch_bounds__(kThreads) void k_amr_step(const AmrStepArgs<T> A, const typename WSel<T, EQ>::type W,
-                                                       const AcOrbitWeights<T>* __restrict__ wdev) {
+__global__ __launch_bounds__((amr_threads<M, PAIR>()), (amr_waves<T, EQ, M, PAIR>())) void k_amr_step(
+    const WithWeights<AmrStepArgs<T>, typename AmrW<T, EQ>::type> P, const AcOrbitWeights<T>* __restrict__ wdev) {
+  const AmrStepArgs<T>& A = P.a;
   static_assert(EQ == 0 || EQ == 1, "constant-coefficient equations only");
   static_assert(!PAIR || TY >= M + 2, "a fused pair steps the whole layer-1 region in one block");
   constexpr int NCOMP = EQ == 1 ? 3 : 1;
+  constexpr int NT = amr_threads<M, PAIR>();
   constexpr int NR = TY + 3;
   constexpr int NC = M + 5;
   __shared__ StepLds<T, NCOMP, NR, NC, kLdsAlias> L;
@@ -2055,7 +1978,9 @@ __global__ __launch_bounds__(kThreads) void k_amr_step(const AmrStepArgs<T> A, c
   const int tile = local - pl * tiles;
   const int patch = A.first[k] + pl;
   const int ilo = -region, ihi = M + region;
-  const int jlo = ilo + tile * rows;
+  // staged rows jlo - 1 ..; a pair kernel's blocks stage a whole patch's rows,
+  // whatever their region
+  const int jlo = PAIR ? -1 : ilo + tile * rows;
   const int jhi = min(jlo + rows, ihi);
   if (jlo >= jhi) return;  // block-uniform; cannot happen for the compiled (m, TY) pairs
   const int cur = (A.mask >> lvl) & 1;
@@ -2074,7 +1999,7 @@ __global__ __launch_bounds__(kThreads) void k_amr_step(const AmrStepArgs<T> A, c
   const int lo = region == 0 ? -1 : -2, hi = M + 2 - (region == 0 ? 1 : 0);
   {
     constexpr int PE = NR * NC;
-    constexpr int PER = (PE + kThreads - 1) / kThreads;
+    constexpr int PER = (PE + NT - 1) / NT;
     // element offsets fit in 32 bits (checked on the host): the loads take a
     // uniform plane base and a 32-bit per-lane offset
     const uint32_t plane32 = uint32_t(M + 5) * uint32_t(A.pitch);
@@ -2083,7 +2008,7 @@ __global__ __launch_bounds__(kThreads) void k_amr_step(const AmrStepArgs<T> A, c
     uint32_t use = 0;  // bit 4u + kind: position u, kind loaded
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
-      const int e = int(threadIdx.x) + u * kThreads;
+      const int e = int(threadIdx.x) + u * NT;
       const int rr = e / NC, x = e - rr * NC;
       const int j = jlo - 1 + rr, i = x - kGhost;
       const bool valid = e < PE && j <= hi && j >= lo && i >= lo && i <= hi;
@@ -2110,19 +2035,19 @@ __global__ __launch_bounds__(kThreads) void k_amr_step(const AmrStepArgs<T> A, c
           for (int q = 0; q < NCOMP; ++q) v[u][kind][q] = in[kind][off[u][kind] + uint32_t(q) * cstride];
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
-      const int e = int(threadIdx.x) + u * kThreads;
+      const int e = int(threadIdx.x) + u * NT;
       const int rr = e / NC, x = e - rr * NC;
 #pragma unroll
       for (int kind = 0; kind < 4; ++kind)
         if ((use >> (4 * u + kind)) & 1u)
 #pragma unroll
-          for (int q = 0; q < NCOMP; ++q) L.in[kind][q][rr][x] = v[u][kind][q];
+          for (int q = 0; q < NCOMP; ++q) L.in(kind, q, rr, x) = v[u][kind][q];
     }
   }
   if (gn != 0x1ffu) {
     const int nent = region == 0 ? A.ninner : A.nentries;
     const int4* const prow = A.plan + size_t(patch) * A.nentries;
-    for (int e = threadIdx.x; e < nent; e += kThreads) {
+    for (int e = threadIdx.x; e < nent; e += NT) {
       const int32_t code = A.entries[e];
       const int kind = code >> 24, i = ((code >> 12) & 0xfff) - kGhost, j = (code & 0xfff) - kGhost;
       const int rr = j - (jlo - 1);
@@ -2131,7 +2056,7 @@ __global__ __launch_bounds__(kThreads) void k_amr_step(const AmrStepArgs<T> A, c
       const T* own = in[kind] + size_t(patch) * plane + size_t(j + kGhost) * A.pitch + (i + kGhost);
 #pragma unroll
       for (int q = 0; q < NCOMP; ++q)
-        L.in[kind][q][rr][i + kGhost] = planned_value<T>(A.p, A.mask, A.npatch, A.pitch, M, A.fw, op, own, q);
+        L.in(kind, q, rr, i + kGhost) = planned_value<T>(A.p, A.mask, A.npatch, A.pitch, M, A.fw, op, own, q);
     }
   }
   __syncthreads();
@@ -2152,24 +2077,31 @@ __global__ __launch_bounds__(kThreads) void k_amr_step(const AmrStepArgs<T> A, c
   io.len_dt_y = A.len_dt_y[k];
   io.reg = (A.reg && A.side_mask) ? A.reg : nullptr;
   io.smask = io.reg ? A.side_mask[patch] : 0u;
-  bool pair = false;
-  if constexpr (PAIR) pair = A.pair && k == A.nlev - 1;
-  if (pair) {
-    // the finest level's pair of substeps (Sec. 3.2).  The first advances the
-    // layer-1 region (cells [-1, m], nodes [-1, m+1]) into LDS; the second
-    // steps the interior from exactly those values.  They are what a fill
-    // would stage at the odd time point: the fill there has no coarser
-    // sources, so coarse-fine ghosts keep the layer-1 values, and a
-    // same-level neighbour's interior is the same arithmetic on the same
-    // data.
-    if constexpr (PAIR) {
-      step_compute<T, EQ, M, TY, true>(L, io, amr_weights<T, EQ>(wdev, W), jlo, jhi, T(0), T(0));
+  const auto& W = amr_weights<T, EQ>(wdev, P);
+  constexpr bool BULK = NT == kThreads;
+  if constexpr (PAIR) {
+    // Whole-patch blocks, their regions known to the compiler (which takes
+    // fewer registers than with the region as a variable).  The finest
+    // level's pair of substeps (Sec. 3.2): the first advances the layer-1
+    // region (cells [-1, m], nodes [-1, m+1]) into LDS; the second steps the
+    // interior from exactly those values.  They are what a fill would stage
+    // at the odd time point: the fill there has no coarser sources, so
+    // coarse-fine ghosts keep the layer-1 values, and a same-level
+    // neighbour's interior is the same arithmetic on the same data.
+    const bool pair = A.pair && k == A.nlev - 1;
+    if (region == 1) {
+      io.region = 1;
+      if (!pair) {
+        step_compute<T, EQ, M, TY, false, NT, BULK>(L, io, W, -1, M + 1, T(0), T(0));
+        return;
+      }
+      step_compute<T, EQ, M, TY, true, NT, BULK>(L, io, W, -1, M + 1, T(0), T(0));
       __syncthreads();
-      io.region = 0;  // interior
-      step_compute<T, EQ, M, TY>(L, io, amr_weights<T, EQ>(wdev, W), 0, M, T(0), T(0), -jlo);
     }
+    io.region = 0;
+    step_compute<T, EQ, M, TY, false, NT, BULK>(L, io, W, 0, M, T(0), T(0), 1);
   } else {
-    step_compute<T, EQ, M, TY>(L, io, amr_weights<T, EQ>(wdev, W), jlo, jhi, T(0), T(0));
+    step_compute<T, EQ, M, TY, false, NT, BULK>(L, io, W, jlo, jhi, T(0), T(0));
   }
 }
 
@@ -2502,14 +2434,10 @@ hipError_t scratch_sums(double** ptr) {
 // ---------------------------------------------------------------------------
 
 // The weights a patch step of equation EQ takes from the host's table
-// (acoustics: the orbit form of AcAllWeights; advection: the first member of
-// AdvAllWeights).
+// (advection: the first member of AdvAllWeights).
 template <typename T, int EQ>
 static const typename WSel<T, EQ>::type& step_weights(const void* p) {
-  if constexpr (EQ == 1)
-    return static_cast<const AcAllWeights<T>*>(p)->orbit;
-  else
-    return *static_cast<const typename WSel<T, EQ>::type*>(p);
+  return *static_cast<const typename WSel<T, EQ>::type*>(p);
 }
 
 template <typename T, int EQ, int M, int TY>
@@ -2527,11 +2455,11 @@ static hipError_t launch_step_t(const StepLaunch& s, hipStream_t st) {
   const int span = M + 2 * s.region;
   const int tiles = (span + TY - 1) / TY;
   const dim3 grid(unsigned(s.count * tiles));
-  const auto& W = step_weights<T, EQ>(s.weights);
+  const WithWeights<StepArgs<T>, typename WSel<T, EQ>::type> P{A, step_weights<T, EQ>(s.weights)};
   if (s.gnx > 0)
-    hipLaunchKernelGGL((k_patch_step<T, EQ, M, TY, true>), grid, dim3(kThreads), 0, st, A, W);
+    hipLaunchKernelGGL((k_patch_step<T, EQ, M, TY, true>), grid, dim3(kThreads), 0, st, P);
   else
-    hipLaunchKernelGGL((k_patch_step<T, EQ, M, TY, false>), grid, dim3(kThreads), 0, st, A, W);
+    hipLaunchKernelGGL((k_patch_step<T, EQ, M, TY, false>), grid, dim3(kThreads), 0, st, P);
   return hipGetLastError();
 }
 
@@ -2601,8 +2529,10 @@ static hipError_t launch_amr_t(const AmrStepLaunch& s, hipStream_t st) {
   A.gnflags = s.gnflags;
   A.pair = PAIR && s.pair;
   const auto* wdev = static_cast<const AcOrbitWeights<T>*>(s.weights_dev);
-  const auto& W = step_weights<T, EQ>(s.weights);
-  hipLaunchKernelGGL((k_amr_step<T, EQ, M, TY, PAIR>), dim3(unsigned(blocks)), dim3(kThreads), 0, st, A, W, wdev);
+  WithWeights<AmrStepArgs<T>, typename AmrW<T, EQ>::type> P{A, {}};
+  if constexpr (EQ == 0) P.w = step_weights<T, EQ>(s.weights);
+  hipLaunchKernelGGL((k_amr_step<T, EQ, M, TY, PAIR>), dim3(unsigned(blocks)), dim3((amr_threads<M, PAIR>())), 0, st, P,
+                     wdev);
   return hipGetLastError();
 }
 
@@ -2733,15 +2663,15 @@ static hipError_t launch_adv_t(const AdvanceLaunch& s, hipStream_t st) {
     else
       hipLaunchKernelGGL((k_level_advance_adv<T, M, K, NT, false>), grid, dim3(NT), 0, st, A, W);
   } else {
-    hipLaunchKernelGGL((k_level_advance<T, M, K, NT>), grid, dim3(NT), 0, st, A,
-                       static_cast<const AcAllWeights<T>*>(s.weights)->dense);
+    const WithWeights<AdvanceArgs<T>, AcOrbitWeights<T>> P{A, *static_cast<const AcOrbitWeights<T>*>(s.weights)};
+    hipLaunchKernelGGL((k_level_advance<T, M, K, NT>), grid, dim3(NT), 0, st, P);
   }
   return hipGetLastError();
 }
 
 // Supported (m, K, threads) shapes of the level advance, per precision and
-// equation.  LDS: advection 10 E^2 words, acoustics 21 E^2 words, with
-// E = m + 2K + 1.
+// equation.  LDS: advection 10 E^2 words with E = m + 2K + 1 (two-pass
+// kernel), acoustics 12 (m + 5)(m + 2K + 1) words.
 #define AF_ADV_SHAPES(X)                                                                                 \
   X(float, 0, 32, 1, 256) X(float, 0, 32, 2, 256) X(float, 0, 32, 2, 512) X(float, 0, 32, 4, 512)      \
   X(float, 0, 32, 4, 1024) X(float, 0, 32, 5, 1024) X(float, 0, 32, 6, 768) X(float, 0, 32, 6, 1024)   \

@@ -18,7 +18,7 @@ struct StepLaunch {
   double* reg;
   const uint8_t* side_mask;
   const int32_t* leaf_xy;  // [npatch][2] patch (ix, iy); rotation only
-  const void* weights;  // AdvAllWeights<T>, AcAllWeights<T> or RotParams<T>, ... matching fp32/eq
+  const void* weights;  // AdvAllWeights<T>, AcOrbitWeights<T> or RotParams<T>, ... matching fp32/eq
   int gnx = 0, gny = 0;  // > 0: complete level, cells outside a patch come from its neighbours
 };
 
@@ -60,7 +60,7 @@ struct AmrStepLaunch {
   const FillWeights* fw;
   const int32_t* nbr;
   const uint32_t* gnflags;
-  const void* weights;  // AdvAllWeights<T> or AcAllWeights<T>
+  const void* weights;  // AdvAllWeights<T> or AcOrbitWeights<T>
   const void* weights_dev;  // acoustics: AcOrbitWeights<T> on the device
   // the last level (the finest, region layer 1) takes both substeps of its
   // pair in one block (m = 8 or 16; whole-patch tiles)
