@@ -265,6 +265,53 @@ const void* weights_dev_for(af_ctx* c, double dtdx, double dtdy) {
   return d;
 }
 
+// One step's parameters on a level with cells dx x dy, formed in FP64.
+
+template <typename T>
+void rot_params(const af_problem& P, double dx, double dy, double dt, RotParams<T>* W) {
+  for (int k = 0; k < 2; ++k) {
+    const double th = P.omega * (k + 1) * 0.5 * dt, sh = std::sin(0.5 * th);
+    const double v = 2.0 * sh * sh, s = std::sin(th);  // 1 - cos without cancellation
+    W->vx[k] = T(v / dx);
+    W->sx[k] = T(s / dx);
+    W->vy[k] = T(v / dy);
+    W->sy[k] = T(s / dy);
+  }
+  W->x0 = T(P.x0); W->y0 = T(P.y0); W->dx = T(dx); W->dy = T(dy);
+  W->omega = T(P.omega); W->xc = T(P.xc); W->yc = T(P.yc);
+}
+
+template <typename T>
+void swirl_params(const af_problem& P, double dx, double dy, double t, double dt, SwirlParams<T>* W) {
+  // cos(pi s) at every time the step needs, formed as the traces form them
+  // (t + tau, then stage offsets -tau/2, -tau)
+  constexpr double kPi = 3.14159265358979323846264338327950288;
+  for (int k = 0; k < 2; ++k) {
+    const double tau = (k + 1) * 0.5 * dt, t1 = t + tau;
+    W->tau[k] = T(tau);
+    W->h6[k] = T(tau / 6.0);
+    W->cos_rk[k][0] = T(std::cos(kPi * t1));
+    W->cos_rk[k][1] = T(std::cos(kPi * (t1 - 0.5 * tau)));
+    W->cos_rk[k][2] = T(std::cos(kPi * (t1 - tau)));
+  }
+  for (int k = 0; k < 3; ++k) W->cos_fx[k] = T(std::cos(kPi * (t + 0.5 * k * dt)));
+  W->x0 = T(P.x0); W->y0 = T(P.y0); W->dx = T(dx); W->dy = T(dy);
+  W->idx = T(1.0 / dx);
+  W->idy = T(1.0 / dy);
+  W->kx = T(std::sin(kPi * dx) / (kPi * dx));
+  W->ky = T(std::sin(kPi * dy) / (kPi * dy));
+  W->small = kPi * dt <= kSmallAngle;  // |a|, |b| <= 1
+}
+
+template <typename T>
+void burgers_params(double dx, double dy, double dt, BurgersParams<T>* W) {
+  for (int k = 0; k < 2; ++k) {
+    const double tau = (k + 1) * 0.5 * dt;
+    W->tdx[k] = T(tau / dx);
+    W->tdy[k] = T(tau / dy);
+  }
+}
+
 BufLaunch make_buf(const af_ctx* c, const af_state* b0, const af_state* b1, uint32_t mask) {
   BufLaunch B;
   for (int k = 0; k < 4; ++k) {
@@ -610,50 +657,16 @@ static af_status patch_step_gather(af_ctx* ctx, const af_state* in, af_state* ou
   L.gny = gny;
   if (ctx->P.eq == AF_ROTATION) {
     // the rotation angle depends on dt itself, not on dt/dx: no cache
-    const double th[2] = {ctx->P.omega * 0.5 * dt, ctx->P.omega * dt};
-    for (int t = 0; t < 2; ++t) {
-      rp64.cs[t] = std::cos(th[t]);
-      rp64.sn[t] = std::sin(th[t]);
-    }
-    rp64.x0 = ctx->P.x0; rp64.y0 = ctx->P.y0; rp64.dx = dx; rp64.dy = dy;
-    rp64.omega = ctx->P.omega; rp64.xc = ctx->P.xc; rp64.yc = ctx->P.yc;
-    rp32.cs[0] = float(rp64.cs[0]); rp32.cs[1] = float(rp64.cs[1]);
-    rp32.sn[0] = float(rp64.sn[0]); rp32.sn[1] = float(rp64.sn[1]);
-    rp32.x0 = float(rp64.x0); rp32.y0 = float(rp64.y0); rp32.dx = float(dx); rp32.dy = float(dy);
-    rp32.omega = float(rp64.omega); rp32.xc = float(rp64.xc); rp32.yc = float(rp64.yc);
+    rot_params(ctx->P, dx, dy, dt, &rp64);
+    rot_params(ctx->P, dx, dy, dt, &rp32);
     L.weights = ctx->fp32() ? static_cast<const void*>(&rp32) : static_cast<const void*>(&rp64);
   } else if (ctx->P.eq == AF_SWIRL) {
-    // cos(pi s) at every time the step needs, formed as the traces form them
-    // (t + tau, then stage offsets -tau/2, -tau)
-    constexpr double kPi = 3.14159265358979323846264338327950288;
-    const double tau[2] = {0.5 * dt, dt};
-    for (int k = 0; k < 2; ++k) {
-      const double t1 = t + tau[k], hh = -tau[k];
-      sp64.tau[k] = tau[k];
-      sp64.cos_rk[k][0] = std::cos(kPi * t1);
-      sp64.cos_rk[k][1] = std::cos(kPi * (t1 + 0.5 * hh));
-      sp64.cos_rk[k][2] = std::cos(kPi * (t1 + hh));
-    }
-    for (int k = 0; k < 3; ++k) sp64.cos_fx[k] = std::cos(kPi * (t + 0.5 * k * dt));
-    sp64.x0 = ctx->P.x0; sp64.y0 = ctx->P.y0; sp64.dx = dx; sp64.dy = dy;
-    sp64.kx = std::sin(kPi * dx) / (kPi * dx);
-    sp64.ky = std::sin(kPi * dy) / (kPi * dy);
-    sp32.x0 = float(sp64.x0); sp32.y0 = float(sp64.y0); sp32.dx = float(dx); sp32.dy = float(dy);
-    sp32.kx = float(sp64.kx); sp32.ky = float(sp64.ky);
-    for (int k = 0; k < 2; ++k) {
-      sp32.tau[k] = float(sp64.tau[k]);
-      for (int q = 0; q < 3; ++q) sp32.cos_rk[k][q] = float(sp64.cos_rk[k][q]);
-    }
-    for (int k = 0; k < 3; ++k) sp32.cos_fx[k] = float(sp64.cos_fx[k]);
+    swirl_params(ctx->P, dx, dy, t, dt, &sp64);
+    swirl_params(ctx->P, dx, dy, t, dt, &sp32);
     L.weights = ctx->fp32() ? static_cast<const void*>(&sp32) : static_cast<const void*>(&sp64);
   } else if (ctx->P.eq == AF_BURGERS) {
-    for (int k = 0; k < 2; ++k) {
-      const double tau = (k + 1) * 0.5 * dt;
-      bp64.tdx[k] = tau / dx;
-      bp64.tdy[k] = tau / dy;
-      bp32.tdx[k] = float(bp64.tdx[k]);
-      bp32.tdy[k] = float(bp64.tdy[k]);
-    }
+    burgers_params(dx, dy, dt, &bp64);
+    burgers_params(dx, dy, dt, &bp32);
     L.weights = ctx->fp32() ? static_cast<const void*>(&bp32) : static_cast<const void*>(&bp64);
   } else {
     L.weights = weights_for(ctx, dt / dx, dt / dy);

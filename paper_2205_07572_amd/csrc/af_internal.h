@@ -201,11 +201,12 @@ struct CFFace {
 };
 
 // Solid-body rotation (Sec. 4.2) for one step: the node positions of a patch
-// and the rotation that traces a node back over tau = dt/2 (index 0) and dt
-// (index 1).
+// and the displacement of a node over tau = dt/2 (index 0) and dt (index 1) in
+// cells: with (rx, ry) the node relative to the centre, (rx vx - ry sx,
+// ry vy + rx sy).
 template <typename T>
 struct RotParams {
-  T cs[2], sn[2];     // cos, sin of omega tau
+  T vx[2], sx[2], vy[2], sy[2];  // (1 - cos omega tau) / dx, sin / dx, the same over dy
   T x0, y0, dx, dy;   // domain origin, cell size of the level
   T omega, xc, yc;    // a = -omega (y - yc), b = omega (x - xc)
 };
@@ -218,9 +219,15 @@ struct SwirlParams {
   T x0, y0, dx, dy;  // domain origin, cell size of the level
   T kx, ky;          // sin(pi dx) / (pi dx), sin(pi dy) / (pi dy)
   T tau[2];          // dt/2, dt: the two traces back to t
+  T h6[2], idx, idy; // tau / 6, 1 / dx, 1 / dy
   T cos_rk[2][3];    // cos(pi s) at the Runge-Kutta times t+tau, t+tau/2, t of each trace
   T cos_fx[3];       // cos(pi s) at t, t+dt/2, t+dt (Simpson times of the fluxes)
+  int32_t small;     // pi dt (a point's largest move) is a small angle
 };
+
+// Angles up to which the swirl shifts a point's sine and cosine by their
+// Taylor polynomials.
+constexpr double kSmallAngle = 0.4;
 
 // Burgers (Sec. 2.2): tau / dx and tau / dy for tau = dt/2 and dt.
 template <typename T>
