@@ -312,6 +312,35 @@ void burgers_params(double dx, double dy, double dt, BurgersParams<T>* W) {
   }
 }
 
+// Parameters of levels l0 .. F for their steps from time point tau of the
+// coarse step [t0, t0 + dt0] (tau in steps of level F), then those of level
+// F's next step (a fused pair's second).
+template <typename T>
+struct LevelParams {
+  union {
+    RotParams<T> rot[kMaxLevels + 1];
+    SwirlParams<T> swirl[kMaxLevels + 1];
+    BurgersParams<T> burgers[kMaxLevels + 1];
+  };
+  LevelParams() {}
+};
+
+template <typename T>
+const void* level_params(const af_ctx* ctx, int l0, int F, int tau, double t0, double dt0, LevelParams<T>* w) {
+  const int n = F - l0 + 1;
+  for (int k = 0; k <= n; ++k) {
+    const int l = k < n ? l0 + k : F, at = k < n ? tau : tau + 1;
+    const double dtl = dt0 / double(1 << l), t = t0 + double(at) / double(1 << F) * dt0;
+    const double dx = ctx->dx(l), dy = ctx->dy(l);
+    switch (ctx->P.eq) {
+      case AF_ROTATION: rot_params(ctx->P, dx, dy, dtl, &w->rot[k]); break;
+      case AF_SWIRL: swirl_params(ctx->P, dx, dy, t, dtl, &w->swirl[k]); break;
+      default: burgers_params(dx, dy, dtl, &w->burgers[k]);
+    }
+  }
+  return w;
+}
+
 BufLaunch make_buf(const af_ctx* c, const af_state* b0, const af_state* b1, uint32_t mask) {
   BufLaunch B;
   for (int k = 0; k < 4; ++k) {
@@ -1217,7 +1246,7 @@ struct Driver {
     return AF_OK;
   }
 
-  // ---- batched coarse step (constant coefficients, Sec. 3.2): one launch
+  // ---- batched coarse step (Sec. 3.2): one launch
   // per substep start time for all levels that start a step then, with the
   // ghost data staged from the fill plans; before it, one launch for the
   // conservative fix of the levels that just completed a pair and the
@@ -1243,10 +1272,14 @@ struct Driver {
     return AF_OK;
   }
 
+  // the batched step addresses a DOF array with 32-bit element offsets
+  bool offsets_fit() const {
+    return double(bufs[0].npatch) * (ctx->P.m + 5) * bufs[0].pitch * ctx->ncomp < 2147483648.0;
+  }
+
   af_status batched_step(int tau, int l0) {
     const int F = h->H.finest;
-    // the batched step addresses a DOF array with 32-bit element offsets
-    if (double(bufs[0].npatch) * (ctx->P.m + 5) * bufs[0].pitch * ctx->ncomp >= 2147483648.0)
+    if (!offsets_fit())
       return fail(AF_ERR_LAYOUT, "af_amr_coarse_step: a DOF array of 2^31 or more elements");
     const double dt0 = dt0_;
     AmrStepLaunch L{};
@@ -1286,7 +1319,13 @@ struct Driver {
     L.fw = ctx->d_fillw;
     L.nbr = h->d_nbr;
     L.gnflags = h->d_gnflags;
-    L.weights = weights_for(ctx, L.dtdx, L.dtdy);
+    L.leaf_xy = h->d_xy;
+    LevelParams<float> p32;
+    LevelParams<double> p64;
+    if (ctx->P.eq == AF_ADVECTION || ctx->P.eq == AF_ACOUSTICS)
+      L.weights = weights_for(ctx, L.dtdx, L.dtdy);
+    else
+      L.weights = ctx->fp32() ? level_params(ctx, l0, F, tau, t0_, dt0_, &p32) : level_params(ctx, l0, F, tau, t0_, dt0_, &p64);
     if (!L.weights) return fail(AF_ERR_STATE, "acoustic stencils lack their mirror symmetry");
     if (ctx->P.eq == AF_ACOUSTICS && !(L.weights_dev = weights_dev_for(ctx, L.dtdx, L.dtdy)))
       return fail(AF_ERR_DEVICE, "acoustic weight upload failed");
@@ -1313,7 +1352,7 @@ struct Driver {
   double* ev_cells = nullptr;
   int max_ev = 0, nev = 0;
 
-  double dt0_ = 0.0;
+  double t0_ = 0.0, dt0_ = 0.0;
   bool pair_ = false;
   // several coarse steps in one call (af_amr_coarse_steps): the last launch
   // of a step, the fix of levels 0..F-1, joins the first launch of the next
@@ -1321,8 +1360,9 @@ struct Driver {
   bool defer_fix = false;    // leave this step's final fix to the next step
   bool pending_fix = false;  // the previous step's final fix is still to make
 
-  af_status coarse_step_batched(double dt0) {
+  af_status coarse_step_batched(double t0, double dt0) {
     const int F = h->H.finest;
+    t0_ = t0;
     dt0_ = dt0;
     af_status s;
     for (int l = 0; l <= F; ++l)
@@ -1350,7 +1390,10 @@ struct Driver {
   }
 
   af_status coarse_step(double t0, double dt0) {
-    if (!gnx && (ctx->P.eq == AF_ADVECTION || ctx->P.eq == AF_ACOUSTICS)) return coarse_step_batched(dt0);
+    // constant coefficients: always (a larger array is an error); variable
+    // velocities: the recursion takes what the 32-bit offsets do not reach
+    if (!gnx && (ctx->P.eq == AF_ADVECTION || ctx->P.eq == AF_ACOUSTICS || offsets_fit()))
+      return coarse_step_batched(t0, dt0);
     if (!gnx) {
       af_status s = af_ghost_fill(ctx, h, bufs, mask, 0, 0, st);
       if (s != AF_OK) return s;

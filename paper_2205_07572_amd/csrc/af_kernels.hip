@@ -429,8 +429,6 @@ struct StepIO {
 template <typename T, int EQ, int M, int TY, bool TO_LDS = false, int NT = kThreads, bool BULK = false, typename L_t>
 __device__ __forceinline__ void step_compute(L_t& L, const StepIO<T>& A, const typename WSel<T, EQ>::type& W,
                                              int jlo, int jhi, T px0, T py0, int rofs = 0) {
-  static_assert(!TO_LDS || ((EQ == 0 || EQ == 1) && !L_t::kSeparate),
-                "a fused pair needs a constant-coefficient equation and the aliased LDS layout");
   constexpr int NCOMP = EQ == 1 ? 3 : 1;
   constexpr int NC = M + 5;
   const int patch = A.patch;
@@ -1950,6 +1948,7 @@ struct AmrStepArgs {
   const int32_t* nbr;              // [nleaves][9] same-level neighbours (k_fill_plan)
   const uint32_t* gnflags;         // [nleaves] directions staged by the same-level gather
   int32_t pair;                    // the last level takes both substeps of its pair
+  const int32_t* leaf_xy;          // [npatch][2] patch (ix, iy); rotation and swirl only
 };
 
 // Interior DOFs of a patch that no fill writes (af_ctx_create's fill set is
@@ -2014,33 +2013,46 @@ constexpr int amr_waves() {
   return EQ == 1 && amr_threads<M, PAIR>() == 512 ? (sizeof(T) == 4 ? 8 : 5) : 1;
 }
 
-// The stencil weights a batched step reads: advection those of its argument,
-// acoustics a device copy through wdev (a read-only pointer argument; the
-// argument segment cost the launches of small hierarchies 0.7 us each).
+// The weights or parameters a batched step reads: advection those of its
+// argument, acoustics a device copy through wdev (a read-only pointer
+// argument; the argument segment cost the launches of small hierarchies 0.7 us
+// each).  The equations with variable velocities take one set per level (cell
+// sizes, time steps, the times of a level's step), and `second` for the
+// second substep of a fused pair.
 struct NoWeights {};
+template <typename W>
+struct LevelParams {
+  W lev[kMaxLevels], second;
+};
 template <typename T, int EQ>
-struct AmrW { using type = AdvWeights<T>; };
+struct AmrW { using type = LevelParams<typename WSel<T, EQ>::type>; };
+template <typename T>
+struct AmrW<T, 0> { using type = AdvWeights<T>; };
 template <typename T>
 struct AmrW<T, 1> { using type = NoWeights; };
 template <typename T, int EQ, typename P_t>
-__device__ __forceinline__ const typename WSel<T, EQ>::type& amr_weights(const AcOrbitWeights<T>* wdev, const P_t& P) {
-  if constexpr (EQ == 1)
+__device__ __forceinline__ const typename WSel<T, EQ>::type& amr_weights(const AcOrbitWeights<T>* wdev, const P_t& P,
+                                                                         int k, bool second) {
+  if constexpr (EQ == 1) {
     return *wdev;
-  else
+  } else if constexpr (EQ == 0) {
     return weights_of(P);
+  } else {
+    const auto& W = weights_of(P);
+    return second ? W.second : W.lev[k];
+  }
 }
 
 template <typename T, int EQ, int M, int TY, bool PAIR>
 __global__ __launch_bounds__((amr_threads<M, PAIR>()), (amr_waves<T, EQ, M, PAIR>())) void k_amr_step(
     const WithWeights<AmrStepArgs<T>, typename AmrW<T, EQ>::type> P, const AcOrbitWeights<T>* __restrict__ wdev) {
   const AmrStepArgs<T>& A = P.a;
-  static_assert(EQ == 0 || EQ == 1, "constant-coefficient equations only");
   static_assert(!PAIR || TY >= M + 2, "a fused pair steps the whole layer-1 region in one block");
   constexpr int NCOMP = EQ == 1 ? 3 : 1;
   constexpr int NT = amr_threads<M, PAIR>();
   constexpr int NR = TY + 3;
   constexpr int NC = M + 5;
-  __shared__ StepLds<T, NCOMP, NR, NC, kLdsAlias> L;
+  __shared__ StepLds<T, NCOMP, NR, NC, EQ == 3 ? kLdsSwirl : kLdsAlias> L;
 
   // ---- block -> (level, patch, tile).  Each level's block range is a
   // multiple of 8 long, so every XCD takes an equal share of every level (the
@@ -2142,6 +2154,14 @@ __global__ __launch_bounds__((amr_threads<M, PAIR>()), (amr_waves<T, EQ, M, PAIR
         L.in(kind, q, rr, i + kGhost) = planned_value<T>(A.p, A.mask, A.npatch, A.pitch, M, A.fw, op, own, q);
     }
   }
+  const auto& W = amr_weights<T, EQ>(wdev, P, k, false);
+  // rotation, swirl: lower-left corner of the patch's cell (0,0)
+  T px0 = T(0), py0 = T(0);
+  if constexpr (EQ == 2 || EQ == 3) {
+    px0 = W.x0 + T(A.leaf_xy[2 * patch] * M) * W.dx;
+    py0 = W.y0 + T(A.leaf_xy[2 * patch + 1] * M) * W.dy;
+  }
+  if constexpr (EQ == 3) swirl_tables<T, M, NR, NT>(L, W, px0, py0, jlo - 1);
   __syncthreads();
 
   StepIO<T> io;
@@ -2160,7 +2180,6 @@ __global__ __launch_bounds__((amr_threads<M, PAIR>()), (amr_waves<T, EQ, M, PAIR
   io.len_dt_y = A.len_dt_y[k];
   io.reg = (A.reg && A.side_mask) ? A.reg : nullptr;
   io.smask = io.reg ? A.side_mask[patch] : 0u;
-  const auto& W = amr_weights<T, EQ>(wdev, P);
   constexpr bool BULK = NT == kThreads;
   if constexpr (PAIR) {
     // Whole-patch blocks, their regions known to the compiler (which takes
@@ -2175,16 +2194,16 @@ __global__ __launch_bounds__((amr_threads<M, PAIR>()), (amr_waves<T, EQ, M, PAIR
     if (region == 1) {
       io.region = 1;
       if (!pair) {
-        step_compute<T, EQ, M, TY, false, NT, BULK>(L, io, W, -1, M + 1, T(0), T(0));
+        step_compute<T, EQ, M, TY, false, NT, BULK>(L, io, W, -1, M + 1, px0, py0);
         return;
       }
-      step_compute<T, EQ, M, TY, true, NT, BULK>(L, io, W, -1, M + 1, T(0), T(0));
+      step_compute<T, EQ, M, TY, true, NT, BULK>(L, io, W, -1, M + 1, px0, py0);
       __syncthreads();
     }
     io.region = 0;
-    step_compute<T, EQ, M, TY, false, NT, BULK>(L, io, W, 0, M, T(0), T(0), 1);
+    step_compute<T, EQ, M, TY, false, NT, BULK>(L, io, amr_weights<T, EQ>(wdev, P, k, region == 1), 0, M, px0, py0, 1);
   } else {
-    step_compute<T, EQ, M, TY, false, NT, BULK>(L, io, W, jlo, jhi, T(0), T(0));
+    step_compute<T, EQ, M, TY, false, NT, BULK>(L, io, W, jlo, jhi, px0, py0);
   }
 }
 
@@ -2611,9 +2630,15 @@ static hipError_t launch_amr_t(const AmrStepLaunch& s, hipStream_t st) {
   A.nbr = s.nbr;
   A.gnflags = s.gnflags;
   A.pair = PAIR && s.pair;
+  A.leaf_xy = s.leaf_xy;
   const auto* wdev = static_cast<const AcOrbitWeights<T>*>(s.weights_dev);
   WithWeights<AmrStepArgs<T>, typename AmrW<T, EQ>::type> P{A, {}};
   if constexpr (EQ == 0) P.w = step_weights<T, EQ>(s.weights);
+  if constexpr (EQ >= 2) {
+    const auto* w = static_cast<const typename WSel<T, EQ>::type*>(s.weights);
+    for (int k = 0; k < s.nlev; ++k) P.w.lev[k] = w[k];
+    P.w.second = w[s.nlev];
+  }
   hipLaunchKernelGGL((k_amr_step<T, EQ, M, TY, PAIR>), dim3(unsigned(blocks)), dim3((amr_threads<M, PAIR>())), 0, st, P,
                      wdev);
   return hipGetLastError();
@@ -2643,6 +2668,9 @@ hipError_t launch_amr_step(const AmrStepLaunch& s, hipStream_t st) {
   switch (s.eq) {
     case 0: return s.fp32 ? launch_amr_m<float, 0>(s, st) : launch_amr_m<double, 0>(s, st);
     case 1: return s.fp32 ? launch_amr_m<float, 1>(s, st) : launch_amr_m<double, 1>(s, st);
+    case 2: return s.fp32 ? launch_amr_m<float, 2>(s, st) : launch_amr_m<double, 2>(s, st);
+    case 3: return s.fp32 ? launch_amr_m<float, 3>(s, st) : launch_amr_m<double, 3>(s, st);
+    case 4: return s.fp32 ? launch_amr_m<float, 4>(s, st) : launch_amr_m<double, 4>(s, st);
     default: return hipErrorInvalidValue;
   }
 }

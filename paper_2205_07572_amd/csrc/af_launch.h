@@ -39,8 +39,7 @@ struct BufLaunch {
   uint32_t mask;
 };
 
-// One time point of the batched subcycled coarse step (constant-coefficient
-// equations): levels lev0 .. lev0 + nlev - 1 step together; level lev0 + k
+// One time point of the batched subcycled coarse step: levels lev0 .. lev0 + nlev - 1 step together; level lev0 + k
 // holds leaves [first[k], first[k] + count[k]) and steps `region[k]`.
 struct AmrStepLaunch {
   bool fp32;
@@ -60,7 +59,11 @@ struct AmrStepLaunch {
   const FillWeights* fw;
   const int32_t* nbr;
   const uint32_t* gnflags;
-  const void* weights;  // AdvAllWeights<T> or AcOrbitWeights<T>
+  const int32_t* leaf_xy;   // [npatch][2] patch (ix, iy); rotation and swirl only
+  // AdvAllWeights<T> or AcOrbitWeights<T>; the other equations: RotParams<T>,
+  // SwirlParams<T> or BurgersParams<T> of the nlev levels, then those of the
+  // second substep of a fused pair
+  const void* weights;
   const void* weights_dev;  // acoustics: AcOrbitWeights<T> on the device
   // the last level (the finest, region layer 1) takes both substeps of its
   // pair in one block (m = 8 or 16; whole-patch tiles)
