@@ -283,9 +283,9 @@ af_status af_reduce_sum_noalloc(af_ctx* ctx, const af_hier* h, const af_state* b
  * closed-square nodes to the other buffer.  Equal to nsteps x (af_ghost_fill
  * + af_patch_step) up to rounding order: for advection with the upwind source
  * pattern (a, b > 0, both directional Courant numbers below 1/2) or a mirror
- * image of it (a < 0, b < 0) each step is one pass in which a cell's new average is a fixed combination of the 25 old
- * DOFs of its source cells, composed on the host from eq. 2dfv and eq.
- * Simpson-2d.  AF_ADVECTION and AF_ACOUSTICS only (AF_ERR_ARG for the other
+ * image of it (a < 0, b < 0) each step is one pass in which a cell's new
+ * average is a fixed combination of the 25 old DOFs of its source cells,
+ * composed on the host from eq. 2dfv and eq. Simpson-2d.  AF_ADVECTION and AF_ACOUSTICS only (AF_ERR_ARG for the other
  * equations, which step with af_patch_step).  The level's data moves between
  * bufs[0] and bufs[1] (*level_buf_mask bit `level` updated after every
  * launch); ghost layers of the result are NOT filled.
@@ -295,8 +295,8 @@ af_status af_level_advance(af_ctx* ctx, af_hier* h, af_state* bufs, uint32_t* le
 /* level-advance kernel shapes (steps per launch K, block size) available for
  * the context's problem; af_ctx_set_advance_shape picks one (autotuner).  For
  * advection the list includes shapes that only the upwind one-pass kernel
- * runs (both Courant numbers positive and below 1/2, so that every node
- * traces back, as in Sec. 2.1, into the upwind neighbour cell).  With other
+ * runs (both Courant numbers below 1/2 in size and not zero, so that every
+ * node traces back, as in Sec. 2.1, into the upwind neighbour cell).  With other
  * weights af_level_advance replaces such a shape by the default one. */
 int32_t af_ctx_advance_shapes(const af_ctx* ctx, int32_t* ks, int32_t* nts, int32_t cap);
 /* the shapes of that list that only the upwind one-pass kernel runs (the
@@ -305,10 +305,11 @@ int32_t af_ctx_advance_shapes(const af_ctx* ctx, int32_t* ks, int32_t* nts, int3
  * cap of them to the optional arrays */
 int32_t af_ctx_advance_shapes_upwind(const af_ctx* ctx, int32_t* ks, int32_t* nts, int32_t cap);
 af_status af_ctx_set_advance_shape(af_ctx* ctx, int32_t k, int32_t nt);
-/* the shape af_level_advance will use (the tuned one, else the default: the
- * largest K, then the smallest block), for advection with both velocity
+/* the shape set by af_ctx_set_advance_shape or af_autotune, else the default:
+ * the largest K, then the smallest block, for advection with both velocity
  * components positive assuming time steps small enough for the upwind
- * pattern */
+ * pattern.  Where none is set af_level_advance chooses by the level's number
+ * of patches (the block size, and K beyond 256 patches) */
 af_status af_ctx_get_advance_shape(const af_ctx* ctx, int32_t* k, int32_t* nt);
 
 /* af_autotune -- picks, by timing `reps` launches of each candidate with HIP

@@ -950,6 +950,37 @@ af_status level_grid(af_hier* h, int level, int* nx, int* ny) {
 
 constexpr int kOneBlockPerCu = 256;  // patches up to which a CU gets one block
 
+// The shape for a level of `count` patches where none is set: the one with
+// the most steps in progress on a CU, of equal ones the largest block.  Up to
+// one patch per CU that is the largest K, and the block's waves are all the
+// latency hiding there is (FP32 advection, m = 16, 256 patches, 16 steps: 256
+// threads 18.4 us, 1024 12.2; acoustics, two steps: 14.9, with 512 threads
+// 10.9).  With more patches two resident blocks, which hide each other's
+// barriers, count twice (FP32, m = 32, 2025 patches: 20 steps of one
+// 1024-thread block 8.7 us per step, 12 of two 512-thread blocks 7.1; FP64's
+// blocks fill the LDS, there K = 12 stays, 13.5 us per step against 16.1 of
+// K = 4).  With several patches per CU the work on the halo counts, not the
+// latency: at most K = m / 2 (FP32, m = 16, per step: K = 8 against 16 1.28
+// and 1.12 us for 400 patches, 1.80 and 1.91 for 1024, 18.0 and 23.6 for
+// 16384), in FP64 m / 4 where blocks share a CU (m = 16, per step: K = 4
+// against 8 4.50 and 4.46 us for 1681 patches, 8.3 and 9.0 for 4096, 15.1 and
+// 17.1 for 8100).  The acoustic kernel of 256 threads catches up (FP32, two
+// steps, with 256 and 512 threads: 36 and 33 us for 2025 patches, 114 and 115
+// for 8100, 242 and 252 for 16384).
+void level_shape(const af_ctx* c, bool up, int count, int* k, int* nt) {
+  int ks[32], nts[32], best = 0;
+  const int n = level_advance_shapes(c->fp32(), c->P.eq, c->P.m, ks, nts, 32, up);
+  const bool small = c->P.eq == AF_ACOUSTICS && count > 32 * kOneBlockPerCu;
+  *k = *nt = 0;
+  for (int i = 0; i < n; ++i) {
+    if (count > 3 * kOneBlockPerCu && ks[i] > c->P.m / 2) continue;
+    const int r = level_advance_resident(c->fp32(), c->P.eq, c->P.m, ks[i], nts[i], up);
+    if (!c->fp32() && count > 6 * kOneBlockPerCu && r > 1 && ks[i] > c->P.m / 4) continue;
+    const int score = ks[i] * (count > kOneBlockPerCu ? std::min(r, 2) : 1);
+    if (score > best || (score == best && (nts[i] < *nt) == small)) { best = score; *k = ks[i]; *nt = nts[i]; }
+  }
+}
+
 // The shape set on the context if it runs here (up: the weights have the
 // upwind pattern), else the largest K with the smallest block.
 void default_advance_shape(const af_ctx* c, bool up, int* k, int* nt) {
@@ -1051,7 +1082,10 @@ af_status af_level_advance(af_ctx* ctx, af_hier* h, af_state* bufs, uint32_t* ma
   if (!L.weights) return fail(AF_ERR_STATE, "acoustic stencils lack their mirror symmetry");
   const bool up = level_advance_up_pattern(L.fp32, L.eq, L.weights);
   int K, NT;
-  default_advance_shape(ctx, up, &K, &NT);
+  if (ctx->adv_k)
+    default_advance_shape(ctx, up, &K, &NT);
+  else
+    level_shape(ctx, up, count, &K, &NT);
   if (K == 0) return fail(AF_ERR_ARG, "no level-advance kernel for this (precision, equation, m)");
   int ks[32], nts[32];
   const int n = level_advance_shapes(ctx->fp32(), ctx->P.eq, ctx->P.m, ks, nts, 32, up);
@@ -1080,7 +1114,7 @@ af_status af_level_advance(af_ctx* ctx, af_hier* h, af_state* bufs, uint32_t* ma
       if (kk == 0) return fail(AF_ERR_STATE, "no level-advance kernel short enough for the remaining steps");
       nt = 0;
       for (int i = 0; i < n; ++i)
-        if (ks[i] == kk && nt != NT && (nt == 0 || nts[i] == NT || (nts[i] > nt) == (count <= kOneBlockPerCu))) nt = nts[i];
+        if (ks[i] == kk && !(ctx->adv_k && nt == NT) && (nt == 0 || (ctx->adv_k && nts[i] == NT) || (nts[i] > nt) == (count <= kOneBlockPerCu))) nt = nts[i];
     }
     L.k = kk;
     L.nt = nt;

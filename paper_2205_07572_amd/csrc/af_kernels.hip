@@ -1545,8 +1545,12 @@ __global__ __launch_bounds__(NT, (UpGeom<T, M, K, NT>::OCC)) void k_level_advanc
         // cell's own average, by far the largest term, comes last: the
         // partial sums before it round at the size of the update (FP32, 11
         // to 128 steps: half the error against 64 bits of the order that
-        // began with it)
-        T avg = T(0);
+        // began with it).  The other averages come first, so that their
+        // registers free early (last, the 768-thread shape needed 92, and
+        // then no longer fits two blocks per CU)
+        T avg = wq[kUpA] * wa[u][0];
+        avg += wq[kUpA + 1] * wa[u][1];
+        avg += wq[kUpA + 2] * wa[u + 1][0];
 #pragma unroll
         for (int dj = -1; dj <= 1; ++dj)
 #pragma unroll
@@ -1559,9 +1563,6 @@ __global__ __launch_bounds__(NT, (UpGeom<T, M, K, NT>::OCC)) void k_level_advanc
         for (int dj = -1; dj <= 1; ++dj)
 #pragma unroll
           for (int di = -1; di <= 0; ++di) avg += wq[kUpY + (dj + 1) * 2 + (di + 1)] * w2[u + 1 + dj][1 + di];
-        avg += wq[kUpA] * wa[u][0];
-        avg += wq[kUpA + 1] * wa[u][1];
-        avg += wq[kUpA + 2] * wa[u + 1][0];
         avg += wq[kUpA + 3] * wa[u + 1][1];
         if (s + 1 < K || !UpGeom<T, M, K, NT>::DIRECT) {
           if (tok) {  // strips past the region store into rows no later read touches
@@ -2741,10 +2742,13 @@ static bool adv_up_pattern(const AdvWeights<T>& W) {
   return up;
 }
 
+template <typename T>
+static bool adv_one_pass(const void* weights) {
+  const auto& W = *static_cast<const AdvAllWeights<T>*>(weights);
+  return adv_up_pattern(W.w) || adv_up_pattern(W.mirrored);
+}
 bool level_advance_up_pattern(bool fp32, int eq, const void* weights) {
-  if (eq != 0) return false;
-  return fp32 ? adv_up_pattern(static_cast<const AdvAllWeights<float>*>(weights)->w)
-              : adv_up_pattern(static_cast<const AdvAllWeights<double>*>(weights)->w);
+  return eq == 0 && (fp32 ? adv_one_pass<float>(weights) : adv_one_pass<double>(weights));
 }
 
 template <typename T, int EQ, int M, int K, int NT>
@@ -2793,7 +2797,9 @@ static hipError_t launch_adv_t(const AdvanceLaunch& s, hipStream_t st) {
   X(double, 0, 32, 4, 1024) X(double, 0, 32, 5, 1024)                                                   \
   X(double, 0, 16, 1, 256) X(double, 0, 16, 2, 256) X(double, 0, 16, 4, 256)                            \
   X(float, 1, 16, 1, 256) X(float, 1, 16, 2, 256) X(float, 1, 32, 1, 512) X(float, 1, 32, 2, 512)      \
-  X(double, 1, 16, 1, 256) X(double, 1, 16, 2, 256)
+  X(double, 1, 16, 1, 256) X(double, 1, 16, 2, 256)                                                     \
+  X(float, 1, 16, 1, 512) X(float, 1, 16, 2, 512) X(float, 1, 32, 2, 1024) X(double, 1, 16, 1, 512)     \
+  X(double, 1, 16, 2, 512)
 
 // Advection shapes that only the upwind one-pass kernel runs: its gathered
 // block has side m + K + 1, where the two-pass kernel's LDS would not hold
@@ -2802,16 +2808,55 @@ static hipError_t launch_adv_t(const AdvanceLaunch& s, hipStream_t st) {
   X(float, 32, 12, 1024) X(float, 32, 14, 1024) X(float, 32, 16, 1024) X(float, 32, 18, 1024)            \
   X(float, 32, 20, 1024) X(float, 32, 10, 512)                                                          \
   X(float, 32, 12, 512) X(float, 16, 12, 256) X(float, 16, 16, 256)                                      \
+  X(float, 16, 12, 512) X(float, 16, 16, 512) X(float, 16, 12, 1024) X(float, 16, 14, 1024)              \
+  X(float, 16, 16, 1024)                                                                                \
   X(double, 32, 6, 1024) X(double, 32, 8, 1024) X(double, 32, 10, 1024) X(double, 32, 12, 1024)           \
-  X(double, 16, 8, 256)
+  X(double, 16, 8, 256) X(double, 16, 8, 512) X(double, 16, 12, 1024)
 
 template <typename T, int M, int K, int NT>
 static hipError_t launch_up_t(const AdvanceLaunch& s, hipStream_t st) {
-  const AdvWeights<T>& W = static_cast<const AdvAllWeights<T>*>(s.weights)->w;
-  if (!adv_up_pattern(W)) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((k_level_advance_up<T, M, K, NT, false>), dim3(unsigned(s.count)), dim3(NT), 0, st, advance_args<T>(s),
-                     W);
+  const AdvAllWeights<T>& all = *static_cast<const AdvAllWeights<T>*>(s.weights);
+  AdvanceArgs<T> A = advance_args<T>(s);
+  A.mirror_x = all.mirror_x;
+  A.mirror_y = all.mirror_y;
+  const dim3 grid(unsigned(s.count));
+  if (adv_up_pattern(all.w))
+    hipLaunchKernelGGL((k_level_advance_up<T, M, K, NT, false>), grid, dim3(NT), 0, st, A, all.w);
+  else if (adv_up_pattern(all.mirrored))
+    hipLaunchKernelGGL((k_level_advance_up<T, M, K, NT, true>), grid, dim3(NT), 0, st, A, all.mirrored);
+  else
+    return hipErrorInvalidValue;
   return hipGetLastError();
+}
+
+// Blocks of a level-advance shape that a CU holds at once, by LDS and by 1024
+// threads (the one-pass kernel's 96 to 117 registers).
+template <typename T, int EQ, int M, int K, int NT>
+static int adv_resident(bool up) {
+  size_t lds;
+  if constexpr (EQ == 0)
+    lds = up ? sizeof(UpLds<T, M, K, NT>) : sizeof(AdvLds<T, M, K, StripRows<M, K, NT>::value>);
+  else
+    lds = sizeof(StepLds<T, 3, (K == 2 ? M + 2 : M) + 3, M + 5, kLdsAlias>);
+  return int(std::min<size_t>(160 * 1024 / lds, 1024 / NT));
+}
+template <typename T, int M, int K, int NT>
+static int up_resident() {
+  return int(std::min<size_t>(160 * 1024 / sizeof(UpLds<T, M, K, NT>), 1024 / NT));
+}
+
+int level_advance_resident(bool fp32, int eq, int m, int k, int nt, bool up) {
+#define AF_ADV_RES(T_, EQ_, M_, K_, NT_)                                                             \
+  if ((std::is_same<T_, float>::value == fp32) && eq == EQ_ && m == M_ && k == K_ && nt == NT_) \
+    return adv_resident<T_, EQ_, M_, K_, NT_>(up);
+  AF_ADV_SHAPES(AF_ADV_RES)
+#undef AF_ADV_RES
+#define AF_UP_RES(T_, M_, K_, NT_)                                                                 \
+  if ((std::is_same<T_, float>::value == fp32) && eq == 0 && m == M_ && k == K_ && nt == NT_) \
+    return up_resident<T_, M_, K_, NT_>();
+  AF_UP_SHAPES(AF_UP_RES)
+#undef AF_UP_RES
+  return 0;
 }
 
 hipError_t launch_level_advance(const AdvanceLaunch& s, hipStream_t st) {

@@ -98,8 +98,10 @@ hipError_t launch_level_advance(const AdvanceLaunch& s, hipStream_t st);
 // returns their count.  With up, also the shapes only the upwind one-pass
 // kernel runs.
 int level_advance_shapes(bool fp32, int eq, int m, int* ks, int* nts, int cap, bool up);
-// Whether advection weights take every node from the upwind source pattern
-// (false for acoustics).
+// Blocks of a shape that a CU holds at once.
+int level_advance_resident(bool fp32, int eq, int m, int k, int nt, bool up);
+// Whether advection weights take every node from the upwind source pattern or
+// a mirror image of it (false for acoustics).
 bool level_advance_up_pattern(bool fp32, int eq, const void* weights);
 // nblocks x kThreads threads, 8 chains x 16 x iters FMAs each
 hipError_t launch_fma_probe(bool fp32, void* out, int nblocks, int iters, hipStream_t st);
