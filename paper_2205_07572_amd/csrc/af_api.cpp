@@ -120,6 +120,7 @@ struct af_hier {
   af_ctx* ctx = nullptr;
   std::shared_ptr<DevPool> pool;  // the context's (the tables below come from it)
   Hier H;
+  unsigned char* d_tables = nullptr;  // the block that holds d_lut .. d_faces and d_impure
   int32_t* d_lut = nullptr;
   int32_t* d_level = nullptr;
   int32_t* d_ix = nullptr;
@@ -378,17 +379,28 @@ af_status hier_device(af_hier* h) {
     xy[2 * k] = vx[k];
     xy[2 * k + 1] = vy[k];
   }
+  // one block and one copy for all tables
+  std::vector<unsigned char> image;
+  auto add = [&](const auto& v) {
+    const size_t at = (image.size() + 255) / 256 * 256, bytes = v.size() * sizeof(v[0]);
+    image.resize(at + std::max<size_t>(1, bytes));
+    if (bytes) std::memcpy(&image[at], v.data(), bytes);
+    return at;
+  };
+  image.reserve(h->H.lut.size() * 4 + size_t(n) * 25 + h->all_faces.size() * sizeof(CFFace) + 4096);
+  const size_t o_lut = add(h->H.lut), o_level = add(lv), o_ix = add(vx), o_iy = add(vy), o_xy = add(xy),
+               o_side = add(h->H.side_mask), o_faces = add(h->all_faces), o_impure = add(h->impure);
   hipError_t err;
-  DevPool& pool = *h->pool;
-  h->d_lut = pool_upload(pool, h->H.lut, &err);
-  if (err == hipSuccess) h->d_level = pool_upload(pool, lv, &err);
-  if (err == hipSuccess) h->d_ix = pool_upload(pool, vx, &err);
-  if (err == hipSuccess) h->d_iy = pool_upload(pool, vy, &err);
-  if (err == hipSuccess) h->d_side_mask = pool_upload(pool, h->H.side_mask, &err);
-  if (err == hipSuccess) h->d_xy = pool_upload(pool, xy, &err);
-  if (err == hipSuccess) h->d_faces = pool_upload(pool, h->all_faces, &err);
-  if (err == hipSuccess) h->d_impure = pool_upload(pool, h->impure, &err);
+  unsigned char* base = h->d_tables = pool_upload(*h->pool, image, &err);
   if (err != hipSuccess) return fail(AF_ERR_DEVICE, std::string("hierarchy upload: ") + hipGetErrorString(err));
+  h->d_lut = reinterpret_cast<int32_t*>(base + o_lut);
+  h->d_level = reinterpret_cast<int32_t*>(base + o_level);
+  h->d_ix = reinterpret_cast<int32_t*>(base + o_ix);
+  h->d_iy = reinterpret_cast<int32_t*>(base + o_iy);
+  h->d_xy = reinterpret_cast<int32_t*>(base + o_xy);
+  h->d_side_mask = base + o_side;
+  h->d_faces = reinterpret_cast<CFFace*>(base + o_faces);
+  h->d_impure = reinterpret_cast<int32_t*>(base + o_impure);
   HierDev& D = h->dev;
   D.lut = h->d_lut;
   D.plevel = h->d_level;
@@ -547,14 +559,8 @@ af_status af_hier_create(af_ctx* ctx, int32_t n, const int32_t* level, const int
   h->face_off[h->H.lmax + 1] = int(h->all_faces.size());
   // leaves whose eight neighbours are not all leaves of their own level
   h->impure_off.assign(h->H.lmax + 2, 0);
-  for (int k = 0; k < n; ++k) {
-    const Leaf& L = h->H.leaves[k];
-    bool pure = true;
-    for (int dy = -1; dy <= 1 && pure; ++dy)
-      for (int dx = -1; dx <= 1 && pure; ++dx)
-        if ((dx || dy) && h->H.find(L.level, L.ix + dx, L.iy + dy) < 0) pure = false;
-    if (!pure) h->impure.push_back(k);
-  }
+  for (int k = 0; k < n; ++k)
+    if (!h->H.pure[k]) h->impure.push_back(k);
   for (int l = 0, e = 0; l <= h->H.lmax + 1; ++l) {
     while (e < int(h->impure.size()) && h->H.leaves[h->impure[e]].level < l) ++e;
     h->impure_off[l] = e;
@@ -569,10 +575,7 @@ af_status af_hier_destroy(af_hier* h) {
   // the tables go back to the pool once no queued work can read them
   if (h->on_device) (void)hipDeviceSynchronize();
   DevPool& pool = *h->pool;
-  for (void* p : {static_cast<void*>(h->d_lut), static_cast<void*>(h->d_level), static_cast<void*>(h->d_ix),
-                  static_cast<void*>(h->d_iy), static_cast<void*>(h->d_side_mask), static_cast<void*>(h->d_xy),
-                  static_cast<void*>(h->d_faces), static_cast<void*>(h->d_nbr), static_cast<void*>(h->d_gnflags),
-                  static_cast<void*>(h->d_impure)})
+  for (void* p : {static_cast<void*>(h->d_tables), static_cast<void*>(h->d_nbr), static_cast<void*>(h->d_gnflags)})
     pool.put(p);
   for (int4* p : h->d_plan) pool.put(p);
   for (uint32_t* p : h->d_plan_flags) pool.put(p);

@@ -15,12 +15,13 @@
 namespace af {
 
 namespace {
-long long wrapi(long long v, long long n) { return ((v % n) + n) % n; }
+// v modulo n; one step outside [0, n), as a neighbour is, without a division
+inline long long wrapi(long long v, long long n) {
+  if (v < 0) v += n;
+  else if (v >= n) v -= n;
+  return v >= 0 && v < n ? v : ((v % n) + n) % n;
+}
 }  // namespace
-
-int Hier::npx(int l) const { return n0x << l; }
-int Hier::npy(int l) const { return n0y << l; }
-
 int Hier::find(int l, long long px, long long py) const {
   if (l < 0 || l > lmax) return -1;
   const long long nx = npx(l), ny = npy(l);
@@ -81,20 +82,26 @@ std::string Hier::build(const std::vector<Leaf>& in) {
   }
   if (area != (long long)n0x * n0y << (2 * lmax)) return "leaves do not cover the domain";
   // 2:1 balance across edges and corners (periodic): the level-l positions
-  // around every leaf must be covered by leaves of level >= l-1
-  for (const Leaf& L : leaves)
+  // around every leaf must be covered by leaves of level >= l-1.  A leaf is
+  // pure if all eight are leaves of its own level.
+  pure.assign(n, 1);
+  for (int k = 0; k < n; ++k) {
+    const Leaf& L = leaves[k];
     for (int dy = -1; dy <= 1; ++dy)
       for (int dx = -1; dx <= 1; ++dx) {
-        if (!dx && !dy) continue;
+        if ((!dx && !dy) || find(L.level, L.ix + dx, L.iy + dy) >= 0) continue;
+        pure[k] = 0;
         int lev;
-        if (cover(L.level, L.ix + dx, L.iy + dy, &lev) >= 0 && lev < L.level - 1)
+        if (cover(L.level - 1, (L.ix + dx) >> 1, (L.iy + dy) >> 1, &lev) >= 0 && lev < L.level - 1)
           return "hierarchy is not 2:1 balanced";
       }
+  }
   // side relations
   rel.assign(size_t(n) * 4, 0);
   side_mask.assign(n, 0);
   static const int sdx[4] = {-1, 1, 0, 0}, sdy[4] = {0, 0, -1, 1};
   for (int k = 0; k < n; ++k) {
+    if (pure[k]) continue;
     const Leaf& L = leaves[k];
     for (int s = 0; s < 4; ++s) {
       const long long px = L.ix + sdx[s], py = L.iy + sdy[s];
@@ -106,42 +113,40 @@ std::string Hier::build(const std::vector<Leaf>& in) {
       if (r != 0) side_mask[k] |= uint8_t(1 << s);
     }
   }
-  // coarse-fine faces per coarse level, grouped by coarse cell
+  // coarse-fine faces per coarse level, in the order (coarse leaf, cell row,
+  // cell column, side)
   faces.assign(lmax + 1, {});
   for (int k = 0; k < n; ++k) {
+    if (pure[k]) continue;
     const Leaf& C = leaves[k];
+    int fine[4][2];  // the two leaves facing side s
+    bool any = false;
     for (int s = 0; s < 4; ++s) {
       if (rel[size_t(k) * 4 + s] != 1) continue;
-      for (int t = 0; t < m; ++t) {
-        CFFace F;
-        F.coarse = k;
-        F.side = s;
-        F.k = t;
-        // the two fine faces facing coarse face t: fine index 2 (base + t)
-        const long long base = (s < 2) ? (long long)C.iy * m : (long long)C.ix * m;
-        const long long f0 = 2 * (base + t);
-        long long fpx, fpy;
-        if (s < 2) {
-          fpx = (s == 0) ? 2LL * C.ix - 1 : 2LL * C.ix + 2;
-          fpy = f0 / m;
-        } else {
-          fpy = (s == 2) ? 2LL * C.iy - 1 : 2LL * C.iy + 2;
-          fpx = f0 / m;
-        }
-        F.fine = find(C.level + 1, fpx, fpy);
-        if (F.fine < 0) return "internal: missing fine neighbour";
-        F.fk = int(f0 - (f0 / m) * m);
-        faces[C.level].push_back(F);
+      any = true;
+      for (int q = 0; q < 2; ++q) {
+        const long long fx = s == 0 ? 2LL * C.ix - 1 : s == 1 ? 2LL * C.ix + 2 : 2LL * C.ix + q;
+        const long long fy = s == 2 ? 2LL * C.iy - 1 : s == 3 ? 2LL * C.iy + 2 : 2LL * C.iy + q;
+        if ((fine[s][q] = find(C.level + 1, fx, fy)) < 0) return "internal: missing fine neighbour";
       }
     }
-  }
-  for (auto& fl : faces) {
-    auto cell = [&](const CFFace& F) {
-      const int ci = F.side == 0 ? 0 : (F.side == 1 ? m - 1 : F.k);
-      const int cj = F.side == 2 ? 0 : (F.side == 3 ? m - 1 : F.k);
-      return std::make_tuple(F.coarse, cj, ci, F.side);
-    };
-    std::stable_sort(fl.begin(), fl.end(), [&](const CFFace& a, const CFFace& b) { return cell(a) < cell(b); });
+    if (!any) continue;
+    for (int cj = 0; cj < m; ++cj)
+      for (int ci = 0; ci < m; ci += (cj == 0 || cj == m - 1) ? 1 : m - 1)
+        for (int s = 0; s < 4; ++s) {
+          const bool on = s == 0 ? ci == 0 : s == 1 ? ci == m - 1 : s == 2 ? cj == 0 : cj == m - 1;
+          if (!on || rel[size_t(k) * 4 + s] != 1) continue;
+          CFFace F;
+          F.coarse = k;
+          F.side = s;
+          F.k = s < 2 ? cj : ci;
+          // the two fine faces facing coarse face F.k: 2 F.k and the next,
+          // m of them on each fine leaf
+          const int q = 2 * F.k >= m ? 1 : 0;
+          F.fine = fine[s][q];
+          F.fk = 2 * F.k - q * m;
+          faces[C.level].push_back(F);
+        }
   }
   finest = 0;
   for (const Leaf& L : leaves) finest = std::max(finest, L.level);
@@ -155,10 +160,7 @@ std::vector<Leaf> Hier::regrid(const int8_t* tags) const {
   // table; scanning them level by level, row by row gives the (level, iy, ix)
   // order of the result
   const size_t total = lut.size();
-  auto at = [&](int l, long long px, long long py) {
-    const long long nx = npx(l), ny = npy(l);
-    return size_t(lut_off[l] + wrapi(py, ny) * nx + wrapi(px, nx));
-  };
+  auto at = [&](int l, int px, int py) { return size_t(lut_off[l]) + size_t(py) * size_t(npx(l)) + size_t(px); };
   std::vector<uint8_t> cur(total, 0), was(total, 0);
   std::vector<int8_t> old_tag(total, 0);
   for (size_t k = 0; k < leaves.size(); ++k) {
@@ -172,50 +174,48 @@ std::vector<Leaf> Hier::regrid(const int8_t* tags) const {
       cur[e] = 1;
     }
   }
-  // leaf of the set covering position (l, px, py), itself or an ancestor
-  auto covering = [&](int l, long long px, long long py, int* lev) -> bool {
+  // level of the leaf of the set covering position (l, px, py) inside the
+  // domain, itself or an ancestor; -1 if the position is subdivided
+  auto covering = [&](int l, int px, int py) {
     for (int k = l; k >= 0; --k)
-      if (cur[at(k, px >> (l - k), py >> (l - k))]) {
-        *lev = k;
-        return true;
-      }
-    return false;
+      if (cur[at(k, px >> (l - k), py >> (l - k))]) return k;
+    return -1;
   };
   // every leaf of the set, in (level, iy, ix) order
   auto for_each = [&](auto&& f) {
     for (int l = 0; l <= lmax; ++l)
-      for (int iy = 0; iy < npy(l); ++iy)
+      for (int iy = 0; iy < npy(l); ++iy) {
+        const uint8_t* row = &cur[at(l, 0, iy)];
         for (int ix = 0; ix < npx(l); ++ix)
-          if (cur[size_t(lut_off[l] + (long long)iy * npx(l) + ix)]) f(l, ix, iy);
+          if (row[ix]) f(l, ix, iy);
+      }
   };
-  // balance closure: a leaf two levels coarser than a touching leaf splits
-  std::vector<uint8_t> mark(total, 0);
-  std::vector<Leaf> split;
-  for (;;) {
-    split.clear();
-    for_each([&](int l, int ix, int iy) {
-      for (int dy = -1; dy <= 1; ++dy)
-        for (int dx = -1; dx <= 1; ++dx) {
-          if (!dx && !dy) continue;
-          const long long px = wrapi(ix + dx, npx(l)), py = wrapi(iy + dy, npy(l));
-          int lev;
-          if (covering(l, px, py, &lev) && lev <= l - 2) {
-            const Leaf S{lev, int(px >> (l - lev)), int(py >> (l - lev))};
-            uint8_t& m = mark[at(S.level, S.ix, S.iy)];
-            if (!m) {
-              m = 1;
-              split.push_back(S);
-            }
+  // balance closure: a leaf two levels coarser than a touching leaf splits,
+  // and its children are looked at in their turn (the closure does not depend
+  // on the order; a leaf once in balance stays so, since others only split)
+  std::vector<Leaf> todo;
+  for_each([&](int l, int ix, int iy) {
+    if (l >= 2) todo.push_back({l, ix, iy});
+  });
+  while (!todo.empty()) {
+    const Leaf L = todo.back();
+    todo.pop_back();
+    if (!cur[at(L.level, L.ix, L.iy)]) continue;  // split meanwhile
+    for (int dy = -1; dy <= 1; ++dy)
+      for (int dx = -1; dx <= 1; ++dx) {
+        if (!dx && !dy) continue;
+        const int px = int(wrapi(L.ix + dx, npx(L.level))), py = int(wrapi(L.iy + dy, npy(L.level)));
+        int lev;
+        while ((lev = covering(L.level, px, py)) >= 0 && lev <= L.level - 2) {
+          const int sx = px >> (L.level - lev), sy = py >> (L.level - lev);
+          cur[at(lev, sx, sy)] = 0;
+          for (int q = 0; q < 4; ++q) {
+            const Leaf C{lev + 1, 2 * sx + (q & 1), 2 * sy + (q >> 1)};
+            cur[at(C.level, C.ix, C.iy)] = 1;
+            if (C.level >= 2) todo.push_back(C);
           }
         }
-    });
-    if (split.empty()) break;
-    for (const Leaf& S : split) {
-      const size_t e = at(S.level, S.ix, S.iy);
-      mark[e] = 0;
-      cur[e] = 0;
-      for (int q = 0; q < 4; ++q) cur[at(S.level + 1, 2 * S.ix + (q & 1), 2 * S.iy + (q >> 1))] = 1;
-    }
+      }
   }
   // families: all four siblings are leaves tagged -1, and no sibling has a
   // subdivided level-l neighbour position outside the family
@@ -232,8 +232,8 @@ std::vector<Leaf> Hier::regrid(const int8_t* tags) const {
       for (int dy = -1; dy <= 1 && ok; ++dy)
         for (int dx = -1; dx <= 1 && ok; ++dx) {
           if (!dx && !dy) continue;
-          int lev;
-          if (!covering(l, wrapi(sx + dx, npx(l)), wrapi(sy + dy, npy(l)), &lev)) ok = false;  // finer leaves touch the parent
+          // finer leaves touch the parent
+          if (covering(l, int(wrapi(sx + dx, npx(l))), int(wrapi(sy + dy, npy(l)))) < 0) ok = false;
         }
     }
     if (ok) parents.push_back({l - 1, ix >> 1, iy >> 1});

@@ -21,11 +21,12 @@ struct Hier {
   std::vector<int> level_first, level_count;
   std::vector<int8_t> rel;        // [n][4] side relations
   std::vector<uint8_t> side_mask; // [n]
+  std::vector<uint8_t> pure;      // [n] the eight neighbours are leaves of the same level
   std::vector<std::vector<CFFace>> faces;  // per coarse level
   int finest = 0;
 
-  int npx(int l) const;
-  int npy(int l) const;
+  int npx(int l) const { return n0x << l; }
+  int npy(int l) const { return n0y << l; }
   int find(int l, long long px, long long py) const;
   int cover(int l, long long px, long long py, int* lev) const;
   // builds all tables; returns an error message or "" on success
