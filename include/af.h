@@ -247,7 +247,7 @@ af_status af_hier_regrid(af_ctx* ctx, const af_hier* old, const int8_t* tags, af
  * for fine averages); coarsened leaves average four children and copy fine
  * vertices.  Writes every leaf of new_h into `dst` (ghosts are not filled:
  * call af_ghost_fill(tmin=0, smin=0) after), and resolves new_h's ghost-fill
- * plans, so that its first coarse step does not.  Synchronises the stream. */
+ * plan, so that its first coarse step does not.  Synchronises the stream. */
 af_status af_regrid_apply(af_ctx* ctx, const af_hier* old, const af_state* old_bufs,
                           uint32_t old_mask, const af_hier* new_h, af_state* dst,
                           hipStream_t stream);

@@ -136,12 +136,13 @@ struct af_hier {
   std::vector<int> nbr_ok;
   HierDev dev{};
   std::map<GraphKey, hipGraphExec_t> graphs;
-  // ghost-fill plans per lowest source level (built on first use)
-  std::vector<int4*> d_plan;
-  std::vector<uint32_t*> d_plan_flags;
-  std::vector<int4*> d_canon_ops;  // per source bound: the vertex copies of k_amr_sync
-  // with the plan of source bound 0: same-level neighbours [n][9] and the
-  // directions the batched step stages by a same-level gather [n]
+  // ghost-fill plan and, in the same block (built on first use), its flags per
+  // leaf, the vertex copies of k_amr_sync ([impure][boundary entries]; null if
+  // none), same-level neighbours [n][9] and the directions the batched step
+  // stages by a same-level gather [n]
+  int4* d_plan = nullptr;
+  uint32_t* d_plan_flags = nullptr;
+  int4* d_canon_ops = nullptr;
   int32_t* d_nbr = nullptr;
   uint32_t* d_gnflags = nullptr;
   // leaves with a neighbour of another level (the only ones a coarser
@@ -575,11 +576,7 @@ af_status af_hier_destroy(af_hier* h) {
   // the tables go back to the pool once no queued work can read them
   if (h->on_device) (void)hipDeviceSynchronize();
   DevPool& pool = *h->pool;
-  for (void* p : {static_cast<void*>(h->d_tables), static_cast<void*>(h->d_nbr), static_cast<void*>(h->d_gnflags)})
-    pool.put(p);
-  for (int4* p : h->d_plan) pool.put(p);
-  for (uint32_t* p : h->d_plan_flags) pool.put(p);
-  for (int4* p : h->d_canon_ops) pool.put(p);
+  for (void* p : {static_cast<void*>(h->d_tables), static_cast<void*>(h->d_plan)}) pool.put(p);
   delete h;
   return AF_OK;
 }
@@ -719,45 +716,29 @@ af_status af_patch_step(af_ctx* ctx, const af_state* in, af_state* out, int32_t 
 
 namespace {
 
-// The fill plan of hierarchy h for sources of level >= smin (smin <= lmax),
-// resolved on the device on first use.  The plan depends on the leaf set and
-// m only, so it serves every buffer pair and every lower target bound.
-af_status fill_plan(af_ctx* ctx, af_hier* h, int smin, hipStream_t stream) {
-  if (int(h->d_plan.size()) <= h->H.lmax) {
-    h->d_plan.resize(h->H.lmax + 1, nullptr);
-    h->d_plan_flags.resize(h->H.lmax + 1, nullptr);
-    h->d_canon_ops.resize(h->H.lmax + 1, nullptr);
-  }
-  if (h->d_plan[smin]) return AF_OK;
+// The fill plan of hierarchy h, resolved on the device on first use.  The plan
+// depends on the leaf set and m only, so it serves every buffer pair, target
+// bound and source bound.  With it the batched step's vertex copies.
+af_status fill_plan(af_ctx* ctx, af_hier* h, hipStream_t stream) {
+  if (h->d_plan) return AF_OK;
   af_status s;
   if ((s = ctx_device(ctx)) != AF_OK || (s = hier_device(h)) != AF_OK) return s;
-  const size_t n = h->H.leaves.size();
-  int4* plan = nullptr;
-  uint32_t* flags = nullptr;
+  const size_t n = h->H.leaves.size(), ncanon = h->impure.size(), nbnd = ctx->h_bnd.size();
   DevPool& pool = *h->pool;
-  AF_HIP(pool.get(reinterpret_cast<void**>(&plan), std::max<size_t>(1, n * size_t(ctx->nentries)) * sizeof(int4)));
-  if (pool.get(reinterpret_cast<void**>(&flags), std::max<size_t>(1, n) * sizeof(uint32_t)) != hipSuccess) {
-    pool.put(plan);
-    return fail(AF_ERR_DEVICE, "fill plan allocation");
-  }
-  h->d_plan[smin] = plan;
-  h->d_plan_flags[smin] = flags;
-  if (smin == 0) {
-    AF_HIP(pool.get(reinterpret_cast<void**>(&h->d_nbr), std::max<size_t>(1, n) * 9 * sizeof(int32_t)));
-    AF_HIP(pool.get(reinterpret_cast<void**>(&h->d_gnflags), std::max<size_t>(1, n) * sizeof(uint32_t)));
-  }
-  AF_HIP(launch_fill_plan(h->dev, ctx->d_entries, ctx->nentries, ctx->P.m, smin, plan, flags,
-                          smin == 0 ? h->d_nbr : nullptr, smin == 0 ? h->d_gnflags : nullptr, stream));
-  // the batched step's vertex copies for this bound, resolved from the plan
-  const int ncanon = int(h->impure.size()) - h->impure_off[smin];
-  const int nbnd = int(ctx->h_bnd.size());
-  if (ncanon > 0 && nbnd > 0) {
-    int4* ops = nullptr;
-    AF_HIP(pool.get(reinterpret_cast<void**>(&ops), size_t(ncanon) * nbnd * sizeof(int4)));
-    h->d_canon_ops[smin] = ops;
-    AF_HIP(launch_canon_ops(plan, ctx->d_entries, ctx->nentries, ctx->d_bnd, nbnd, h->d_impure + h->impure_off[smin],
-                            ncanon, h->d_level, ops, stream));
-  }
+  // plan, copies, then the words per leaf: flags, gather flags, neighbours
+  const size_t ops = n * size_t(ctx->nentries), copies = ncanon * nbnd;
+  int4* plan = nullptr;
+  AF_HIP(pool.get(reinterpret_cast<void**>(&plan), (ops + copies) * sizeof(int4) + n * 11 * sizeof(int32_t)));
+  h->d_plan = plan;
+  h->d_canon_ops = copies ? plan + ops : nullptr;
+  h->d_plan_flags = reinterpret_cast<uint32_t*>(plan + ops + copies);
+  h->d_gnflags = h->d_plan_flags + n;
+  h->d_nbr = reinterpret_cast<int32_t*>(h->d_gnflags + n);
+  AF_HIP(launch_fill_plan(h->dev, ctx->d_entries, ctx->nentries, ctx->P.m, plan, h->d_plan_flags, h->d_nbr,
+                          h->d_gnflags, stream));
+  if (copies)
+    AF_HIP(launch_canon_ops(plan, ctx->d_entries, ctx->nentries, ctx->d_bnd, int(nbnd), h->d_impure, int(ncanon),
+                            h->d_level, h->d_canon_ops, stream));
   return AF_OK;
 }
 
@@ -775,7 +756,7 @@ af_status af_ghost_fill(af_ctx* ctx, const af_hier* hc, af_state* bufs, uint32_t
   for (int l = tmin; l <= h->H.lmax && first < 0; ++l)
     if (h->H.level_count[l]) first = h->H.level_first[l];
   if (first < 0) return AF_OK;
-  if ((s = fill_plan(ctx, h, smin, stream)) != AF_OK) return s;
+  if ((s = fill_plan(ctx, h, stream)) != AF_OK) return s;
   // the coarse->fine phase is needed only if some target level has leaves
   // one level down that may serve as sources
   bool need_b = false;
@@ -784,8 +765,8 @@ af_status af_ghost_fill(af_ctx* ctx, const af_hier* hc, af_state* bufs, uint32_t
   const int n = int(h->H.leaves.size()) - first;
   const BufLaunch b = make_buf(ctx, &bufs[0], &bufs[1], mask);
   for (int phase = 0; phase < (need_b ? 2 : 1); ++phase)
-    AF_HIP(launch_fill_apply(ctx->fp32(), b, h->dev, ctx->d_entries, ctx->nentries, h->d_plan[smin],
-                             h->d_plan_flags[smin], ctx->d_fillw, first, n, phase, stream));
+    AF_HIP(launch_fill_apply(ctx->fp32(), b, h->dev, ctx->d_entries, ctx->nentries, h->d_plan,
+                             h->d_plan_flags, ctx->d_fillw, first, n, phase, smin, stream));
   return AF_OK;
 }
 
@@ -877,12 +858,9 @@ af_status af_regrid_apply(af_ctx* ctx, const af_hier* old, const af_state* old_b
   if (err == hipSuccess) err = hipStreamSynchronize(stream);
   if (err == hipSuccess) ctx->pool->put(d_tr);  // after a failure the block stays out of the pool
   if (err != hipSuccess) return fail(AF_ERR_DEVICE, std::string("transfer: ") + hipGetErrorString(err));
-  // the new hierarchy's ghost-fill plans, so that its first coarse step
-  // does not resolve them
-  af_hier* nhm = const_cast<af_hier*>(nh);
-  for (int l = 0; l <= nhm->H.finest; ++l)
-    if ((s = fill_plan(ctx, nhm, l, stream)) != AF_OK) return s;
-  return AF_OK;
+  // the new hierarchy's ghost-fill plan, so that its first coarse step
+  // does not resolve it
+  return fill_plan(ctx, const_cast<af_hier*>(nh), stream);
 }
 
 af_status af_reduce_sum(af_ctx* ctx, const af_hier* h, const af_state* bufs, uint32_t mask, double* out,
@@ -1296,8 +1274,9 @@ struct Driver {
     S.plevel = h->d_level;
     S.reg = reg;
     S.inv_area0 = 1.0 / (ctx->dx(0) * ctx->dy(0));
-    if (smin >= 0 && smin <= F && h->d_canon_ops[smin]) {
-      S.cops = h->d_canon_ops[smin];
+    if (smin >= 0 && smin <= F && h->d_canon_ops) {
+      S.cops = h->d_canon_ops + size_t(h->impure_off[smin]) * ctx->h_bnd.size();
+      S.smin = smin;
       S.ncops = (int(h->impure.size()) - h->impure_off[smin]) * int(ctx->h_bnd.size());
     }
     if (fix_lo <= fix_hi) {
@@ -1349,7 +1328,7 @@ struct Driver {
     L.c = ctx->P.c;
     L.reg = reg;
     L.side_mask = h->d_side_mask;
-    L.plan = h->d_plan[l0];
+    L.plan = h->d_plan;
     L.entries = ctx->d_entries;
     L.nentries = ctx->nentries;
     L.ninner = ctx->ninner;
@@ -1402,8 +1381,7 @@ struct Driver {
     t0_ = t0;
     dt0_ = dt0;
     af_status s;
-    for (int l = 0; l <= F; ++l)
-      if ((s = fill_plan(ctx, h, l, st)) != AF_OK) return s;
+    if ((s = fill_plan(ctx, h, st)) != AF_OK) return s;
     // fused pairs: the launch of each even time point also takes the finest
     // level's second substep, so the odd time points (where only level F
     // starts a step) need no launch
@@ -1505,8 +1483,8 @@ af_status af_amr_coarse_step(af_ctx* ctx, af_hier* h, af_state* bufs, uint32_t* 
       if (ctx->P.eq == AF_ADVECTION || ctx->P.eq == AF_ACOUSTICS) weights_for(ctx, dtl / ctx->dx(l), dtl / ctx->dy(l));
       if (ctx->P.eq == AF_ACOUSTICS && !global && !weights_dev_for(ctx, dtl / ctx->dx(l), dtl / ctx->dy(l)))
         return fail(AF_ERR_DEVICE, "acoustic weight upload failed");
-      if ((s = fill_plan(ctx, h, l, stream)) != AF_OK) return s;
     }
+    if ((s = fill_plan(ctx, h, stream)) != AF_OK) return s;
     hipStream_t cs;
     AF_HIP(hipStreamCreateWithFlags(&cs, hipStreamNonBlocking));
     hipGraph_t g;

@@ -1619,12 +1619,6 @@ __device__ __forceinline__ size_t at(const Bufs<T>& B, int comp, int patch, int 
   return ((size_t(comp) * B.npatch + patch) * (B.m + 5) + size_t(j + kGhost)) * B.pitch + (i + kGhost);
 }
 
-__device__ __forceinline__ long long fdiv(long long a, long long b) {
-  long long q = a / b;
-  if ((a % b != 0) && ((a < 0) != (b < 0))) --q;
-  return q;
-}
-
 __device__ __forceinline__ int lut_find(const HierDev& H, int l, long long px, long long py) {
   if (l < 0 || l > H.lmax) return -1;
   const long long nx = (long long)H.npx0 << l, ny = (long long)H.npy0 << l;
@@ -1686,93 +1680,93 @@ __device__ double quarter_avg(const Bufs<T>& B, int level, int comp, int patch, 
 // Ghost fill (Sec. 3.1, 3.2).  entries: packed (kind << 24) | ((i+2) << 12) |
 // (j+2) for every DOF of the fill set of a patch.
 //
-// The source of each fill-set DOF depends only on the leaf set and on the
-// lowest level allowed to serve as a source, so it is resolved once per
-// hierarchy (k_fill_plan) into an op; every fill then applies the ops
-// (k_fill_apply).  Phase 0 applies same-level and finer sources, phase 1
-// (after it, since a coarse reconstruction reads nodes that phase 0 may
-// rewrite on coarse-fine lines) the coarser ones.
+// The source of each fill-set DOF depends only on the leaf set, so it is
+// resolved once per hierarchy (k_fill_plan) into an op; every fill then
+// applies the ops (k_fill_apply).  A fill that admits sources of level >= smin
+// only drops the ops with a coarser source: an average has one covering leaf
+// (or the four finer ones), and a node takes the finest leaf that holds it, so
+// a bound never brings in another source.  Phase 0 applies same-level and
+// finer sources, phase 1 (after it, since a coarse reconstruction reads nodes
+// that phase 0 may rewrite on coarse-fine lines) the coarser ones.
 // ---------------------------------------------------------------------------
 
-// Source of fill-set DOF `code` of leaf t: averages from the same level, else
-// the mean of four finer averages, else the Simpson average of the coarser
-// reconstruction over the covered quarter; nodes from the finest leaf whose
-// closed square holds them (candidates of one level in the order (hi,hi),
-// (lo,hi), (hi,lo), (lo,lo)), the coarser reconstruction last.  Sources
-// below level smin are not used; a DOF with no source keeps its value.
-__device__ int4 fill_resolve(const HierDev& H, int m, int smin, int t, int32_t code) {
+// The leaves around leaf t, by patch offset: same[3][3] and, relative to the
+// first of its four children and to its parent, finer[4][4] (offsets -1 .. 2)
+// and coarser[3][3]; -1 where there is none of that level.
+struct FillNbr {
+  int32_t same[9], finer[16], coarser[9];
+};
+
+// a / p rounded down for -p <= a < 3 p
+__device__ __forceinline__ int div3(int a, int p) { return int(a >= 0) + int(a >= p) + int(a >= 2 * p) - 1; }
+
+// Source of fill-set DOF `code` of leaf t (level lt, bx, by: its quarter of its
+// parent): averages from the same level, else the mean of four finer averages,
+// else the Simpson average of the coarser reconstruction over the covered
+// quarter; nodes from the finest leaf whose closed square holds them
+// (candidates of one level in the order (hi,hi), (lo,hi), (hi,lo), (lo,lo)),
+// the coarser reconstruction last.  A DOF with no source keeps its value.
+// Positions are relative to the leaf (to its parent), where they are small:
+// every division is a few comparisons (m >= 5, kGhost = 2).
+__device__ int4 fill_resolve(const FillNbr& N, int m, int t, int lt, int bx, int by, int32_t code) {
   const int4 none = make_int4(-1, 0, 0, 0);
   const int kind = code >> 24, i = ((code >> 12) & 0xfff) - kGhost, j = (code & 0xfff) - kGhost;
-  const int lt = H.plevel[t];
-  const long long I = (long long)H.pix[t] * m + i, J = (long long)H.piy[t] * m + j;
   if (kind == 0) {
-    int src = -1, rel = 0;
-    if (lt >= smin) src = lut_find(H, lt, fdiv(I, m), fdiv(J, m));
-    if (src < 0 && lt + 1 <= H.lmax && lt + 1 >= smin) {
-      src = lut_find(H, lt + 1, fdiv(2 * I, m), fdiv(2 * J, m));
-      rel = 1;
-    }
-    if (src < 0 && lt - 1 >= 0 && lt - 1 >= smin) {
-      src = lut_find(H, lt - 1, fdiv(I, 2 * m), fdiv(J, 2 * m));
-      rel = -1;
-    }
+    int qx = div3(i, m), qy = div3(j, m);
+    int src = N.same[(qy + 1) * 3 + qx + 1];
+    if (src >= 0) return make_int4(src, fill_info(FO_COPY, 0, lt, 0, 0), i - qx * m, j - qy * m);
+    qx = div3(2 * i, m);
+    qy = div3(2 * j, m);
+    src = N.finer[(qy + 1) * 4 + qx + 1];
+    if (src >= 0) return make_int4(src, fill_info(FO_MEAN4, 0, lt + 1, 0, 0), 2 * i - qx * m, 2 * j - qy * m);
+    const int I = bx * m + i, J = by * m + j;
+    qx = div3(I, 2 * m);
+    qy = div3(J, 2 * m);
+    src = N.coarser[(qy + 1) * 3 + qx + 1];
     if (src < 0) return none;
-    if (rel == 0)
-      return make_int4(src, fill_info(FO_COPY, 0, lt, 0, 0), int(I - fdiv(I, m) * m), int(J - fdiv(J, m) * m));
-    if (rel == 1)
-      return make_int4(src, fill_info(FO_MEAN4, 0, lt + 1, 0, 0), int(2 * I - fdiv(2 * I, m) * m),
-                       int(2 * J - fdiv(2 * J, m) * m));
-    const long long CI = fdiv(I, 2), CJ = fdiv(J, 2);
-    const int qx = (I - 2 * CI == 0) ? 0 : 1, qy = (J - 2 * CJ == 0) ? 0 : 1;
-    return make_int4(src, fill_info(FO_QAVG, 0, lt - 1, kFillPoints + qx + 2 * qy, 1), int(CI - fdiv(CI, m) * m),
-                     int(CJ - fdiv(CJ, m) * m));
+    return make_int4(src, fill_info(FO_QAVG, 0, lt - 1, kFillPoints + (I & 1) + 2 * (J & 1), 1), (I >> 1) - qx * m,
+                     (J >> 1) - qy * m);
   }
   // node position in level-(lt+1) half-cell units
-  const long long FX = 4 * I + (kind == 3 ? 2 : 0);
-  const long long FY = 4 * J + (kind == 2 ? 2 : 0);
-  int src = -1, rel = 0, sh = 0;
-  long long sx = 0, sy = 0;  // source-local position in level-(lt+1) half-cell units
-  for (int k = lt + 1; k >= lt - 1 && src < 0; --k) {
-    if (k < 0 || k > H.lmax || k < smin) continue;
-    sh = lt + 1 - k;
-    const long long P = 2LL * m << sh;
-    const long long hx = fdiv(FX, P), hy = fdiv(FY, P);
-    const bool bx = (FX - hx * P) == 0, by = (FY - hy * P) == 0;
-    const int ox[4] = {0, 1, 0, 1}, oy[4] = {0, 0, 1, 1};
+  const int X0 = 4 * i + (kind == 3 ? 2 : 0), Y0 = 4 * j + (kind == 2 ? 2 : 0);
+  int src = -1, rel = 2, sx = 0, sy = 0;  // source-local position in level-(lt+1) half-cell units
+#pragma unroll
+  for (int r = 1; r >= -1; --r) {
+    if (src >= 0) break;
+    const int P = (2 * m) << (1 - r);  // a patch of level lt + r
+    const int FX = r < 0 ? X0 + 4 * bx * m : X0, FY = r < 0 ? Y0 + 4 * by * m : Y0;
+    const int hx = div3(FX, P), hy = div3(FY, P);
+    const bool edge_x = FX == hx * P, edge_y = FY == hy * P;
+    const int32_t* tab = r > 0 ? N.finer : (r == 0 ? N.same : N.coarser);
+    const int w = r > 0 ? 4 : 3;
+#pragma unroll
     for (int o = 0; o < 4; ++o) {
-      if (ox[o] && !bx) continue;
-      if (oy[o] && !by) continue;
-      const int id = lut_find(H, k, hx - ox[o], hy - oy[o]);
-      if (id < 0) continue;
-      src = id;
-      rel = k - lt;
-      sx = FX - (hx - ox[o]) * P;
-      sy = FY - (hy - oy[o]) * P;
-      break;
+      const int ox = o & 1, oy = o >> 1;
+      if (src >= 0 || (ox && !edge_x) || (oy && !edge_y)) continue;
+      src = tab[(hy - oy + 1) * w + hx - ox + 1];
+      if (src >= 0) {
+        rel = r;
+        sx = FX - (hx - ox) * P;
+        sy = FY - (hy - oy) * P;
+      }
     }
   }
   if (src < 0) return none;
-  const long long unit = 1LL << sh;
   if (rel >= 0) {
-    const long long X = sx / unit, Y = sy / unit;  // source half-cell units
-    if (rel == 0 && src == t) {
-      // the target itself: keep unless the match is a periodic image
-      const long long Xt = 2 * i + (kind == 3 ? 1 : 0), Yt = 2 * j + (kind == 2 ? 1 : 0);
-      if (X == Xt && Y == Yt) return none;
-    }
+    const int X = rel ? sx : sx / 2, Y = rel ? sy : sy / 2;  // source half-cell units
+    // the target itself: keep unless the match is a periodic image
+    if (rel == 0 && src == t && X == X0 / 2 && Y == Y0 / 2) return none;
     const int ls = lt + rel;
-    const bool ex = (X % 2) == 0, ey = (Y % 2) == 0;
-    if (ex && ey) return make_int4(src, fill_info(FO_COPY, 1, ls, 0, 0), int(X / 2), int(Y / 2));
-    if (ex) return make_int4(src, fill_info(FO_COPY, 2, ls, 0, 0), int(X / 2), int((Y - 1) / 2));
-    return make_int4(src, fill_info(FO_COPY, 3, ls, 0, 0), int((X - 1) / 2), int(Y / 2));
+    const bool ex = (X & 1) == 0, ey = (Y & 1) == 0;
+    if (ex && ey) return make_int4(src, fill_info(FO_COPY, 1, ls, 0, 0), X / 2, Y / 2);
+    if (ex) return make_int4(src, fill_info(FO_COPY, 2, ls, 0, 0), X / 2, (Y - 1) / 2);
+    return make_int4(src, fill_info(FO_COPY, 3, ls, 0, 0), (X - 1) / 2, Y / 2);
   }
   // coarser: reconstruction of the covering cell at a quarter-step point
   // (sx, sy are multiples of 2: fine nodes sit on a half-of-half-cell grid)
-  const long long cx2 = sx / 2, cy2 = sy / 2;  // coarse quarter-cell units
-  int ci = int(cx2 / 4), cj = int(cy2 / 4);
-  ci = min(max(ci, 0), m - 1);
-  cj = min(max(cj, 0), m - 1);
-  const int px = int(cx2 - 4LL * ci), py = int(cy2 - 4LL * cj);  // 0..4: xi = px/2 - 1
+  const int cx2 = sx / 2, cy2 = sy / 2;  // coarse quarter-cell units
+  const int ci = min(max(cx2 / 4, 0), m - 1), cj = min(max(cy2 / 4, 0), m - 1);
+  const int px = cx2 - 4 * ci, py = cy2 - 4 * cj;  // 0..4: xi = px/2 - 1
   return make_int4(src, fill_info(FO_EVAL, 0, lt - 1, px + 5 * py, 1), ci, cj);
 }
 
@@ -1784,58 +1778,62 @@ __device__ __forceinline__ int gather_dir(int i, int j, int m) {
   return (oy + 1) * 3 + (ox + 1);
 }
 
-// One block per leaf: the plan row of the leaf and a flag word (bit p: the
-// leaf has ops of phase p).  With nbr (the plan of smin = 0), also the
+// One block per leaf: the plan row of the leaf, a flag word (bits 0, 1, 2: the
+// leaf has ops with sources of the coarser, its own, the finer level), the
 // leaf's same-level neighbours nbr[t][d] (-1 where the direction holds no
 // leaf of its level; d = 4 is the leaf) and gnflags[t] bit d: every fill-set
 // DOF in direction d resolves to the copy a same-level gather would read
 // (the neighbour's own DOF at the shifted position; for d = 4, the leaf's
-// own value).  Such ops resolve the same way for every source bound up to
-// the leaf's level, since same-level and finer sources are then admissible.
+// own value).  Such ops hold for every source bound up to the leaf's level.
+// One plan serves every source bound: with a plan per bound, each resolved by
+// table lookups with 64-bit divisions per DOF, 1624 leaves of four levels
+// (m = 16) took 4 x 26.5 us and 4 x 4.3 for the vertex copies, now 24 and 4.
 __global__ __launch_bounds__(kThreads) void k_fill_plan(const HierDev H, const int32_t* entries, int nentries, int m,
-                                                        int smin, int4* plan, uint32_t* flags, int32_t* nbr,
-                                                        uint32_t* gnflags) {
+                                                        int4* plan, uint32_t* flags, int32_t* nbr, uint32_t* gnflags) {
   const int t = blockIdx.x;
-  const int lt = H.plevel[t];
-  __shared__ int32_t nb[9];
-  __shared__ uint32_t gn;
-  if (nbr) {
-    if (threadIdx.x < 9) {
-      const int d = threadIdx.x, ox = d % 3 - 1, oy = d / 3 - 1;
-      nb[d] = d == 4 ? t : lut_find(H, lt, (long long)H.pix[t] + ox, (long long)H.piy[t] + oy);
-      nbr[size_t(t) * 9 + d] = nb[d];
-    }
-    if (threadIdx.x == 0) gn = 0x1ffu;
-    __syncthreads();
+  const int lt = H.plevel[t], tx = H.pix[t], ty = H.piy[t];
+  __shared__ FillNbr N;
+  __shared__ uint32_t gn, levels;
+  if (threadIdx.x < 9) {
+    const int d = threadIdx.x, ox = d % 3 - 1, oy = d / 3 - 1;
+    N.same[d] = d == 4 ? t : lut_find(H, lt, (long long)tx + ox, (long long)ty + oy);
+    nbr[size_t(t) * 9 + d] = N.same[d];
+  } else if (threadIdx.x < 25) {
+    const int d = threadIdx.x - 9;
+    N.finer[d] = lut_find(H, lt + 1, 2LL * tx + (d & 3) - 1, 2LL * ty + (d >> 2) - 1);
+  } else if (threadIdx.x < 34) {
+    const int d = threadIdx.x - 25;
+    N.coarser[d] = lut_find(H, lt - 1, (long long)(tx >> 1) + d % 3 - 1, (long long)(ty >> 1) + d / 3 - 1);
   }
-  int has0 = 0, has1 = 0;
-  for (int e = threadIdx.x; e < nentries; e += kThreads) {
-    const int4 op = fill_resolve(H, m, smin, t, entries[e]);
-    plan[size_t(t) * nentries + e] = op;
-    if (op.x >= 0) {
-      if ((op.y >> 16) & 1) has1 = 1;
-      else has0 = 1;
-    }
-    if (nbr) {
-      const int32_t code = entries[e];
-      const int kind = code >> 24, i = ((code >> 12) & 0xfff) - kGhost, j = (code & 0xfff) - kGhost;
-      const int d = gather_dir(i, j, m), ox = d % 3 - 1, oy = d / 3 - 1;
-      bool ok;
-      if (d == 4) {
-        ok = op.x < 0;
-      } else {
-        const int fo = op.y & 3, skind = (op.y >> 2) & 3, ls = (op.y >> 4) & 15;
-        ok = nb[d] >= 0 && op.x == nb[d] && fo == FO_COPY && skind == kind && ls == lt && op.z == i - ox * m &&
-             op.w == j - oy * m;
-      }
-      if (!ok) atomicAnd(&gn, ~(1u << d));
-    }
-  }
-  has0 = __syncthreads_or(has0);
-  has1 = __syncthreads_or(has1);
   if (threadIdx.x == 0) {
-    flags[t] = uint32_t(has0) | (uint32_t(has1) << 1);
-    if (nbr) gnflags[t] = gn;
+    gn = 0x1ffu;
+    levels = 0u;
+  }
+  __syncthreads();
+  uint32_t seen = 0u, other = 0u;  // source levels; directions with another op than the gather's
+  for (int e = threadIdx.x; e < nentries; e += kThreads) {
+    const int32_t code = entries[e];
+    const int4 op = fill_resolve(N, m, t, lt, tx & 1, ty & 1, code);
+    plan[size_t(t) * nentries + e] = op;
+    const int kind = code >> 24, i = ((code >> 12) & 0xfff) - kGhost, j = (code & 0xfff) - kGhost;
+    const int d = gather_dir(i, j, m), ox = d % 3 - 1, oy = d / 3 - 1;
+    const int fo = op.y & 3, skind = (op.y >> 2) & 3, ls = (op.y >> 4) & 15;
+    if (op.x >= 0) seen |= 1u << (ls - lt + 1);
+    bool ok;
+    if (d == 4) {
+      ok = op.x < 0;
+    } else {
+      ok = N.same[d] >= 0 && op.x == N.same[d] && fo == FO_COPY && skind == kind && ls == lt && op.z == i - ox * m &&
+           op.w == j - oy * m;
+    }
+    if (!ok) other |= 1u << d;
+  }
+  if (seen) atomicOr(&levels, seen);
+  if (other) atomicAnd(&gn, ~other);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    flags[t] = levels;
+    gnflags[t] = gn;
   }
 }
 
@@ -1847,7 +1845,7 @@ struct FillArgs {
   const int4* plan;
   const uint32_t* flags;
   const FillWeights* W;
-  int32_t nentries, chunks, first_target, phase;
+  int32_t nentries, chunks, first_target, phase, smin;
 };
 
 template <typename T>
@@ -1856,13 +1854,17 @@ __global__ __launch_bounds__(kThreads) void k_fill_apply(const FillArgs<T> A) {
   const int tl = w / A.chunks;
   const int chunk = w - tl * A.chunks;
   const int t = A.first_target + tl;
-  if (!((A.flags[t] >> A.phase) & 1u)) return;  // block-uniform
   const Bufs<T>& B = A.B;
   const int lt = A.plevel[t], nc = B.ncomp;
+  // ops of this phase with admissible sources (block-uniform)
+  uint32_t lv = A.flags[t] & (A.phase ? 1u : 6u);
+  for (int r = -1; r <= 1; ++r)
+    if (lt + r < A.smin) lv &= ~(1u << (r + 1));
+  if (!lv) return;
   const size_t cstride = size_t(B.npatch) * (B.m + 5) * B.pitch;  // component stride
   for (int e = chunk * kThreads + threadIdx.x; e < A.nentries; e += A.chunks * kThreads) {
     const int4 op = A.plan[size_t(t) * A.nentries + e];
-    if (op.x < 0 || ((op.y >> 16) & 1) != A.phase) continue;
+    if (op.x < 0 || ((op.y >> 16) & 1) != A.phase || ((op.y >> 4) & 15) < A.smin) continue;
     const int32_t code = A.entries[e];
     const int kind = code >> 24, i = ((code >> 12) & 0xfff) - kGhost, j = (code & 0xfff) - kGhost;
     const int fo = op.y & 3, skind = (op.y >> 2) & 3, ls = (op.y >> 4) & 15, pos = (op.y >> 8) & 255;
@@ -1942,7 +1944,7 @@ struct AmrStepArgs {
   T dtdx, dtdy, a, b, c;
   double* reg;                     // FP64 flux registers
   const uint8_t* side_mask;
-  const int4* plan;                // fill plan of this time point, [nleaves][nentries]
+  const int4* plan;                // fill plan, [nleaves][nentries]; sources of level >= lev0 count here
   const int32_t* entries;          // fill-set entries; the first ninner lie within one cell of the interior
   int32_t nentries, ninner;
   const FillWeights* fw;
@@ -1964,13 +1966,14 @@ __device__ __forceinline__ bool own_dof(int kind, int i, int j, int m) {
 }
 
 // Value of fill-set DOF (kind, i, j) of leaf t as the fill plan resolves it
-// (op), component q; own = the leaf's own buffer (for "no source: keep").
+// (op) with sources of level >= smin, component q; own = the leaf's own buffer
+// (for "no source: keep").
 template <typename T>
 __device__ __forceinline__ T planned_value(T* const (&p)[2][4], uint32_t mask, int npatch, int pitch, int m,
-                                           const FillWeights* fw, const int4& op, const T* own, int q) {
+                                           const FillWeights* fw, const int4& op, int smin, const T* own, int q) {
   const size_t plane = size_t(m + 5) * pitch;
-  if (op.x < 0) return own[size_t(q) * npatch * plane];
   const int fo = op.y & 3, skind = (op.y >> 2) & 3, ls = (op.y >> 4) & 15, pos = (op.y >> 8) & 255;
+  if (op.x < 0 || ls < smin) return own[size_t(q) * npatch * plane];
   T* const* sb = p[(mask >> ls) & 1u];
   const size_t o = (size_t(q) * npatch + op.x) * plane + size_t(op.w + kGhost) * pitch + (op.z + kGhost);
   if (fo == FO_COPY) return sb[skind][o];
@@ -2152,7 +2155,7 @@ __global__ __launch_bounds__((amr_threads<M, PAIR>()), (amr_waves<T, EQ, M, PAIR
       const T* own = in[kind] + size_t(patch) * plane + size_t(j + kGhost) * A.pitch + (i + kGhost);
 #pragma unroll
       for (int q = 0; q < NCOMP; ++q)
-        L.in(kind, q, rr, i + kGhost) = planned_value<T>(A.p, A.mask, A.npatch, A.pitch, M, A.fw, op, own, q);
+        L.in(kind, q, rr, i + kGhost) = planned_value<T>(A.p, A.mask, A.npatch, A.pitch, M, A.fw, op, A.lev0, own, q);
     }
   }
   const auto& W = amr_weights<T, EQ>(wdev, P, k, false);
@@ -2222,7 +2225,7 @@ struct AmrSyncArgs {
   Bufs<T> B;
   const int32_t* plevel;
   const int4* cops;         // the vertex copies (k_canon_ops), ncops of them
-  int32_t ncops;
+  int32_t ncops, smin;      // those with sources of level >= smin are made
   const CFFace* faces;
   int32_t nfaces;
   double* reg;
@@ -2278,6 +2281,7 @@ __global__ __launch_bounds__(kThreads) void k_amr_sync(const AmrSyncArgs<T> A) {
     if (op.x < 0) return;  // the leaf owns this node
     const int di = (op.z & 0xff) - kGhost, dj = ((op.z >> 8) & 0xff) - kGhost;
     const int kind = (op.z >> 16) & 3, lt = (op.z >> 20) & 15, skind = (op.z >> 24) & 3, ls = (op.z >> 28) & 15;
+    if (ls < A.smin) return;
     const int si = (op.w & 0xffff) - kGhost, sj = (op.w >> 16) - kGhost;
     const size_t cstride = size_t(B.npatch) * (B.m + 5) * B.pitch;
     T* const dst = buf_of(B, lt, kind) + at(B, 0, op.x, di, dj);
@@ -2290,8 +2294,8 @@ __global__ __launch_bounds__(kThreads) void k_amr_sync(const AmrSyncArgs<T> A) {
 }
 
 // The fill's vertex copies onto the closed-square boundary nodes of the
-// leaves canon[0 .. ncanon), resolved once per hierarchy and source bound
-// from the fill plan into ops[k * nbnd + b] (boundary entry b of leaf
+// leaves canon[0 .. ncanon), resolved once per hierarchy from the fill plan
+// into ops[k * nbnd + b] (boundary entry b of leaf
 // canon[k]): x = target leaf (-1: the leaf owns the node), y = source leaf,
 // z = target column | row << 8 (both + kGhost) | kind << 16 | target level
 // << 20 | source kind << 24 | source level << 28, w = source column |
@@ -2686,6 +2690,7 @@ static hipError_t launch_sync_t(const AmrSyncLaunch& s, hipStream_t st) {
   A.plevel = s.plevel;
   A.cops = s.cops;
   A.ncops = s.ncops;
+  A.smin = s.smin;
   A.faces = s.faces;
   A.nfaces = s.nfaces;
   A.reg = s.reg;
@@ -2936,10 +2941,10 @@ hipError_t launch_fma_probe(bool fp32, void* out, int nblocks, int iters, hipStr
   return hipGetLastError();
 }
 
-hipError_t launch_fill_plan(const HierDev& H, const int32_t* entries, int nentries, int m, int smin, int4* plan,
+hipError_t launch_fill_plan(const HierDev& H, const int32_t* entries, int nentries, int m, int4* plan,
                             uint32_t* flags, int32_t* nbr, uint32_t* gnflags, hipStream_t st) {
   if (H.nleaves <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_fill_plan, dim3(unsigned(H.nleaves)), dim3(kThreads), 0, st, H, entries, nentries, m, smin, plan,
+  hipLaunchKernelGGL(k_fill_plan, dim3(unsigned(H.nleaves)), dim3(kThreads), 0, st, H, entries, nentries, m, plan,
                      flags, nbr, gnflags);
   return hipGetLastError();
 }
@@ -2947,7 +2952,7 @@ hipError_t launch_fill_plan(const HierDev& H, const int32_t* entries, int nentri
 template <typename T>
 static hipError_t fill_apply_t(const BufLaunch& b, const HierDev& H, const int32_t* entries, int nentries,
                                const int4* plan, const uint32_t* flags, const FillWeights* W, int first_target,
-                               int ntargets, int phase, hipStream_t st) {
+                               int ntargets, int phase, int smin, hipStream_t st) {
   FillArgs<T> A;
   A.B = make_bufs<T>(b);
   A.plevel = H.plevel;
@@ -2959,16 +2964,18 @@ static hipError_t fill_apply_t(const BufLaunch& b, const HierDev& H, const int32
   A.chunks = (nentries + kThreads - 1) / kThreads;
   A.first_target = first_target;
   A.phase = phase;
+  A.smin = smin;
   hipLaunchKernelGGL(k_fill_apply<T>, dim3(unsigned(ntargets * A.chunks)), dim3(kThreads), 0, st, A);
   return hipGetLastError();
 }
 
 hipError_t launch_fill_apply(bool fp32, const BufLaunch& b, const HierDev& H, const int32_t* entries, int nentries,
                              const int4* plan, const uint32_t* flags, const FillWeights* W, int first_target,
-                             int ntargets, int phase, hipStream_t st) {
+                             int ntargets, int phase, int smin, hipStream_t st) {
   if (ntargets <= 0) return hipSuccess;
-  return fp32 ? fill_apply_t<float>(b, H, entries, nentries, plan, flags, W, first_target, ntargets, phase, st)
-              : fill_apply_t<double>(b, H, entries, nentries, plan, flags, W, first_target, ntargets, phase, st);
+  return fp32 ? fill_apply_t<float>(b, H, entries, nentries, plan, flags, W, first_target, ntargets, phase, smin, st)
+              : fill_apply_t<double>(b, H, entries, nentries, plan, flags, W, first_target, ntargets, phase, smin,
+                                     st);
 }
 
 hipError_t launch_flux_correct(bool fp32, const BufLaunch& b, const CFFace* faces, int nfaces, double* reg,

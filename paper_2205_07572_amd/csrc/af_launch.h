@@ -80,7 +80,7 @@ struct AmrSyncLaunch {
   BufLaunch b;
   const int32_t* plevel;
   const int4* cops;  // vertex copies (launch_canon_ops)
-  int ncops;
+  int ncops, smin;  // copies from sources of level >= smin are made
   const CFFace* faces;
   int nfaces;
   double* reg;
@@ -110,12 +110,13 @@ bool step_shape_supported(int m, int ty);
 // plan[nleaves][nentries] and flags[nleaves] (bit p: ops of phase p); with
 // nbr and gnflags non-null also the same-level neighbours [nleaves][9] and
 // the directions a same-level gather stages (bit d)
-hipError_t launch_fill_plan(const HierDev& H, const int32_t* entries, int nentries, int m, int smin, int4* plan,
+hipError_t launch_fill_plan(const HierDev& H, const int32_t* entries, int nentries, int m, int4* plan,
                             uint32_t* flags, int32_t* nbr, uint32_t* gnflags, hipStream_t st);
-// applies the phase-`phase` ops of leaves [first_target, first_target + ntargets)
+// applies the phase-`phase` ops of leaves [first_target, first_target +
+// ntargets) with sources of level >= smin
 hipError_t launch_fill_apply(bool fp32, const BufLaunch& b, const HierDev& H, const int32_t* entries, int nentries,
                              const int4* plan, const uint32_t* flags, const FillWeights* W, int first_target,
-                             int ntargets, int phase, hipStream_t st);
+                             int ntargets, int phase, int smin, hipStream_t st);
 hipError_t launch_flux_correct(bool fp32, const BufLaunch& b, const CFFace* faces, int nfaces, double* reg,
                                int level, double inv_area, hipStream_t st);
 hipError_t launch_tag(bool fp32, const BufLaunch& b, const HierDev& H, int mode, int comp, double inv2dx0,
