@@ -1619,12 +1619,14 @@ __device__ __forceinline__ size_t at(const Bufs<T>& B, int comp, int patch, int 
   return ((size_t(comp) * B.npatch + patch) * (B.m + 5) + size_t(j + kGhost)) * B.pitch + (i + kGhost);
 }
 
-__device__ __forceinline__ int lut_find(const HierDev& H, int l, long long px, long long py) {
+// Leaf at position (px, py) of level l, at most one extent outside the domain;
+// -1 if it is no leaf.
+__device__ __forceinline__ int lut_find(const HierDev& H, int l, int px, int py) {
   if (l < 0 || l > H.lmax) return -1;
-  const long long nx = (long long)H.npx0 << l, ny = (long long)H.npy0 << l;
-  px = ((px % nx) + nx) % nx;
-  py = ((py % ny) + ny) % ny;
-  return H.lut[H.lut_off[l] + py * nx + px];
+  const int nx = H.npx0 << l, ny = H.npy0 << l;
+  px = px < 0 ? px + nx : (px >= nx ? px - nx : px);
+  py = py < 0 ? py + ny : (py >= ny ? py - ny : py);
+  return H.lut[size_t(H.lut_off[l]) + size_t(py) * size_t(nx) + size_t(px)];
 }
 
 __device__ __forceinline__ double lagr(int a, double s) {
@@ -1787,7 +1789,7 @@ __device__ __forceinline__ int gather_dir(int i, int j, int m) {
 // own value).  Such ops hold for every source bound up to the leaf's level.
 // One plan serves every source bound: with a plan per bound, each resolved by
 // table lookups with 64-bit divisions per DOF, 1624 leaves of four levels
-// (m = 16) took 4 x 26.5 us and 4 x 4.3 for the vertex copies, now 24 and 4.
+// (m = 16) took 4 x 26.5 us and 4 x 4.3 for the vertex copies, now 22 and 4.
 __global__ __launch_bounds__(kThreads) void k_fill_plan(const HierDev H, const int32_t* entries, int nentries, int m,
                                                         int4* plan, uint32_t* flags, int32_t* nbr, uint32_t* gnflags) {
   const int t = blockIdx.x;
@@ -1796,14 +1798,14 @@ __global__ __launch_bounds__(kThreads) void k_fill_plan(const HierDev H, const i
   __shared__ uint32_t gn, levels;
   if (threadIdx.x < 9) {
     const int d = threadIdx.x, ox = d % 3 - 1, oy = d / 3 - 1;
-    N.same[d] = d == 4 ? t : lut_find(H, lt, (long long)tx + ox, (long long)ty + oy);
+    N.same[d] = d == 4 ? t : lut_find(H, lt, tx + ox, ty + oy);
     nbr[size_t(t) * 9 + d] = N.same[d];
   } else if (threadIdx.x < 25) {
     const int d = threadIdx.x - 9;
-    N.finer[d] = lut_find(H, lt + 1, 2LL * tx + (d & 3) - 1, 2LL * ty + (d >> 2) - 1);
+    N.finer[d] = lut_find(H, lt + 1, 2 * tx + (d & 3) - 1, 2 * ty + (d >> 2) - 1);
   } else if (threadIdx.x < 34) {
     const int d = threadIdx.x - 25;
-    N.coarser[d] = lut_find(H, lt - 1, (long long)(tx >> 1) + d % 3 - 1, (long long)(ty >> 1) + d / 3 - 1);
+    N.coarser[d] = lut_find(H, lt - 1, (tx >> 1) + d % 3 - 1, (ty >> 1) + d / 3 - 1);
   }
   if (threadIdx.x == 0) {
     gn = 0x1ffu;
@@ -2407,61 +2409,77 @@ __global__ __launch_bounds__(kThreads) void k_tag(Bufs<T> B, HierDev H, int mode
 }
 
 // ---------------------------------------------------------------------------
-// Regrid transfer (Sec. 3.1): one block per new leaf.
+// Regrid transfer (Sec. 3.1): one block per new leaf and DOF kind, so that the
+// kind's extents are constants and a thread has all components of a DOF in
+// flight (one block per leaf with divisions by a variable m, one component at
+// a time, on 1624 leaves of m = 16 in FP32: 51 us, now 26).
 // ---------------------------------------------------------------------------
 
-template <typename T>
-__global__ __launch_bounds__(kThreads) void k_transfer(Bufs<T> OLD, HierDev HO, Bufs<T> NEW, const Transfer* tr) {
-  const int p = blockIdx.x;
-  const Transfer X = tr[p];
-  const int m = NEW.m, nc = NEW.ncomp;
-  const int n_avg = m * m, n_c = (m + 1) * (m + 1), n_x = m * (m + 1), n_y = (m + 1) * m;
-  const int total = n_avg + n_c + n_x + n_y;
-  for (int e = threadIdx.x; e < total; e += kThreads) {
-    int kind, i, j;
-    if (e < n_avg) { kind = 0; i = e % m; j = e / m; }
-    else if (e < n_avg + n_c) { const int f = e - n_avg; kind = 1; i = f % (m + 1); j = f / (m + 1); }
-    else if (e < n_avg + n_c + n_x) { const int f = e - n_avg - n_c; kind = 2; i = f % (m + 1); j = f / (m + 1); }
-    else { const int f = e - n_avg - n_c - n_x; kind = 3; i = f % m; j = f / m; }
-    for (int q = 0; q < nc; ++q) {
-      double val;
-      if (X.mode == 0) {
-        const int s = X.src[0];
-        val = buf_of(OLD, HO.plevel[s], kind)[at(OLD, q, s, i, j)];
-      } else if (X.mode == 1) {
-        const int s = X.src[0];
-        const int ls = HO.plevel[s];
-        if (kind == 0) {
-          const int fi = X.qx * m + i, fj = X.qy * m + j;
-          val = quarter_avg(OLD, ls, q, s, fi >> 1, fj >> 1, (fi & 1) ? 0.0 : -1.0, (fj & 1) ? 0.0 : -1.0);
-        } else {
-          // node position in parent half-cell units
-          double xs = double(X.qx * m + i), ys = double(X.qy * m + j);
-          if (kind == 2) ys += 0.5;
-          if (kind == 3) xs += 0.5;
-          int ci = min(max(int(floor(xs / 2.0)), 0), m - 1), cj = min(max(int(floor(ys / 2.0)), 0), m - 1);
-          val = eval_cell(OLD, ls, q, s, ci, cj, xs - (2.0 * ci + 1.0), ys - (2.0 * cj + 1.0));
-        }
+template <typename T, int M, int NC, int KIND>
+__device__ __forceinline__ void transfer_kind(const Bufs<T>& OLD, const HierDev& HO, const Bufs<T>& NEW,
+                                              const Transfer& X, int p) {
+  constexpr int W = M + (KIND == 1 || KIND == 2), N = W * (M + (KIND == 1 || KIND == 3));
+  const size_t oldc = size_t(OLD.npatch) * (M + 5) * OLD.pitch, newc = size_t(NEW.npatch) * (M + 5) * NEW.pitch;
+#pragma unroll 2
+  for (int e = threadIdx.x; e < N; e += kThreads) {
+    const int j = e / W, i = e - j * W;
+    T val[NC];
+    if (X.mode == 0) {
+      const int s = X.src[0];
+      const T* o = buf_of(OLD, HO.plevel[s], KIND) + at(OLD, 0, s, i, j);
+#pragma unroll
+      for (int q = 0; q < NC; ++q) val[q] = o[q * oldc];
+    } else if (X.mode == 1) {
+      const int s = X.src[0];
+      const int ls = HO.plevel[s];
+      if (KIND == 0) {
+        const int fi = X.qx * M + i, fj = X.qy * M + j;
+#pragma unroll
+        for (int q = 0; q < NC; ++q)
+          val[q] = T(quarter_avg(OLD, ls, q, s, fi >> 1, fj >> 1, (fi & 1) ? 0.0 : -1.0, (fj & 1) ? 0.0 : -1.0));
       } else {
-        if (kind == 0) {
-          const int fi = 2 * i, fj = 2 * j;
-          const int qx = fi / m, qy = fj / m;
-          const int s = X.src[qy * 2 + qx];
-          const T* av = buf_of(OLD, HO.plevel[s], 0);
-          const int li = fi - qx * m, lj = fj - qy * m;
-          val = 0.25 * ((double(av[at(OLD, q, s, li, lj)]) + double(av[at(OLD, q, s, li + 1, lj)])) +
-                        (double(av[at(OLD, q, s, li, lj + 1)]) + double(av[at(OLD, q, s, li + 1, lj + 1)])));
-        } else {
-          int FX = 2 * i, FY = 2 * j;
-          if (kind == 2) FY += 1;
-          if (kind == 3) FX += 1;
-          const int qx = min(FX / m, 1), qy = min(FY / m, 1);
-          const int s = X.src[qy * 2 + qx];
-          val = buf_of(OLD, HO.plevel[s], 1)[at(OLD, q, s, FX - qx * m, FY - qy * m)];
-        }
+        // node position in parent half-cell units
+        double xs = double(X.qx * M + i), ys = double(X.qy * M + j);
+        if (KIND == 2) ys += 0.5;
+        if (KIND == 3) xs += 0.5;
+        const int ci = min(max(int(floor(xs / 2.0)), 0), M - 1), cj = min(max(int(floor(ys / 2.0)), 0), M - 1);
+#pragma unroll
+        for (int q = 0; q < NC; ++q)
+          val[q] = T(eval_cell(OLD, ls, q, s, ci, cj, xs - (2.0 * ci + 1.0), ys - (2.0 * cj + 1.0)));
       }
-      NEW.p[0][kind][at(NEW, q, p, i, j)] = T(val);
+    } else if (KIND == 0) {
+      const int qx = 2 * i / M, qy = 2 * j / M;
+      const int s = X.src[qy * 2 + qx];
+      const T* o = buf_of(OLD, HO.plevel[s], 0) + at(OLD, 0, s, 2 * i - qx * M, 2 * j - qy * M);
+      const int P = OLD.pitch;
+#pragma unroll
+      for (int q = 0; q < NC; ++q) {
+        const T* av = o + q * oldc;
+        val[q] = T(0.25 * ((double(av[0]) + double(av[1])) + (double(av[P]) + double(av[P + 1]))));
+      }
+    } else {
+      const int FX = 2 * i + (KIND == 3), FY = 2 * j + (KIND == 2);
+      const int qx = min(FX / M, 1), qy = min(FY / M, 1);
+      const int s = X.src[qy * 2 + qx];
+      const T* o = buf_of(OLD, HO.plevel[s], 1) + at(OLD, 0, s, FX - qx * M, FY - qy * M);
+#pragma unroll
+      for (int q = 0; q < NC; ++q) val[q] = o[q * oldc];
     }
+    T* const d = NEW.p[0][KIND] + at(NEW, 0, p, i, j);
+#pragma unroll
+    for (int q = 0; q < NC; ++q) d[q * newc] = val[q];
+  }
+}
+
+template <typename T, int M, int NC>
+__global__ __launch_bounds__(kThreads) void k_transfer(Bufs<T> OLD, HierDev HO, Bufs<T> NEW, const Transfer* tr) {
+  const int p = int(blockIdx.x) >> 2;
+  const Transfer X = tr[p];
+  switch (blockIdx.x & 3) {
+    case 0: return transfer_kind<T, M, NC, 0>(OLD, HO, NEW, X, p);
+    case 1: return transfer_kind<T, M, NC, 1>(OLD, HO, NEW, X, p);
+    case 2: return transfer_kind<T, M, NC, 2>(OLD, HO, NEW, X, p);
+    default: return transfer_kind<T, M, NC, 3>(OLD, HO, NEW, X, p);
   }
 }
 
@@ -3003,16 +3021,30 @@ hipError_t launch_tag(bool fp32, const BufLaunch& b, const HierDev& H, int mode,
   return hipGetLastError();
 }
 
+template <typename T, int NC>
+static hipError_t transfer_t(const BufLaunch& old_b, const HierDev& HO, const BufLaunch& new_b, const Transfer* tr,
+                             int nnew, hipStream_t st) {
+  const dim3 grid(4u * unsigned(nnew)), block(kThreads);
+  const Bufs<T> O = make_bufs<T>(old_b), N = make_bufs<T>(new_b);
+  switch (old_b.m) {
+    case 8: hipLaunchKernelGGL((k_transfer<T, 8, NC>), grid, block, 0, st, O, HO, N, tr); break;
+    case 16: hipLaunchKernelGGL((k_transfer<T, 16, NC>), grid, block, 0, st, O, HO, N, tr); break;
+    case 32: hipLaunchKernelGGL((k_transfer<T, 32, NC>), grid, block, 0, st, O, HO, N, tr); break;
+    case 64: hipLaunchKernelGGL((k_transfer<T, 64, NC>), grid, block, 0, st, O, HO, N, tr); break;
+    case 128: hipLaunchKernelGGL((k_transfer<T, 128, NC>), grid, block, 0, st, O, HO, N, tr); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
 hipError_t launch_transfer(bool fp32, const BufLaunch& old_b, const HierDev& HO, const BufLaunch& new_b,
                            const Transfer* tr, int nnew, hipStream_t st) {
   if (nnew <= 0) return hipSuccess;
-  if (fp32)
-    hipLaunchKernelGGL(k_transfer<float>, dim3(unsigned(nnew)), dim3(kThreads), 0, st, make_bufs<float>(old_b),
-                       HO, make_bufs<float>(new_b), tr);
-  else
-    hipLaunchKernelGGL(k_transfer<double>, dim3(unsigned(nnew)), dim3(kThreads), 0, st, make_bufs<double>(old_b),
-                       HO, make_bufs<double>(new_b), tr);
-  return hipGetLastError();
+  if (old_b.ncomp == 1)
+    return fp32 ? transfer_t<float, 1>(old_b, HO, new_b, tr, nnew, st)
+                : transfer_t<double, 1>(old_b, HO, new_b, tr, nnew, st);
+  return fp32 ? transfer_t<float, 3>(old_b, HO, new_b, tr, nnew, st)
+              : transfer_t<double, 3>(old_b, HO, new_b, tr, nnew, st);
 }
 
 hipError_t launch_sum(bool fp32, const BufLaunch& b, const HierDev& H, double area0, double* part, double* out,
