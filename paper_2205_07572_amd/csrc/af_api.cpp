@@ -1271,7 +1271,6 @@ struct Driver {
     AmrSyncLaunch S{};
     S.fp32 = ctx->fp32();
     S.b = make_buf(ctx, &bufs[0], &bufs[1], mask);
-    S.plevel = h->d_level;
     S.reg = reg;
     S.inv_area0 = 1.0 / (ctx->dx(0) * ctx->dy(0));
     if (smin >= 0 && smin <= F && h->d_canon_ops) {
@@ -1283,6 +1282,8 @@ struct Driver {
       const int off = h->face_off[fix_lo];
       S.faces = h->d_faces + off;
       S.nfaces = h->face_off[fix_hi + 1] - off;
+      S.lev0 = fix_lo;
+      for (int l = fix_lo; l <= fix_hi; ++l) S.face_end[l] = h->face_off[l + 1] - off;
     }
     AF_HIP(launch_amr_sync(S, st));
     return AF_OK;

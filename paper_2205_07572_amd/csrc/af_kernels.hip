@@ -2225,54 +2225,76 @@ __global__ __launch_bounds__((amr_threads<M, PAIR>()), (amr_waves<T, EQ, M, PAIR
 template <typename T>
 struct AmrSyncArgs {
   Bufs<T> B;
-  const int32_t* plevel;
   const int4* cops;         // the vertex copies (k_canon_ops), ncops of them
   int32_t ncops, smin;      // those with sources of level >= smin are made
   const CFFace* faces;
-  int32_t nfaces;
+  int32_t nfaces, lev0;           // faces of coarse levels lev0 .., level l's end at face_end[l]
+  int32_t face_end[kMaxLevels];
   double* reg;
   double inv_area0;         // 1 / (dx_0 dy_0); level l: times 4^l
 };
 
-template <typename T>
-__device__ void reflux_face_group(const Bufs<T>& B, const CFFace* faces, int nfaces, int f, double* reg,
-                                  const int32_t* plevel, double inv_area0) {
-  const int m = B.m, nc = B.ncomp;
-  auto cell_of = [&](const CFFace& F, int* ci, int* cj) {
-    *ci = F.side == 0 ? 0 : (F.side == 1 ? m - 1 : F.k);
-    *cj = F.side == 2 ? 0 : (F.side == 3 ? m - 1 : F.k);
+// The fix of the coarse cell whose faces begin at f (a cell of a corner has
+// two, of the x and of the y direction; nothing if f is the second).  Every
+// load is issued as soon as its address is known: face list, then registers
+// and averages of all components, then the stores.
+template <typename T, int NC>
+__device__ __forceinline__ void reflux_cell(const AmrSyncArgs<T>& A, int f) {
+  const Bufs<T>& B = A.B;
+  const int m = B.m;
+  const CFFace F[2] = {A.faces[f], A.faces[min(f + 1, A.nfaces - 1)]};
+  const CFFace P = A.faces[max(f - 1, 0)];
+  auto ci = [&](const CFFace& G) { return G.side == 0 ? 0 : (G.side == 1 ? m - 1 : G.k); };
+  auto cj = [&](const CFFace& G) { return G.side == 2 ? 0 : (G.side == 3 ? m - 1 : G.k); };
+  auto same = [&](const CFFace& G, const CFFace& H) {
+    return G.coarse == H.coarse && ci(G) == ci(H) && cj(G) == cj(H);
   };
-  int ci, cj;
-  cell_of(faces[f], &ci, &cj);
-  if (f > 0) {
-    int pi, pj;
-    cell_of(faces[f - 1], &pi, &pj);
-    if (faces[f - 1].coarse == faces[f].coarse && pi == ci && pj == cj) return;
+  if (f > 0 && same(P, F[0])) return;
+  const int n = f + 1 < A.nfaces && same(F[1], F[0]) ? 2 : 1;
+  int level = A.lev0;
+  while (f >= A.face_end[level]) ++level;
+  const double inv_area = A.inv_area0 * double(1LL << (2 * level));
+  T* const av = buf_of(B, level, 0) + at(B, 0, F[0].coarse, ci(F[0]), cj(F[0]));
+  const size_t cstride = size_t(B.npatch) * (m + 5) * B.pitch;
+  double* Rc[2];
+  double* Rf[2];
+  double c[2][NC], r0[2][NC], r1[2][NC];
+  T a[NC];
+#pragma unroll
+  for (int g = 0; g < 2; ++g) {
+    Rc[g] = A.reg + (size_t(F[g].coarse) * 4 + F[g].side) * m * NC + size_t(F[g].k) * NC;
+    Rf[g] = A.reg + (size_t(F[g].fine) * 4 + (F[g].side ^ 1)) * m * NC + size_t(F[g].fk) * NC;
+    if (g < n)
+#pragma unroll
+      for (int q = 0; q < NC; ++q) {
+        c[g][q] = Rc[g][q];
+        r0[g][q] = Rf[g][q];
+        r1[g][q] = Rf[g][NC + q];
+      }
   }
-  const int level = plevel[faces[f].coarse];
-  const double inv_area = inv_area0 * double(1LL << (2 * level));
-  T* av = buf_of(B, level, 0);
-  for (int g = f; g < nfaces; ++g) {
-    const CFFace F = faces[g];
-    int gi, gj;
-    cell_of(F, &gi, &gj);
-    if (F.coarse != faces[f].coarse || gi != ci || gj != cj) break;
-    const double sgn = (F.side == 1 || F.side == 3) ? 1.0 : -1.0;
-    const int opp = F.side ^ 1;
-    double* Rc = reg + (size_t(F.coarse) * 4 + F.side) * m * nc + size_t(F.k) * nc;
-    double* Rf = reg + (size_t(F.fine) * 4 + opp) * m * nc + size_t(F.fk) * nc;
-    for (int q = 0; q < nc; ++q) {
-      const double rf = Rf[q] + Rf[nc + q];
-      const size_t idx = at(B, q, F.coarse, ci, cj);
-      av[idx] = T(double(av[idx]) + sgn * (Rc[q] - rf) * inv_area);
-      Rc[q] = 0.0;
-      Rf[q] = 0.0;
-      Rf[nc + q] = 0.0;
+#pragma unroll
+  for (int q = 0; q < NC; ++q) a[q] = av[q * cstride];
+#pragma unroll
+  for (int g = 0; g < 2; ++g) {
+    if (g >= n) continue;
+    const double sgn = (F[g].side & 1) ? 1.0 : -1.0;
+#pragma unroll
+    for (int q = 0; q < NC; ++q) {
+      a[q] = T(double(a[q]) + sgn * (c[g][q] - (r0[g][q] + r1[g][q])) * inv_area);
+      Rc[g][q] = 0.0;
+      Rf[g][q] = 0.0;
+      Rf[g][NC + q] = 0.0;
     }
   }
+#pragma unroll
+  for (int q = 0; q < NC; ++q) av[q * cstride] = a[q];
 }
 
-template <typename T>
+// A launch is a chain of loads and little else, so the chain is kept short: a
+// copy loads its op, then all components (1792 leaves of four levels, three
+// components, FP32: 6.5 us per launch with one component at a time and the
+// level of a face read from the leaf, 5.2 now).
+template <typename T, int NC>
 __global__ __launch_bounds__(kThreads) void k_amr_sync(const AmrSyncArgs<T> A) {
   const Bufs<T>& B = A.B;
   const int cblocks = (A.ncops + kThreads - 1) / kThreads;
@@ -2288,11 +2310,15 @@ __global__ __launch_bounds__(kThreads) void k_amr_sync(const AmrSyncArgs<T> A) {
     const size_t cstride = size_t(B.npatch) * (B.m + 5) * B.pitch;
     T* const dst = buf_of(B, lt, kind) + at(B, 0, op.x, di, dj);
     const T* const src = buf_of(B, ls, skind) + at(B, 0, op.y, si, sj);
-    for (int q = 0; q < B.ncomp; ++q) dst[q * cstride] = src[q * cstride];
+    T v[NC];
+#pragma unroll
+    for (int q = 0; q < NC; ++q) v[q] = src[q * cstride];
+#pragma unroll
+    for (int q = 0; q < NC; ++q) dst[q * cstride] = v[q];
     return;
   }
   const int f = (int(blockIdx.x) - cblocks) * kThreads + int(threadIdx.x);
-  if (f < A.nfaces) reflux_face_group(B, A.faces, A.nfaces, f, A.reg, A.plevel, A.inv_area0);
+  if (f < A.nfaces) reflux_cell<T, NC>(A, f);
 }
 
 // The fill's vertex copies onto the closed-square boundary nodes of the
@@ -2705,7 +2731,6 @@ template <typename T>
 static hipError_t launch_sync_t(const AmrSyncLaunch& s, hipStream_t st) {
   AmrSyncArgs<T> A;
   A.B = make_bufs<T>(s.b);
-  A.plevel = s.plevel;
   A.cops = s.cops;
   A.ncops = s.ncops;
   A.smin = s.smin;
@@ -2713,9 +2738,14 @@ static hipError_t launch_sync_t(const AmrSyncLaunch& s, hipStream_t st) {
   A.nfaces = s.nfaces;
   A.reg = s.reg;
   A.inv_area0 = s.inv_area0;
+  A.lev0 = s.lev0;
+  for (int l = 0; l < kMaxLevels; ++l) A.face_end[l] = s.face_end[l];
   const int blocks = (s.ncops + kThreads - 1) / kThreads + (s.nfaces + kThreads - 1) / kThreads;
   if (blocks == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_amr_sync<T>, dim3(unsigned(blocks)), dim3(kThreads), 0, st, A);
+  if (s.b.ncomp == 1)
+    hipLaunchKernelGGL((k_amr_sync<T, 1>), dim3(unsigned(blocks)), dim3(kThreads), 0, st, A);
+  else
+    hipLaunchKernelGGL((k_amr_sync<T, 3>), dim3(unsigned(blocks)), dim3(kThreads), 0, st, A);
   return hipGetLastError();
 }
 

@@ -78,11 +78,11 @@ hipError_t launch_amr_step(const AmrStepLaunch& s, hipStream_t st);
 struct AmrSyncLaunch {
   bool fp32;
   BufLaunch b;
-  const int32_t* plevel;
   const int4* cops;  // vertex copies (launch_canon_ops)
   int ncops, smin;  // copies from sources of level >= smin are made
   const CFFace* faces;
   int nfaces;
+  int lev0, face_end[kMaxLevels];  // coarse level of the first faces; where a level's faces end
   double* reg;
   double inv_area0;
 };
