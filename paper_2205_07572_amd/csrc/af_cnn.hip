@@ -550,27 +550,33 @@ struct DofPtrs {
   const T* p[2][4];
 };
 
+// One block per leaf, one thread per cell: the leaf's level and the channel's
+// plane are uniform and four channels are in flight (one thread per element,
+// with three 64-bit divisions each, on 1792 leaves: 18 us, now
+// 11).
 template <typename T>
-__global__ void k_features(const DofPtrs<T> D, uint32_t mask, int npatch, int pitch, int ncomp,
-                           const int32_t* plevel, int first, int n, const float* mean, const float* inv_std, int nin,
-                           float* x) {
-  const long total = long(n) * nin * kPix;
-  for (long e = blockIdx.x * long(blockDim.x) + threadIdx.x; e < total; e += long(gridDim.x) * blockDim.x) {
-    const int p = int(e % kPix);
-    const long bc = e / kPix;
-    const int ch = int(bc % nin), b = int(bc / nin);
-    const int leaf = first + b;
-    const int l = plevel[leaf];
-    float v;
-    if (ch >= 12 || ch / 4 >= ncomp) {
-      v = ch >= 12 ? float(l) : 0.f;
-    } else {
-      const int q = ch / 4, kind = ch % 4;
-      const T* base = D.p[(mask >> l) & 1][kind];
-      const int i = p % kImg, j = p / kImg;
-      v = float(base[((size_t(q) * npatch + leaf) * (kImg + 5) + (j + kGhost)) * pitch + (i + kGhost)]);
+__global__ __launch_bounds__(kPix) void k_features(const DofPtrs<T> D, uint32_t mask, int npatch, int pitch, int ncomp,
+                                                   const int32_t* plevel, int first, const float* mean,
+                                                   const float* inv_std, int nin, float* x) {
+  constexpr int U = 4;
+  const int leaf = first + int(blockIdx.x), l = plevel[leaf];
+  const int p = threadIdx.x, i = p % kImg, j = p / kImg;
+  float* const out = x + size_t(blockIdx.x) * nin * kPix + p;
+  for (int c0 = 0; c0 < nin; c0 += U) {
+    float v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int ch = c0 + u;
+      v[u] = ch >= 12 ? float(l) : 0.f;
+      if (ch < nin && ch < 12 && ch / 4 < ncomp)
+        v[u] = float(D.p[(mask >> l) & 1][ch % 4][((size_t(ch / 4) * npatch + leaf) * (kImg + 5) + (j + kGhost)) * pitch +
+                                                  (i + kGhost)]);
     }
-    x[e] = (v - mean[ch]) * inv_std[ch];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int ch = c0 + u;
+      if (ch < nin) out[size_t(ch) * kPix] = (v[u] - mean[ch]) * inv_std[ch];
+    }
   }
 }
 
@@ -803,23 +809,23 @@ af_status af_cnn_features(af_ctx* ctx, af_cnn* c, const af_hier* h, const af_sta
   af_status s = af_internal_tag_view(ctx, h, bufs, &v);
   if (s != AF_OK) return cfail(s, "af_cnn_features: bad context, hierarchy or buffers");
   if (v.m != kImg) return cfail(AF_ERR_ARG, "af_cnn_features: the tagger takes 16x16 patches");
-  const long total = long(v.nleaves) * c->nin * kPix;
+  if (v.nleaves <= 0) return AF_OK;
   if (v.fp32) {
     DofPtrs<float> D;
     for (int k = 0; k < 4; ++k) {
       D.p[0][k] = static_cast<const float*>(v.dof0[k]);
       D.p[1][k] = static_cast<const float*>(v.dof1[k]);
     }
-    hipLaunchKernelGGL(k_features<float>, dim3(grid_for(total)), dim3(256), 0, st, D, mask, v.npatch, v.pitch,
-                       v.ncomp, v.plevel, 0, v.nleaves, c->d_norm, c->d_norm + c->nin, c->nin, x);
+    hipLaunchKernelGGL(k_features<float>, dim3(unsigned(v.nleaves)), dim3(kPix), 0, st, D, mask, v.npatch, v.pitch,
+                       v.ncomp, v.plevel, 0, c->d_norm, c->d_norm + c->nin, c->nin, x);
   } else {
     DofPtrs<double> D;
     for (int k = 0; k < 4; ++k) {
       D.p[0][k] = static_cast<const double*>(v.dof0[k]);
       D.p[1][k] = static_cast<const double*>(v.dof1[k]);
     }
-    hipLaunchKernelGGL(k_features<double>, dim3(grid_for(total)), dim3(256), 0, st, D, mask, v.npatch, v.pitch,
-                       v.ncomp, v.plevel, 0, v.nleaves, c->d_norm, c->d_norm + c->nin, c->nin, x);
+    hipLaunchKernelGGL(k_features<double>, dim3(unsigned(v.nleaves)), dim3(kPix), 0, st, D, mask, v.npatch, v.pitch,
+                       v.ncomp, v.plevel, 0, c->d_norm, c->d_norm + c->nin, c->nin, x);
   }
   CNN_HIP(hipGetLastError());
   return AF_OK;
