@@ -426,7 +426,8 @@ struct StepIO {
 // reads the sums from where they will be stored.  rofs: staged row of cell
 // row j is j - jlo + 1 + rofs (the pair's second substep reads the first's
 // rows).
-template <typename T, int EQ, int M, int TY, bool TO_LDS = false, int NT = kThreads, bool BULK = false, typename L_t>
+template <typename T, int EQ, int M, int TY, bool TO_LDS = false, int NT = kThreads, bool BULK = false, int USE = 0,
+          typename L_t>
 __device__ __forceinline__ void step_compute(L_t& L, const StepIO<T>& A, const typename WSel<T, EQ>::type& W,
                                              int jlo, int jhi, T px0, T py0, int rofs = 0) {
   constexpr int NCOMP = EQ == 1 ? 3 : 1;
@@ -2016,7 +2017,9 @@ constexpr int amr_threads() {
 }
 template <typename T, int EQ, int M, bool PAIR>
 constexpr int amr_waves() {
-  return EQ == 1 && amr_threads<M, PAIR>() == 512 ? (sizeof(T) == 4 ? 8 : 5) : 1;
+  if (EQ != 1) return 1;
+  if (amr_threads<M, PAIR>() == 512) return sizeof(T) == 4 ? 8 : 5;
+  return 1;
 }
 
 // The weights or parameters a batched step reads: advection those of its
@@ -2036,13 +2039,16 @@ template <typename T>
 struct AmrW<T, 0> { using type = AdvWeights<T>; };
 template <typename T>
 struct AmrW<T, 1> { using type = NoWeights; };
-template <typename T, int EQ, typename P_t>
+template <typename T, int EQ, bool PAIR, typename P_t>
 __device__ __forceinline__ const typename WSel<T, EQ>::type& amr_weights(const AcOrbitWeights<T>* wdev, const P_t& P,
                                                                          int k, bool second) {
   if constexpr (EQ == 1) {
     return *wdev;
   } else if constexpr (EQ == 0) {
-    return weights_of(P);
+    // a single step's weights fit beside it; a pair, which uses them twice,
+    // reads them where they are used
+    if constexpr (PAIR) return weights_of(P);
+    else return P.w;
   } else {
     const auto& W = weights_of(P);
     return second ? W.second : W.lev[k];
@@ -2160,7 +2166,7 @@ __global__ __launch_bounds__((amr_threads<M, PAIR>()), (amr_waves<T, EQ, M, PAIR
         L.in(kind, q, rr, i + kGhost) = planned_value<T>(A.p, A.mask, A.npatch, A.pitch, M, A.fw, op, A.lev0, own, q);
     }
   }
-  const auto& W = amr_weights<T, EQ>(wdev, P, k, false);
+  const auto& W = amr_weights<T, EQ, PAIR>(wdev, P, k, false);
   // rotation, swirl: lower-left corner of the patch's cell (0,0)
   T px0 = T(0), py0 = T(0);
   if constexpr (EQ == 2 || EQ == 3) {
@@ -2186,7 +2192,11 @@ __global__ __launch_bounds__((amr_threads<M, PAIR>()), (amr_waves<T, EQ, M, PAIR
   io.len_dt_y = A.len_dt_y[k];
   io.reg = (A.reg && A.side_mask) ? A.reg : nullptr;
   io.smask = io.reg ? A.side_mask[patch] : 0u;
-  constexpr bool BULK = NT == kThreads;
+  // a patch of 32 x 32 in tiles gains more from the registers that single loads
+  // save (FP64, 8 x 8 patches of three levels, two coarse steps: 582 us with the
+  // orbits gathered in bulk, 457 without; FP32 296 and 260), the small pair
+  // kernel from the loads in flight
+  constexpr bool BULK = PAIR && NT == kThreads;
   if constexpr (PAIR) {
     // Whole-patch blocks, their regions known to the compiler (which takes
     // fewer registers than with the region as a variable).  The finest
@@ -2207,9 +2217,11 @@ __global__ __launch_bounds__((amr_threads<M, PAIR>()), (amr_waves<T, EQ, M, PAIR
       __syncthreads();
     }
     io.region = 0;
-    step_compute<T, EQ, M, TY, false, NT, BULK>(L, io, amr_weights<T, EQ>(wdev, P, k, region == 1), 0, M, px0, py0, 1);
+    step_compute<T, EQ, M, TY, false, NT, BULK>(L, io, amr_weights<T, EQ, PAIR>(wdev, P, k, region == 1), 0, M, px0, py0, 1);
   } else {
-    step_compute<T, EQ, M, TY, false, NT, BULK>(L, io, W, jlo, jhi, px0, py0);
+    // (a copy of its own: shared with k_patch_step it was compiled to 177
+    // registers in FP64 and lost a wave)
+    step_compute<T, EQ, M, TY, false, NT, BULK, 1>(L, io, W, jlo, jhi, px0, py0);
   }
 }
 
