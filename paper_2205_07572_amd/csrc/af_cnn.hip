@@ -800,6 +800,24 @@ struct AfTagView {
 };
 extern "C" af_status af_internal_tag_view(const af_ctx* ctx, const af_hier* h, const af_state* bufs, AfTagView* v);
 
+namespace {
+// One block per leaf, at most 2^23 a launch: a grid is limited to 2^32
+// threads (beyond it the count wraps without an error).
+template <typename T>
+void launch_features(const AfTagView& v, uint32_t mask, const float* norm, int nin, float* x, hipStream_t st) {
+  DofPtrs<T> D;
+  for (int k = 0; k < 4; ++k) {
+    D.p[0][k] = static_cast<const T*>(v.dof0[k]);
+    D.p[1][k] = static_cast<const T*>(v.dof1[k]);
+  }
+  constexpr int kLeaves = 1 << 23;
+  for (int first = 0; first < v.nleaves; first += kLeaves)
+    hipLaunchKernelGGL(k_features<T>, dim3(unsigned(std::min(v.nleaves - first, kLeaves))), dim3(kPix), 0, st, D, mask,
+                       v.npatch, v.pitch, v.ncomp, v.plevel, first, norm, norm + nin, nin,
+                       x + size_t(first) * nin * kPix);
+}
+}  // namespace
+
 extern "C" {
 
 af_status af_cnn_features(af_ctx* ctx, af_cnn* c, const af_hier* h, const af_state* bufs, uint32_t mask,
@@ -810,23 +828,8 @@ af_status af_cnn_features(af_ctx* ctx, af_cnn* c, const af_hier* h, const af_sta
   if (s != AF_OK) return cfail(s, "af_cnn_features: bad context, hierarchy or buffers");
   if (v.m != kImg) return cfail(AF_ERR_ARG, "af_cnn_features: the tagger takes 16x16 patches");
   if (v.nleaves <= 0) return AF_OK;
-  if (v.fp32) {
-    DofPtrs<float> D;
-    for (int k = 0; k < 4; ++k) {
-      D.p[0][k] = static_cast<const float*>(v.dof0[k]);
-      D.p[1][k] = static_cast<const float*>(v.dof1[k]);
-    }
-    hipLaunchKernelGGL(k_features<float>, dim3(unsigned(v.nleaves)), dim3(kPix), 0, st, D, mask, v.npatch, v.pitch,
-                       v.ncomp, v.plevel, 0, c->d_norm, c->d_norm + c->nin, c->nin, x);
-  } else {
-    DofPtrs<double> D;
-    for (int k = 0; k < 4; ++k) {
-      D.p[0][k] = static_cast<const double*>(v.dof0[k]);
-      D.p[1][k] = static_cast<const double*>(v.dof1[k]);
-    }
-    hipLaunchKernelGGL(k_features<double>, dim3(unsigned(v.nleaves)), dim3(kPix), 0, st, D, mask, v.npatch, v.pitch,
-                       v.ncomp, v.plevel, 0, c->d_norm, c->d_norm + c->nin, c->nin, x);
-  }
+  if (v.fp32) launch_features<float>(v, mask, c->d_norm, c->nin, x, st);
+  else launch_features<double>(v, mask, c->d_norm, c->nin, x, st);
   CNN_HIP(hipGetLastError());
   return AF_OK;
 }

@@ -2510,8 +2510,9 @@ __device__ __forceinline__ void transfer_kind(const Bufs<T>& OLD, const HierDev&
 }
 
 template <typename T, int M, int NC>
-__global__ __launch_bounds__(kThreads) void k_transfer(Bufs<T> OLD, HierDev HO, Bufs<T> NEW, const Transfer* tr) {
-  const int p = int(blockIdx.x) >> 2;
+__global__ __launch_bounds__(kThreads) void k_transfer(Bufs<T> OLD, HierDev HO, Bufs<T> NEW, const Transfer* tr,
+                                                       int first) {
+  const int p = first + (int(blockIdx.x) >> 2);
   const Transfer X = tr[p];
   switch (blockIdx.x & 3) {
     case 0: return transfer_kind<T, M, NC, 0>(OLD, HO, NEW, X, p);
@@ -3063,17 +3064,29 @@ hipError_t launch_tag(bool fp32, const BufLaunch& b, const HierDev& H, int mode,
   return hipGetLastError();
 }
 
+// Leaves a launch of four blocks per leaf takes: a grid is limited to 2^32
+// threads (beyond it the count wraps without an error).
+constexpr int kTransferLeaves = 1 << 21;
+static_assert(4ull * kTransferLeaves * kThreads < 1ull << 32, "one launch's threads");
+
+template <typename T, int M, int NC>
+static void transfer_range(const Bufs<T>& O, const HierDev& HO, const Bufs<T>& N, const Transfer* tr, int nnew,
+                           hipStream_t st) {
+  for (int first = 0; first < nnew; first += kTransferLeaves)
+    hipLaunchKernelGGL((k_transfer<T, M, NC>), dim3(4u * unsigned(std::min(nnew - first, kTransferLeaves))),
+                       dim3(kThreads), 0, st, O, HO, N, tr, first);
+}
+
 template <typename T, int NC>
 static hipError_t transfer_t(const BufLaunch& old_b, const HierDev& HO, const BufLaunch& new_b, const Transfer* tr,
                              int nnew, hipStream_t st) {
-  const dim3 grid(4u * unsigned(nnew)), block(kThreads);
   const Bufs<T> O = make_bufs<T>(old_b), N = make_bufs<T>(new_b);
   switch (old_b.m) {
-    case 8: hipLaunchKernelGGL((k_transfer<T, 8, NC>), grid, block, 0, st, O, HO, N, tr); break;
-    case 16: hipLaunchKernelGGL((k_transfer<T, 16, NC>), grid, block, 0, st, O, HO, N, tr); break;
-    case 32: hipLaunchKernelGGL((k_transfer<T, 32, NC>), grid, block, 0, st, O, HO, N, tr); break;
-    case 64: hipLaunchKernelGGL((k_transfer<T, 64, NC>), grid, block, 0, st, O, HO, N, tr); break;
-    case 128: hipLaunchKernelGGL((k_transfer<T, 128, NC>), grid, block, 0, st, O, HO, N, tr); break;
+    case 8: transfer_range<T, 8, NC>(O, HO, N, tr, nnew, st); break;
+    case 16: transfer_range<T, 16, NC>(O, HO, N, tr, nnew, st); break;
+    case 32: transfer_range<T, 32, NC>(O, HO, N, tr, nnew, st); break;
+    case 64: transfer_range<T, 64, NC>(O, HO, N, tr, nnew, st); break;
+    case 128: transfer_range<T, 128, NC>(O, HO, N, tr, nnew, st); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
