@@ -1395,6 +1395,7 @@ __global__ __launch_bounds__(NT, (UpGeom<T, M, K, NT>::OCC)) void k_level_advanc
                                                                                    const AdvWeights<T> W) {
   constexpr int R = UpStripRows<M, K, NT>::value;
   using P = UpPlan<T, M, K, R>;
+  static_assert(K <= M, "the halo ends in the next patch (mirrored: with the first nodes of the one after it)");
   constexpr int E0 = P::E0;
   constexpr int AS0 = UpGeom<T, M, K, NT>::AS0, AS1 = UpGeom<T, M, K, NT>::AS1;  // array strides of the buffers
   constexpr typename P::Table kTab = P::table();
@@ -1453,15 +1454,25 @@ __global__ __launch_bounds__(NT, (UpGeom<T, M, K, NT>::OCC)) void k_level_advanc
           for (int kind = 0; kind < 4; ++kind) v[u][kind] = A.in[kind][off];
           continue;
         }
-        // the cell and node positions of the patch that (i, j) stands for
+        // the cell and node positions of the patch that (i, j) stands for.  At
+        // i = -K with K = M the node is entry 0 of the patch two on (entry M of
+        // the next one is a copy of it, which need not be current).
         size_t ox[2], oy[2];  // [0] cell, [1] node
 #pragma unroll
         for (int n = 0; n < 2; ++n) {
           const int ii = A.mirror_x ? M - 1 + n - i : i, jj = A.mirror_y ? M - 1 + n - j : j;
-          const int dx = ii < 0 ? -1 : (ii >= M ? 1 : 0), dy = jj < 0 ? -1 : (jj >= M ? 1 : 0);
+          int dx = ii < 0 ? -1 : (ii >= M ? 1 : 0), dy = jj < 0 ? -1 : (jj >= M ? 1 : 0);
+          if (K >= M && n) {
+            dx += ii >= 2 * M;
+            dy += jj >= 2 * M;
+          }
           int px = pix + dx, py = piy + dy;
           px = px < 0 ? px + A.nx : (px >= A.nx ? px - A.nx : px);
           py = py < 0 ? py + A.ny : (py >= A.ny ? py - A.ny : py);
+          if (K >= M && n) {  // two patches on, of a level one patch wide
+            px = px >= A.nx ? px - A.nx : px;
+            py = py >= A.ny ? py - A.ny : py;
+          }
           ox[n] = size_t(px) * plane + (ii - dx * M + kGhost);
           oy[n] = size_t(A.first + py * A.nx) * plane + size_t(jj - dy * M + kGhost) * A.pitch;
         }
