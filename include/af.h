@@ -330,10 +330,10 @@ af_status af_autotune(af_ctx* ctx, af_hier* h, af_state* bufs, int32_t level, do
  * bufs[0] and bufs[1]; *level_buf_mask is updated.  flux_reg: FP64
  * [npatch][4][m][ncomp], zero on entry (left zero on exit).
  * flags: AF_STEP_GRAPH replays a hipGraph captured on first use for this
- * (hierarchy, mask, dt0, and t0 for AF_SWIRL; at most 64 graphs are kept per
- * hierarchy, the stream is drained and the cache emptied when it is full, so
- * AF_SWIRL graphs are reused only at repeated t0); AF_STEP_GLOBAL takes one
- * step of dt0 on every level at once, without subcycling (global time
+ * (hierarchy, mask, dt0, t0 for AF_SWIRL, and the context's tile height and
+ * fused-pairs switch; at most 64 graphs are kept per hierarchy, the stream is
+ * drained and the cache emptied when it is full, so AF_SWIRL graphs are reused
+ * only at repeated t0); AF_STEP_GLOBAL takes one step of dt0 on every level at once, without subcycling (global time
  * stepping, the corollary of Sec. 4.3; dt0 must satisfy the finest level's
  * CFL): full fill, every level steps its interior, then the conservative
  * fix of every level.

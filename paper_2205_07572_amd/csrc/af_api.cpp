@@ -111,9 +111,11 @@ struct GraphKey {
   const double* reg;
   double t0;    // only for time-dependent fields (else 0)
   int32_t flags;
-  bool operator<(const GraphKey& o) const {
-    return std::tie(mask, dt0, b0, b1, reg, t0, flags) < std::tie(o.mask, o.dt0, o.b0, o.b1, o.reg, o.t0, o.flags);
-  }
+  // options of the context that shape the launches
+  bool fused_pairs;
+  int32_t ty;
+  auto tied() const { return std::tie(mask, dt0, b0, b1, reg, t0, flags, fused_pairs, ty); }
+  bool operator<(const GraphKey& o) const { return tied() < o.tied(); }
 };
 
 struct af_hier {
@@ -1468,7 +1470,7 @@ af_status af_amr_coarse_step(af_ctx* ctx, af_hier* h, af_state* bufs, uint32_t* 
     return s;
   }
   const GraphKey key{*mask, dt0, bufs[0].dof[0], bufs[1].dof[0], flux_reg, ctx->P.eq == AF_SWIRL ? t0 : 0.0,
-                     flags};
+                     flags, ctx->fused_pairs, ctx->ty};
   auto it = h->graphs.find(key);
   if (it == h->graphs.end()) {
     // a time-dependent field keys its graphs by t0 as well, so the cache is
