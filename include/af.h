@@ -128,7 +128,9 @@ int32_t af_ctx_get_tile(const af_ctx* ctx);
  * finest level F >= 2, one block takes both substeps of a pair of level F
  * (Sec. 3.2) from one staging of its halo, the first (layer-1 region) into
  * on-chip memory, the second from there, and the launches of the odd time
- * points go away.  Results are bit-identical with it off; only which of the
+ * points go away.  Not for a hierarchy whose level F touches the domain's
+ * boundary where the velocity field is not periodic there (AF_ROTATION;
+ * AF_SWIRL unless lx and ly are whole numbers).  Results are bit-identical with it off; only which of the
  * two buffers holds level F in the middle of a coarse step differs.
  * AF_ERR_ARG for a null ctx or on not 0 or 1. */
 af_status af_ctx_set_fused_pairs(af_ctx* ctx, int32_t on);

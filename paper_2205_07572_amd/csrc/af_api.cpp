@@ -136,6 +136,7 @@ struct af_hier {
   // per level: -1 not checked, 1 the level is the complete row-major patch
   // array (the level advance can run on it), 0 otherwise
   std::vector<int> nbr_ok;
+  bool finest_on_edge = false;  // a leaf of the finest level touches the domain's boundary
   HierDev dev{};
   std::map<GraphKey, hipGraphExec_t> graphs;
   // ghost-fill plan and, in the same block (built on first use), its flags per
@@ -560,6 +561,10 @@ af_status af_hier_create(af_ctx* ctx, int32_t n, const int32_t* level, const int
     h->all_faces.insert(h->all_faces.end(), h->H.faces[l].begin(), h->H.faces[l].end());
   }
   h->face_off[h->H.lmax + 1] = int(h->all_faces.size());
+  const int F = h->H.finest;
+  for (const Leaf& L : h->H.leaves)
+    if (L.level == F && (L.ix == 0 || L.iy == 0 || L.ix == h->H.npx(F) - 1 || L.iy == h->H.npy(F) - 1))
+      h->finest_on_edge = true;
   // leaves whose eight neighbours are not all leaves of their own level
   h->impure_off.assign(h->H.lmax + 2, 0);
   for (int k = 0; k < n; ++k)
@@ -1291,6 +1296,18 @@ struct Driver {
     return AF_OK;
   }
 
+  // Fused pairs keep the first substep's values of the halo for the second.  A
+  // same-level neighbour computes the same ones, unless it lies across the
+  // periodic boundary and the velocity field there is not periodic: the
+  // rotation's, and the swirl's (period 1) on a domain that is no whole number
+  // of periods long.  Such a hierarchy takes the two substeps in two launches,
+  // between which the halo is staged anew.
+  bool pairs_hold() const {
+    const af_problem& P = ctx->P;
+    const bool periodic = P.eq == AF_SWIRL ? P.lx == std::floor(P.lx) && P.ly == std::floor(P.ly) : P.eq != AF_ROTATION;
+    return periodic || !h->finest_on_edge;
+  }
+
   // the batched step addresses a DOF array with 32-bit element offsets
   bool offsets_fit() const {
     return double(bufs[0].npatch) * (ctx->P.m + 5) * bufs[0].pitch * ctx->ncomp < 2147483648.0;
@@ -1388,7 +1405,7 @@ struct Driver {
     // fused pairs: the launch of each even time point also takes the finest
     // level's second substep, so the odd time points (where only level F
     // starts a step) need no launch
-    pair_ = ctx->fused_pairs && F >= 2 && amr_pair_supported(ctx->P.m);
+    pair_ = ctx->fused_pairs && F >= 2 && amr_pair_supported(ctx->P.m) && pairs_hold();
     for (int tau = 0; tau < (1 << F); tau += pair_ ? 2 : 1) {
       // the coarsest level that starts a step at tau
       const int l0 = tau == 0 ? 0 : F - __builtin_ctz(unsigned(tau));
