@@ -282,9 +282,12 @@ void rot_params(const af_problem& P, double dx, double dy, double dt, RotParams<
     W->vy[k] = T(v / dy);
     W->sy[k] = T(s / dy);
   }
-  W->x0 = T(P.x0); W->y0 = T(P.y0); W->dx = T(dx); W->dy = T(dy);
+  W->x0 = T(P.x0); W->y0 = T(P.y0); W->hdx = T(0.5 * dx); W->hdy = T(0.5 * dy);
   W->omega = T(P.omega); W->xc = T(P.xc); W->yc = T(P.yc);
 }
+
+// a whole number of the swirl's periods
+bool whole(double l) { return l == std::floor(l); }
 
 template <typename T>
 void swirl_params(const af_problem& P, double dx, double dy, double t, double dt, SwirlParams<T>* W) {
@@ -300,12 +303,14 @@ void swirl_params(const af_problem& P, double dx, double dy, double t, double dt
     W->cos_rk[k][2] = T(std::cos(kPi * (t1 - tau)));
   }
   for (int k = 0; k < 3; ++k) W->cos_fx[k] = T(std::cos(kPi * (t + 0.5 * k * dt)));
-  W->x0 = T(P.x0); W->y0 = T(P.y0); W->dx = T(dx); W->dy = T(dy);
+  W->x0 = T(P.x0); W->y0 = T(P.y0); W->hdx = T(0.5 * dx); W->hdy = T(0.5 * dy);
   W->idx = T(1.0 / dx);
   W->idy = T(1.0 / dy);
   W->kx = T(std::sin(kPi * dx) / (kPi * dx));
   W->ky = T(std::sin(kPi * dy) / (kPi * dy));
   W->small = kPi * dt <= kSmallAngle;  // |a|, |b| <= 1
+  W->nx = whole(P.lx) ? int32_t(std::lround(P.lx / dx)) : 0;
+  W->ny = whole(P.ly) ? int32_t(std::lround(P.ly / dy)) : 0;
 }
 
 template <typename T>
@@ -1304,7 +1309,7 @@ struct Driver {
   // between which the halo is staged anew.
   bool pairs_hold() const {
     const af_problem& P = ctx->P;
-    const bool periodic = P.eq == AF_SWIRL ? P.lx == std::floor(P.lx) && P.ly == std::floor(P.ly) : P.eq != AF_ROTATION;
+    const bool periodic = P.eq == AF_SWIRL ? whole(P.lx) && whole(P.ly) : P.eq != AF_ROTATION;
     return periodic || !h->finest_on_edge;
   }
 

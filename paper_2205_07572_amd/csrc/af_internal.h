@@ -207,7 +207,7 @@ struct CFFace {
 template <typename T>
 struct RotParams {
   T vx[2], sx[2], vy[2], sy[2];  // (1 - cos omega tau) / dx, sin / dx, the same over dy
-  T x0, y0, dx, dy;   // domain origin, cell size of the level
+  T x0, y0, hdx, hdy; // domain origin, half a cell of the level
   T omega, xc, yc;    // a = -omega (y - yc), b = omega (x - xc)
 };
 
@@ -216,13 +216,14 @@ struct RotParams {
 // cell; cos(pi s) is supplied for every time the step needs.
 template <typename T>
 struct SwirlParams {
-  T x0, y0, dx, dy;  // domain origin, cell size of the level
+  T x0, y0, hdx, hdy;  // domain origin, half a cell of the level
   T kx, ky;          // sin(pi dx) / (pi dx), sin(pi dy) / (pi dy)
   T tau[2];          // dt/2, dt: the two traces back to t
   T h6[2], idx, idy; // tau / 6, 1 / dx, 1 / dy
   T cos_rk[2][3];    // cos(pi s) at the Runge-Kutta times t+tau, t+tau/2, t of each trace
   T cos_fx[3];       // cos(pi s) at t, t+dt/2, t+dt (Simpson times of the fluxes)
   int32_t small;     // pi dt (a point's largest move) is a small angle
+  int32_t nx, ny;    // cells along the domain where that is a whole number of periods, else 0
 };
 
 // Angles up to which the swirl shifts a point's sine and cosine by their

@@ -112,6 +112,24 @@ __device__ __forceinline__ int xcd_patch(int b, int n) {
   return x * q + min(x, r) + b / kXcd;
 }
 
+// Arithmetic of the equations with variable velocities.  A position is formed
+// from the index on the level, not from a patch's corner, and every
+// multiply-add is written as one, so that a value does not depend on the patch,
+// the region or the kernel that computes it: two substeps fused in one block
+// give the values of two launches bit for bit (left to the compiler, the choice
+// of which product of a sum to fuse differed between the kernels).
+__device__ __forceinline__ float fmadd(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fmadd(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
+// Coordinate of half-cell index h of a level (2 i: the low face of cell i).
+template <typename T>
+__device__ __forceinline__ T half_pos(T x0, T hdx, T h) {
+  return fmadd(h, hdx, x0);
+}
+// The swirl's: where the domain is a whole number of periods long, an index past
+// its boundary (at n; n = 0: not so) stands for its periodic image.
+__device__ __forceinline__ int wrap_index(int h, int n) { return h < 0 ? h + n : (h >= n && n > 0 ? h - n : h); }
+
 // sin and cos of pi times a coordinate
 template <typename T>
 struct SinCos {
@@ -157,9 +175,10 @@ struct StepLds<T, NCOMP, NR, NC, kLdsSwirl> {
   static constexpr bool kSeparate = true;
   D in;
   T s[2][3][NCOMP][NR - 2][NC];
-  // sin and cos of pi x and pi y at the low faces and centres of the staged
-  // columns and rows, in turn
+  // x and y, and sin and cos of pi x and pi y, at the low faces and centres of
+  // the staged columns and rows, in turn
   SinCos<T> tx[2 * NC + 1], ty[2 * NR + 1];
+  T px[2 * NC + 1], py[2 * NR + 1];
   __device__ __forceinline__ T& ts(int k, int q, int jj, int ii) { return s[0][k][q][jj][ii]; }
   __device__ __forceinline__ T& ts2(int k, int q, int jj, int ii) { return s[1][k][q][jj][ii]; }
 };
@@ -320,9 +339,11 @@ __device__ __forceinline__ void sincos_pi(float v, float* s, float* c) { sincosp
 __device__ __forceinline__ void sincos_pi(double v, double* s, double* c) { sincospi(v, s, c); }
 
 template <typename T>
-__device__ __forceinline__ void swirl_vel(const SwirlParams<T>& W, SinCos<T> x, SinCos<T> y, T cpt, T* a, T* b) {
-  *a = -cpt * W.ky * (x.s * x.s) * (T(2) * y.s * y.c);
-  *b = cpt * W.kx * (T(2) * x.s * x.c) * (y.s * y.s);
+__device__ __forceinline__ void swirl_vel(const SwirlParams<T>& W, SinCos<T> x, SinCos<T> y, T cpt, T* a, T* b,
+                                          T a0 = T(0), T b0 = T(0)) {
+#pragma clang fp contract(off)
+  *a = fmadd(-cpt * W.ky * (x.s * x.s), T(2) * y.s * y.c, a0);
+  *b = fmadd(cpt * W.kx * (T(2) * x.s * x.c), y.s * y.s, b0);
 }
 
 // sin and cos of pi (x + d) from those of pi x, for |pi d| <= kSmallAngle: the
@@ -334,27 +355,28 @@ __device__ __forceinline__ void swirl_vel(const SwirlParams<T>& W, SinCos<T> x, 
 // of the kernel's instructions: see swirl_tables for the measured gain.
 template <typename T>
 __device__ __forceinline__ SinCos<T> shifted(SinCos<T> x, T d) {
+#pragma clang fp contract(off)
   const T z = T(kPiD) * d, z2 = z * z;
   T ps, pc;
   if constexpr (sizeof(T) == 8) {
     ps = T(1.0 / 6227020800.0);
-    ps = ps * z2 - T(1.0 / 39916800.0);
-    ps = ps * z2 + T(1.0 / 362880.0);
-    ps = ps * z2 - T(1.0 / 5040.0);
+    ps = fmadd(ps, z2, T(-1.0 / 39916800.0));
+    ps = fmadd(ps, z2, T(1.0 / 362880.0));
+    ps = fmadd(ps, z2, T(-1.0 / 5040.0));
     pc = T(1.0 / 479001600.0);
-    pc = pc * z2 - T(1.0 / 3628800.0);
-    pc = pc * z2 + T(1.0 / 40320.0);
+    pc = fmadd(pc, z2, T(-1.0 / 3628800.0));
+    pc = fmadd(pc, z2, T(1.0 / 40320.0));
   } else {
     ps = T(-1.0 / 5040.0);
     pc = T(1.0 / 40320.0);
   }
-  ps = ps * z2 + T(1.0 / 120.0);
-  ps = ps * z2 - T(1.0 / 6.0);
-  pc = pc * z2 - T(1.0 / 720.0);
-  pc = pc * z2 + T(1.0 / 24.0);
-  pc = pc * z2 - T(0.5);
-  const T sd = z + z * (z2 * ps), cd1 = z2 * pc;  // sin z, cos z - 1
-  return {x.s + (x.s * cd1 + x.c * sd), x.c + (x.c * cd1 - x.s * sd)};
+  ps = fmadd(ps, z2, T(1.0 / 120.0));
+  ps = fmadd(ps, z2, T(-1.0 / 6.0));
+  pc = fmadd(pc, z2, T(-1.0 / 720.0));
+  pc = fmadd(pc, z2, T(1.0 / 24.0));
+  pc = fmadd(pc, z2, T(-0.5));
+  const T sd = fmadd(z, z2 * ps, z), cd1 = z2 * pc;  // sin z, cos z - 1
+  return {x.s + fmadd(x.s, cd1, x.c * sd), x.c + fmadd(x.c, cd1, -(x.s * sd))};
 }
 
 // Source cell of a node's foot and the reference coordinate in it, in one
@@ -372,9 +394,10 @@ __device__ __forceinline__ SinCos<T> shifted(SinCos<T> x, T d) {
 // 1024 x 1024 cells in FP64 201 and 156.
 template <typename T, bool FACE>
 __device__ __forceinline__ int foot(T disp, T* ref) {
+#pragma clang fp contract(off)
   if constexpr (FACE) {
     const bool below = disp > T(0);
-    *ref = (below ? T(1) : T(-1)) - T(2) * disp;
+    *ref = fmadd(T(-2), disp, below ? T(1) : T(-1));
     return below ? -1 : 0;
   } else {
     const int o = (disp < T(-0.5) ? 1 : 0) - (disp > T(0.5) ? 1 : 0);
@@ -388,16 +411,18 @@ __device__ __forceinline__ int foot(T disp, T* ref) {
 // 9 nodal values, centre value from "average = Simpson sum".
 template <typename T, typename D>
 __device__ __forceinline__ T rot_eval(const D& s, int r, int c, T xi, T eta) {
+#pragma clang fp contract(off)
   const T hx = T(0.5) * xi, hy = T(0.5) * eta;
-  const T lx[3] = {hx * xi - hx, T(1) - xi * xi, hx * xi + hx};
-  const T ly[3] = {hy * eta - hy, T(1) - eta * eta, hy * eta + hy};
+  const T lx[3] = {fmadd(hx, xi, -hx), fmadd(-xi, xi, T(1)), fmadd(hx, xi, hx)};
+  const T ly[3] = {fmadd(hy, eta, -hy), fmadd(-eta, eta, T(1)), fmadd(hy, eta, hy)};
   const T ll = s(1, 0, r, c), rl = s(1, 0, r, c + 1), lu = s(1, 0, r + 1, c), ru = s(1, 0, r + 1, c + 1);
   const T xl = s(2, 0, r, c), xr = s(2, 0, r, c + 1), yb = s(3, 0, r, c), yt = s(3, 0, r + 1, c);
-  const T mid = T(2.25) * s(0, 0, r, c) - T(0.0625) * ((ll + rl) + (lu + ru)) - T(0.25) * ((xl + xr) + (yb + yt));
-  const T b = lx[0] * ll + lx[1] * yb + lx[2] * rl;
-  const T m = lx[0] * xl + lx[1] * mid + lx[2] * xr;
-  const T t = lx[0] * lu + lx[1] * yt + lx[2] * ru;
-  return ly[0] * b + ly[1] * m + ly[2] * t;
+  const T mid = fmadd(T(-0.25), (xl + xr) + (yb + yt),
+                      fmadd(T(-0.0625), (ll + rl) + (lu + ru), T(2.25) * s(0, 0, r, c)));
+  const T b = fmadd(lx[2], rl, fmadd(lx[1], yb, lx[0] * ll));
+  const T m = fmadd(lx[2], xr, fmadd(lx[1], mid, lx[0] * xl));
+  const T t = fmadd(lx[2], ru, fmadd(lx[1], yt, lx[0] * lu));
+  return fmadd(ly[2], t, fmadd(ly[1], m, ly[0] * b));
 }
 
 // The compute part of a patch step on a staged block (shared by the one-level
@@ -425,11 +450,12 @@ struct StepIO {
 // onto the staged nodes, so the node values go in after the update, which
 // reads the sums from where they will be stored.  rofs: staged row of cell
 // row j is j - jlo + 1 + rofs (the pair's second substep reads the first's
-// rows).
+// rows).  gx0, gy0: index of the patch's cell (0, 0) on its level (rotation,
+// swirl).
 template <typename T, int EQ, int M, int TY, bool TO_LDS = false, int NT = kThreads, bool BULK = false, int USE = 0,
           typename L_t>
 __device__ __forceinline__ void step_compute(L_t& L, const StepIO<T>& A, const typename WSel<T, EQ>::type& W,
-                                             int jlo, int jhi, T px0, T py0, int rofs = 0) {
+                                             int jlo, int jhi, int gx0, int gy0, int rofs = 0) {
   constexpr int NCOMP = EQ == 1 ? 3 : 1;
   constexpr int NC = M + 5;
   const int patch = A.patch;
@@ -505,18 +531,25 @@ __device__ __forceinline__ void step_compute(L_t& L, const StepIO<T>& A, const t
       // -omega tau about (xc, yc); swirl (Sec. 4.3): one classical Runge-Kutta
       // step back along the characteristic.  q^n there from its cell's
       // reconstruction.
+      [[maybe_unused]] const T hx = T(2 * (gx0 + i)), hy = T(2 * (gy0 + j));  // rotation
       auto node = [&](auto kc) {
+#pragma clang fp contract(off)
         constexpr int kind = decltype(kc)::value;
         if (kind == NK_XEDGE && !has_x) return;
         if (kind == NK_YEDGE && !has_y) return;
         constexpr bool FX = kind != NK_YEDGE, FY = kind != NK_XEDGE;  // on the cell's low x-face, y-face
-        const T x = px0 + (T(i) + (FX ? T(0) : T(0.5))) * W.dx, y = py0 + (T(j) + (FY ? T(0) : T(0.5))) * W.dy;
+        T x, y;
         [[maybe_unused]] SinCos<T> tx, ty;
         [[maybe_unused]] T ax = T(0), by = T(0);  // swirl: the velocity at the node over cos(pi t)
         if constexpr (EQ == 3) {
-          tx = L.tx[2 * c + (FX ? 0 : 1)];
-          ty = L.ty[2 * r + (FY ? 0 : 1)];
+          x = L.px[2 * c + !FX];
+          y = L.py[2 * r + !FY];
+          tx = L.tx[2 * c + !FX];
+          ty = L.ty[2 * r + !FY];
           swirl_vel(W, tx, ty, T(1), &ax, &by);
+        } else {
+          x = half_pos(W.x0, W.hdx, FX ? hx : hx + T(1));
+          y = half_pos(W.y0, W.hdy, FY ? hy : hy + T(1));
         }
         T val[2];
 #pragma unroll
@@ -524,13 +557,14 @@ __device__ __forceinline__ void step_compute(L_t& L, const StepIO<T>& A, const t
           T dispx, dispy;  // node - foot in cells
           if constexpr (EQ == 2) {
             const T rx = x - W.xc, ry = y - W.yc;
-            dispx = rx * W.vx[t] - ry * W.sx[t];
-            dispy = ry * W.vy[t] + rx * W.sy[t];
+            dispx = fmadd(rx, W.vx[t], -(ry * W.sx[t]));
+            dispy = fmadd(ry, W.vy[t], rx * W.sy[t]);
           } else {
             const T h = W.tau[t], hh = T(0.5) * h;
             const T a1 = W.cos_rk[t][0] * ax, b1 = W.cos_rk[t][0] * by;
-            T a2, b2, a3, b3, a4, b4;
-            auto at = [&](T dx, T dy, T cpt, T* a, T* b) {
+            T a2, b2, a3, b3, a14, b14;
+            // a0, b0 and the velocity at the node moved by (-dx, -dy)
+            auto at = [&](T dx, T dy, T cpt, T a0, T b0, T* a, T* b) {
               SinCos<T> u, v;
               if (W.small) {  // uniform
                 u = shifted(tx, -dx);
@@ -539,17 +573,17 @@ __device__ __forceinline__ void step_compute(L_t& L, const StepIO<T>& A, const t
                 sincos_pi(x - dx, &u.s, &u.c);
                 sincos_pi(y - dy, &v.s, &v.c);
               }
-              swirl_vel(W, u, v, cpt, a, b);
+              swirl_vel(W, u, v, cpt, a, b, a0, b0);
             };
-            at(hh * a1, hh * b1, W.cos_rk[t][1], &a2, &b2);
-            at(hh * a2, hh * b2, W.cos_rk[t][1], &a3, &b3);
-            at(h * a3, h * b3, W.cos_rk[t][2], &a4, &b4);
-            const T sa = (a1 + a4) + T(2) * (a2 + a3), sb = (b1 + b4) + T(2) * (b2 + b3);
+            at(hh * a1, hh * b1, W.cos_rk[t][1], T(0), T(0), &a2, &b2);
+            at(hh * a2, hh * b2, W.cos_rk[t][1], T(0), T(0), &a3, &b3);
+            at(h * a3, h * b3, W.cos_rk[t][2], a1, b1, &a14, &b14);
+            const T sa = fmadd(T(2), a2 + a3, a14), sb = fmadd(T(2), b2 + b3, b14);
             if constexpr (sizeof(T) == 8) {
               // the foot is a position, rounded as one: what position
               // arithmetic gives, to the last digits
-              dispx = (x - (x - W.h6[t] * sa)) * W.idx;
-              dispy = (y - (y - W.h6[t] * sb)) * W.idy;
+              dispx = (x - fmadd(-W.h6[t], sa, x)) * W.idx;
+              dispy = (y - fmadd(-W.h6[t], sb, y)) * W.idy;
             } else {
               dispx = W.h6[t] * W.idx * sa;
               dispy = W.h6[t] * W.idy * sb;
@@ -577,6 +611,7 @@ __device__ __forceinline__ void step_compute(L_t& L, const StepIO<T>& A, const t
       // node.  The time sum holds the fluxes q^2/2 (Simpson in time).
       auto av = [&](int rr, int cc) { return L.in(0, 0, rr, cc); };
       auto node = [&](auto kc) {
+#pragma clang fp contract(off)
         constexpr int kind = decltype(kc)::value;
         if (kind == NK_XEDGE && !has_x) return;
         if (kind == NK_YEDGE && !has_y) return;
@@ -602,7 +637,8 @@ __device__ __forceinline__ void step_compute(L_t& L, const StepIO<T>& A, const t
           val[t] = Q;
         }
         const T cur = L.in(kind + 1, 0, r, c);
-        tsv[it][kind][0] = (T(0.5) * cur * cur + T(2) * val[0] * val[0]) + T(0.5) * val[1] * val[1];
+        tsv[it][kind][0] =
+            fmadd(T(0.5) * val[1], val[1], fmadd(T(2) * val[0], val[0], T(0.5) * cur * cur));
         emit(it, kind, 0, wrow, obase, val[1]);
       };
       node(std::integral_constant<int, NK_CORNER>());
@@ -694,6 +730,7 @@ __device__ __forceinline__ void step_compute(L_t& L, const StepIO<T>& A, const t
       fL[0] = A.a * FL[0] * inv36; fR[0] = A.a * FR[0] * inv36;
       gB[0] = A.b * GB[0] * inv36; gT[0] = A.b * GT[0] * inv36;
     } else if constexpr (EQ == 3) {
+#pragma clang fp contract(off)
       // swirl (eq. swirlF, swirlG): the face-midpoint velocity at t, t+dt/2,
       // t+dt times the Simpson sum of the three nodes at that time
       const int rr = jj + 1 + rofs, cc = ii + coff;  // staged position of cell (i, j)
@@ -727,29 +764,33 @@ __device__ __forceinline__ void step_compute(L_t& L, const StepIO<T>& A, const t
       const T ST[3] = {face_sum(Q0(1, 0, rr + 1, cc), Q0(3, 0, rr + 1, cc), Q0(1, 0, rr + 1, cc + 1)),
                        face_sum(Qh(NK_CORNER, 0, jj + 1, ii), Qh(NK_YEDGE, 0, jj + 1, ii), Qh(NK_CORNER, 0, jj + 1, ii + 1)),
                        face_sum(Qf(NK_CORNER, 0, jj + 1, ii), Qf(NK_YEDGE, 0, jj + 1, ii), Qf(NK_CORNER, 0, jj + 1, ii + 1))};
-      fL[0] = (aL[0] * SL[0] + T(4) * aL[1] * SL[1] + aL[2] * SL[2]) * inv36;
-      fR[0] = (aR[0] * SR[0] + T(4) * aR[1] * SR[1] + aR[2] * SR[2]) * inv36;
-      gB[0] = (bB[0] * SB[0] + T(4) * bB[1] * SB[1] + bB[2] * SB[2]) * inv36;
-      gT[0] = (bT[0] * ST[0] + T(4) * bT[1] * ST[1] + bT[2] * ST[2]) * inv36;
+      fL[0] = fmadd(aL[2], SL[2], fmadd(T(4) * aL[1], SL[1], aL[0] * SL[0])) * inv36;
+      fR[0] = fmadd(aR[2], SR[2], fmadd(T(4) * aR[1], SR[1], aR[0] * SR[0])) * inv36;
+      gB[0] = fmadd(bB[2], SB[2], fmadd(T(4) * bB[1], SB[1], bB[0] * SB[0])) * inv36;
+      gT[0] = fmadd(bT[2], ST[2], fmadd(T(4) * bT[1], ST[1], bT[0] * ST[0])) * inv36;
     } else if constexpr (EQ == 4) {
+#pragma clang fp contract(off)
       // Burgers: the time sums already hold f = g = q^2/2
       fL[0] = FL[0] * inv36; fR[0] = FR[0] * inv36;
       gB[0] = GB[0] * inv36; gT[0] = GT[0] * inv36;
     } else if constexpr (EQ == 2) {
+#pragma clang fp contract(off)
       // rotation: f = a(node) q with a = -omega (y - yc) on x-faces (a depends
       // on y only) and g = b(node) q with b = omega (x - xc) on y-faces
-      const T a0 = -W.omega * (py0 + T(j) * W.dy - W.yc);
-      const T a1 = -W.omega * (py0 + (T(j) + T(0.5)) * W.dy - W.yc);
-      const T a2 = -W.omega * (py0 + T(j + 1) * W.dy - W.yc);
-      const T b0 = W.omega * (px0 + T(i) * W.dx - W.xc);
-      const T b1 = W.omega * (px0 + (T(i) + T(0.5)) * W.dx - W.xc);
-      const T b2 = W.omega * (px0 + T(i + 1) * W.dx - W.xc);
-      fL[0] = (a0 * ts(NK_CORNER, 0, jj, ii) + T(4) * a1 * ts(NK_XEDGE, 0, jj, ii) + a2 * ts(NK_CORNER, 0, jj + 1, ii)) * inv36;
-      fR[0] = (a0 * ts(NK_CORNER, 0, jj, ii + 1) + T(4) * a1 * ts(NK_XEDGE, 0, jj, ii + 1) +
-               a2 * ts(NK_CORNER, 0, jj + 1, ii + 1)) * inv36;
-      gB[0] = (b0 * ts(NK_CORNER, 0, jj, ii) + T(4) * b1 * ts(NK_YEDGE, 0, jj, ii) + b2 * ts(NK_CORNER, 0, jj, ii + 1)) * inv36;
-      gT[0] = (b0 * ts(NK_CORNER, 0, jj + 1, ii) + T(4) * b1 * ts(NK_YEDGE, 0, jj + 1, ii) +
-               b2 * ts(NK_CORNER, 0, jj + 1, ii + 1)) * inv36;
+      T a[3], b[3];
+      const T hx = T(2 * (gx0 + i)), hy = T(2 * (gy0 + j));
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        a[k] = -W.omega * (half_pos(W.y0, W.hdy, hy + T(k)) - W.yc);
+        b[k] = W.omega * (half_pos(W.x0, W.hdx, hx + T(k)) - W.xc);
+      }
+      auto simpson = [&](const T(&v)[3], T lo, T mid, T hi) {
+        return fmadd(v[2], hi, fmadd(T(4) * v[1], mid, v[0] * lo)) * inv36;
+      };
+      fL[0] = simpson(a, ts(NK_CORNER, 0, jj, ii), ts(NK_XEDGE, 0, jj, ii), ts(NK_CORNER, 0, jj + 1, ii));
+      fR[0] = simpson(a, ts(NK_CORNER, 0, jj, ii + 1), ts(NK_XEDGE, 0, jj, ii + 1), ts(NK_CORNER, 0, jj + 1, ii + 1));
+      gB[0] = simpson(b, ts(NK_CORNER, 0, jj, ii), ts(NK_YEDGE, 0, jj, ii), ts(NK_CORNER, 0, jj, ii + 1));
+      gT[0] = simpson(b, ts(NK_CORNER, 0, jj + 1, ii), ts(NK_YEDGE, 0, jj + 1, ii), ts(NK_CORNER, 0, jj + 1, ii + 1));
     } else {
       fL[0] = A.c * FL[1] * inv36; fL[1] = A.c * FL[0] * inv36; fL[2] = T(0);
       fR[0] = A.c * FR[1] * inv36; fR[1] = A.c * FR[0] * inv36; fR[2] = T(0);
@@ -759,7 +800,13 @@ __device__ __forceinline__ void step_compute(L_t& L, const StepIO<T>& A, const t
 #pragma unroll
     for (int q = 0; q < NCOMP; ++q) {
       const T Q = L.in(0, q, jj + 1 + rofs, ii + coff);
-      const T Qn = Q - A.dtdx * (fR[q] - fL[q]) - A.dtdy * (gT[q] - gB[q]);
+      T Qn;
+      if constexpr (EQ >= 2) {
+#pragma clang fp contract(off)
+        Qn = fmadd(-A.dtdy, gT[q] - gB[q], fmadd(-A.dtdx, fR[q] - fL[q], Q));
+      } else {
+        Qn = Q - A.dtdx * (fR[q] - fL[q]) - A.dtdy * (gT[q] - gB[q]);
+      }
       if constexpr (TO_LDS) {
         L.in(0, q, jj + 1 + rofs, ii + coff) = Qn;  // read only by this thread
       } else {
@@ -808,17 +855,16 @@ __device__ __forceinline__ void step_compute(L_t& L, const StepIO<T>& A, const t
 // cells in 32 x 32-cell patches fell from 95 to 53 us in FP32, from 152 to 88
 // in FP64.
 template <typename T, int M, int NR, int NT, typename L_t>
-__device__ __forceinline__ void swirl_tables(L_t& L, const SwirlParams<T>& W, T px0, T py0, int j0) {
+__device__ __forceinline__ void swirl_tables(L_t& L, const SwirlParams<T>& W, int gx0, int gy0, int j0) {
   constexpr int NX = 2 * (M + 5) + 1, NY = 2 * NR + 1;
   for (int e = threadIdx.x; e < NX + NY; e += NT) {
+    const bool is_x = e < NX;
+    const int h = is_x ? wrap_index(2 * (gx0 - kGhost) + e, 2 * W.nx) : wrap_index(2 * (gy0 + j0) + e - NX, 2 * W.ny);
+    const T x = half_pos(is_x ? W.x0 : W.y0, is_x ? W.hdx : W.hdy, T(h));
     SinCos<T> v;
-    if (e < NX) {
-      sincos_pi(px0 + (T(0.5) * T(e) - T(kGhost)) * W.dx, &v.s, &v.c);
-      L.tx[e] = v;
-    } else {
-      sincos_pi(py0 + (T(0.5) * T(e - NX) + T(j0)) * W.dy, &v.s, &v.c);
-      L.ty[e - NX] = v;
-    }
+    sincos_pi(x, &v.s, &v.c);
+    (is_x ? L.px[e] : L.py[e - NX]) = x;
+    (is_x ? L.tx[e] : L.ty[e - NX]) = v;
   }
 }
 
@@ -880,13 +926,13 @@ __global__ __launch_bounds__(kThreads) void k_patch_step(
         [&](int rr, int x) { return size_t(min(jlo - 1 + rr, M + 2) + kGhost) * A.pitch + x; },
         [&](int p, int r, int x) { return L.in.pos(p / NCOMP, p % NCOMP, r, x); });
   }
-  // rotation, swirl: lower-left corner of the patch's cell (0,0)
-  T px0 = T(0), py0 = T(0);
+  // rotation, swirl: index of the patch's cell (0,0) on its level
+  int gx0 = 0, gy0 = 0;
   if constexpr (EQ == 2 || EQ == 3) {
-    px0 = W.x0 + T(A.leaf_xy[2 * patch] * M) * W.dx;
-    py0 = W.y0 + T(A.leaf_xy[2 * patch + 1] * M) * W.dy;
+    gx0 = A.leaf_xy[2 * patch] * M;
+    gy0 = A.leaf_xy[2 * patch + 1] * M;
   }
-  if constexpr (EQ == 3) swirl_tables<T, M, NR, kThreads>(L, W, px0, py0, jlo - 1);
+  if constexpr (EQ == 3) swirl_tables<T, M, NR, kThreads>(L, W, gx0, gy0, jlo - 1);
   __syncthreads();
   StepIO<T> io;
 #pragma unroll
@@ -904,7 +950,7 @@ __global__ __launch_bounds__(kThreads) void k_patch_step(
   io.len_dt_y = A.len_dt_y;
   io.reg = A.side_mask ? A.reg : nullptr;
   io.smask = (A.reg && A.side_mask) ? A.side_mask[patch] : 0u;
-  step_compute<T, EQ, M, TY>(L, io, W, jlo, jhi, px0, py0);
+  step_compute<T, EQ, M, TY>(L, io, W, jlo, jhi, gx0, gy0);
 }
 
 // ---------------------------------------------------------------------------
@@ -994,11 +1040,11 @@ __global__ __launch_bounds__(NT) void k_level_advance(
   io.smask = 0u;
   if constexpr (K == 2) {
     io.region = 1;
-    step_compute<T, 1, M, TY, true, NT>(L, io, W, -1, M + 1, T(0), T(0));
+    step_compute<T, 1, M, TY, true, NT>(L, io, W, -1, M + 1, 0, 0);
     __syncthreads();
   }
   io.region = 0;
-  step_compute<T, 1, M, TY, false, NT>(L, io, W, 0, M, T(0), T(0), -jlo);
+  step_compute<T, 1, M, TY, false, NT>(L, io, W, 0, M, 0, 0, -jlo);
 }
 
 // ---------------------------------------------------------------------------
@@ -2178,13 +2224,13 @@ __global__ __launch_bounds__((amr_threads<M, PAIR>()), (amr_waves<T, EQ, M, PAIR
     }
   }
   const auto& W = amr_weights<T, EQ, PAIR>(wdev, P, k, false);
-  // rotation, swirl: lower-left corner of the patch's cell (0,0)
-  T px0 = T(0), py0 = T(0);
+  // rotation, swirl: index of the patch's cell (0,0) on its level
+  int gx0 = 0, gy0 = 0;
   if constexpr (EQ == 2 || EQ == 3) {
-    px0 = W.x0 + T(A.leaf_xy[2 * patch] * M) * W.dx;
-    py0 = W.y0 + T(A.leaf_xy[2 * patch + 1] * M) * W.dy;
+    gx0 = A.leaf_xy[2 * patch] * M;
+    gy0 = A.leaf_xy[2 * patch + 1] * M;
   }
-  if constexpr (EQ == 3) swirl_tables<T, M, NR, NT>(L, W, px0, py0, jlo - 1);
+  if constexpr (EQ == 3) swirl_tables<T, M, NR, NT>(L, W, gx0, gy0, jlo - 1);
   __syncthreads();
 
   StepIO<T> io;
@@ -2221,18 +2267,18 @@ __global__ __launch_bounds__((amr_threads<M, PAIR>()), (amr_waves<T, EQ, M, PAIR
     if (region == 1) {
       io.region = 1;
       if (!pair) {
-        step_compute<T, EQ, M, TY, false, NT, BULK>(L, io, W, -1, M + 1, px0, py0);
+        step_compute<T, EQ, M, TY, false, NT, BULK>(L, io, W, -1, M + 1, gx0, gy0);
         return;
       }
-      step_compute<T, EQ, M, TY, true, NT, BULK>(L, io, W, -1, M + 1, px0, py0);
+      step_compute<T, EQ, M, TY, true, NT, BULK>(L, io, W, -1, M + 1, gx0, gy0);
       __syncthreads();
     }
     io.region = 0;
-    step_compute<T, EQ, M, TY, false, NT, BULK>(L, io, amr_weights<T, EQ, PAIR>(wdev, P, k, region == 1), 0, M, px0, py0, 1);
+    step_compute<T, EQ, M, TY, false, NT, BULK>(L, io, amr_weights<T, EQ, PAIR>(wdev, P, k, region == 1), 0, M, gx0, gy0, 1);
   } else {
     // (a copy of its own: shared with k_patch_step it was compiled to 177
     // registers in FP64 and lost a wave)
-    step_compute<T, EQ, M, TY, false, NT, BULK, 1>(L, io, W, jlo, jhi, px0, py0);
+    step_compute<T, EQ, M, TY, false, NT, BULK, 1>(L, io, W, jlo, jhi, gx0, gy0);
   }
 }
 

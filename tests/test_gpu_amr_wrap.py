@@ -1,7 +1,7 @@
 """Fused pairs of the batched coarse step where the finest level lies inside
 the domain and where it straddles the periodic boundary, for the equations
-with variable velocities, and the step without them: both follow the recursion
-of Sec. 3.2.  The rotation's field is not periodic,
+with variable velocities: bit for bit the step without fused pairs, which in
+turn follows the recursion of Sec. 3.2.  The rotation's field is not periodic,
 nor is the swirl's on a domain that is no whole number of periods long, so
 across the boundary a patch and its neighbour evaluate a shared position from
 different coordinates."""
@@ -24,8 +24,11 @@ def _shift(leaves):
                                 for l, i, j in leaves])
 
 
+# the shifted domains have cell boundaries that are no short binary fractions
 EQS = {"rotation": dict(eq=af.ROTATION, x0=-1.0, y0=-1.0, lx=2.0, ly=2.0, omega=1.0),
-       "swirl": dict(eq=af.SWIRL), "swirl_1.5": dict(eq=af.SWIRL, x0=0.1, lx=1.5, ly=1.5),
+       "rotation_shifted": dict(eq=af.ROTATION, x0=-0.9, y0=-1.1, lx=1.9, ly=1.9, omega=1.0),
+       "swirl": dict(eq=af.SWIRL), "swirl_shifted": dict(eq=af.SWIRL, x0=0.1, y0=0.3),
+       "swirl_1.5": dict(eq=af.SWIRL, x0=0.1, lx=1.5, ly=1.5),
        "burgers": dict(eq=af.BURGERS, qmax=1.0)}
 
 
@@ -41,7 +44,7 @@ def test_fused_pairs(eq, where, m, prec):
     P = af.Problem(prec=prec, m=m, n0x=N0, n0y=N0, lmax=2, **EQS[eq])
     rng = np.random.default_rng(m)
     blocks = [{k: rng.uniform(0.2, 0.6, (1, m + 5, m + 5)) for k in KINDS} for _ in leaves]
-    t0, dt0 = 0.2, 0.4 * P.dx(0) / (1.5 if eq == "rotation" else 1.0)
+    t0, dt0 = 0.2, 0.4 * P.dx(0) / (1.5 if P.eq == af.ROTATION else 1.0)
     closed = closed_masks(m)
     out = {}
     for name in ("recursion", "unfused", "fused"):
@@ -70,3 +73,4 @@ def test_fused_pairs(eq, where, m, prec):
     eps = 2.0 ** -53 * 16 * m * N0 if prec == af.FP64 else 2.0 ** -24 * 4 * 4
     for name in ("unfused", "fused"):
         assert diff(name, "recursion") <= 4 * 8 * 3 * eps, name
+    assert diff("fused", "unfused") == 0.0
