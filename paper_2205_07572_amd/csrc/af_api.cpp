@@ -190,6 +190,16 @@ af_status check_state(const af_ctx* c, const af_state* s, int need_patches, cons
   return AF_OK;
 }
 
+// Whether the plane of a patch is below 4 GiB, as the kernels that store with
+// 32-bit offsets need it: the step of a complete level from its neighbours'
+// interiors, the acoustic level advance and the batched step (whose arrays,
+// below 2^31 elements and, with two levels, of four patches at least, hold no
+// wider plane).  Wider ones take ghost fills and patch steps, which address with
+// 64 bits.
+bool narrow_planes(const af_ctx* c, const af_state& s) {
+  return double(c->P.m + 5) * s.pitch * double(c->elem()) < 4294967296.0;
+}
+
 af_status check_cfl(const af_ctx* c, int level, double dt) {
   if (!(dt >= 0.0) || !std::isfinite(dt)) return fail(AF_ERR_ARG, "dt must be finite and >= 0");
   const double dx = c->dx(level), dy = c->dy(level);
@@ -1080,6 +1090,17 @@ af_status af_level_advance(af_ctx* ctx, af_hier* h, af_state* bufs, uint32_t* ma
   else
     level_shape(ctx, up, count, &K, &NT);
   if (K == 0) return fail(AF_ERR_ARG, "no level-advance kernel for this (precision, equation, m)");
+  if (ctx->P.eq == AF_ACOUSTICS && !narrow_planes(ctx, bufs[0])) {
+    for (int k = 0; k < nsteps; ++k) {
+      const int cur = (*mask >> level) & 1;
+      if ((s = af_ghost_fill(ctx, h, bufs, *mask, level, level, stream)) != AF_OK ||
+          (s = af_patch_step(ctx, &bufs[cur], &bufs[cur ^ 1], first, count, level, dt, 0.0, AF_REGION_INTERIOR,
+                             nullptr, nullptr, nullptr, stream)) != AF_OK)
+        return s;
+      *mask ^= (1u << level);
+    }
+    return AF_OK;
+  }
   int ks[32], nts[32];
   const int n = level_advance_shapes(ctx->fp32(), ctx->P.eq, ctx->P.m, ks, nts, 32, up);
   int done = 0;
@@ -1431,8 +1452,10 @@ struct Driver {
 
   af_status coarse_step(double t0, double dt0) {
     // constant coefficients: always (a larger array is an error); variable
-    // velocities: the recursion takes what the 32-bit offsets do not reach
-    if (!gnx && (ctx->P.eq == AF_ADVECTION || ctx->P.eq == AF_ACOUSTICS || offsets_fit()))
+    // velocities: the recursion takes what the 32-bit offsets do not reach.
+    // It also takes a single level of too wide planes.
+    const bool wide_level = h->H.finest == 0 && !narrow_planes(ctx, bufs[0]);
+    if (!gnx && !wide_level && (ctx->P.eq == AF_ADVECTION || ctx->P.eq == AF_ACOUSTICS || offsets_fit()))
       return coarse_step_batched(t0, dt0);
     if (!gnx) {
       af_status s = af_ghost_fill(ctx, h, bufs, mask, 0, 0, st);
@@ -1460,7 +1483,7 @@ struct Driver {
     // a hierarchy that is one complete level steps without a fill
     if (h->H.finest == 0) {
       int nx, ny;
-      if (level_grid(h, 0, &nx, &ny) == AF_OK) {
+      if (narrow_planes(ctx, bufs[0]) && level_grid(h, 0, &nx, &ny) == AF_OK) {
         gnx = nx;
         gny = ny;
       }

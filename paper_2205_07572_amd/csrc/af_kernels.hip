@@ -452,8 +452,12 @@ struct StepIO {
 // row j is j - jlo + 1 + rofs (the pair's second substep reads the first's
 // rows).  gx0, gy0: index of the patch's cell (0, 0) on its level (rotation,
 // swirl).
-template <typename T, int EQ, int M, int TY, bool TO_LDS = false, int NT = kThreads, bool BULK = false, int USE = 0,
-          typename L_t>
+// O: type of the byte offset of an entry in its plane.  32 bits are a vector
+// register and an addition less per store, and hold a plane below 4 GiB (the
+// kernels that take them get no other, see narrow_planes on the host); 64 bits
+// hold every plane.
+template <typename T, int EQ, int M, int TY, typename O, bool TO_LDS = false, int NT = kThreads, bool BULK = false,
+          int USE = 0, typename L_t>
 __device__ __forceinline__ void step_compute(L_t& L, const StepIO<T>& A, const typename WSel<T, EQ>::type& W,
                                              int jlo, int jhi, int gx0, int gy0, int rofs = 0) {
   constexpr int NCOMP = EQ == 1 ? 3 : 1;
@@ -489,7 +493,7 @@ __device__ __forceinline__ void step_compute(L_t& L, const StepIO<T>& A, const t
   T nv[TO_LDS ? MAXIT : 1][3][NCOMP];  // TO_LDS: the new node values, stored after the barrier
   // a new node value: to HBM (if `keep`, the rows and columns this tile
   // owns), or held for LDS
-  auto emit = [&](int it, int kind, int q, bool keep, uint32_t o, T v) {
+  auto emit = [&](int it, int kind, int q, bool keep, O o, T v) {
     if constexpr (TO_LDS) {
       nv[it][kind][q] = v;
     } else {
@@ -497,7 +501,7 @@ __device__ __forceinline__ void step_compute(L_t& L, const StepIO<T>& A, const t
     }
   };
   // byte offset of entry (i, j) in a plane
-  auto entry = [&](int i, int j) { return uint32_t((j + kGhost) * A.pitch + (i + kGhost)) * uint32_t(sizeof(T)); };
+  auto entry = [&](int i, int j) { return (O(j + kGhost) * O(A.pitch) + O(i + kGhost)) * O(sizeof(T)); };
   Walk2 w(threadIdx.x, NT, WN);
 #pragma unroll
   for (int it = 0; it < MAXIT; ++it, w.next()) {
@@ -509,7 +513,7 @@ __device__ __forceinline__ void step_compute(L_t& L, const StepIO<T>& A, const t
     const bool wrow = (jj < nrow) || last_tile;
     const bool has_x = jj < nrow;      // xedge (i,j) belongs to rows [jlo, jhi)
     const bool has_y = ii < span;      // yedge (i,j) belongs to cols [ilo, ihi)
-    const uint32_t obase = entry(i, j);
+    const O obase = entry(i, j);
     if constexpr (EQ == 0) {
 #pragma unroll
       for (int kind = 0; kind < 3; ++kind) {
@@ -666,7 +670,7 @@ __device__ __forceinline__ void step_compute(L_t& L, const StepIO<T>& A, const t
         if (K == NK_XEDGE && jj >= nrow) continue;  // x-edges of rows [jlo, jhi)
         if (K == NK_YEDGE && ii >= span) continue;  // y-edges of cols [ilo, ihi)
         const int r = jj + 1 + rofs, c = ii + coff;
-        const uint32_t obase = entry(ilo + ii, jlo + jj);
+        const O obase = entry(ilo + ii, jlo + jj);
         const bool wst = K == NK_XEDGE || jj < nrow || last_tile;
         T acc[2][3] = {{T(0), T(0), T(0)}, {T(0), T(0), T(0)}};
         if constexpr (sizeof(T) == 8) {
@@ -712,7 +716,7 @@ __device__ __forceinline__ void step_compute(L_t& L, const StepIO<T>& A, const t
   for (Walk2 w(threadIdx.x, NT, span); w.y < nrow; w.next()) {
     const int ii = w.x, jj = w.y;
     const int i = ilo + ii, j = jlo + jj;
-    const uint32_t obase = entry(i, j);
+    const O obase = entry(i, j);
     T FL[NCOMP], FR[NCOMP], GB[NCOMP], GT[NCOMP];
 #pragma unroll
     for (int q = 0; q < NCOMP; ++q) {
@@ -950,7 +954,7 @@ __global__ __launch_bounds__(kThreads) void k_patch_step(
   io.len_dt_y = A.len_dt_y;
   io.reg = A.side_mask ? A.reg : nullptr;
   io.smask = (A.reg && A.side_mask) ? A.side_mask[patch] : 0u;
-  step_compute<T, EQ, M, TY>(L, io, W, jlo, jhi, gx0, gy0);
+  step_compute<T, EQ, M, TY, std::conditional_t<GN, uint32_t, size_t>>(L, io, W, jlo, jhi, gx0, gy0);
 }
 
 // ---------------------------------------------------------------------------
@@ -1040,11 +1044,11 @@ __global__ __launch_bounds__(NT) void k_level_advance(
   io.smask = 0u;
   if constexpr (K == 2) {
     io.region = 1;
-    step_compute<T, 1, M, TY, true, NT>(L, io, W, -1, M + 1, 0, 0);
+    step_compute<T, 1, M, TY, uint32_t, true, NT>(L, io, W, -1, M + 1, 0, 0);
     __syncthreads();
   }
   io.region = 0;
-  step_compute<T, 1, M, TY, false, NT>(L, io, W, 0, M, 0, 0, -jlo);
+  step_compute<T, 1, M, TY, uint32_t, false, NT>(L, io, W, 0, M, 0, 0, -jlo);
 }
 
 // ---------------------------------------------------------------------------
@@ -2267,18 +2271,18 @@ __global__ __launch_bounds__((amr_threads<M, PAIR>()), (amr_waves<T, EQ, M, PAIR
     if (region == 1) {
       io.region = 1;
       if (!pair) {
-        step_compute<T, EQ, M, TY, false, NT, BULK>(L, io, W, -1, M + 1, gx0, gy0);
+        step_compute<T, EQ, M, TY, uint32_t, false, NT, BULK>(L, io, W, -1, M + 1, gx0, gy0);
         return;
       }
-      step_compute<T, EQ, M, TY, true, NT, BULK>(L, io, W, -1, M + 1, gx0, gy0);
+      step_compute<T, EQ, M, TY, uint32_t, true, NT, BULK>(L, io, W, -1, M + 1, gx0, gy0);
       __syncthreads();
     }
     io.region = 0;
-    step_compute<T, EQ, M, TY, false, NT, BULK>(L, io, amr_weights<T, EQ, PAIR>(wdev, P, k, region == 1), 0, M, gx0, gy0, 1);
+    step_compute<T, EQ, M, TY, uint32_t, false, NT, BULK>(L, io, amr_weights<T, EQ, PAIR>(wdev, P, k, region == 1), 0, M, gx0, gy0, 1);
   } else {
     // (a copy of its own: shared with k_patch_step it was compiled to 177
     // registers in FP64 and lost a wave)
-    step_compute<T, EQ, M, TY, false, NT, BULK, 1>(L, io, W, jlo, jhi, gx0, gy0);
+    step_compute<T, EQ, M, TY, uint32_t, false, NT, BULK, 1>(L, io, W, jlo, jhi, gx0, gy0);
   }
 }
 

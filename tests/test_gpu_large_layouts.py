@@ -1,5 +1,6 @@
 """Layouts past the edge of 32-bit arithmetic: more leaves than one launch of
-four blocks of 256 threads per leaf can take (a grid holds 2^32 threads)."""
+four blocks of 256 threads per leaf can take (a grid holds 2^32 threads), and a
+row pitch that makes the plane of one patch larger than 4 GiB."""
 import os
 
 import numpy as np
@@ -18,6 +19,49 @@ def _need(bytes_):
     if torch.cuda.mem_get_info()[0] < bytes_ + (8 << 30):
         pytest.skip("not enough device memory")
     return torch
+
+
+@pytest.mark.parametrize("call", ["patch_step", "coarse_step", "level_advance"])
+@pytest.mark.parametrize("eq,m", [(af.ADVECTION, 8), (af.BURGERS, 8), (af.ACOUSTICS, 16)])
+def test_wide_rows(eq, m, call):
+    if call == "level_advance" and (eq == af.BURGERS or m == 8):
+        pytest.skip("no level-advance kernel for it")
+    P = af.Problem(eq=eq, prec=af.FP32, m=m, a=1.0, b=0.5, c=1.0, qmax=1.0)
+    S = m + 5
+    wide = (1 << 30) // (m + 1) + 1  # elements: the last rows that a step writes begin past 2^32 bytes
+    torch = _need(2 * 4 * P.ncomp * S * wide * 4)
+    ctx = af.Context(P)
+    h = af.Hierarchy(ctx, afsynth.uniform_leaves(1, 1, 0))
+    rng = np.random.default_rng(2)
+    # periodic data on one patch: the high lines and ghost layers repeat the interior
+    core = torch.from_numpy(rng.uniform(0.2, 0.6, (4, P.ncomp, 1, m, m)).astype(np.float32)).cuda()
+    idx = (torch.arange(S, device="cuda") - 2) % m
+    block = core[..., idx, :][..., idx]
+    out = []
+    for pitch in (S, wide):
+        bufs = [torch.empty((4, P.ncomp, 1, S, pitch), dtype=torch.float32, device="cuda") for _ in range(2)]
+        for b in bufs:
+            b[..., :S] = block
+        dt = 0.4 * P.dx(0)
+        if call == "patch_step":
+            ctx.patch_step(bufs[0], bufs[1], 0, 1, 0, dt)
+            mask = 1
+        elif call == "coarse_step":
+            reg = torch.zeros((1, 4, m, P.ncomp), dtype=torch.float64, device="cuda")
+            mask = ctx.amr_coarse_step(h, bufs, 0, dt, reg)
+        else:
+            mask = ctx.level_advance(h, bufs, 0, 0, dt, 2)
+        torch.cuda.synchronize()
+        r = bufs[mask & 1][..., 2:3 + m, 2:3 + m].clone()
+        r[0, ..., m, :] = r[0, ..., :, m] = r[2, ..., m, :] = r[3, ..., :, m] = 0  # entries that no step defines
+        out.append(r)
+        del bufs, b
+        torch.cuda.empty_cache()
+    # the same arithmetic, but the two layouts may take different kernels: each
+    # of at most two steps sums up to 60 products of values below 1, 32 units
+    # of rounding at most
+    assert float((out[0] - out[1]).abs().max()) <= 64 * 2.0 ** -24
+    assert float((out[0][1] - block[1, ..., 2:3 + m, 2:3 + m]).abs().max()) > 1e-3  # a step was made
 
 
 def test_transfer_of_many_leaves():
