@@ -622,12 +622,11 @@ struct af_cnn {
   float* d_m1 = nullptr;
   float* d_m2 = nullptr;
   float* d_grad = nullptr;
-  // inputs and logits of af_cnn_tag for up to cap leaves
+  // workspace for up to cap samples: inputs and logits of af_cnn_tag, and the
+  // rows of gradient sums of af_cnn_loss_grad's blocks
   int cap = 0;
   float* d_logits = nullptr;
   float* d_feat = nullptr;
-  // training: the blocks' rows of gradient sums
-  int part_rows = 0;
   float* d_part = nullptr;
   float* d_norm = nullptr;  // mean[nin], inv_std[nin]
 };
@@ -646,14 +645,18 @@ af_status cfail(af_status s, const std::string& m) {
 
 int grid_for(long n) { return int(std::min<long>((n + 255) / 256, 8192)); }
 
-af_status ensure_tag(af_cnn* c, int n) {
+// The workspace of every entry point for n samples: after one call of any of
+// them the others allocate nothing up to that size (and can be captured).
+af_status ensure_batch(af_cnn* c, int n) {
   if (n <= c->cap) return AF_OK;
   (void)hipFree(c->d_logits);
   (void)hipFree(c->d_feat);
-  c->d_logits = c->d_feat = nullptr;
+  (void)hipFree(c->d_part);
+  c->d_logits = c->d_feat = c->d_part = nullptr;
   c->cap = 0;
   CNN_HIP(hipMalloc(&c->d_logits, size_t(n) * kClasses * 4));
   CNN_HIP(hipMalloc(&c->d_feat, size_t(n) * c->nin * kPix * 4));
+  CNN_HIP(hipMalloc(&c->d_part, size_t(std::min(n, kCnnRows)) * kPart * 4));
   c->cap = n;
   return AF_OK;
 }
@@ -747,6 +750,8 @@ af_status af_cnn_set_normalization(af_cnn* c, const float* mean, const float* in
 
 af_status af_cnn_forward(af_cnn* c, const float* x, int32_t B, float* logits, float* acts, hipStream_t st) {
   if (!c || !x || !logits || B <= 0) return cfail(AF_ERR_ARG, "bad argument");
+  af_status s = ensure_batch(c, B);
+  if (s != AF_OK) return s;
   CnnArgs A = cnn_args(c, x, B);
   A.logits = logits;
   A.acts = acts;
@@ -757,14 +762,9 @@ af_status af_cnn_forward(af_cnn* c, const float* x, int32_t B, float* logits, fl
 af_status af_cnn_loss_grad(af_cnn* c, const float* x, const int32_t* labels, int32_t B, float* loss, float* grad,
                            float* dacts, hipStream_t st) {
   if (!c || !x || !labels || !loss || B <= 0) return cfail(AF_ERR_ARG, "bad argument");
+  af_status s = ensure_batch(c, B);
+  if (s != AF_OK) return s;
   const int rows = std::min(B, kCnnRows);
-  if (rows > c->part_rows) {
-    (void)hipFree(c->d_part);
-    c->d_part = nullptr;
-    c->part_rows = 0;
-    CNN_HIP(hipMalloc(&c->d_part, size_t(rows) * kPart * 4));
-    c->part_rows = rows;
-  }
   CnnArgs A = cnn_args(c, x, B);
   A.labels = labels;
   A.dacts = dacts;
@@ -840,7 +840,7 @@ af_status af_cnn_tag(af_ctx* ctx, af_cnn* c, const af_hier* h, const af_state* b
   AfTagView v;
   af_status s = af_internal_tag_view(ctx, h, bufs, &v);
   if (s != AF_OK) return cfail(s, "af_cnn_tag: bad context, hierarchy or buffers");
-  if ((s = ensure_tag(c, v.nleaves)) != AF_OK) return s;
+  if ((s = ensure_batch(c, v.nleaves)) != AF_OK) return s;
   if ((s = af_cnn_features(ctx, c, h, bufs, mask, c->d_feat, st)) != AF_OK) return s;
   if ((s = af_cnn_forward(c, c->d_feat, v.nleaves, c->d_logits, nullptr, st)) != AF_OK) return s;
   hipLaunchKernelGGL(k_combine_tags, dim3((v.nleaves + 255) / 256), dim3(256), 0, st, c->d_logits, plain, v.plevel,
