@@ -953,6 +953,23 @@ af_status level_grid(af_hier* h, int level, int* nx, int* ny) {
 
 constexpr int kOneBlockPerCu = 256;  // patches up to which a CU gets one block
 
+// The level-advance shapes of the context's problem (up: with those that only
+// the upwind one-pass kernel runs) for a level of `count` patches: a grid holds
+// less than 2^32 threads.
+struct Shapes {
+  AdvanceShape s[kMaxAdvanceShapes];
+  int n = 0;
+  const AdvanceShape* begin() const { return s; }
+  const AdvanceShape* end() const { return s + n; }
+};
+Shapes advance_shapes(const af_ctx* c, bool up, int count = 0) {
+  Shapes L;
+  const int n = level_advance_shapes(c->fp32(), c->P.eq, c->P.m, up, L.s);
+  for (int i = 0; i < n; ++i)
+    if (uint64_t(count) * uint64_t(L.s[i].nt) < uint64_t(1) << 32) L.s[L.n++] = L.s[i];
+  return L;
+}
+
 // The shape for a level of `count` patches where none is set: the one with
 // the most steps in progress on a CU, of equal ones the largest block.  Up to
 // one patch per CU that is the largest K, and the block's waves are all the
@@ -970,44 +987,68 @@ constexpr int kOneBlockPerCu = 256;  // patches up to which a CU gets one block
 // 17.1 for 8100).  The acoustic kernel of 256 threads catches up (FP32, two
 // steps, with 256 and 512 threads: 36 and 33 us for 2025 patches, 114 and 115
 // for 8100, 242 and 252 for 16384).
-void level_shape(const af_ctx* c, bool up, int count, int* k, int* nt) {
-  int ks[32], nts[32], best = 0;
-  const int n = level_advance_shapes(c->fp32(), c->P.eq, c->P.m, ks, nts, 32, up);
+AdvanceShape level_shape(const af_ctx* c, const Shapes& shapes, int count) {
   const bool small = c->P.eq == AF_ACOUSTICS && count > 32 * kOneBlockPerCu;
-  *k = *nt = 0;
-  for (int i = 0; i < n; ++i) {
-    if (count > 3 * kOneBlockPerCu && ks[i] > c->P.m / 2) continue;
-    const int r = level_advance_resident(c->fp32(), c->P.eq, c->P.m, ks[i], nts[i], up);
-    if (!c->fp32() && count > 6 * kOneBlockPerCu && r > 1 && ks[i] > c->P.m / 4) continue;
-    const int score = ks[i] * (count > kOneBlockPerCu ? std::min(r, 2) : 1);
-    if (score > best || (score == best && (nts[i] < *nt) == small)) { best = score; *k = ks[i]; *nt = nts[i]; }
+  AdvanceShape best{0, 0, 0};
+  int best_score = 0;
+  for (const AdvanceShape& S : shapes) {
+    if (count > 3 * kOneBlockPerCu && S.k > c->P.m / 2) continue;
+    if (!c->fp32() && count > 6 * kOneBlockPerCu && S.resident > 1 && S.k > c->P.m / 4) continue;
+    const int score = S.k * (count > kOneBlockPerCu ? std::min(S.resident, 2) : 1);
+    if (score > best_score || (score == best_score && (S.nt < best.nt) == small)) {
+      best_score = score;
+      best = S;
+    }
   }
+  return best;
 }
 
-// The shape set on the context if it runs here (up: the weights have the
-// upwind pattern), else the largest K with the smallest block.
-void default_advance_shape(const af_ctx* c, bool up, int* k, int* nt) {
-  int ks[32], nts[32];
-  const int n = level_advance_shapes(c->fp32(), c->P.eq, c->P.m, ks, nts, 32, up);
-  *k = 0;
-  *nt = 0;
-  if (c->adv_k) {
-    for (int i = 0; i < n; ++i)
-      if (ks[i] == c->adv_k && nts[i] == c->adv_nt) { *k = ks[i]; *nt = nts[i]; return; }
+// The shape set on the context if it is one of these, else the largest K with
+// the smallest block (k = 0 if there is none).
+AdvanceShape default_advance_shape(const af_ctx* c, const Shapes& shapes) {
+  AdvanceShape best{0, 0, 0};
+  for (const AdvanceShape& S : shapes) {
+    if (c->adv_k && S.k == c->adv_k && S.nt == c->adv_nt) return S;
+    if (S.k > best.k || (S.k == best.k && S.nt < best.nt)) best = S;
   }
-  // default: the largest K with the smallest block
-  for (int i = 0; i < n; ++i)
-    if (ks[i] > *k || (ks[i] == *k && nts[i] < *nt)) { *k = ks[i]; *nt = nts[i]; }
+  return best;
+}
+
+// Steps of the next launch where `rest` steps are left and the lengths in the
+// set `ks` (bit k) can be launched, K <= 20 the longest: as few launches as
+// possible, of those the most even ones.  A launch costs a part that does not
+// depend on its steps, and per step the more the longer it is, so of equally
+// many launches middling ones are the faster (512^2 cells, FP32, 128 steps, K =
+// 20: six launches of 20 and one of 8, 160 us; one of 20 and six of 18, 156).
+// But a length that leaves a rest of several short launches costs more than it
+// saves (FP64, m = 32, 256 patches, 17 steps: 10 + 6 + 1 39.0 us, 12 + 5 34.3).
+int next_steps(uint64_t ks, int K, int rest) {
+  auto shortest = [&](int at_least, uint64_t rests) {  // rests: bit r, a rest of r is welcome
+    for (int k = at_least; k <= K; ++k)
+      if ((ks >> k & 1) && (rest - k > 63 || (rests >> (rest - k) & 1))) return k;
+    return K;
+  };
+  if (rest > 3 * K) {
+    const int n = (rest + K - 1) / K;
+    return shortest((rest + n - 1) / n, ~uint64_t(0));
+  }
+  // sums of n lengths, bit by bit, until one is the rest (at most 60)
+  uint64_t sums = 1;
+  for (int n = 1;; ++n) {
+    uint64_t next = 0;
+    for (int k = 1; k <= K; ++k)
+      if (ks >> k & 1) next |= sums << k;
+    if (next >> rest & 1) return shortest((rest + n - 1) / n, sums);
+    sums = next;
+  }
 }
 
 }  // namespace
 
 af_status af_ctx_set_advance_shape(af_ctx* ctx, int32_t k, int32_t nt) {
   if (!ctx) return fail(AF_ERR_ARG, "null ctx");
-  int ks[32], nts[32];
-  const int n = level_advance_shapes(ctx->fp32(), ctx->P.eq, ctx->P.m, ks, nts, 32, true);
-  for (int i = 0; i < n; ++i)
-    if (ks[i] == k && nts[i] == nt) {
+  for (const AdvanceShape& S : advance_shapes(ctx, true))
+    if (S.k == k && S.nt == nt) {
       ctx->adv_k = k;
       ctx->adv_nt = nt;
       return AF_OK;
@@ -1017,37 +1058,35 @@ af_status af_ctx_set_advance_shape(af_ctx* ctx, int32_t k, int32_t nt) {
 
 af_status af_ctx_get_advance_shape(const af_ctx* ctx, int32_t* k, int32_t* nt) {
   if (!ctx || !k || !nt) return fail(AF_ERR_ARG, "null argument");
-  int kk, nn;
-  // the upwind pattern needs both velocity components positive (and small
-  // enough time steps)
-  default_advance_shape(ctx, ctx->P.eq == AF_ADVECTION && ctx->P.a > 0 && ctx->P.b > 0, &kk, &nn);
-  *k = kk;
-  *nt = nn;
+  // of the shapes that only the upwind pattern runs, those of positive
+  // velocities
+  const AdvanceShape S =
+      default_advance_shape(ctx, advance_shapes(ctx, ctx->P.eq == AF_ADVECTION && ctx->P.a > 0 && ctx->P.b > 0));
+  *k = S.k;
+  *nt = S.nt;
   return AF_OK;
 }
 
 int32_t af_ctx_advance_shapes(const af_ctx* ctx, int32_t* ks, int32_t* nts, int32_t cap) {
   if (!ctx) return -1;
-  int k2[32], n2[32];
-  const int n = level_advance_shapes(ctx->fp32(), ctx->P.eq, ctx->P.m, k2, n2, 32, true);
-  for (int i = 0; i < n && i < cap; ++i) {
-    if (ks) ks[i] = k2[i];
-    if (nts) nts[i] = n2[i];
+  const Shapes all = advance_shapes(ctx, true);
+  for (int i = 0; i < all.n && i < cap; ++i) {
+    if (ks) ks[i] = all.s[i].k;
+    if (nts) nts[i] = all.s[i].nt;
   }
-  return n;
+  return all.n;
 }
 
 int32_t af_ctx_advance_shapes_upwind(const af_ctx* ctx, int32_t* ks, int32_t* nts, int32_t cap) {
   if (!ctx) return -1;
-  int k2[32], n2[32];
   // the list with the upwind-only shapes holds the two-pass shapes first
-  const int two = level_advance_shapes(ctx->fp32(), ctx->P.eq, ctx->P.m, k2, n2, 32, false);
-  const int all = level_advance_shapes(ctx->fp32(), ctx->P.eq, ctx->P.m, k2, n2, 32, true);
-  for (int i = two; i < all && i - two < cap; ++i) {
-    if (ks) ks[i - two] = k2[i];
-    if (nts) nts[i - two] = n2[i];
+  const Shapes all = advance_shapes(ctx, true);
+  const int two = advance_shapes(ctx, false).n;
+  for (int i = two; i < all.n && i - two < cap; ++i) {
+    if (ks) ks[i - two] = all.s[i].k;
+    if (nts) nts[i - two] = all.s[i].nt;
   }
-  return all - two;
+  return all.n - two;
 }
 
 af_status af_level_advance(af_ctx* ctx, af_hier* h, af_state* bufs, uint32_t* mask, int32_t level, double dt,
@@ -1084,12 +1123,9 @@ af_status af_level_advance(af_ctx* ctx, af_hier* h, af_state* bufs, uint32_t* ma
   L.weights = weights_for(ctx, dt / dx, dt / dy);
   if (!L.weights) return fail(AF_ERR_STATE, "acoustic stencils lack their mirror symmetry");
   const bool up = level_advance_up_pattern(L.fp32, L.eq, L.weights);
-  int K, NT;
-  if (ctx->adv_k)
-    default_advance_shape(ctx, up, &K, &NT);
-  else
-    level_shape(ctx, up, count, &K, &NT);
-  if (K == 0) return fail(AF_ERR_ARG, "no level-advance kernel for this (precision, equation, m)");
+  const Shapes shapes = advance_shapes(ctx, up, count);
+  const AdvanceShape S = ctx->adv_k ? default_advance_shape(ctx, shapes) : level_shape(ctx, shapes, count);
+  if (S.k == 0) return fail(AF_ERR_ARG, "no level-advance kernel for this (precision, equation, m)");
   if (ctx->P.eq == AF_ACOUSTICS && !narrow_planes(ctx, bufs[0])) {
     for (int k = 0; k < nsteps; ++k) {
       const int cur = (*mask >> level) & 1;
@@ -1101,37 +1137,30 @@ af_status af_level_advance(af_ctx* ctx, af_hier* h, af_state* bufs, uint32_t* ma
     }
     return AF_OK;
   }
-  int ks[32], nts[32];
-  const int n = level_advance_shapes(ctx->fp32(), ctx->P.eq, ctx->P.m, ks, nts, 32, up);
+  // The block size of a launch of k steps.  A set shape's where it is compiled
+  // for k.  Else, with one block per CU at most, the largest (its waves are all
+  // the latency hiding there is: K = 8, 256 patches, 1024 threads 11.9 us, 512
+  // 13.4), with more the smallest; lengths whose blocks share a CU less than the
+  // chosen shape's are left out then (FP32, m = 32, 1024 patches, 13 steps: 7 +
+  // 6 with 1024 threads for the 7 65 us, 12 + 1 57).
+  int block[64] = {};
+  uint64_t ks = 0;
+  for (const AdvanceShape& A : shapes) {
+    if (A.k > S.k) continue;
+    if (!ctx->adv_k && count > kOneBlockPerCu && std::min(A.resident, 2) < std::min(S.resident, 2)) continue;
+    int& nt = block[A.k];
+    const bool better = ctx->adv_k ? nt != S.nt && (A.nt == S.nt || A.nt < nt)
+                                   : (A.nt > nt) == (count <= kOneBlockPerCu);
+    if (nt == 0 || better) nt = A.nt;
+    ks |= uint64_t(1) << A.k;
+  }
+  if (!ctx->adv_k) block[S.k] = S.nt;
+  if (!(ks & 2)) return fail(AF_ERR_STATE, "no level-advance kernel short enough for the remaining steps");
   int done = 0;
   while (done < nsteps) {
-    // As many launches as K steps each would take, of about equal length:
-    // the shortest shape of at most K steps that spreads the rest evenly, or
-    // where the rest is shorter than every such shape the longest that fits.
-    // A launch costs a part that does not depend on its steps and per step
-    // the more the longer it is, so a full-length launch and a short tail
-    // cost more than two middling ones (512^2 FP32, 128 steps, K = 20: six
-    // launches of 20 and one of 8, 160 us; one of 20 and six of 18, 156).
-    // Of shapes with the same steps the tuned block size, else the largest
-    // where a CU gets one block at most (its waves are all the latency
-    // hiding there is: K = 8, 256 patches, 1024 threads 11.9 us, 512 13.4),
-    // else the smallest.
-    int kk = K, nt = NT;
-    const int rest = nsteps - done, left = (rest + K - 1) / K, even = (rest + left - 1) / left;
-    if (even < K) {
-      kk = 0;
-      for (int i = 0; i < n; ++i)
-        if (ks[i] >= even && ks[i] <= std::min(K, rest) && (kk == 0 || ks[i] < kk)) kk = ks[i];
-      if (kk == 0)
-        for (int i = 0; i < n; ++i)
-          if (ks[i] <= rest && ks[i] > kk) kk = ks[i];
-      if (kk == 0) return fail(AF_ERR_STATE, "no level-advance kernel short enough for the remaining steps");
-      nt = 0;
-      for (int i = 0; i < n; ++i)
-        if (ks[i] == kk && !(ctx->adv_k && nt == NT) && (nt == 0 || (ctx->adv_k && nts[i] == NT) || (nts[i] > nt) == (count <= kOneBlockPerCu))) nt = nts[i];
-    }
+    const int kk = next_steps(ks, S.k, nsteps - done);
     L.k = kk;
-    L.nt = nt;
+    L.nt = block[kk];
     const int cur = (*mask >> level) & 1;
     for (int k = 0; k < 4; ++k) {
       L.in[k] = bufs[cur].dof[k];
@@ -1224,21 +1253,19 @@ af_status af_autotune(af_ctx* ctx, af_hier* h, af_state* bufs, int32_t level, do
   double best_adv = -1.0;
   int gnx, gny;
   if (s == AF_OK && level_grid(h, level, &gnx, &gny) == AF_OK) {
-    int ks[32], nts[32];
     const bool up = level_advance_up_pattern(ctx->fp32(), ctx->P.eq,
                                              weights_for(ctx, dt / ctx->dx(level), dt / ctx->dy(level)));
-    const int n = level_advance_shapes(ctx->fp32(), ctx->P.eq, ctx->P.m, ks, nts, 32, up);
     double b2 = 1e300;
     int bk = 0, bn = 0;
-    for (int i = 0; i < n; ++i) {
-      ctx->adv_k = ks[i];
-      ctx->adv_nt = nts[i];
+    for (const AdvanceShape& A : advance_shapes(ctx, up, count)) {
+      ctx->adv_k = A.k;
+      ctx->adv_nt = A.nt;
       uint32_t mk = 0;
       double us;
-      s = timed([&]() { return af_level_advance(ctx, h, bufs, &mk, level, dt, ks[i], stream); }, &us);
+      s = timed([&]() { return af_level_advance(ctx, h, bufs, &mk, level, dt, A.k, stream); }, &us);
       if (s != AF_OK) break;
-      us /= ks[i];
-      if (us < b2) { b2 = us; bk = ks[i]; bn = nts[i]; }
+      us /= A.k;
+      if (us < b2) { b2 = us; bk = A.k; bn = A.nt; }
     }
     ctx->adv_k = bk;
     ctx->adv_nt = bn;

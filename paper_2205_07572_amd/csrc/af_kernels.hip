@@ -2979,8 +2979,8 @@ static hipError_t launch_up_t(const AdvanceLaunch& s, hipStream_t st) {
 // Blocks of a level-advance shape that a CU holds at once, by LDS and by 1024
 // threads (the one-pass kernel's 96 to 117 registers).
 template <typename T, int EQ, int M, int K, int NT>
-static int adv_resident(bool up) {
-  size_t lds;
+static constexpr int adv_resident(bool up) {
+  size_t lds = 0;
   if constexpr (EQ == 0)
     lds = up ? sizeof(UpLds<T, M, K, NT>) : sizeof(AdvLds<T, M, K, StripRows<M, K, NT>::value>);
   else
@@ -2988,22 +2988,8 @@ static int adv_resident(bool up) {
   return int(std::min<size_t>(160 * 1024 / lds, 1024 / NT));
 }
 template <typename T, int M, int K, int NT>
-static int up_resident() {
+static constexpr int up_resident() {
   return int(std::min<size_t>(160 * 1024 / sizeof(UpLds<T, M, K, NT>), 1024 / NT));
-}
-
-int level_advance_resident(bool fp32, int eq, int m, int k, int nt, bool up) {
-#define AF_ADV_RES(T_, EQ_, M_, K_, NT_)                                                             \
-  if ((std::is_same<T_, float>::value == fp32) && eq == EQ_ && m == M_ && k == K_ && nt == NT_) \
-    return adv_resident<T_, EQ_, M_, K_, NT_>(up);
-  AF_ADV_SHAPES(AF_ADV_RES)
-#undef AF_ADV_RES
-#define AF_UP_RES(T_, M_, K_, NT_)                                                                 \
-  if ((std::is_same<T_, float>::value == fp32) && eq == 0 && m == M_ && k == K_ && nt == NT_) \
-    return up_resident<T_, M_, K_, NT_>();
-  AF_UP_SHAPES(AF_UP_RES)
-#undef AF_UP_RES
-  return 0;
 }
 
 hipError_t launch_level_advance(const AdvanceLaunch& s, hipStream_t st) {
@@ -3021,22 +3007,16 @@ hipError_t launch_level_advance(const AdvanceLaunch& s, hipStream_t st) {
   return hipErrorInvalidValue;
 }
 
-int level_advance_shapes(bool fp32, int eq, int m, int* ks, int* nts, int cap, bool up) {
+int level_advance_shapes(bool fp32, int eq, int m, bool up, AdvanceShape (&out)[kMaxAdvanceShapes]) {
   int n = 0;
-#define AF_ADV_LIST(T_, EQ_, M_, K_, NT_)                                                  \
-  if ((std::is_same<T_, float>::value == fp32) && eq == EQ_ && m == M_ && n < cap) { \
-    ks[n] = K_;                                                                           \
-    nts[n] = NT_;                                                                         \
-    ++n;                                                                                  \
-  }
+#define AF_ADV_LIST(T_, EQ_, M_, K_, NT_)                                             \
+  if ((std::is_same<T_, float>::value == fp32) && eq == EQ_ && m == M_)              \
+    out[n++] = {K_, NT_, up ? adv_resident<T_, EQ_, M_, K_, NT_>(true) : adv_resident<T_, EQ_, M_, K_, NT_>(false)};
   AF_ADV_SHAPES(AF_ADV_LIST)
 #undef AF_ADV_LIST
-#define AF_UP_LIST(T_, M_, K_, NT_)                                                                \
-  if (up && (std::is_same<T_, float>::value == fp32) && eq == 0 && m == M_ && n < cap) { \
-    ks[n] = K_;                                                                                   \
-    nts[n] = NT_;                                                                                 \
-    ++n;                                                                                          \
-  }
+#define AF_UP_LIST(T_, M_, K_, NT_)                                                         \
+  if (up && (std::is_same<T_, float>::value == fp32) && eq == 0 && m == M_)                 \
+    out[n++] = {K_, NT_, up_resident<T_, M_, K_, NT_>()};
   AF_UP_SHAPES(AF_UP_LIST)
 #undef AF_UP_LIST
   return n;

@@ -96,10 +96,13 @@ hipError_t launch_patch_step(const StepLaunch& s, hipStream_t st);
 hipError_t launch_level_advance(const AdvanceLaunch& s, hipStream_t st);
 // Fills the level-advance shapes (K, threads) for (precision, equation, m) and
 // returns their count.  With up, also the shapes only the upwind one-pass
-// kernel runs.
-int level_advance_shapes(bool fp32, int eq, int m, int* ks, int* nts, int cap, bool up);
-// Blocks of a shape that a CU holds at once.
-int level_advance_resident(bool fp32, int eq, int m, int k, int nt, bool up);
+// kernel runs, and `resident` is that kernel's.
+struct AdvanceShape {
+  int k, nt;     // steps per launch, threads per block
+  int resident;  // blocks that a CU holds at once
+};
+constexpr int kMaxAdvanceShapes = 40;
+int level_advance_shapes(bool fp32, int eq, int m, bool up, AdvanceShape (&out)[kMaxAdvanceShapes]);
 // Whether advection weights take every node from the upwind source pattern or
 // a mirror image of it (false for acoustics).
 bool level_advance_up_pattern(bool fp32, int eq, const void* weights);

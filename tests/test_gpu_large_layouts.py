@@ -1,6 +1,6 @@
 """Layouts past the edge of 32-bit arithmetic: more leaves than one launch of
-four blocks of 256 threads per leaf can take (a grid holds 2^32 threads), and a
-row pitch that makes the plane of one patch larger than 4 GiB."""
+four blocks of 256 threads per leaf, or one of 1024, can take (a grid holds less
+than 2^32 threads), and a row pitch that makes the plane of one patch larger than 4 GiB."""
 import os
 
 import numpy as np
@@ -79,3 +79,29 @@ def test_transfer_of_many_leaves():
     torch.cuda.synchronize()
     for k, (r, c) in enumerate(((8, 8), (9, 9), (8, 9), (9, 8))):
         assert torch.equal(src[k, :, :, 2:2 + r, 2:2 + c], dst[k, :, :, 2:2 + r, 2:2 + c]), k
+
+
+def test_level_advance_of_many_patches():
+    """A set block size whose grid would reach 2^32 threads is replaced."""
+    n0, m = 2056, 16
+    P = af.Problem(eq=af.ADVECTION, prec=af.FP32, m=m, n0x=n0, n0y=n0, lx=float(n0), ly=float(n0), a=1.0, b=0.5)
+    torch = _need(4 * 4 * n0 * n0 * 21 * 21 * 4)
+    iy, ix = np.divmod(np.arange(n0 * n0), n0)
+    leaves = np.stack([np.zeros_like(ix), ix, iy], 1)
+    ctx = af.Context(P)
+    start = ctx.new_state(n0 * n0)
+    start.uniform_(-1.0, 1.0)
+    h = af.Hierarchy(ctx, leaves)
+    out = []
+    for shape in ((8, 256), (16, 1024)):
+        ctx.set_advance_shape(*shape)
+        bufs = [start.clone(), torch.zeros_like(start)]
+        mask = ctx.level_advance(h, bufs, 0, 0, 0.4 * P.dx(0), 16)
+        torch.cuda.synchronize()
+        s = bufs[mask & 1][:, :, -4096:, 2:2 + m, 2:2 + m].clone()
+        out.append(s)
+        del bufs
+        torch.cuda.empty_cache()
+    # rounding of about 10 operations of weight 1 per step, in random order
+    assert float((out[0] - out[1]).abs().max()) <= 16 * 16 * 2.0 ** -24
+    assert float(out[0].abs().max()) > 0.1
