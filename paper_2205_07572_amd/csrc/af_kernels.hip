@@ -1,7 +1,7 @@
 // af_kernels.hip -- gfx950 kernels of the Active Flux patch-step library.
 //
-// Every kernel uses 256-thread blocks (four 64-wide wavefronts).  State
-// arrays are structure-of-arrays: four DOF kinds, each [ncomp][npatch]
+// Blocks have kThreads = 256 threads (four 64-wide wavefronts) where no other
+// size is given.  State arrays are structure-of-arrays: four DOF kinds, each [ncomp][npatch]
 // [m+5][pitch] (see include/af.h).
 #include <hip/hip_runtime.h>
 
@@ -366,8 +366,9 @@ __device__ __forceinline__ void swirl_vel(const SwirlParams<T>& W, SinCos<T> x, 
 }
 
 // sin and cos of pi (x + d) from those of pi x, for |pi d| <= kSmallAngle: the
-// Taylor polynomials of sin and cos (terms left out: below 2e-18 of 1 in
-// FP64 and 2e-9 in FP32) and the addition theorems.  A Runge-Kutta stage
+// Taylor polynomials of sin and cos (the first terms left out, at 0.4: 8.2e-19
+// of the sine and 3.1e-17 of the cosine in FP64, below half a unit of 1; 7.2e-10
+// and 2.9e-11 in FP32) and the addition theorems.  A Runge-Kutta stage
 // moves a point by at most one cell (|a|, |b| <= 1 and the Courant number),
 // so every step with pi dt <= kSmallAngle takes this; a longer one calls
 // sincospi.  A cell's nodes make 36 such pairs per step, and sincospi was most
@@ -437,7 +438,7 @@ __device__ __forceinline__ T rot_eval(const D& s, int r, int c, T xi, T eta) {
   const T ll = s(1, 0, r, c), rl = s(1, 0, r, c + 1), lu = s(1, 0, r + 1, c), ru = s(1, 0, r + 1, c + 1);
   const T xl = s(2, 0, r, c), xr = s(2, 0, r, c + 1), yb = s(3, 0, r, c), yt = s(3, 0, r + 1, c);
   const T mid = fmadd(T(-0.25), (xl + xr) + (yb + yt),
-                      fmadd(T(-0.0625), (ll + rl) + (lu + ru), T(2.25) * s(0, 0, r, c)));
+                      fmadd(T(2.25), s(0, 0, r, c), T(-0.0625) * ((ll + rl) + (lu + ru))));
   const T b = fmadd(lx[2], rl, fmadd(lx[1], yb, lx[0] * ll));
   const T m = fmadd(lx[2], xr, fmadd(lx[1], mid, lx[0] * xl));
   const T t = fmadd(lx[2], ru, fmadd(lx[1], yt, lx[0] * lu));
@@ -474,7 +475,7 @@ struct StepIO {
 // O: type of the byte offset of an entry in its plane.  32 bits are a vector
 // register and an addition less per store, and hold a plane below 4 GiB (the
 // kernels that take them get no other, see narrow_planes on the host); 64 bits
-// hold every plane.
+// hold every plane.  USE: no effect but a copy of its own (see k_amr_step).
 template <typename T, int EQ, int M, int TY, typename O, bool TO_LDS = false, int NT = kThreads, bool BULK = false,
           int USE = 0, typename L_t>
 __device__ __forceinline__ void step_compute(L_t& L, const StepIO<T>& A, const typename WSel<T, EQ>::type& W,
@@ -580,8 +581,8 @@ __device__ __forceinline__ void step_compute(L_t& L, const StepIO<T>& A, const t
           T dispx, dispy;  // node - foot in cells
           if constexpr (EQ == 2) {
             const T rx = x - W.xc, ry = y - W.yc;
-            dispx = fmadd(rx, W.vx[t], -(ry * W.sx[t]));
-            dispy = fmadd(ry, W.vy[t], rx * W.sy[t]);
+            dispx = fmadd(-ry, W.sx[t], rx * W.vx[t]);
+            dispy = fmadd(rx, W.sy[t], ry * W.vy[t]);
           } else {
             const T h = W.tau[t], hh = T(0.5) * h;
             const T a1 = W.cos_rk[t][0] * ax, b1 = W.cos_rk[t][0] * by;
@@ -749,6 +750,7 @@ __device__ __forceinline__ void step_compute(L_t& L, const StepIO<T>& A, const t
     // physical fluxes of the Simpson sums: advection f = a q, g = b q;
     // acoustics f = c (u, p, 0), g = c (v, 0, p)  (Sec. 2.3)
     T fL[NCOMP], fR[NCOMP], gB[NCOMP], gT[NCOMP];
+    [[maybe_unused]] T sL, sR, sB, sT;  // variable velocities: the same before the division by 36
     if constexpr (EQ == 0) {
       fL[0] = A.a * FL[0] * inv36; fR[0] = A.a * FR[0] * inv36;
       gB[0] = A.b * GB[0] * inv36; gT[0] = A.b * GT[0] * inv36;
@@ -787,15 +789,14 @@ __device__ __forceinline__ void step_compute(L_t& L, const StepIO<T>& A, const t
       const T ST[3] = {face_sum(Q0(1, 0, rr + 1, cc), Q0(3, 0, rr + 1, cc), Q0(1, 0, rr + 1, cc + 1)),
                        face_sum(Qh(NK_CORNER, 0, jj + 1, ii), Qh(NK_YEDGE, 0, jj + 1, ii), Qh(NK_CORNER, 0, jj + 1, ii + 1)),
                        face_sum(Qf(NK_CORNER, 0, jj + 1, ii), Qf(NK_YEDGE, 0, jj + 1, ii), Qf(NK_CORNER, 0, jj + 1, ii + 1))};
-      fL[0] = fmadd(aL[2], SL[2], fmadd(T(4) * aL[1], SL[1], aL[0] * SL[0])) * inv36;
-      fR[0] = fmadd(aR[2], SR[2], fmadd(T(4) * aR[1], SR[1], aR[0] * SR[0])) * inv36;
-      gB[0] = fmadd(bB[2], SB[2], fmadd(T(4) * bB[1], SB[1], bB[0] * SB[0])) * inv36;
-      gT[0] = fmadd(bT[2], ST[2], fmadd(T(4) * bT[1], ST[1], bT[0] * ST[0])) * inv36;
+      sL = fmadd(aL[2], SL[2], fmadd(T(4) * aL[1], SL[1], aL[0] * SL[0]));
+      sR = fmadd(aR[2], SR[2], fmadd(T(4) * aR[1], SR[1], aR[0] * SR[0]));
+      sB = fmadd(bB[2], SB[2], fmadd(T(4) * bB[1], SB[1], bB[0] * SB[0]));
+      sT = fmadd(bT[2], ST[2], fmadd(T(4) * bT[1], ST[1], bT[0] * ST[0]));
     } else if constexpr (EQ == 4) {
 #pragma clang fp contract(off)
       // Burgers: the time sums already hold f = g = q^2/2
-      fL[0] = FL[0] * inv36; fR[0] = FR[0] * inv36;
-      gB[0] = GB[0] * inv36; gT[0] = GT[0] * inv36;
+      sL = FL[0]; sR = FR[0]; sB = GB[0]; sT = GT[0];
     } else if constexpr (EQ == 2) {
 #pragma clang fp contract(off)
       // rotation: f = a(node) q with a = -omega (y - yc) on x-faces (a depends
@@ -808,12 +809,12 @@ __device__ __forceinline__ void step_compute(L_t& L, const StepIO<T>& A, const t
         b[k] = W.omega * (half_pos(W.x0, W.hdx, hx + T(k)) - W.xc);
       }
       auto simpson = [&](const T(&v)[3], T lo, T mid, T hi) {
-        return fmadd(v[2], hi, fmadd(T(4) * v[1], mid, v[0] * lo)) * inv36;
+        return fmadd(v[2], hi, fmadd(T(4) * v[1], mid, v[0] * lo));
       };
-      fL[0] = simpson(a, ts(NK_CORNER, 0, jj, ii), ts(NK_XEDGE, 0, jj, ii), ts(NK_CORNER, 0, jj + 1, ii));
-      fR[0] = simpson(a, ts(NK_CORNER, 0, jj, ii + 1), ts(NK_XEDGE, 0, jj, ii + 1), ts(NK_CORNER, 0, jj + 1, ii + 1));
-      gB[0] = simpson(b, ts(NK_CORNER, 0, jj, ii), ts(NK_YEDGE, 0, jj, ii), ts(NK_CORNER, 0, jj, ii + 1));
-      gT[0] = simpson(b, ts(NK_CORNER, 0, jj + 1, ii), ts(NK_YEDGE, 0, jj + 1, ii), ts(NK_CORNER, 0, jj + 1, ii + 1));
+      sL = simpson(a, ts(NK_CORNER, 0, jj, ii), ts(NK_XEDGE, 0, jj, ii), ts(NK_CORNER, 0, jj + 1, ii));
+      sR = simpson(a, ts(NK_CORNER, 0, jj, ii + 1), ts(NK_XEDGE, 0, jj, ii + 1), ts(NK_CORNER, 0, jj + 1, ii + 1));
+      sB = simpson(b, ts(NK_CORNER, 0, jj, ii), ts(NK_YEDGE, 0, jj, ii), ts(NK_CORNER, 0, jj, ii + 1));
+      sT = simpson(b, ts(NK_CORNER, 0, jj + 1, ii), ts(NK_YEDGE, 0, jj + 1, ii), ts(NK_CORNER, 0, jj + 1, ii + 1));
     } else {
       fL[0] = A.c * FL[1] * inv36; fL[1] = A.c * FL[0] * inv36; fL[2] = T(0);
       fR[0] = A.c * FR[1] * inv36; fR[1] = A.c * FR[0] * inv36; fR[2] = T(0);
@@ -826,7 +827,9 @@ __device__ __forceinline__ void step_compute(L_t& L, const StepIO<T>& A, const t
       T Qn;
       if constexpr (EQ >= 2) {
 #pragma clang fp contract(off)
-        Qn = fmadd(-A.dtdy, gT[q] - gB[q], fmadd(-A.dtdx, fR[q] - fL[q], Q));
+        fL[0] = sL * inv36; fR[0] = sR * inv36;
+        gB[0] = sB * inv36; gT[0] = sT * inv36;
+        Qn = fmadd(-A.dtdy, fmadd(sT, inv36, -gB[0]), fmadd(-A.dtdx, fmadd(sR, inv36, -fL[0]), Q));
       } else {
         Qn = Q - A.dtdx * (fR[q] - fL[q]) - A.dtdy * (gT[q] - gB[q]);
       }
@@ -1991,8 +1994,7 @@ __global__ __launch_bounds__(kThreads) void k_fill_apply(const FillArgs<T> A) {
 }
 
 // ---------------------------------------------------------------------------
-// Batched subcycled coarse step (Sec. 3.2) for the constant-coefficient
-// equations: one launch per substep start time steps every patch of every
+// Batched subcycled coarse step (Sec. 3.2): one launch per substep start time steps every patch of every
 // level that starts a step then.
 //
 // With the finest level F and time points tau = 0 .. 2^F - 1 in units of the
@@ -2096,6 +2098,8 @@ template <int M, bool PAIR>
 constexpr int amr_threads() {
   return PAIR && M == 16 ? 512 : kThreads;
 }
+// (FP64: 5 holds the kernel to 96 registers.  A block adds two waves to a SIMD,
+// so four are resident.)
 template <typename T, int EQ, int M, bool PAIR>
 constexpr int amr_waves() {
   if (EQ != 1) return 1;
@@ -2286,7 +2290,9 @@ __global__ __launch_bounds__((amr_threads<M, PAIR>()), (amr_waves<T, EQ, M, PAIR
     // interior from exactly those values.  They are what a fill would stage
     // at the odd time point: the fill there has no coarser sources, so
     // coarse-fine ghosts keep the layer-1 values, and a same-level
-    // neighbour's interior is the same arithmetic on the same data.
+    // neighbour's interior is the same arithmetic on the same data (but for
+    // a velocity field that is not periodic, across the domain's boundary:
+    // the host fuses no pairs there).
     const bool pair = A.pair && k == A.nlev - 1;
     if (region == 1) {
       io.region = 1;
