@@ -287,10 +287,12 @@ af_status af_reduce_sum_noalloc(af_ctx* ctx, const af_hier* h, const af_state* b
  * pattern (a, b > 0, both directional Courant numbers below 1/2) or a mirror
  * image of it (a < 0, b < 0) each step is one pass in which a cell's new
  * average is a fixed combination of the 25 old DOFs of its source cells,
- * composed on the host from eq. 2dfv and eq. Simpson-2d.  AF_ADVECTION and AF_ACOUSTICS only (AF_ERR_ARG for the other
- * equations, which step with af_patch_step).  The level's data moves between
- * bufs[0] and bufs[1] (*level_buf_mask bit `level` updated after every
- * launch); ghost layers of the result are NOT filled.
+ * composed on the host from eq. 2dfv and eq. Simpson-2d.  AF_ADVECTION and
+ * AF_ACOUSTICS only (AF_ERR_ARG for the other equations, which step with
+ * af_patch_step).  The level's data moves between bufs[0] and bufs[1]
+ * (*level_buf_mask bit `level` updated after every launch); ghost layers of
+ * the result are NOT filled.  For a patch plane of 4 GiB or more the acoustic
+ * steps are ghost fills and patch steps.
  * --------------------------------------------------------------------- */
 af_status af_level_advance(af_ctx* ctx, af_hier* h, af_state* bufs, uint32_t* level_buf_mask,
                            int32_t level, double dt, int32_t nsteps, hipStream_t stream);
@@ -307,11 +309,13 @@ int32_t af_ctx_advance_shapes(const af_ctx* ctx, int32_t* ks, int32_t* nts, int3
  * cap of them to the optional arrays */
 int32_t af_ctx_advance_shapes_upwind(const af_ctx* ctx, int32_t* ks, int32_t* nts, int32_t cap);
 af_status af_ctx_set_advance_shape(af_ctx* ctx, int32_t k, int32_t nt);
-/* the shape set by af_ctx_set_advance_shape or af_autotune, else the default:
- * the largest K, then the smallest block, for advection with both velocity
- * components positive assuming time steps small enough for the upwind
- * pattern.  Where none is set af_level_advance chooses by the level's number
- * of patches (the block size, and K beyond 256 patches) */
+/* the shape set by af_ctx_set_advance_shape or af_autotune, which
+ * af_level_advance uses for every launch of K steps.  Where none is set, the
+ * largest K, then the smallest block, of the shapes that run for every time
+ * step, and for advection with both velocity components positive also of the
+ * upwind-only ones; af_level_advance then does not take this one but chooses
+ * by the velocity's signs and the level's number of patches (the block size,
+ * and K beyond 256 patches) */
 af_status af_ctx_get_advance_shape(const af_ctx* ctx, int32_t* k, int32_t* nt);
 
 /* af_autotune -- picks, by timing `reps` launches of each candidate with HIP
@@ -335,14 +339,15 @@ af_status af_autotune(af_ctx* ctx, af_hier* h, af_state* bufs, int32_t level, do
  * (hierarchy, mask, dt0, t0 for AF_SWIRL, and the context's tile height and
  * fused-pairs switch; at most 64 graphs are kept per hierarchy, the stream is
  * drained and the cache emptied when it is full, so AF_SWIRL graphs are reused
- * only at repeated t0); AF_STEP_GLOBAL takes one step of dt0 on every level at once, without subcycling (global time
- * stepping, the corollary of Sec. 4.3; dt0 must satisfy the finest level's
- * CFL): full fill, every level steps its interior, then the conservative
- * fix of every level.
+ * only at repeated t0); AF_STEP_GLOBAL takes one step of dt0 on every level
+ * at once, without subcycling (global time stepping, the corollary of Sec.
+ * 4.3; dt0 must satisfy the finest level's CFL): full fill, every level steps
+ * its interior, then the conservative fix of every level.
  * A hierarchy that is one complete level steps without the fill: its patch
  * steps read the cells outside a patch from the neighbours' interiors (the
- * values the fill would copy).  Otherwise, for AF_ADVECTION and AF_ACOUSTICS
- * the subcycled step is batched by start time: with F the finest level and
+ * values the fill would copy).  Otherwise the subcycled step is batched by
+ * start time (a DOF array of 2^31 or more elements takes the recursion, for
+ * AF_ADVECTION and AF_ACOUSTICS it is AF_ERR_LAYOUT): with F the finest level and
  * tau = 0 .. 2^F - 1 in finest steps, one launch steps every patch of every
  * level that starts a step at tau, reading each ghost DOF from the source
  * the fill of that time resolves it to (same-level copy, mean of four finer

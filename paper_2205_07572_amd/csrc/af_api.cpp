@@ -983,8 +983,9 @@ Shapes advance_shapes(const af_ctx* c, bool up, int count = 0) {
 // latency: at most K = m / 2 (FP32, m = 16, per step: K = 8 against 16 1.28
 // and 1.12 us for 400 patches, 1.80 and 1.91 for 1024, 18.0 and 23.6 for
 // 16384), in FP64 m / 4 where blocks share a CU (m = 16, per step: K = 4
-// against 8 4.50 and 4.46 us for 1681 patches, 8.3 and 9.0 for 4096, 15.1 and
-// 17.1 for 8100).  The acoustic kernel of 256 threads catches up (FP32, two
+// against 8 with 512 threads 3.78 and 3.60 us for 1295 patches, within 1.5% of
+// each other from 1560 to 2025, 4.98 and 5.14 for 2160, 6.20 and 6.64 for 3072;
+// 15.1 and 17.1, with 256 threads, for 8100).  The acoustic kernel of 256 threads catches up (FP32, two
 // steps, with 256 and 512 threads: 36 and 33 us for 2025 patches, 114 and 115
 // for 8100, 242 and 252 for 16384).
 AdvanceShape level_shape(const af_ctx* c, const Shapes& shapes, int count) {
@@ -1021,7 +1022,7 @@ AdvanceShape default_advance_shape(const af_ctx* c, const Shapes& shapes) {
 // many launches middling ones are the faster (512^2 cells, FP32, 128 steps, K =
 // 20: six launches of 20 and one of 8, 160 us; one of 20 and six of 18, 156).
 // But a length that leaves a rest of several short launches costs more than it
-// saves (FP64, m = 32, 256 patches, 17 steps: 10 + 6 + 1 39.0 us, 12 + 5 34.3).
+// saves (FP64, m = 32, 256 patches, 17 steps: 10 + 6 + 1 39.0 us, 12 + 5 34.4).
 int next_steps(uint64_t ks, int K, int rest) {
   auto shortest = [&](int at_least, uint64_t rests) {  // rests: bit r, a rest of r is welcome
     for (int k = at_least; k <= K; ++k)

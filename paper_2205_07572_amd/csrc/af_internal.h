@@ -176,7 +176,9 @@ struct AdvAllWeights {
 
 // Acoustics: p = K.p - Dx.u - Dy.v ; u = K.u - Dx.p ; v = K.v - Dy.p
 // (eq. ERFormula: K is M_R + R d/dR M_R, Dx and Dy are R M_R of the x- and
-// y-derivative), each a vector over the node's neighbourhood.
+// y-derivative), each a vector over the node's neighbourhood.  The kernels take
+// them in mirror-orbit form (AcOrbitWeights); this is the form that that one is
+// checked against.
 template <typename T>
 struct AcWeights {
   T corner[2][3][kNbCorner];  // [tau][K,Dx,Dy][entry]

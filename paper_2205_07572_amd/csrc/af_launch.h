@@ -39,8 +39,9 @@ struct BufLaunch {
   uint32_t mask;
 };
 
-// One time point of the batched subcycled coarse step: levels lev0 .. lev0 + nlev - 1 step together; level lev0 + k
-// holds leaves [first[k], first[k] + count[k]) and steps `region[k]`.
+// One time point of the batched subcycled coarse step: levels lev0 .. lev0 +
+// nlev - 1 step together; level lev0 + k holds leaves [first[k], first[k] +
+// count[k]) and steps `region[k]`.
 struct AmrStepLaunch {
   bool fp32;
   int eq, m, ty;
@@ -109,10 +110,11 @@ bool level_advance_up_pattern(bool fp32, int eq, const void* weights);
 // nblocks x kThreads threads, 8 chains x 16 x iters FMAs each
 hipError_t launch_fma_probe(bool fp32, void* out, int nblocks, int iters, hipStream_t st);
 bool step_shape_supported(int m, int ty);
-// resolves the fill sources of every leaf (sources of level >= smin) into
-// plan[nleaves][nentries] and flags[nleaves] (bit p: ops of phase p); with
-// nbr and gnflags non-null also the same-level neighbours [nleaves][9] and
-// the directions a same-level gather stages (bit d)
+// resolves the fill sources of every leaf into plan[nleaves][nentries] (one
+// plan for every source bound) and flags[nleaves] (bits 0, 1, 2: ops with
+// sources of the coarser, the leaf's, the finer level), the same-level
+// neighbours nbr[nleaves][9] and the directions a same-level gather stages
+// gnflags[nleaves] (bit d)
 hipError_t launch_fill_plan(const HierDev& H, const int32_t* entries, int nentries, int m, int4* plan,
                             uint32_t* flags, int32_t* nbr, uint32_t* gnflags, hipStream_t st);
 // applies the phase-`phase` ops of leaves [first_target, first_target +

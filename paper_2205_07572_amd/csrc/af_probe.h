@@ -30,8 +30,8 @@ af_status af_fma_probe(int32_t prec, void* out, int32_t nblocks, int32_t iters, 
  * 2 * max_launches of them, created with timing enabled).  *nlaunch receives
  * the number of launches timed; cell_updates (host, max_launches entries, or
  * NULL) the interior leaf cell-updates of each.  Hierarchies stepped by the
- * one-level path or the per-level path (variable coefficients) record
- * nothing. */
+ * one-level path record nothing, nor do DOF arrays of 2^31 or more elements
+ * (the recursion level by level, variable velocities only). */
 af_status af_amr_coarse_step_timed(af_ctx* ctx, af_hier* h, af_state* bufs, uint32_t* level_buf_mask, double t0,
                                    double dt0, double* flux_reg, hipStream_t stream, void** events,
                                    int32_t max_launches, int32_t* nlaunch, double* cell_updates);
