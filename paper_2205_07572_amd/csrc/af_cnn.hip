@@ -621,11 +621,11 @@ struct af_cnn {
   float* d_m1 = nullptr;
   float* d_m2 = nullptr;
   float* d_grad = nullptr;
-  // workspace for up to cap samples: inputs and logits of af_cnn_tag, and the
-  // rows of gradient sums of af_cnn_loss_grad's blocks
+  // workspace for up to cap samples, one block: inputs and logits of af_cnn_tag,
+  // and the rows of gradient sums of af_cnn_loss_grad's blocks
   int cap = 0;
-  float* d_logits = nullptr;
   float* d_feat = nullptr;
+  float* d_logits = nullptr;
   float* d_part = nullptr;
   float* d_norm = nullptr;  // mean[nin], inv_std[nin]
 };
@@ -648,14 +648,13 @@ int grid_for(long n) { return int(std::min<long>((n + 255) / 256, 8192)); }
 // them the others allocate nothing up to that size (and can be captured).
 af_status ensure_batch(af_cnn* c, int n) {
   if (n <= c->cap) return AF_OK;
-  (void)hipFree(c->d_logits);
   (void)hipFree(c->d_feat);
-  (void)hipFree(c->d_part);
-  c->d_logits = c->d_feat = c->d_part = nullptr;
+  c->d_feat = c->d_logits = c->d_part = nullptr;
   c->cap = 0;
-  CNN_HIP(hipMalloc(&c->d_logits, size_t(n) * kClasses * 4));
-  CNN_HIP(hipMalloc(&c->d_feat, size_t(n) * c->nin * kPix * 4));
-  CNN_HIP(hipMalloc(&c->d_part, size_t(std::min(n, kCnnRows)) * kPart * 4));
+  const size_t feat = size_t(n) * c->nin * kPix, part = size_t(std::min(n, kCnnRows)) * kPart;
+  CNN_HIP(hipMalloc(&c->d_feat, (feat + part + size_t(n) * kClasses) * 4));
+  c->d_part = c->d_feat + feat;
+  c->d_logits = c->d_part + part;
   c->cap = n;
   return AF_OK;
 }
@@ -715,9 +714,7 @@ af_status af_cnn_destroy(af_cnn* c) {
   (void)hipFree(c->d_m1);
   (void)hipFree(c->d_m2);
   (void)hipFree(c->d_grad);
-  (void)hipFree(c->d_logits);
   (void)hipFree(c->d_feat);
-  (void)hipFree(c->d_part);
   (void)hipFree(c->d_norm);
   delete c;
   return AF_OK;
