@@ -1148,7 +1148,7 @@ af_status af_level_advance(af_ctx* ctx, af_hier* h, af_state* bufs, uint32_t* ma
   uint64_t ks = 0;
   for (const AdvanceShape& A : shapes) {
     if (A.k > S.k) continue;
-    if (!ctx->adv_k && count > kOneBlockPerCu && std::min(A.resident, 2) < std::min(S.resident, 2)) continue;
+    if (!ctx->adv_k && count > kOneBlockPerCu && A.k > 1 && std::min(A.resident, 2) < std::min(S.resident, 2)) continue;
     int& nt = block[A.k];
     const bool better = ctx->adv_k ? nt != S.nt && (A.nt == S.nt || A.nt < nt)
                                    : (A.nt > nt) == (count <= kOneBlockPerCu);
